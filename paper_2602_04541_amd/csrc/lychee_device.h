@@ -23,12 +23,22 @@ struct SharedAttn {
     int32_t late_have;
     uint32_t scan[kWaves + 1];                  // block_scan scratch of the key filter
 };
+constexpr int kBinBits = 11;               // a level of the select splits its range of keys into 2048 bins
+constexpr int kBins = 1 << kBinBits;
+constexpr int kFewKeys = 256;              // so few entries are ranked against one another, one per thread
+constexpr int kMapWords = 4096;            // words of the position bitmap: a window of 131072 positions
 struct SharedSelect {
-    uint32_t hist[4096];                   // radix histograms; position bitmap of the ordered write
-    uint32_t samp[kSampleTilesMax * 16];   // ordered keys of the threshold sample
-    uint32_t found[2];
-    uint32_t chunk_at[kThreads];           // ordered write: output rank of the first position of each
-    uint16_t word_at[4096];                //   run of 16 bitmap words, and of each word within its run
+    union {
+        uint32_t hist[4096];               // digit counts (threshold); bin counts (select)
+        unsigned long long mass[4096];     // probability mass per digit (Top-p)
+        uint2 map[kMapWords];              // ordered write: bitmap word, positions chosen before it
+    };
+    uint32_t samp[kSampleTilesMax * 16];   // ordered keys of the threshold sample; staged positions
+    unsigned long long few[kFewKeys];      // (key, ~position) of the entries around the last place
+    uint32_t n_few;
+    uint32_t wave_tot[kWaves];
+    uint32_t found[3];
+    uint32_t range[2][kWaves];
 };
 struct SharedCombine {
     float w[kMaxWg];
@@ -63,6 +73,13 @@ __device__ __forceinline__ float dpp_f32(float x)
 {
     return __builtin_bit_cast(
         float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), kCtrl, 0xF, 0xF, false));
+}
+
+// (lanes without a source lane, or outside the row mask, get 0)
+template <int kCtrl, int kRowMask = 0xF>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kCtrl, kRowMask, 0xF, false);
 }
 
 // Sum over the 16 lanes of a DPP row; every lane of the row ends with the same bits.
@@ -104,6 +121,33 @@ __device__ __forceinline__ float max_halves32(float x)
     const uint32_t u = __builtin_bit_cast(uint32_t, x);
     const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
     return fmaxf(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
+}
+
+// Smallest and largest of a wavefront's 64 values, in every lane.
+__device__ __forceinline__ uint32_t wave_min(uint32_t x)
+{
+    x = min(x, dpp_u32<0xB1>(x));
+    x = min(x, dpp_u32<0x4E>(x));
+    x = min(x, dpp_u32<0x141>(x));
+    x = min(x, dpp_u32<0x140>(x));
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = min((uint32_t)r[0], (uint32_t)r[1]);
+    const auto h = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return min((uint32_t)h[0], (uint32_t)h[1]);
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) { return ~wave_min(~x); }
+
+// Inclusive prefix sum over the 64 lanes of a wavefront, by row shifts and row broadcasts (plain
+// vector instructions; six exchanges through the LDS crossbar take about ten times as long).
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x)
+{
+    x += dpp_u32<0x111>(x);  // row_shr 1, 2, 4, 8: prefix sums inside every row of 16 lanes
+    x += dpp_u32<0x112>(x);
+    x += dpp_u32<0x114>(x);
+    x += dpp_u32<0x118>(x);
+    x += dpp_u32<0x142, 0xA>(x);  // row_bcast15: the row before, into rows 1 and 3
+    x += dpp_u32<0x143, 0xC>(x);  // row_bcast31: the first half, into rows 2 and 3
+    return x;
 }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -207,6 +251,16 @@ __device__ __forceinline__ int budget_of(const Common &c, int L)
 // scalar address arithmetic in the streaming loop).
 constexpr int kDescWords = (int)(sizeof(LayerDesc) / 4);
 static_assert(sizeof(LayerDesc) % 4 == 0 && kDescWords <= kThreads, "one word per thread");
+
+// The thread's index, opaque to the compiler where it is taken: what is computed from it stays inside
+// the unit that asks (left visible, every unit's per-thread LDS and list addresses were computed
+// once, at the top of the kernel, kept across everything and spilled).
+__device__ __forceinline__ int fresh_tid()
+{
+    uint32_t t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return (int)t;
+}
 
 // A value that is the same in every lane, said so to the compiler (a scalar register).
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }

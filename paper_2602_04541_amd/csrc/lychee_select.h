@@ -82,9 +82,10 @@ __device__ __forceinline__ void combine_segment(const Common &c, const LayerDesc
 {
     constexpr int kU = NH <= 2 ? 8 : 4;  // slots per thread and group
     constexpr int kSlots = 8 * kU;       // slots per group
-    const int lane = threadIdx.x & 63;
-    const int o8 = threadIdx.x >> 5;  // which eighth of a group's slots
-    const int c4 = threadIdx.x & 31;  // which 4 columns
+    const int tid = fresh_tid();
+    const int lane = tid & 63;
+    const int o8 = tid >> 5;  // which eighth of a group's slots
+    const int c4 = tid & 31;  // which 4 columns
     int64_t bh[NH];
     {
         uint32_t mk = hmask;
@@ -146,10 +147,10 @@ __device__ __forceinline__ void combine_segment(const Common &c, const LayerDesc
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
         reinterpret_cast<float4 *>(sh.red + (h * 8 + o8) * kHeadDim)[c4] = acc[h];
-        if (threadIdx.x == 0) sh.l[h] = Ls[h];
+        if (tid == 0) sh.l[h] = Ls[h];
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < NH * kHeadDim; i += kThreads) {
+    for (int i = tid; i < NH * kHeadDim; i += kThreads) {
         const int h = i / kHeadDim, col = i % kHeadDim;
         float o = 0.0f;
 #pragma unroll
@@ -255,25 +256,25 @@ __device__ __forceinline__ void threshold_unit(const Common &c, const LayerDesc 
                                                SharedSelect &sh, Pool &pool, unsigned long long *publish = nullptr,
                                                uint32_t gen = 0, const ThrSplit split = ThrSplit())
 {
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int tid = fresh_tid();
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
     const int rs = lane >> 4;
     const int ch = lane & 15;
     const int L = pool.len[b];  // staged by the kernel, clamped
     const int n = budget_of(c, L);
     const int64_t row = (int64_t)b * p.n_rgroups + rgi;
     auto emit = [&](uint32_t key) {
-        if (threadIdx.x != 0) return;
+        if (tid != 0) return;
         if (publish != nullptr)
             __hip_atomic_store((LYCHEE_GLOBAL unsigned long long *)publish, ((unsigned long long)gen << 32) | key,
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        else
-            gstore(p.thr + row, key);
+        gstore(p.thr + row, key);  // (the row's select starts from it)
     };
-    if (publish == nullptr && threadIdx.x == 0) gstore(p.list_count + row, (int32_t)0);
-    if (split.sub == 0 && p.q_keep != nullptr && (int)threadIdx.x < c.group * (kHeadDim / 8)) {
+    if (publish == nullptr && tid == 0) gstore(p.list_count + row, (int32_t)0);
+    if (split.sub == 0 && p.q_keep != nullptr && tid < c.group * (kHeadDim / 8)) {
         // the group's query rows (consecutive heads, 16 chunks of 16 bytes each)
-        const int64_t at = ((int64_t)b * c.n_q_heads + p.rgroup[rgi] * c.group) * kHeadDim + threadIdx.x * 8;
+        const int64_t at = ((int64_t)b * c.n_q_heads + p.rgroup[rgi] * c.group) * kHeadDim + tid * 8;
         *(LYCHEE_GLOBAL u32x4_t *)(p.q_keep + at) = *(const LYCHEE_GLOBAL u32x4_t *)(p.q + at);
     }
     if (n == L || L <= kDirectLen || 2 * (int64_t)n >= L) {
@@ -291,7 +292,7 @@ __device__ __forceinline__ void threshold_unit(const Common &c, const LayerDesc 
     load_q<NH>(c, p.q, b, g, hmask, qf);
     const uint16_t *kbase = p.k_cache + (int64_t)b * c.stride_b + (int64_t)g * c.stride_h;
     const float sel_mul = c.scale / (float)NH;
-    for (int i = threadIdx.x; i < 4096; i += kThreads) sh.hist[i] = 0;
+    for (int i = tid; i < 4096; i += kThreads) sh.hist[i] = 0;
     __syncthreads();
 
     constexpr int kBatch = 8;  // groups of 16 sampled rows a wavefront has in flight
@@ -331,7 +332,7 @@ __device__ __forceinline__ void threshold_unit(const Common &c, const LayerDesc 
         // leave the keys, count this unit in; the last one to arrive goes on with all of them
         wait_stores();
         __syncthreads();
-        if (threadIdx.x == 0) {
+        if (tid == 0) {
             const uint32_t old = __hip_atomic_fetch_add((LYCHEE_GLOBAL uint32_t *)split.arrived, 1u, __ATOMIC_RELAXED,
                                                         __HIP_MEMORY_SCOPE_AGENT);
             const bool last = old == (uint32_t)split.n_sub - 1u;
@@ -343,7 +344,7 @@ __device__ __forceinline__ void threshold_unit(const Common &c, const LayerDesc 
         __syncthreads();
         if (!last) return;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        for (int i = threadIdx.x; i < n_sample; i += kThreads) {
+        for (int i = tid; i < n_sample; i += kThreads) {
             const uint32_t key = gload(split.keys + i);
             sh.samp[i] = key;
             atomicAdd(&sh.hist[key >> 20], 1u);
@@ -358,9 +359,9 @@ __device__ __forceinline__ void threshold_unit(const Common &c, const LayerDesc 
         // the sample's target-th largest key: top 12 bits, then the next 10
         uint32_t d1, rest1, d2, rest2;
         find_digit<4096>(sh.hist, target, sh.found, pool.scan, d1, rest1);
-        for (int i = threadIdx.x; i < 1024; i += kThreads) sh.hist[i] = 0;
+        for (int i = tid; i < 1024; i += kThreads) sh.hist[i] = 0;
         __syncthreads();
-        for (int i = threadIdx.x; i < n_sample; i += kThreads) {
+        for (int i = tid; i < n_sample; i += kThreads) {
             const uint32_t key = sh.samp[i];
             if ((key >> 20) == d1) atomicAdd(&sh.hist[(key >> 10) & 1023u], 1u);
         }
@@ -376,8 +377,9 @@ __device__ __forceinline__ void threshold_unit(const Common &c, const LayerDesc 
 template <int NH>
 __device__ __forceinline__ void score_row_unit(const Common &c, const LayerDesc &p, int b, int g, int L, float *sel)
 {
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int tid = fresh_tid();
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
     const int rs = lane >> 4;
     const int ch = lane & 15;
     const uint32_t hmask = p.rmask[g] & ((1u << c.group) - 1u);
@@ -408,194 +410,289 @@ __device__ __forceinline__ void score_row_unit(const Common &c, const LayerDesc 
 }
 
 // The three sources of (ordered key, position) entries the select unit ranks.  for_each may
-// also hand out "no entry" (position kNoEntry).  The visitors below fold everything that
-// decides whether an entry counts into one flag, with bitwise operators, and guard a single
-// LDS operation with it: short-circuit conditions made the compiler keep a lane mask per entry
-// and condition, spill them, and branch several times per entry.
+// also hand out "no entry": key 0, below every real key, and position kNoEntry; for_window
+// hands out at least the entries of `count` positions from w0 on.  The visitors below fold
+// everything that decides whether an entry counts into one flag, with bitwise operators, and
+// guard a single LDS operation with it: short-circuit conditions made the compiler keep a lane
+// mask per entry and condition, spill them, and branch several times per entry.
 constexpr uint32_t kNoEntry = 0xFFFFFFFFu;
-constexpr int kSelRegs = 40;  // entries one thread keeps in registers
-struct RegEntries {           // up to kThreads * kSelRegs list entries, loaded once
-    uint32_t key[kSelRegs], pos[kSelRegs];
-    __device__ __forceinline__ void load(const unsigned long long *list, int total)
+// (A key of 0 would be a NaN with every bit set, which no score is.  "No entry" needs no test of its
+// own that way: a range [lo, hi] with lo >= 1 leaves it out, since 0 - lo wraps beyond hi - lo.
+// Tested separately it was one lane mask per entry, kept from pass to pass and spilled.)
+__device__ __forceinline__ uint32_t real_key(uint32_t key) { return key > 1u ? key : 1u; }
+constexpr int kEntryBatch = 32;  // entries a thread loads before it looks at the first of them
+constexpr int kSelRegs = 40;     // entries one thread keeps in registers
+struct RegEntries {           // up to kThreads * kSelRegs list entries, loaded once: beside a streaming
+    uint32_t key[kSelRegs], pos[kSelRegs];  // launch every pass over memory costs a microsecond or two
+    int tid;
+    int left;                 // entries, uniform: whole groups of eight registers beyond them are skipped
+    __device__ __forceinline__ void load(const unsigned long long *list, int total, int tid_)
     {
+        tid = tid_;
+        left = total;
 #pragma unroll
         for (int e = 0; e < kSelRegs; ++e) {
-            const int i = threadIdx.x + e * kThreads;
-            const unsigned long long v = gload(list + (i < total ? i : 0));  // total >= 1
-            key[e] = (uint32_t)v;
+            if (e % 8 == 0 && e * kThreads >= left) break;
+            const int i = e * kThreads + tid;
+            const unsigned long long v = gload(list + (i < total ? i : total - 1));
+            key[e] = i < total ? real_key((uint32_t)v) : 0u;
             pos[e] = i < total ? (uint32_t)(v >> 32) : kNoEntry;
         }
     }
-    template <typename F>
+    template <int kBatch = 8, typename F>
     __device__ __forceinline__ void for_each(F f) const
     {
 #pragma unroll
-        for (int e = 0; e < kSelRegs; ++e) f(key[e], pos[e]);
+        for (int e = 0; e < kSelRegs; ++e) {
+            if (e % 8 == 0 && e * kThreads >= left) break;
+            f(key[e], pos[e]);
+        }
     }
+    template <typename F>
+    __device__ __forceinline__ void for_window(uint32_t, uint32_t, F f) const { for_each(f); }
 };
 struct ListEntries {          // a longer list, read from memory on every pass
     const unsigned long long *list;
     int total;
-    template <typename F>
+    int tid;
+    template <int kBatch = kEntryBatch, typename F>
     __device__ __forceinline__ void for_each(F f) const
     {
-        for (int i0 = threadIdx.x; i0 < total; i0 += 8 * kThreads) {
-            unsigned long long v[8];
+        for (int i0 = 0; i0 < total; i0 += kBatch * kThreads) {
+            const int left = total - i0;  // groups of eight registers beyond it are skipped (uniform)
+            unsigned long long v[kBatch];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = i0 + u * kThreads;
+            for (int u = 0; u < kBatch; ++u) {
+                if (u % 8 == 0 && u * kThreads >= left) break;
+                const int i = i0 + u * kThreads + tid;
                 v[u] = gload(list + (i < total ? i : total - 1));  // unconditional: the loads overlap
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                f((uint32_t)v[u], i0 + u * kThreads < total ? (uint32_t)(v[u] >> 32) : kNoEntry);
+            for (int u = 0; u < kBatch; ++u) {
+                if (u % 8 == 0 && u * kThreads >= left) break;
+                const bool ok = i0 + u * kThreads + tid < total;
+                f(ok ? real_key((uint32_t)v[u]) : 0u, ok ? (uint32_t)(v[u] >> 32) : kNoEntry);
+            }
         }
     }
+    template <typename F>
+    __device__ __forceinline__ void for_window(uint32_t, uint32_t, F f) const { for_each(f); }
 };
 struct RowEntries {           // every row of the sequence, from its recomputed scores
     const float *sel;
     int total;
+    int tid;
     template <typename F>
-    __device__ __forceinline__ void for_each(F f) const
+    __device__ __forceinline__ void for_window(uint32_t w0, uint32_t count, F f) const
     {
-        for (int i0 = threadIdx.x; i0 < total; i0 += 8 * kThreads) {
+        const int end = (int)(count < (uint32_t)total - w0 ? w0 + count : (uint32_t)total);
+        for (int i0 = (int)w0 + tid; i0 < end; i0 += 8 * kThreads) {
             float v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int i = i0 + u * kThreads;
-                v[u] = gload(sel + (i < total ? i : total - 1));
+                v[u] = gload(sel + (i < end ? i : end - 1));
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int i = i0 + u * kThreads;
-                f(ordered_key(v[u]), i < total ? (uint32_t)i : kNoEntry);
+                f(i < end ? real_key(ordered_key(v[u])) : 0u, i < end ? (uint32_t)i : kNoEntry);
             }
         }
     }
+    template <int kBatch = 8, typename F>
+    __device__ __forceinline__ void for_each(F f) const { for_window(0u, (uint32_t)total, f); }
 };
 
-// The `need`-th largest of the 32-bit values val(key, pos) over the entries that pass
-// `among`, by radix select (12 + 10 + 10 bits); `rest` = how many entries equal to the
-// result are among the `need` largest.
-template <typename Entries, typename Val, typename Among, typename Pool>
-__device__ __forceinline__ uint32_t radix_select(const Entries &E, uint32_t need, Val val, Among among,
-                                                 uint32_t &rest, SharedSelect &sh, Pool &pool)
+// Among the counted bins, taken from the highest down, the one at which `need` entries are reached:
+// its number, how many of its entries are needed, and how many it has.  Every thread sums eight
+// neighbouring bins (two 16-byte reads); need must not exceed the count of all bins.
+struct Bin {
+    uint32_t bin, need, count;
+};
+__device__ __forceinline__ Bin find_bin(uint32_t need, SharedSelect &sh, int tid)
 {
-    uint32_t prefix = 0, prefix_mask = 0;
+    static_assert(kBins == 8 * kThreads, "eight bins per thread");
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+    const int first = kBins - 8 - 8 * tid;
+    const uint4 lo4 = *reinterpret_cast<const uint4 *>(sh.hist + first);
+    const uint4 hi4 = *reinterpret_cast<const uint4 *>(sh.hist + first + 4);
+    const uint32_t c[8] = {hi4.w, hi4.z, hi4.y, hi4.x, lo4.w, lo4.z, lo4.y, lo4.x};
+    uint32_t sum = 0;
 #pragma unroll
-    for (int pass = 0; pass < 3; ++pass) {
-        const int shift = pass == 0 ? 20 : (pass == 1 ? 10 : 0);
-        const int n_bins = pass == 0 ? 4096 : 1024;
-        const uint32_t digit_mask = (uint32_t)n_bins - 1u;
-        for (int i = threadIdx.x; i < n_bins; i += kThreads) sh.hist[i] = 0;
-        __syncthreads();
-        E.for_each([&](uint32_t key, uint32_t pos) {
-            const uint32_t v = val(key, pos);
-            const bool in = (pos != kNoEntry) & among(key, pos) & ((v & prefix_mask) == prefix);
-            if (in) atomicAdd(&sh.hist[(v >> shift) & digit_mask], 1u);
-        });
-        __syncthreads();
-        uint32_t digit, left;
-        if (pass == 0)
-            find_digit<4096>(sh.hist, need, sh.found, pool.scan, digit, left);
-        else
-            find_digit<1024>(sh.hist, need, sh.found, pool.scan, digit, left);
-        prefix |= digit << shift;
-        prefix_mask |= digit_mask << shift;
-        need = left;
+    for (int j = 0; j < 8; ++j) sum += c[j];
+    const uint32_t incl = wave_scan(sum);
+    if (lane == 63) sh.wave_tot[wave] = incl;
+    __syncthreads();
+    uint32_t above = incl - sum;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) above += w < wave ? sh.wave_tot[w] : 0u;
+    if (above < need && need <= above + sum) {  // one thread
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (above < need && need <= above + c[j]) {
+                sh.found[0] = (uint32_t)(first + 7 - j);
+                sh.found[1] = need - above;
+                sh.found[2] = c[j];
+            }
+            above += c[j];
+        }
     }
-    rest = need;
-    return prefix;
+    __syncthreads();
+    return Bin{uni(sh.found[0]), uni(sh.found[1]), uni(sh.found[2])};
 }
 
-// Exact top-n of the entries by key, ties to the lower position (Eq. 2), written to dst in
-// ascending position order.  The entries may come in any order: the n-th largest key T and the
-// number r_eq of entries equal to T that belong to the top n come from a radix select; when
-// more than r_eq entries equal T, a second radix select finds the r_eq-th lowest position
-// among them; the chosen positions are then marked in an LDS bitmap, 131072 positions at a
-// time, and read back in order.
-template <typename Entries, typename Pool>
-__device__ __forceinline__ void select_from(const Entries &E, int n, int L, int32_t *dst, SharedSelect &sh,
-                                            Pool &pool)
+// Values to a bin, as a power of two, of a level that splits a range whole.
+__device__ __forceinline__ int level_shift(uint32_t range)
 {
-    uint32_t r_eq;
-    const uint32_t T = radix_select(
-        E, (uint32_t)n, [](uint32_t key, uint32_t) { return key; }, [](uint32_t, uint32_t) { return true; }, r_eq,
-        sh, pool);
-    uint32_t my_eq = 0;
-    E.for_each([&](uint32_t key, uint32_t pos) { my_eq += (uint32_t)((key == T) & (pos != kNoEntry)); });
-    uint32_t n_eq;
-    (void)block_scan(my_eq, pool.scan, n_eq);
-    uint32_t pos_cut = 0xFFFFFFFEu;  // entries equal to T are taken up to this position
-    if (r_eq < n_eq) {
-        uint32_t unused;
-        pos_cut = ~radix_select(
-            E, r_eq, [](uint32_t, uint32_t pos) { return ~pos; }, [&](uint32_t key, uint32_t) { return key == T; },
-            unused, sh, pool);
-    }
-    constexpr uint32_t kWindow = 4096u * 32u;
-    constexpr int kPer = 4096 / kThreads;
-    uint32_t base = 0;
-    for (uint32_t w0 = 0; w0 < (uint32_t)L; w0 += kWindow) {
-        for (int i = threadIdx.x; i < 4096; i += kThreads) sh.hist[i] = 0;
+    return range >= (uint32_t)kBins ? 32 - __builtin_clz(range) - kBinBits : 0;
+}
+
+// The entries that pass `among` and whose value lies in [lo, hi], `count` of them, of which the
+// `need` with the largest values are wanted.
+struct Cut {
+    uint32_t lo, hi, need, count;
+};
+// Narrows [lo, hi] around the need-th largest value until at most `few` entries are left in it, or
+// all that are left are equal.  A level splits the range it is given evenly, 2^shift values to a bin
+// (the last bin takes what lies beyond), not by fixed digits of the value: the candidates of
+// a row lie within a few octaves, whose top digits are a few dozen different ones, and 64 lanes
+// that count into the same few LDS words are served one after the other.
+template <typename Entries, typename Val, typename Among>
+__device__ __forceinline__ Cut narrow(const Entries &E, Cut cut, int shift, uint32_t few, Val val, Among among,
+                                      SharedSelect &sh)
+{
+    while (cut.hi != cut.lo && cut.count > few) {  // (uniform)
+        const uint32_t range = cut.hi - cut.lo;
+        uint4 *h4 = reinterpret_cast<uint4 *>(sh.hist);
+        h4[E.tid] = h4[E.tid + kThreads] = make_uint4(0, 0, 0, 0);
         __syncthreads();
         E.for_each([&](uint32_t key, uint32_t pos) {
-            const uint32_t rel = pos - w0;  // "no entry" lies outside every window
-            const bool take = ((key > T) | ((key == T) & (pos <= pos_cut))) & (rel < kWindow);
-            if (take) atomicOr(&sh.hist[rel >> 5], 1u << (rel & 31u));
+            const uint32_t at = val(key, pos) - cut.lo;
+            const bool in = among(key, pos) & (at <= range);
+            if (in) atomicAdd(&sh.hist[min(at >> shift, (uint32_t)kBins - 1u)], 1u);
         });
         __syncthreads();
-        // Thread t counts bitmap words 16 t .. 16 t + 15; the scan gives the output rank of every
-        // run of 16 words and, inside a run, of every word.
-        uint32_t cnt = 0;
-#pragma unroll 4
-        for (int j = 0; j < kPer; ++j) {
-            sh.word_at[threadIdx.x * kPer + j] = (uint16_t)cnt;  // (at most 16 * 32 positions before it)
-            cnt += (uint32_t)__builtin_popcount(sh.hist[threadIdx.x * kPer + j]);
+        const Bin b = find_bin(cut.need, sh, E.tid);
+        cut.lo += b.bin << shift;
+        const uint32_t left = cut.hi - cut.lo, width = (1u << shift) - 1u;
+        cut.hi = b.bin == (uint32_t)kBins - 1u || left < width ? cut.hi : cut.lo + width;
+        cut.need = b.need;
+        cut.count = b.count;
+        shift = level_shift(cut.hi - cut.lo);
+    }
+    return cut;
+}
+
+// Exact top-n of the `total` entries by key, ties to the lower position (Eq. 2), written to dst in
+// ascending position order.  The entries may come in any order.  The range of keys is narrowed
+// around the n-th largest until it holds at most kFewKeys entries, which are then ranked against
+// one another by (key, position); equal keys that are more than that are cut at a position found
+// the same way.  The chosen positions are marked in an LDS bitmap, 131072 positions at a
+// time; a prefix sum over its words gives every chosen position its place, and each entry
+// writes itself there.
+//
+// One workgroup, a chain of LDS passes and barriers: latency bounds it.  Counting by fixed digits,
+// three passes always, with the positions read back by walking the bitmap's bits, took 15.7 us
+// from the loads to the last store for any row (7500 candidates, k = 4096: see the figures at
+// select_unit).
+template <typename Entries, typename Pool>
+__device__ __forceinline__ void select_from(const Entries &E, uint32_t floor_key, int total, int n, int L,
+                                            int32_t *dst, SharedSelect &sh, Pool &pool)
+{
+    const int tid = E.tid;
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+    if (tid == 0) sh.n_few = 0;
+    __syncthreads();  // (a list of kFewKeys entries or fewer goes straight to its use)
+    // Rows that were sampled hold keys from their threshold up: the first level covers the eight
+    // octaves above it, 256 bins each.  Others (short rows, blocks, rows ranked whole) start from
+    // the range of all keys, four bins to the octave.
+    const uint32_t lo = floor_key > 1u ? floor_key : 1u;
+    const Cut cut = narrow(
+        E, Cut{lo, 0xFFFFFFFFu, (uint32_t)n, (uint32_t)total}, lo >= 0x80000000u ? 26 - kBinBits : 32 - kBinBits,
+        (uint32_t)kFewKeys, [](uint32_t key, uint32_t) { return key; }, [](uint32_t, uint32_t) { return true; }, sh);
+    const bool all = cut.need == cut.count;  // everything in the range is chosen
+    uint32_t my_few = kNoEntry;              // the position this thread ranked, if it is chosen
+    uint32_t pos_cut = 0;                    // entries of equal keys are chosen up to this position
+    bool by_pos = false;
+    if (!all && cut.count <= (uint32_t)kFewKeys) {
+        E.for_each([&](uint32_t key, uint32_t pos) {
+            const bool in = key - cut.lo <= cut.hi - cut.lo;
+            if (in) sh.few[atomicAdd(&sh.n_few, 1u)] = ((unsigned long long)key << 32) | (uint32_t)~pos;
+        });
+        __syncthreads();
+        if ((uint32_t)tid < cut.count) {
+            const unsigned long long mine = sh.few[tid];
+            uint32_t before = 0;
+            for (uint32_t i = 0; i < cut.count; ++i) before += (uint32_t)(sh.few[i] > mine);
+            if (before < cut.need) my_few = ~(uint32_t)mine;
         }
-        uint32_t tot;
-        const uint32_t at0 = base + block_scan(cnt, pool.scan, tot) - cnt;
-        sh.chunk_at[threadIdx.x] = at0;
+    } else if (!all) {
+        by_pos = true;
+        const Cut at = narrow(
+            E, Cut{~(uint32_t)(L - 1), 0xFFFFFFFFu, cut.need, cut.count}, level_shift((uint32_t)(L - 1)), 0u, [](uint32_t, uint32_t pos) { return ~pos; },
+            [&](uint32_t key, uint32_t) { return key == cut.lo; }, sh);
+        pos_cut = ~at.lo;
+    }
+    constexpr uint32_t kWindow = kMapWords * 32u;
+    uint32_t base = 0;  // positions chosen in earlier windows
+    for (uint32_t w0 = 0; w0 < (uint32_t)L; w0 += kWindow) {
+        const uint32_t span = (uint32_t)L - w0 < kWindow ? (uint32_t)L - w0 : kWindow;
+        const int rounds = (int)(span + 32 * kThreads - 1) / (32 * kThreads);  // words of a wavefront's share / 64
+        __syncthreads();
+        for (int r = 0; r < rounds; ++r) sh.map[r * kThreads + tid] = make_uint2(0, 0);
+        __syncthreads();
+        E.for_window(w0, span, [&](uint32_t key, uint32_t pos) {
+            const uint32_t rel = pos - w0;  // "no entry" lies outside every window
+            const bool in = key - cut.lo <= cut.hi - cut.lo;
+            const bool take = ((key > cut.hi) | (in & (all | (by_pos & (pos <= pos_cut))))) & (rel < span);
+            if (take) atomicOr(&sh.map[rel >> 5].x, 1u << (rel & 31u));
+        });
+        if (my_few - w0 < span) atomicOr(&sh.map[(my_few - w0) >> 5].x, 1u << ((my_few - w0) & 31u));
+        __syncthreads();
+        // wavefront w counts words w * rounds * 64 .. of the window, then gives each its place
+        const uint2 *share = sh.map + wave * rounds * 64 + lane;
+        uint32_t cnt = 0;
+        for (int r = 0; r < rounds; ++r) cnt += (uint32_t)__builtin_popcount(share[r * 64].x);
+        cnt = wave_scan(cnt);
+        if (lane == 63) sh.wave_tot[wave] = cnt;
+        __syncthreads();
+        uint32_t at0 = base, tot = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            at0 += w < wave ? sh.wave_tot[w] : 0u;
+            tot += sh.wave_tot[w];
+        }
+        for (int r = 0; r < rounds; ++r) {
+            const uint32_t c = (uint32_t)__builtin_popcount(share[r * 64].x);
+            const uint32_t incl = wave_scan(c);
+            sh.map[wave * rounds * 64 + lane + r * 64].y = at0 + incl - c;
+            at0 += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        }
         __syncthreads();
         // The positions are put in order in LDS, kStage at a time, and copied out with coalesced
         // write-through stores: the set is in device memory once the unit's stores have
         // completed, whoever reads it next (a gather piece of the same launch, on another XCD,
-        // after an acquire), and a store per position from every lane's own bit loop took four
-        // times as long beside a streaming launch as it does alone.  Here thread t takes words
-        // t, t + 256, ...: selected positions come in clusters (the newest rows, a few hot spans),
-        // and a thread that held 16 neighbouring words would walk a cluster's hundreds of bits
-        // alone while the others wait.
+        // after an acquire).
         constexpr uint32_t kStage = (uint32_t)(sizeof(sh.samp) / sizeof(sh.samp[0]));
-        uint32_t end = base + tot;
-        end = end < (uint32_t)n ? end : (uint32_t)n;
+        const uint32_t end = base + tot;
         for (uint32_t c0 = base; c0 < end; c0 += kStage) {
-            // (eight words at a time: their LDS reads overlap instead of each waiting in its own branch)
-#pragma unroll 1
-            for (int j0 = 0; j0 < kPer; j0 += 8) {
-                uint32_t wd[8], at[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const uint32_t wi = (uint32_t)(j0 + u) * kThreads + threadIdx.x;
-                    wd[u] = sh.hist[wi];
-                    at[u] = sh.chunk_at[wi / kPer] + sh.word_at[wi] - c0;
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const uint32_t first = w0 + ((uint32_t)(j0 + u) * kThreads + threadIdx.x) * 32u;
-                    while (wd[u] != 0) {
-                        const uint32_t bit = (uint32_t)__builtin_ctz(wd[u]);
-                        wd[u] &= wd[u] - 1u;
-                        if (at[u] < kStage) sh.samp[at[u]] = first + bit;
-                        ++at[u];
-                    }
-                }
-            }
+            E.for_window(w0, span, [&](uint32_t, uint32_t pos) {
+                const uint32_t rel = pos - w0;
+                const uint2 word = sh.map[rel < span ? rel >> 5 : 0];
+                const uint32_t bit = 1u << (rel & 31u);
+                const uint32_t at = word.y + (uint32_t)__builtin_popcount(word.x & (bit - 1u)) - c0;
+                const bool put = (rel < span) & ((word.x & bit) != 0) & (at < kStage);
+                if (put) sh.samp[at] = pos;
+            });
             __syncthreads();
             const uint32_t m = end - c0 < kStage ? end - c0 : kStage;
-            for (uint32_t i = threadIdx.x; i < m; i += kThreads) gstore_through(dst + c0 + i, (int32_t)sh.samp[i]);
+            for (uint32_t i = tid; i < m; i += kThreads) gstore_through(dst + c0 + i, (int32_t)sh.samp[i]);
             __syncthreads();
         }
-        base += tot;
+        base = end;
     }
 }
 
@@ -683,11 +780,11 @@ __device__ __forceinline__ int rule_keeps(const Common &c, const Entries &E, int
     if (c.prob_rule == 1) {
         const uint32_t cut = ordered_key(lse + __logf(c.prob_param));
         uint32_t mine = 0;
-        E.for_each([&](uint32_t key, uint32_t pos) { mine += (uint32_t)((pos != kNoEntry) & (key > cut)); });
+        E.template for_each<8>([&](uint32_t key, uint32_t pos) { mine += (uint32_t)(key > cut); });
         (void)block_scan(mine, pool.scan, want);
     } else {
         if (c.prob_param >= 1.0f) return n;  // all of the mass: everything, i.e. the cap
-        unsigned long long *mh = reinterpret_cast<unsigned long long *>(sh.hist);  // 4096 x 8 bytes: hist + samp
+        unsigned long long *mh = sh.mass;
         unsigned long long need = (unsigned long long)((double)c.prob_param * (double)kMassOne);
         need = need < 1 ? 1 : need;
         uint32_t prefix = 0, prefix_mask = 0;
@@ -699,8 +796,8 @@ __device__ __forceinline__ int rule_keeps(const Common &c, const Entries &E, int
             const uint32_t digit_mask = (uint32_t)n_bins - 1u;
             for (int i = threadIdx.x; i < n_bins; i += kThreads) mh[i] = 0;
             __syncthreads();
-            E.for_each([&](uint32_t key, uint32_t pos) {
-                const bool in = (pos != kNoEntry) & ((key & prefix_mask) == prefix);
+            E.template for_each<8>([&](uint32_t key, uint32_t pos) {
+                const bool in = (key != 0u) & ((key & prefix_mask) == prefix);
                 if (in) atomicAdd(&mh[(key >> shift) & digit_mask], mass_of(key, lse));
             });
             __syncthreads();
@@ -722,7 +819,7 @@ __device__ __forceinline__ int rule_keeps(const Common &c, const Entries &E, int
         const unsigned long long each = mass_of(prefix, lse);  // > 0: its digit held mass
         const uint32_t of_last = (uint32_t)((need + each - 1) / each);
         uint32_t mine = 0;
-        E.for_each([&](uint32_t key, uint32_t pos) { mine += (uint32_t)((pos != kNoEntry) & (key > prefix)); });
+        E.template for_each<8>([&](uint32_t key, uint32_t pos) { mine += (uint32_t)(key > prefix); });
         uint32_t above;
         (void)block_scan(mine, pool.scan, above);
         want = above + of_last;
@@ -780,6 +877,7 @@ __device__ __forceinline__ void select_unit(const Common &c, const LayerDesc &p,
     const unsigned long long *list = p.list + row * (int64_t)c.list_row;
     // block-granular: the streaming left every block's score at its place in the list
     const int total = c.block_shift ? L : gload(p.list_count + row);
+    const uint32_t floor_key = c.block_shift ? 0u : gload(p.thr + row);  // no entry lies below it
     // The select is the counter's only reader: it leaves it at zero for the next launch that
     // collects into it (a launch whose streaming runs beside its threshold units has nobody who
     // could clear it first).  Every thread has read it before any thread gets past the barriers
@@ -796,13 +894,13 @@ __device__ __forceinline__ void select_unit(const Common &c, const LayerDesc &p,
     int keep = n;  // what is selected in the end: n, or fewer under a probability rule
     if (total >= n && total <= kThreads * kSelRegs && total <= c.list_row) {
         RegEntries E;
-        E.load(list, total);
+        E.load(list, total, fresh_tid());
         if (PROB && by_prob) keep = rule_keeps(c, E, n, lse, sh, pool);
-        select_from(E, keep, L, dst, sh, pool);
+        select_from(E, floor_key, total, keep, L, dst, sh, pool);
     } else if (total >= n && total <= c.list_row) {
-        const ListEntries E{list, total};
+        const ListEntries E{list, total, fresh_tid()};
         if (PROB && by_prob) keep = rule_keeps(c, E, n, lse, sh, pool);
-        select_from(E, keep, L, dst, sh, pool);
+        select_from(E, floor_key, total, keep, L, dst, sh, pool);
     } else {
         // too few candidates reached the threshold, or too many for the list: rank the row
         // (token-granular only: a block list is always complete)
@@ -816,9 +914,9 @@ __device__ __forceinline__ void select_unit(const Common &c, const LayerDesc &p,
         }
         __threadfence();
         __syncthreads();  // the scores are read back by other threads of the workgroup
-        const RowEntries E{sel, len};
+        const RowEntries E{sel, len, fresh_tid()};
         if (PROB && by_prob) keep = rule_keeps(c, E, n, lse, sh, pool);
-        select_from(E, keep, L, dst, sh, pool);
+        select_from(E, 0u, len, keep, L, dst, sh, pool);
     }
     for (int i = keep + threadIdx.x; i < c.k; i += kThreads) gstore_through(dst + i, (int32_t)-1);
     if (clear_count && threadIdx.x == 0) gstore(p.list_count + row, (int32_t)0);
