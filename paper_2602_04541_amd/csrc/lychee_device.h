@@ -28,13 +28,15 @@ constexpr int kBins = 1 << kBinBits;
 constexpr int kFewKeys = 256;              // so few entries are ranked against one another, one per thread
 constexpr int kMapWords = 4096;            // words of the position bitmap: a window of 131072 positions
 struct SharedSelect {
+    // (hist, map and samp end in a word per lane where entries that do not count go: a store to a
+    // word of its own costs less than a branch around the store for every entry)
     union {
-        uint32_t hist[4096];               // digit counts (threshold); bin counts (select)
+        uint32_t hist[4096 + 64];          // digit counts (threshold); bin counts (select)
         unsigned long long mass[4096];     // probability mass per digit (Top-p)
-        uint2 map[kMapWords];              // ordered write: bitmap word, positions chosen before it
+        uint2 map[kMapWords + 64];         // ordered write: bitmap word, positions chosen before it
     };
-    uint32_t samp[kSampleTilesMax * 16];   // ordered keys of the threshold sample; staged positions
-    unsigned long long few[kFewKeys];      // (key, ~position) of the entries around the last place
+    uint32_t samp[kSampleTilesMax * 16 + 64];  // ordered keys of the threshold sample; staged positions
+    __align__(16) unsigned long long few[kFewKeys];  // (key, ~position) of the entries around the last place
     uint32_t n_few;
     uint32_t wave_tot[kWaves];
     uint32_t found[3];

@@ -22,6 +22,7 @@ constexpr int kMaxWg = 1024;             // upper bound of the grid of one launc
 constexpr int kIdxChunk = 2048;          // set entries staged in LDS at a time
 constexpr int kSampleTilesMin = 128;     // the threshold sample: 128 to 256 tiles of 16 rows
 constexpr int kSampleTilesMax = 256;
+constexpr int kSampleTilesFew = 64;      // fewer, where that still samples enough of the rows that will be chosen
 constexpr int kDirectLen = 4096;         // sequences this short are ranked without a threshold
 constexpr int kCandBuf = 256;            // candidates a wavefront collects in LDS between flushes
 constexpr int kThrSplit = 4;             // units that share a score row's threshold sample in a layer launch

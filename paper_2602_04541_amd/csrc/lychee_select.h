@@ -166,39 +166,93 @@ __device__ __forceinline__ void combine_segment(const Common &c, const LayerDesc
 }
 
 // ------------------------------------------------------------------------------ T and S
-// In the histogram of `n_bins` digits, finds the highest digit d whose suffix count
-// (keys with digit >= d) reaches `need`; returns d and need minus the count above d.
-template <int kBins>
-__device__ __forceinline__ void find_digit(const uint32_t *hist, uint32_t need, uint32_t *found,
-                                           uint32_t *scan_scratch, uint32_t &digit, uint32_t &rest)
+constexpr uint32_t kNoEntry = 0xFFFFFFFFu;
+// (A key of 0 would be a NaN with every bit set, which no score is.  "No entry" needs no test of its
+// own that way: a range [lo, hi] with lo >= 1 leaves it out, since 0 - lo wraps beyond hi - lo.
+// Tested separately it was one lane mask per entry, kept from pass to pass and spilled.)
+__device__ __forceinline__ uint32_t real_key(uint32_t key) { return key > 1u ? key : 1u; }
+constexpr int kEntryBatch = 32;  // entries a thread loads before it looks at the first of them
+
+// Among the counted bins, taken from the highest down, the one at which `need` entries are reached:
+// its number, how many of its entries are needed, and how many it has.  Every thread sums eight
+// neighbouring bins (two 16-byte reads); need must not exceed the count of all bins.
+struct Bin {
+    uint32_t bin, need, count;
+};
+__device__ __forceinline__ Bin find_bin(uint32_t need, SharedSelect &sh, int tid)
 {
-    constexpr int per = kBins / kThreads;
-    uint32_t mine[per];
+    static_assert(kBins == 8 * kThreads, "eight bins per thread");
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+    const int first = kBins - 8 - 8 * tid;
+    const uint4 lo4 = *reinterpret_cast<const uint4 *>(sh.hist + first);
+    const uint4 hi4 = *reinterpret_cast<const uint4 *>(sh.hist + first + 4);
+    const uint32_t c[8] = {hi4.w, hi4.z, hi4.y, hi4.x, lo4.w, lo4.z, lo4.y, lo4.x};
     uint32_t sum = 0;
 #pragma unroll
-    for (int j = 0; j < per; ++j) {
-        mine[j] = hist[kBins - 1 - (threadIdx.x * per + j)];  // bins taken from the top
-        sum += mine[j];
-    }
-    uint32_t total;
-    uint32_t above = block_scan(sum, scan_scratch, total) - sum;
-    if (threadIdx.x == 0) {
-        found[0] = 0;      // need > total: every key qualifies
-        found[1] = need;
-    }
+    for (int j = 0; j < 8; ++j) sum += c[j];
+    const uint32_t incl = wave_scan(sum);
+    if (lane == 63) sh.wave_tot[wave] = incl;
     __syncthreads();
+    uint32_t above = incl - sum;
 #pragma unroll
-    for (int j = 0; j < per; ++j) {
-        if (above < need && need <= above + mine[j]) {
-            found[0] = (uint32_t)(kBins - 1 - (threadIdx.x * per + j));
-            found[1] = need - above;
+    for (int w = 0; w < kWaves; ++w) above += w < wave ? sh.wave_tot[w] : 0u;
+    if (above < need && need <= above + sum) {  // one thread
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (above < need && need <= above + c[j]) {
+                sh.found[0] = (uint32_t)(first + 7 - j);
+                sh.found[1] = need - above;
+                sh.found[2] = c[j];
+            }
+            above += c[j];
         }
-        above += mine[j];
     }
     __syncthreads();
-    digit = found[0];
-    rest = found[1];
-    __syncthreads();
+    return Bin{uni(sh.found[0]), uni(sh.found[1]), uni(sh.found[2])};
+}
+
+// Values to a bin, as a power of two, of a level that splits a range whole.
+__device__ __forceinline__ int level_shift(uint32_t range)
+{
+    return range >= (uint32_t)kBins ? 32 - __builtin_clz(range) - kBinBits : 0;
+}
+
+// The entries that pass `among` and whose value lies in [lo, hi], `count` of them, of which the
+// `need` with the largest values are wanted.
+struct Cut {
+    uint32_t lo, hi, need, count;
+};
+// Narrows [lo, hi] around the need-th largest value until at most `few` entries are left in it, or
+// all that are left are equal.  A level splits the range it is given evenly, 2^shift values to a bin
+// (the last bin takes what lies beyond), not by fixed digits of the value: the candidates of
+// a row lie within a few octaves, whose top digits are a few dozen different ones, and 64 lanes
+// that count into the same few LDS words are served one after the other.
+template <typename Entries, typename Val, typename Among>
+__device__ __forceinline__ Cut narrow(const Entries &E, Cut cut, int shift, uint32_t few, Val val, Among among,
+                                      SharedSelect &sh)
+{
+    const uint32_t lane = (uint32_t)E.tid & 63u;
+    while (cut.hi != cut.lo && cut.count > few) {  // (uniform)
+        const uint32_t range = cut.hi - cut.lo;
+        uint4 *h4 = reinterpret_cast<uint4 *>(sh.hist);
+        h4[E.tid] = h4[E.tid + kThreads] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+        E.for_each([&](uint32_t key, uint32_t pos) {
+            const uint32_t at = val(key, pos) - cut.lo;
+            const bool in = among(key, pos) & (at <= range);
+            atomicAdd(&sh.hist[in ? min(at >> shift, (uint32_t)kBins - 1u) : (uint32_t)kBins + lane], 1u);
+        });
+        __syncthreads();
+        const Bin b = find_bin(cut.need, sh, E.tid);
+        cut.lo += b.bin << shift;
+        const uint32_t left = cut.hi - cut.lo, width = (1u << shift) - 1u;
+        cut.hi = b.bin == (uint32_t)kBins - 1u || left < width ? cut.hi : cut.lo + width;
+        cut.need = b.need;
+        cut.count = b.count;
+        shift = level_shift(cut.hi - cut.lo);
+    }
+    return cut;
 }
 
 template <int NH>
@@ -238,7 +292,11 @@ __device__ __forceinline__ float tile_pooled_score(const uint4 (&kr)[4], const u
 // plus sel_margin (six, unless the caller changes it) standard deviations; the streamed rows
 // that reach it are then very likely at least n and a few thousand more at most.  Whatever the sample yields, the select unit
 // checks the candidate count and ranks the whole row itself when the list cannot be used.
-// The sample is one row at a hashed offset inside each of 2048 to 4096 equal strata.
+// The sample is one row at a hashed offset inside each of 1024 to 4096 equal strata: 2048 and more
+// for long rows, fewer where 64 sampled rows are expected among the top n all the same.
+//
+// Latency bounds it (the row's streaming pieces wait for it at the end of their rows): one round
+// of row loads, a hand-over, one round of key loads, two levels of bins.
 // `publish` != nullptr (launches whose streaming runs beside this unit): the threshold goes, with
 // the launch's generation `gen` in the upper half, into *publish by one 64-bit atomic store, which
 // the row's pieces poll; the candidate counter is not touched (it is zero between uses, and the
@@ -246,6 +304,21 @@ __device__ __forceinline__ float tile_pooled_score(const uint4 (&kr)[4], const u
 // `split` (launches whose streaming waits for the threshold): the row's sample is dealt to n_sub
 // units, each of which reads its share of the rows in one round of loads and leaves the keys in
 // device memory; the unit that arrives last ranks them.  Nobody waits for anybody.
+constexpr int kSampleRegs = kSampleTilesMax * 16 / kThreads;
+struct SampleEntries {  // the sample's keys, in registers (0: none)
+    uint32_t key[kSampleRegs];
+    int tid;
+    int left;
+    template <typename F>
+    __device__ __forceinline__ void for_each(F f) const
+    {
+#pragma unroll
+        for (int e = 0; e < kSampleRegs; ++e) {
+            if (e % 4 == 0 && e * kThreads >= left) break;  // (uniform)
+            f(key[e], 0u);
+        }
+    }
+};
 struct ThrSplit {
     int sub = 0, n_sub = 1;
     uint32_t *keys = nullptr;     // [sample size] scratch of this score row
@@ -285,6 +358,8 @@ __device__ __forceinline__ void threshold_unit(const Common &c, const LayerDesc 
     }
     int n_tiles = L / 1024;
     n_tiles = n_tiles < kSampleTilesMin ? kSampleTilesMin : (n_tiles > kSampleTilesMax ? kSampleTilesMax : n_tiles);
+    const int enough = (int)(4.0f * (float)L / (float)n) + 1;  // tiles of 16 rows that hold 64 of the top n
+    n_tiles = enough < n_tiles ? (enough > kSampleTilesFew ? enough : kSampleTilesFew) : n_tiles;
     const int n_sample = n_tiles * 16;
     const int g = p.rgroup[rgi];
     const uint32_t hmask = p.rmask[g] & ((1u << c.group) - 1u);
@@ -292,8 +367,6 @@ __device__ __forceinline__ void threshold_unit(const Common &c, const LayerDesc 
     load_q<NH>(c, p.q, b, g, hmask, qf);
     const uint16_t *kbase = p.k_cache + (int64_t)b * c.stride_b + (int64_t)g * c.stride_h;
     const float sel_mul = c.scale / (float)NH;
-    for (int i = tid; i < 4096; i += kThreads) sh.hist[i] = 0;
-    __syncthreads();
 
     constexpr int kBatch = 8;  // groups of 16 sampled rows a wavefront has in flight
     // One row at a hashed offset in each of n_sample equal strata of rows 0 .. L-2 (the newest
@@ -310,8 +383,8 @@ __device__ __forceinline__ void threshold_unit(const Common &c, const LayerDesc 
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int i = t * 16 + 4 * j + rs;  // sample number
-                const uint32_t hsh = ((uint32_t)i * 2654435761u + (uint32_t)row * 40503u) >> 12;
-                const int pos = i * stratum + (int)(hsh % (uint32_t)stratum);
+                const uint32_t hsh = ((uint32_t)i * 2654435761u + (uint32_t)row * 40503u) * 2246822519u;
+                const int pos = i * stratum + (int)__umulhi(hsh, (uint32_t)stratum);
                 kr[u][j] = gload_u4(kbase + (int64_t)pos * c.stride_t + ch * 8);
             }
         }
@@ -319,12 +392,10 @@ __device__ __forceinline__ void threshold_unit(const Common &c, const LayerDesc 
         for (int u = 0; u < kBatch; ++u) {
             const uint32_t key = ordered_key(tile_pooled_score<NH>(kr[u], qf, sel_mul));
             if (t0 + u < t_hi && ch < 4) {
-                if (split.n_sub > 1) {
+                if (split.n_sub > 1)
                     gstore_through(split.keys + (t0 + u) * 16 + 4 * ch + rs, key);
-                } else {
+                else
                     sh.samp[(t0 + u) * 16 + 4 * ch + rs] = key;
-                    atomicAdd(&sh.hist[key >> 20], 1u);
-                }
             }
         }
     }
@@ -344,30 +415,29 @@ __device__ __forceinline__ void threshold_unit(const Common &c, const LayerDesc 
         __syncthreads();
         if (!last) return;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        for (int i = tid; i < n_sample; i += kThreads) {
-            const uint32_t key = gload(split.keys + i);
-            sh.samp[i] = key;
-            atomicAdd(&sh.hist[key >> 20], 1u);
-        }
+    } else {
+        __syncthreads();
     }
-    __syncthreads();
+    SampleEntries E;
+    E.tid = tid;
+    E.left = n_sample;
+#pragma unroll
+    for (int e = 0; e < kSampleRegs; ++e) {
+        if (e % 4 == 0 && e * kThreads >= n_sample) break;
+        const int i = e * kThreads + tid;
+        const int at = i < n_sample ? i : n_sample - 1;
+        const uint32_t key = split.n_sub > 1 ? gload(split.keys + at) : sh.samp[at];
+        E.key[e] = i < n_sample ? real_key(key) : 0u;
+    }
     const float f = (float)n_sample * (float)n / (float)L;
     const float want = f + c.sel_margin * sqrtf(f) + 6.0f;
     const uint32_t target = want < 1.0f ? 1u : (want > (float)n_sample ? (uint32_t)n_sample : (uint32_t)want);
     uint32_t t_key = 0;
     if (target < (uint32_t)n_sample) {
-        // the sample's target-th largest key: top 12 bits, then the next 10
-        uint32_t d1, rest1, d2, rest2;
-        find_digit<4096>(sh.hist, target, sh.found, pool.scan, d1, rest1);
-        for (int i = tid; i < 1024; i += kThreads) sh.hist[i] = 0;
-        __syncthreads();
-        for (int i = tid; i < n_sample; i += kThreads) {
-            const uint32_t key = sh.samp[i];
-            if ((key >> 20) == d1) atomicAdd(&sh.hist[(key >> 10) & 1023u], 1u);
-        }
-        __syncthreads();
-        find_digit<1024>(sh.hist, rest1, sh.found, pool.scan, d2, rest2);
-        t_key = (d1 << 20) | (d2 << 10);
+        // the lower end of a narrow range of keys around the sample's target-th largest
+        t_key = narrow(
+            E, Cut{1u, 0xFFFFFFFFu, target, (uint32_t)n_sample}, 32 - kBinBits, 2u, [](uint32_t key, uint32_t) { return key; },
+            [](uint32_t, uint32_t) { return true; }, sh).lo;
     }
     emit(t_key);
 }
@@ -415,26 +485,31 @@ __device__ __forceinline__ void score_row_unit(const Common &c, const LayerDesc 
 // everything that decides whether an entry counts into one flag, with bitwise operators, and
 // guard a single LDS operation with it: short-circuit conditions made the compiler keep a lane
 // mask per entry and condition, spill them, and branch several times per entry.
-constexpr uint32_t kNoEntry = 0xFFFFFFFFu;
-// (A key of 0 would be a NaN with every bit set, which no score is.  "No entry" needs no test of its
-// own that way: a range [lo, hi] with lo >= 1 leaves it out, since 0 - lo wraps beyond hi - lo.
-// Tested separately it was one lane mask per entry, kept from pass to pass and spilled.)
-__device__ __forceinline__ uint32_t real_key(uint32_t key) { return key > 1u ? key : 1u; }
-constexpr int kEntryBatch = 32;  // entries a thread loads before it looks at the first of them
 constexpr int kSelRegs = 40;     // entries one thread keeps in registers
+constexpr int kSelHead = 8;      // and those of them that it asks for first
 struct RegEntries {           // up to kThreads * kSelRegs list entries, loaded once: beside a streaming
     uint32_t key[kSelRegs], pos[kSelRegs];  // launch every pass over memory costs a microsecond or two
     int tid;
     int left;                 // entries, uniform: whole groups of eight registers beyond them are skipped
-    __device__ __forceinline__ void load(const unsigned long long *list, int total, int tid_)
+    unsigned long long head[kSelHead];
+    // The first entries of a list with room for `cap`, asked for before its length is known.
+    __device__ __forceinline__ void load_head(const unsigned long long *list, int cap, int tid_)
     {
         tid = tid_;
+#pragma unroll
+        for (int e = 0; e < kSelHead; ++e) {
+            const int i = e * kThreads + tid;
+            head[e] = gload(list + (i < cap ? i : cap - 1));
+        }
+    }
+    __device__ __forceinline__ void load(const unsigned long long *list, int total)
+    {
         left = total;
 #pragma unroll
         for (int e = 0; e < kSelRegs; ++e) {
             if (e % 8 == 0 && e * kThreads >= left) break;
             const int i = e * kThreads + tid;
-            const unsigned long long v = gload(list + (i < total ? i : total - 1));
+            const unsigned long long v = e < kSelHead ? head[e] : gload(list + (i < total ? i : total - 1));
             key[e] = i < total ? real_key((uint32_t)v) : 0u;
             pos[e] = i < total ? (uint32_t)(v >> 32) : kNoEntry;
         }
@@ -504,87 +579,6 @@ struct RowEntries {           // every row of the sequence, from its recomputed 
     __device__ __forceinline__ void for_each(F f) const { for_window(0u, (uint32_t)total, f); }
 };
 
-// Among the counted bins, taken from the highest down, the one at which `need` entries are reached:
-// its number, how many of its entries are needed, and how many it has.  Every thread sums eight
-// neighbouring bins (two 16-byte reads); need must not exceed the count of all bins.
-struct Bin {
-    uint32_t bin, need, count;
-};
-__device__ __forceinline__ Bin find_bin(uint32_t need, SharedSelect &sh, int tid)
-{
-    static_assert(kBins == 8 * kThreads, "eight bins per thread");
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int first = kBins - 8 - 8 * tid;
-    const uint4 lo4 = *reinterpret_cast<const uint4 *>(sh.hist + first);
-    const uint4 hi4 = *reinterpret_cast<const uint4 *>(sh.hist + first + 4);
-    const uint32_t c[8] = {hi4.w, hi4.z, hi4.y, hi4.x, lo4.w, lo4.z, lo4.y, lo4.x};
-    uint32_t sum = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) sum += c[j];
-    const uint32_t incl = wave_scan(sum);
-    if (lane == 63) sh.wave_tot[wave] = incl;
-    __syncthreads();
-    uint32_t above = incl - sum;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) above += w < wave ? sh.wave_tot[w] : 0u;
-    if (above < need && need <= above + sum) {  // one thread
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            if (above < need && need <= above + c[j]) {
-                sh.found[0] = (uint32_t)(first + 7 - j);
-                sh.found[1] = need - above;
-                sh.found[2] = c[j];
-            }
-            above += c[j];
-        }
-    }
-    __syncthreads();
-    return Bin{uni(sh.found[0]), uni(sh.found[1]), uni(sh.found[2])};
-}
-
-// Values to a bin, as a power of two, of a level that splits a range whole.
-__device__ __forceinline__ int level_shift(uint32_t range)
-{
-    return range >= (uint32_t)kBins ? 32 - __builtin_clz(range) - kBinBits : 0;
-}
-
-// The entries that pass `among` and whose value lies in [lo, hi], `count` of them, of which the
-// `need` with the largest values are wanted.
-struct Cut {
-    uint32_t lo, hi, need, count;
-};
-// Narrows [lo, hi] around the need-th largest value until at most `few` entries are left in it, or
-// all that are left are equal.  A level splits the range it is given evenly, 2^shift values to a bin
-// (the last bin takes what lies beyond), not by fixed digits of the value: the candidates of
-// a row lie within a few octaves, whose top digits are a few dozen different ones, and 64 lanes
-// that count into the same few LDS words are served one after the other.
-template <typename Entries, typename Val, typename Among>
-__device__ __forceinline__ Cut narrow(const Entries &E, Cut cut, int shift, uint32_t few, Val val, Among among,
-                                      SharedSelect &sh)
-{
-    while (cut.hi != cut.lo && cut.count > few) {  // (uniform)
-        const uint32_t range = cut.hi - cut.lo;
-        uint4 *h4 = reinterpret_cast<uint4 *>(sh.hist);
-        h4[E.tid] = h4[E.tid + kThreads] = make_uint4(0, 0, 0, 0);
-        __syncthreads();
-        E.for_each([&](uint32_t key, uint32_t pos) {
-            const uint32_t at = val(key, pos) - cut.lo;
-            const bool in = among(key, pos) & (at <= range);
-            if (in) atomicAdd(&sh.hist[min(at >> shift, (uint32_t)kBins - 1u)], 1u);
-        });
-        __syncthreads();
-        const Bin b = find_bin(cut.need, sh, E.tid);
-        cut.lo += b.bin << shift;
-        const uint32_t left = cut.hi - cut.lo, width = (1u << shift) - 1u;
-        cut.hi = b.bin == (uint32_t)kBins - 1u || left < width ? cut.hi : cut.lo + width;
-        cut.need = b.need;
-        cut.count = b.count;
-        shift = level_shift(cut.hi - cut.lo);
-    }
-    return cut;
-}
-
 // Exact top-n of the `total` entries by key, ties to the lower position (Eq. 2), written to dst in
 // ascending position order.  The entries may come in any order.  The range of keys is narrowed
 // around the n-th largest until it holds at most kFewKeys entries, which are then ranked against
@@ -626,7 +620,18 @@ __device__ __forceinline__ void select_from(const Entries &E, uint32_t floor_key
         if ((uint32_t)tid < cut.count) {
             const unsigned long long mine = sh.few[tid];
             uint32_t before = 0;
-            for (uint32_t i = 0; i < cut.count; ++i) before += (uint32_t)(sh.few[i] > mine);
+            // (pairs, eight at a time: read one by one, each read waits for the one before it; what lies
+            // past the last entry is not counted)
+            for (uint32_t i0 = 0; i0 < cut.count; i0 += 16) {
+                ulonglong2 v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = reinterpret_cast<const ulonglong2 *>(sh.few)[i0 / 2 + u];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    before += (uint32_t)((i0 + 2 * u < cut.count) & (v[u].x > mine));
+                    before += (uint32_t)((i0 + 2 * u + 1 < cut.count) & (v[u].y > mine));
+                }
+            }
             if (before < cut.need) my_few = ~(uint32_t)mine;
         }
     } else if (!all) {
@@ -648,7 +653,7 @@ __device__ __forceinline__ void select_from(const Entries &E, uint32_t floor_key
             const uint32_t rel = pos - w0;  // "no entry" lies outside every window
             const bool in = key - cut.lo <= cut.hi - cut.lo;
             const bool take = ((key > cut.hi) | (in & (all | (by_pos & (pos <= pos_cut))))) & (rel < span);
-            if (take) atomicOr(&sh.map[rel >> 5].x, 1u << (rel & 31u));
+            atomicOr(&sh.map[take ? rel >> 5 : (uint32_t)(kMapWords + lane)].x, 1u << (rel & 31u));
         });
         if (my_few - w0 < span) atomicOr(&sh.map[(my_few - w0) >> 5].x, 1u << ((my_few - w0) & 31u));
         __syncthreads();
@@ -676,7 +681,7 @@ __device__ __forceinline__ void select_from(const Entries &E, uint32_t floor_key
         // write-through stores: the set is in device memory once the unit's stores have
         // completed, whoever reads it next (a gather piece of the same launch, on another XCD,
         // after an acquire).
-        constexpr uint32_t kStage = (uint32_t)(sizeof(sh.samp) / sizeof(sh.samp[0]));
+        constexpr uint32_t kStage = (uint32_t)(sizeof(sh.samp) / sizeof(sh.samp[0])) - 64u;
         const uint32_t end = base + tot;
         for (uint32_t c0 = base; c0 < end; c0 += kStage) {
             E.for_window(w0, span, [&](uint32_t, uint32_t pos) {
@@ -685,7 +690,7 @@ __device__ __forceinline__ void select_from(const Entries &E, uint32_t floor_key
                 const uint32_t bit = 1u << (rel & 31u);
                 const uint32_t at = word.y + (uint32_t)__builtin_popcount(word.x & (bit - 1u)) - c0;
                 const bool put = (rel < span) & ((word.x & bit) != 0) & (at < kStage);
-                if (put) sh.samp[at] = pos;
+                sh.samp[put ? at : kStage + (uint32_t)lane] = pos;
             });
             __syncthreads();
             const uint32_t m = end - c0 < kStage ? end - c0 : kStage;
@@ -875,6 +880,8 @@ __device__ __forceinline__ void select_unit(const Common &c, const LayerDesc &p,
     }
     const int64_t row = (int64_t)b * p.n_rgroups + rgi;
     const unsigned long long *list = p.list + row * (int64_t)c.list_row;
+    RegEntries E;
+    E.load_head(list, c.list_row, fresh_tid());
     // block-granular: the streaming left every block's score at its place in the list
     const int total = c.block_shift ? L : gload(p.list_count + row);
     const uint32_t floor_key = c.block_shift ? 0u : gload(p.thr + row);  // no entry lies below it
@@ -893,14 +900,13 @@ __device__ __forceinline__ void select_unit(const Common &c, const LayerDesc &p,
     }
     int keep = n;  // what is selected in the end: n, or fewer under a probability rule
     if (total >= n && total <= kThreads * kSelRegs && total <= c.list_row) {
-        RegEntries E;
-        E.load(list, total, fresh_tid());
+        E.load(list, total);
         if (PROB && by_prob) keep = rule_keeps(c, E, n, lse, sh, pool);
         select_from(E, floor_key, total, keep, L, dst, sh, pool);
     } else if (total >= n && total <= c.list_row) {
-        const ListEntries E{list, total, fresh_tid()};
-        if (PROB && by_prob) keep = rule_keeps(c, E, n, lse, sh, pool);
-        select_from(E, floor_key, total, keep, L, dst, sh, pool);
+        const ListEntries M{list, total, fresh_tid()};
+        if (PROB && by_prob) keep = rule_keeps(c, M, n, lse, sh, pool);
+        select_from(M, floor_key, total, keep, L, dst, sh, pool);
     } else {
         // too few candidates reached the threshold, or too many for the list: rank the row
         // (token-granular only: a block list is always complete)
@@ -914,9 +920,9 @@ __device__ __forceinline__ void select_unit(const Common &c, const LayerDesc &p,
         }
         __threadfence();
         __syncthreads();  // the scores are read back by other threads of the workgroup
-        const RowEntries E{sel, len, fresh_tid()};
-        if (PROB && by_prob) keep = rule_keeps(c, E, n, lse, sh, pool);
-        select_from(E, 0u, len, keep, L, dst, sh, pool);
+        const RowEntries M{sel, len, fresh_tid()};
+        if (PROB && by_prob) keep = rule_keeps(c, M, n, lse, sh, pool);
+        select_from(M, 0u, len, keep, L, dst, sh, pool);
     }
     for (int i = keep + threadIdx.x; i < c.k; i += kThreads) gstore_through(dst + i, (int32_t)-1);
     if (clear_count && threadIdx.x == 0) gstore(p.list_count + row, (int32_t)0);
