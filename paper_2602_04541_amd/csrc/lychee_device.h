@@ -43,8 +43,9 @@ struct SharedSelect {
     uint32_t range[2][kWaves];
 };
 struct SharedCombine {
-    float w[kMaxWg];
-    float red[kMaxGroup * (kThreads / 32) * kHeadDim];  // (combine_unit uses the first head's share)
+    float w[kMaxGroup][kMaxWg];   // per head: a slot's running maximum, then its weight
+    float ls[kMaxGroup][kMaxWg];  // and its sum of exp
+    float red[(kThreads / 32) * kHeadDim];
     float l[kMaxGroup];
 };
 union SharedUnit {
@@ -152,6 +153,15 @@ __device__ __forceinline__ uint32_t wave_scan(uint32_t x)
     return x;
 }
 
+__device__ __forceinline__ float wave_max_f(float x)
+{
+    x = fmaxf(x, dpp_f32<0xB1>(x));
+    x = fmaxf(x, dpp_f32<0x4E>(x));
+    x = fmaxf(x, dpp_f32<0x141>(x));
+    x = fmaxf(x, dpp_f32<0x140>(x));
+    return max_halves32(max_rows16(x));
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 constexpr float kLog2e = 1.4426950408889634f;
 __device__ __forceinline__ float bf16_lo(uint32_t u) { return __builtin_bit_cast(float, u << 16); }
@@ -170,6 +180,7 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float x)
 // load pipeline of the streaming loop; so every access goes through these casts.
 #define LYCHEE_GLOBAL __attribute__((address_space(1)))
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
 
 template <typename T>
 __device__ __forceinline__ T gload(const T *p)
@@ -205,6 +216,11 @@ __device__ __forceinline__ float4 gload_f4(const float *p)
 {
     const f32x4_t r = *(const LYCHEE_GLOBAL f32x4_t *)p;
     return make_float4(r.x, r.y, r.z, r.w);
+}
+__device__ __forceinline__ float2 gload_f2(const float *p)
+{
+    const f32x2_t r = *(const LYCHEE_GLOBAL f32x2_t *)p;
+    return make_float2(r.x, r.y);
 }
 __device__ __forceinline__ uint4 gload_u4(const void *p)
 {

@@ -27,7 +27,7 @@ __device__ __forceinline__ void combine_unit(const Common &c, const LayerDesc &p
     for (int s = threadIdx.x; s < count; s += kThreads) {
         const float ls = gload(ml + 2 * s + 1);
         const float w = ls > 0.0f ? fast_exp2((gload(ml + 2 * s) - M) * c.scale_log2e) : 0.0f;
-        sh.w[s] = w;
+        sh.w[0][s] = w;
         l_loc = fmaf(w, ls, l_loc);
     }
     const float lsum = block_sum(l_loc, pool.fred);  // also publishes sh.w
@@ -42,7 +42,7 @@ __device__ __forceinline__ void combine_unit(const Common &c, const LayerDesc &p
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const int s = s0 + kLanes * u;
-            wv[u] = s < count ? sh.w[s] : 0.0f;
+            wv[u] = s < count ? sh.w[0][s] : 0.0f;
             v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
             if (wv[u] > 0.0f) v[u] = gload_f4(po + (int64_t)s * kHeadDim + c4 * 4);
         }
@@ -67,100 +67,92 @@ __device__ __forceinline__ void combine_unit(const Common &c, const LayerDesc &p
 }
 
 // The same merge for all NH heads of a segment at once, by the workgroup that has just written the
-// segment's last partial: every load of a group of slots - the (m, l) pairs and the partial
-// outputs of all heads - is issued before the first one is used, so that a group costs about one
-// round trip to memory however many heads it has (the heads one after the other, each with its
-// own rounds of dependent loads, took 20 us for the four heads of a dense layer's segment).  A
-// group is 64 slots for one or two heads and 32 for three or four: 64 registers of loads in
-// flight either way.  Each wavefront keeps the running maximum and sum of every head itself
-// (redundantly: no barrier between groups); thread (o8, c4) sums slots o8, o8 + 8, ... of a
-// group for columns 4 c4 .. 4 c4 + 3, and the eight sums per column are added in a fixed order
-// at the end.
+// segment's last partial.  It stands at the end of the layer's chain and is latency, not bytes: the
+// partial outputs of up to kGrp * kU slots are asked for before anything else; meanwhile wavefront
+// h turns head h's (m, l) pairs into weights (in LDS); then thread (head, group, column quad)
+// sums its group's slots, and the groups are added in a fixed order.  (With every wavefront
+// keeping every head's running maximum and fetching each weight through the LDS crossbar, 12
+// exchanges per head and round and one more per slot, the merge took 6.0 us for 4 heads of 43
+// slots, loads in the L2 or not.)
 template <int NH>
 __device__ __forceinline__ void combine_segment(const Common &c, const LayerDesc &p, int b, int g, uint32_t hmask,
                                                 int count, SharedCombine &sh)
 {
-    constexpr int kU = NH <= 2 ? 8 : 4;  // slots per thread and group
-    constexpr int kSlots = 8 * kU;       // slots per group
+    constexpr int kGrp = NH == 1 ? 8 : (NH == 2 ? 4 : 2);  // slot groups of a head
+    constexpr int kU = 16;                                 // slots a thread has in flight
     const int tid = fresh_tid();
     const int lane = tid & 63;
-    const int o8 = tid >> 5;  // which eighth of a group's slots
+    const int wave = tid >> 6;
     const int c4 = tid & 31;  // which 4 columns
-    int64_t bh[NH];
-    {
+    const int h = (tid >> 5) / kGrp;
+    const int grp = (tid >> 5) % kGrp;
+    // (sequence, head) row of the i-th head of the segment
+    auto row_of = [&](int i) {
         uint32_t mk = hmask;
 #pragma unroll
-        for (int h = 0; h < NH; ++h) {
-            bh[h] = (int64_t)b * c.n_q_heads + g * c.group + __builtin_ctz(mk);
-            mk &= mk - 1;
+        for (int j = 1; j < NH; ++j) mk = j <= i ? mk & (mk - 1) : mk;
+        return (int64_t)b * c.n_q_heads + g * c.group + __builtin_ctz(mk);
+    };
+    const float *po = p.part_o + row_of(h < NH ? h : 0) * c.part_stride * kHeadDim + c4 * 4;
+    float4 v[kU];
+    auto fetch = [&](int s0) {
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            if (u % 4 == 0 && s0 + kGrp * u >= count) break;  // (uniform)
+            const int s = s0 + kGrp * u + grp;
+            v[u] = gload_f4(po + (int64_t)(s < count ? s : count - 1) * kHeadDim);
         }
+    };
+    fetch(0);
+    if (wave < NH) {
+        const float *pm = p.part_ml + row_of(wave) * c.part_stride * 2;
+        float M = kMinusBig;
+        for (int s = lane; s < count; s += 64) {
+            const float2 ml = gload_f2(pm + 2 * s);
+            const float m = ml.y > 0.0f ? ml.x : kMinusBig;  // (a piece without a valid row leaves l = 0)
+            sh.w[wave][s] = m;
+            sh.ls[wave][s] = ml.y > 0.0f ? ml.y : 0.0f;
+            M = fmaxf(M, m);
+        }
+        M = wave_max_f(M);
+        float l = 0.0f;
+        for (int s = lane; s < count; s += 64) {
+            const float ls = sh.ls[wave][s];
+            const float w = ls > 0.0f ? fast_exp2((sh.w[wave][s] - M) * c.scale_log2e) : 0.0f;
+            sh.w[wave][s] = w;
+            l = fmaf(w, ls, l);
+        }
+        l = sum_halves32(sum_rows16(row16_sum(l)));
+        if (lane == 0) sh.l[wave] = l;
     }
-    float M[NH], Ls[NH];
-    float4 acc[NH];
-#pragma unroll
-    for (int h = 0; h < NH; ++h) {
-        M[h] = kMinusBig;
-        Ls[h] = 0.0f;
-        acc[h] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    for (int s0 = 0; s0 < count; s0 += kSlots) {
-        float2 ml[NH];
-        float4 v[NH][kU];
-        const bool mine = lane < kSlots && s0 + lane < count;  // this lane holds a slot of the group
-        const int sl = mine ? s0 + lane : count - 1;
-#pragma unroll
-        for (int h = 0; h < NH; ++h) {
-            const float *pm = p.part_ml + (bh[h] * c.part_stride + sl) * 2;
-            ml[h] = make_float2(gload(pm), gload(pm + 1));
+    __syncthreads();
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (h < NH) {
+        for (int s0 = 0;;) {
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
-                int s = s0 + o8 + 8 * u;
-                s = s < count ? s : count - 1;
-                v[h][u] = gload_f4(p.part_o + (bh[h] * c.part_stride + s) * kHeadDim + c4 * 4);
+                if (u % 4 == 0 && s0 + kGrp * u >= count) break;
+                const int s = s0 + kGrp * u + grp;
+                const float w = s < count ? sh.w[h][s] : 0.0f;
+                acc.x = fmaf(w, v[u].x, acc.x);
+                acc.y = fmaf(w, v[u].y, acc.y);
+                acc.z = fmaf(w, v[u].z, acc.z);
+                acc.w = fmaf(w, v[u].w, acc.w);
             }
+            s0 += kGrp * kU;
+            if (s0 >= count) break;
+            fetch(s0);
         }
-#pragma unroll
-        for (int h = 0; h < NH; ++h) {
-            const bool live = mine && ml[h].y > 0.0f;  // (a piece without a valid row leaves l = 0)
-            float mg = live ? ml[h].x : kMinusBig;
-#pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) mg = fmaxf(mg, __shfl_xor(mg, d));
-            const float m_new = fmaxf(M[h], mg);
-            const float alpha = fast_exp2((M[h] - m_new) * c.scale_log2e);
-            M[h] = m_new;
-            const float wl = live ? fast_exp2((ml[h].x - m_new) * c.scale_log2e) : 0.0f;  // this lane's slot
-            float lg = wl * ml[h].y;
-#pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) lg += __shfl_xor(lg, d);
-            Ls[h] = Ls[h] * alpha + lg;
-            acc[h].x *= alpha, acc[h].y *= alpha, acc[h].z *= alpha, acc[h].w *= alpha;
-#pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const float wu = __shfl(wl, o8 + 8 * u);  // (slots past the end carry weight 0)
-                acc[h].x = fmaf(wu, v[h][u].x, acc[h].x);
-                acc[h].y = fmaf(wu, v[h][u].y, acc[h].y);
-                acc[h].z = fmaf(wu, v[h][u].z, acc[h].z);
-                acc[h].w = fmaf(wu, v[h][u].w, acc[h].w);
-            }
-        }
-    }
-#pragma unroll
-    for (int h = 0; h < NH; ++h) {
-        reinterpret_cast<float4 *>(sh.red + (h * 8 + o8) * kHeadDim)[c4] = acc[h];
-        if (tid == 0) sh.l[h] = Ls[h];
+        reinterpret_cast<float4 *>(sh.red + (h * kGrp + grp) * kHeadDim)[c4] = acc;
     }
     __syncthreads();
     for (int i = tid; i < NH * kHeadDim; i += kThreads) {
-        const int h = i / kHeadDim, col = i % kHeadDim;
+        const int hh = i / kHeadDim, col = i % kHeadDim;
         float o = 0.0f;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) o += sh.red[(h * 8 + j) * kHeadDim + col];
-        const float l = sh.l[h];
-        // (bh[h] with a run-time h: picked without indexing the register array)
-        int64_t row = bh[0];
-#pragma unroll
-        for (int hh = 1; hh < NH; ++hh) row = h == hh ? bh[hh] : row;
-        gstore(p.out + row * kHeadDim + col, f32_to_bf16_rne(l > 0.0f ? o / l : 0.0f));
+        for (int j = 0; j < kGrp; ++j) o += sh.red[(hh * kGrp + j) * kHeadDim + col];
+        const float l = sh.l[hh];
+        gstore(p.out + row_of(hh) * kHeadDim + col, f32_to_bf16_rne(l > 0.0f ? o / l : 0.0f));
     }
     __syncthreads();
 }
