@@ -448,9 +448,10 @@ int check_layer_space(const lychee_shape &s, const LayerDesc &d)
 
 // One launch of lychee_layer_kernel: everything `cur`'s output needs (cur may be null: only the
 // pending select), with the select and set copies of `prev` (may be null) among its front units.
+// select_now: `cur`'s own sets are wanted from this launch (then `prev` is null; no probability rule).
 // Every check happens before the launch; nothing else is enqueued.
 int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, const int32_t *lengths,
-                 const LayerDesc *cur, const LayerDesc *prev, hipStream_t stream)
+                 const LayerDesc *cur, const LayerDesc *prev, hipStream_t stream, bool select_now = false)
 {
     if (cur == nullptr && prev == nullptr) return LYCHEE_OK;
     LayerLaunch p;
@@ -468,7 +469,10 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
     if (cur != nullptr) {
         p.cur = *cur;
         p.has_cur = 1;
-        if (cur->emit_sel && !blocks) units += (int64_t)s.batch * cur->n_rgroups * kThrSplit;
+        // (pieces know the thresholds of rows this short themselves; the units also keep a copy of the queries)
+        p.has_thr = cur->emit_sel && !blocks && (s.max_len > kDirectLen || cur->q_keep != nullptr);
+        if (p.has_thr) units += (int64_t)s.batch * cur->n_rgroups * kThrSplit;
+        if (select_now && cur->copy_keep) units += (int64_t)s.batch * (s.n_kv_heads - cur->n_rgroups);
         if (prev != nullptr)
             for (int g = 0; g < s.n_kv_heads; ++g)
                 if (cur->idx_src[g] != nullptr && cur->idx_src[g] == prev->idx_out &&
@@ -480,11 +484,26 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
         // only front units: one workgroup each, up to the usual grid
         p.c.n_wg = (int32_t)(units < 1 ? 1 : (units > W ? W : units));
     }
-    // The front units get up to a quarter of the grid to themselves (a handful of workgroups in a
-    // batch-1 call); a grid too small to set workgroups aside lets them take pieces afterwards.
+    // The front units get workgroups to themselves, which then have nothing else to do (a grid too small
+    // to set workgroups aside lets them take pieces afterwards): one unit each beside a short
+    // layer, which waits for them; beside a long one as many units in turn, about 10 us each,
+    // as fit a sixth of the streaming (5.5 ns a block of 64 rows at 6 TB/s; max_len bounds
+    // the lengths, which are on the device).  A batch of 8 at 96K set 103 workgroups of 512 aside
+    // for 15 of its 140 us; now 26.
     const int wg = p.c.n_wg;
-    const int front_max = cur == nullptr ? wg : (wg >= 8 ? wg / 4 : wg);
-    p.n_front = (int32_t)(units < front_max ? units : front_max);
+    int64_t aside = units;
+    if (cur != nullptr) {
+        const int64_t seg_blocks = (s.max_len + kBlockRows - 1) / kBlockRows;
+        int64_t rounds = (int64_t)cur->n_rgroups * s.batch * seg_blocks * 11 / 2 / 60000;
+        rounds = rounds < 1 ? 1 : rounds;
+        aside = (units + rounds - 1) / rounds;
+        const int64_t most = wg >= 8 ? wg / (rounds > 1 ? 16 : 4) : wg;
+        aside = aside < most ? aside : most;
+        if (aside < 1 && units > 0) aside = 1;
+    } else if (aside > wg) {
+        aside = wg;
+    }
+    p.n_front = (int32_t)aside;
     p.lead_blocks = ctx->select_lead;
     p.gen = reinterpret_cast<uint32_t *>(ctx->sync_dev + kSyncGen);
     p.exit_count = reinterpret_cast<uint32_t *>(ctx->sync_dev + kSyncExit);
@@ -494,7 +513,7 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
     p.thr_arrived = reinterpret_cast<uint32_t *>(ctx->sync_dev + kSyncArrived);
     const bool selects = prev != nullptr && prev->n_rgroups > 0;
     const bool collects = cur != nullptr && cur->emit_sel;
-    const int build = !(selects || collects) ? 0 : (s.prob_rule != 0 ? 2 : 1);
+    const int build = !(selects || collects) ? 0 : (s.prob_rule != 0 ? 2 : (select_now ? 3 : 1));
     if (!ctx->timing) return launch_layer(p, build, stream) == hipSuccess ? LYCHEE_OK : LYCHEE_EHIP;
     lychee_ctx::Rec rec{cur != nullptr ? LYCHEE_KERNEL_STREAM : LYCHEE_KERNEL_SELECT, take_event(ctx), take_event(ctx)};
     if (rec.start == nullptr || rec.stop == nullptr) return LYCHEE_EHIP;
@@ -684,7 +703,10 @@ int decode_attn(lychee_ctx *ctx, const lychee_shape *shape, const void *q, const
     d.copy_keep = 1;
     d.list_count = count_bank(ctx, 2);
     if ((rc = check_layer_space(*shape, d)) != LYCHEE_OK) return rc;
-    // idx_out is complete when the call's work is: the layer's launch, then its select alone
+    // idx_out is complete when the call's work is: the launch selects as its segments complete.  (The
+    // probability rules select in a launch of their own: inside the streaming one their registers
+    // spilled and cost it more than a launch: 95.7 against 85.7 us for Top-p at 128K.)
+    if (shape->prob_rule == 0) return layer_launch(ctx, *shape, w, lengths, &d, nullptr, stream, true);
     if ((rc = layer_launch(ctx, *shape, w, lengths, &d, nullptr, stream)) != LYCHEE_OK) return rc;
     return layer_launch(ctx, *shape, w, lengths, nullptr, &d, stream);
 }

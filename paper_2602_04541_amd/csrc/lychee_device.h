@@ -25,22 +25,27 @@ struct SharedAttn {
 };
 constexpr int kBinBits = 11;               // a level of the select splits its range of keys into 2048 bins
 constexpr int kBins = 1 << kBinBits;
-constexpr int kFewKeys = 256;              // so few entries are ranked against one another, one per thread
+constexpr int kLastKeys = 64;              // so few entries are ranked against one another, one per thread
 constexpr int kMapWords = 4096;            // words of the position bitmap: a window of 131072 positions
+constexpr int kStage = 8192;               // positions put in order in LDS at a time
+// (hist, bits and stage end in a word per lane where entries that do not count go: a store to a word
+// of its own costs less than a branch around the store for every entry)
 struct SharedSelect {
-    // (hist, map and samp end in a word per lane where entries that do not count go: a store to a
-    // word of its own costs less than a branch around the store for every entry)
     union {
-        uint32_t hist[4096 + 64];          // digit counts (threshold); bin counts (select)
-        unsigned long long mass[4096];     // probability mass per digit (Top-p)
-        uint2 map[kMapWords + 64];         // ordered write: bitmap word, positions chosen before it
+        uint32_t hist[kBins + 64];         // entries per bin
+        uint32_t bits[kMapWords + 64];     // ordered write: the chosen positions of a window
     };
-    uint32_t samp[kSampleTilesMax * 16 + 64];  // ordered keys of the threshold sample; staged positions
-    __align__(16) unsigned long long few[kFewKeys];  // (key, ~position) of the entries around the last place
-    uint32_t n_few;
+    uint16_t before[kMapWords];            //   positions chosen before a word, within its wavefront's share
+    union {
+        uint32_t samp[kSampleTilesMax * 16];  // ordered keys of the threshold sample
+        uint32_t stage[kStage + 64];          // staged positions
+        unsigned long long mass[kBins];       // probability mass per bin (Top-p)
+    };
+    __align__(16) unsigned long long last[kLastKeys];  // (key, ~position) of the entries around the last place
+    unsigned long long cutoff;
+    uint32_t n_last;
     uint32_t wave_tot[kWaves];
     uint32_t found[3];
-    uint32_t range[2][kWaves];
 };
 struct SharedCombine {
     float w[kMaxGroup][kMaxWg];   // per head: a slot's running maximum, then its weight
@@ -54,6 +59,11 @@ union SharedUnit {
 };
 struct SharedPool {
     int32_t ipre[kMaxItems + 1];         // first pooled block of every (layer, sequence) item
+    int32_t len[kMaxBatch];
+    uint32_t scan[kWaves + 1];
+    unsigned long long scan64[kWaves + 1];
+};
+struct SharedSmall {
     int32_t upre[4][kMaxLayers + 1];     // first small unit of every layer, per unit kind
     int32_t len[kMaxBatch];
     uint32_t scan[kWaves + 1];
@@ -210,6 +220,10 @@ __device__ __forceinline__ void gstore_through(uint32_t *p, uint32_t v)
 {
     __hip_atomic_store((LYCHEE_GLOBAL uint32_t *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ void gstore_through(unsigned long long *p, unsigned long long v)
+{
+    __hip_atomic_store((LYCHEE_GLOBAL unsigned long long *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 __device__ __forceinline__ float4 gload_f4(const float *p)
@@ -262,6 +276,13 @@ __device__ __forceinline__ int budget_of(const Common &c, int L)
         n = r < n ? (int)r : n;
     }
     return n;
+}
+
+// A score row of L positions of which n are selected whose threshold follows from the sizes: everything
+// is selected, or every row is a candidate.
+__device__ __forceinline__ bool needs_no_sample(int n, int L)
+{
+    return n == L || L <= kDirectLen || 2 * (int64_t)n >= L;
 }
 
 // Fields of a layer descriptor staged in LDS as 32-bit words.  The values are the same in

@@ -20,9 +20,8 @@ constexpr int kBlockRows = kWaves * kTileRows;  // cache rows per block of the p
 static_assert(kBlockRows == 64, "a pooled block is also the selection block of the block-granular variant");
 constexpr int kMaxWg = 1024;             // upper bound of the grid of one launch
 constexpr int kIdxChunk = 2048;          // set entries staged in LDS at a time
-constexpr int kSampleTilesMin = 128;     // the threshold sample: 128 to 256 tiles of 16 rows
+constexpr int kSampleTilesMin = 64;      // the threshold sample: 64 to 256 tiles of 16 rows
 constexpr int kSampleTilesMax = 256;
-constexpr int kSampleTilesFew = 64;      // fewer, where that still samples enough of the rows that will be chosen
 constexpr int kDirectLen = 4096;         // sequences this short are ranked without a threshold
 constexpr int kCandBuf = 256;            // candidates a wavefront collects in LDS between flushes
 constexpr int kThrSplit = 4;             // units that share a score row's threshold sample in a layer launch
@@ -120,7 +119,9 @@ struct LaunchPlan {
 //   G pieces      cur's sparse gathers; a piece of a KV head in gate_mask polls until the front
 //                 unit that writes that head's inherited set has published it
 //   combine       the workgroup that writes the last partial of a (sequence, KV head, kind)
-//                 segment merges the segment's partials into `out`
+//                 segment merges the segment's partials into `out`; in the build that selects for
+//                 its own layer it then selects the segment's set, and cur's kept sets are
+//                 copied by front units
 // Flags carry the launch's generation, a counter in device memory that the last workgroup to
 // finish advances: a flag of an earlier launch, or of an earlier replay of a captured launch,
 // never matches.
@@ -129,6 +130,7 @@ struct LayerLaunch {
     LayerDesc cur;         // the layer whose rows are streamed and gathered (has_cur)
     LayerDesc prev;        // the layer whose select is pending (has_prev)
     int32_t has_cur, has_prev;
+    int32_t has_thr;       // the launch computes cur's selection thresholds
     int32_t n_front;       // workgroups that run front units
     int32_t lead_blocks;   // blocks of 64 rows the device streams while a select runs: how much
                            // later than the streaming the gated gathers can start
@@ -141,7 +143,7 @@ struct LayerLaunch {
     uint32_t *thr_arrived; // [B * n_rgroups] threshold units of a score row that have left their keys (likewise)
 };
 // 0: no selection anywhere in the launch (the dense baseline); 1: the hybrid build; 2: the one
-// that also knows the probability rules
+// that also knows the probability rules; 3: the hybrid build that selects for `cur` instead of `prev`
 hipError_t launch_layer(const LayerLaunch &plan, int build, hipStream_t stream);
 
 hipError_t launch_units(const LaunchPlan &plan, hipStream_t stream);

@@ -47,6 +47,7 @@ struct SharedLayer {
     uint32_t nb[2][kMaxBatch];     // per kind: blocks of one segment of every sequence
     int32_t run[3];                // the piece loop: next block of this workgroup's run, blocks per run, padded
     uint32_t gen;                  // the generation of this launch's flags
+    uint32_t wanted[kMaxBatch * kMaxKvHeads / 32];  // bit per score row: this workgroup selects its set
 };
 union SharedRole {
     SharedAttn attn;  // a piece
@@ -86,9 +87,13 @@ __device__ __forceinline__ void await_set(const uint32_t *flag, uint32_t gen, ui
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
 }
 
+// SELECTS: 0 no selection in the launch; 1 the select that an earlier call left pending; 2 the same with the
+// probability rules; 3 this layer's own, by whoever completes a segment (nothing pends then: with
+// one select in it every build keeps its registers).
 template <bool COLLECT, int SELECTS>
 __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLaunch P)
 {
+    constexpr bool kNow = SELECTS == 3;
     __shared__ SharedRole sh;
     __shared__ SharedLayer pool;
     // Both layer descriptors are staged in LDS, one word per thread, and read from there.  (The
@@ -106,6 +111,8 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
     // keeps it in a register: the load is not waited for before its first use, late in the launch.
     const uint32_t gen = tid == 0 ? load_agent(P.gen) : 0u;
     if (tid < c.batch) pool.len[tid] = clamp_len(c.lengths[tid], c.max_len);
+    if (SELECTS == 3)
+        for (int i = tid; i < kMaxBatch * kMaxKvHeads / 32; i += kThreads) pool.wanted[i] = 0;
     if (tid < kDescWords) {
         desc_cur[tid] = reinterpret_cast<const uint32_t *>(&P.cur)[tid];
         desc_prev[tid] = reinterpret_cast<const uint32_t *>(&P.prev)[tid];
@@ -118,25 +125,26 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
 
     // ------------------------------------------------------------------ front units
     if (w < P.n_front) {
+        __builtin_amdgcn_s_setprio(3);  // (the launch waits for these; a streaming workgroup shares the CU)
         const int n_rp = P.has_prev ? prev.n_rgroups : 0;
-        const int nS = SELECTS ? c.batch * n_rp : 0;
-        const int nC = P.has_prev && prev.copy_keep ? c.batch * (c.n_kv_heads - n_rp) : 0;
-        const int nT = COLLECT && P.has_cur && cur.emit_sel && c.block_shift == 0 ? c.batch * cur.n_rgroups * kThrSplit : 0;
+        const int nS = SELECTS && !kNow ? c.batch * n_rp : 0;
+        const LayerDesc &kept = kNow ? cur : prev;  // whose kept sets are copied
+        const int n_keep = c.n_kv_heads - kept.n_rgroups;
+        const int nC = (kNow || P.has_prev) && kept.copy_keep ? c.batch * n_keep : 0;
+        const int nT = COLLECT && P.has_thr ? c.batch * cur.n_rgroups * kThrSplit : 0;
         for (int j = w; j < nS + nC + nT; j += P.n_front) {
             if (j < nS) {
                 const int b = j / n_rp;
                 const int g = prev.rgroup[j % n_rp];
-                if (SELECTS == 1) select_unit<false>(c, prev, b, g, sh.unit.sel, pool);
-                if (SELECTS == 2) select_unit<true>(c, prev, b, g, sh.unit.sel, pool);
+                if (SELECTS != 0 && !kNow) select_unit<SELECTS == 2>(c, prev, b, g, sh.unit.sel, pool);
                 publish_set(P.set_flags + b * c.n_kv_heads + g, gen);
             } else if (j < nS + nC) {
-                const int n_keep = c.n_kv_heads - n_rp;
                 const int u = j - nS;
                 const int b = u / n_keep;
                 int want = u % n_keep, g = 0;
                 for (int gg = 0; gg < c.n_kv_heads; ++gg)
-                    if (prev.rindex[gg] == 0xFF && want-- == 0) g = gg;
-                copy_set_unit(c, prev, b, g);
+                    if (kept.rindex[gg] == 0xFF && want-- == 0) g = gg;
+                copy_set_unit(c, kept, b, g);
                 publish_set(P.set_flags + b * c.n_kv_heads + g, gen);
             } else {
                 // a score row's sample is dealt to kThrSplit units: one round of loads each
@@ -159,6 +167,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             }
             __syncthreads();
         }
+        __builtin_amdgcn_s_setprio(0);
     }
 
     // ------------------------------------------------------------------ the two row spaces
@@ -353,7 +362,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                             em.pool_ml = desc_ptr<float>(dw, offsetof(LayerDesc, part_pool)) + row * (2 * (int64_t)c.part_stride);
                         // rows that need no sample have their threshold at once (what the T unit would say)
                         const int n = budget_of(c, pc.len_b);
-                        em.thr_known = n == pc.len_b || pc.len_b <= kDirectLen || 2 * (int64_t)n >= pc.len_b;
+                        em.thr_known = needs_no_sample(n, pc.len_b);
                         em.thr = n == pc.len_b && c.prob_rule == 0 ? 0xFFFFFFFFu : 0u;
                         em.thr_flag = P.thr_flags + row;
                         em.gen = my_gen;
@@ -398,8 +407,28 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                 case 3: combine_segment<3>(c, cur, pc.b, pc.g, pc.hmask, pc.pieces, sh.unit.comb); break;
                 default: combine_segment<4>(c, cur, pc.b, pc.g, pc.hmask, pc.pieces, sh.unit.comb); break;
                 }
+                if (kNow && !gather && tid == 0) {  // every candidate of the row is in its list: its set can be selected
+                    const int row = pc.b * uni(pool.role[0][2]) + (int)desc_u8(dw, offsetof(LayerDesc, rindex) + pc.g);
+                    pool.wanted[row >> 5] |= 1u << (row & 31);
+                }
             }
             __syncthreads();
+        }
+    }
+
+    // ------------------------------------------------------------------ this layer's own sets
+    // The rows of the segments that this workgroup completed, after its last piece.  (Selected inside
+    // the piece loop they took registers from the streaming, which spilled.)
+    if (kNow) {
+        const int n_rseg = uni(pool.role[0][2]);
+        const int n_rows = c.batch * n_rseg;
+        for (int i = 0; i < n_rows; i += 32) {
+            for (uint32_t rows = uni(pool.wanted[i >> 5]); rows != 0; rows &= rows - 1u) {
+                const int row = i + __builtin_ctz(rows);
+                select_unit<false>(c, cur, row / n_rseg, cur.rgroup[row % n_rseg], sh.unit.sel, pool, P.thr_flags + row,
+                                   pool.gen);
+                __syncthreads();
+            }
         }
     }
 
@@ -421,12 +450,12 @@ hipError_t launch_layer(const LayerLaunch &plan, int build, hipStream_t stream)
 {
     if (plan.c.n_wg < 1 || plan.c.n_wg > kMaxWg || plan.n_front > plan.c.n_wg) return hipErrorInvalidValue;
     const dim3 grid(plan.c.n_wg), block(kThreads);
-    if (build == 0)
-        hipLaunchKernelGGL((lychee_layer_kernel<false, 0>), grid, block, 0, stream, plan);
-    else if (build == 1)
-        hipLaunchKernelGGL((lychee_layer_kernel<true, 1>), grid, block, 0, stream, plan);
-    else
-        hipLaunchKernelGGL((lychee_layer_kernel<true, 2>), grid, block, 0, stream, plan);
+    switch (build) {
+    case 0: hipLaunchKernelGGL((lychee_layer_kernel<false, 0>), grid, block, 0, stream, plan); break;
+    case 1: hipLaunchKernelGGL((lychee_layer_kernel<true, 1>), grid, block, 0, stream, plan); break;
+    case 2: hipLaunchKernelGGL((lychee_layer_kernel<true, 2>), grid, block, 0, stream, plan); break;
+    default: hipLaunchKernelGGL((lychee_layer_kernel<true, 3>), grid, block, 0, stream, plan); break;
+    }
     return hipGetLastError();
 }
 

@@ -163,7 +163,7 @@ constexpr uint32_t kNoEntry = 0xFFFFFFFFu;
 // own that way: a range [lo, hi] with lo >= 1 leaves it out, since 0 - lo wraps beyond hi - lo.
 // Tested separately it was one lane mask per entry, kept from pass to pass and spilled.)
 __device__ __forceinline__ uint32_t real_key(uint32_t key) { return key > 1u ? key : 1u; }
-constexpr int kEntryBatch = 32;  // entries a thread loads before it looks at the first of them
+constexpr int kEntryBatch = 16;  // entries a thread loads before it looks at the first of them
 
 // Among the counted bins, taken from the highest down, the one at which `need` entries are reached:
 // its number, how many of its entries are needed, and how many it has.  Every thread sums eight
@@ -284,8 +284,9 @@ __device__ __forceinline__ float tile_pooled_score(const uint4 (&kr)[4], const u
 // plus sel_margin (six, unless the caller changes it) standard deviations; the streamed rows
 // that reach it are then very likely at least n and a few thousand more at most.  Whatever the sample yields, the select unit
 // checks the candidate count and ranks the whole row itself when the list cannot be used.
-// The sample is one row at a hashed offset inside each of 1024 to 4096 equal strata: 2048 and more
-// for long rows, fewer where 64 sampled rows are expected among the top n all the same.
+// The sample is one row at a hashed offset inside each of 1024 to 4096 equal strata, as many as let 128
+// sampled rows be expected among the top n: the threshold then lets through about 1.6 n rows,
+// which a select of n = 4096 holds in registers.
 //
 // Latency bounds it (the row's streaming pieces wait for it at the end of their rows): one round
 // of row loads, a hand-over, one round of key loads, two levels of bins.
@@ -334,7 +335,7 @@ __device__ __forceinline__ void threshold_unit(const Common &c, const LayerDesc 
         if (publish != nullptr)
             __hip_atomic_store((LYCHEE_GLOBAL unsigned long long *)publish, ((unsigned long long)gen << 32) | key,
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        gstore(p.thr + row, key);  // (the row's select starts from it)
+        gstore(p.thr + row, key);  // (a later launch's select starts from it)
     };
     if (publish == nullptr && tid == 0) gstore(p.list_count + row, (int32_t)0);
     if (split.sub == 0 && p.q_keep != nullptr && tid < c.group * (kHeadDim / 8)) {
@@ -342,16 +343,16 @@ __device__ __forceinline__ void threshold_unit(const Common &c, const LayerDesc 
         const int64_t at = ((int64_t)b * c.n_q_heads + p.rgroup[rgi] * c.group) * kHeadDim + tid * 8;
         *(LYCHEE_GLOBAL u32x4_t *)(p.q_keep + at) = *(const LYCHEE_GLOBAL u32x4_t *)(p.q + at);
     }
-    if (n == L || L <= kDirectLen || 2 * (int64_t)n >= L) {
+    if (needs_no_sample(n, L)) {
         // everything is selected anyway (no candidates wanted), or every row is a candidate
         // (a probability rule may keep fewer than everything: it still needs the candidates)
         if (split.sub == 0) emit(n == L && c.prob_rule == 0 ? 0xFFFFFFFFu : 0u);
         return;
     }
-    int n_tiles = L / 1024;
-    n_tiles = n_tiles < kSampleTilesMin ? kSampleTilesMin : (n_tiles > kSampleTilesMax ? kSampleTilesMax : n_tiles);
-    const int enough = (int)(4.0f * (float)L / (float)n) + 1;  // tiles of 16 rows that hold 64 of the top n
-    n_tiles = enough < n_tiles ? (enough > kSampleTilesFew ? enough : kSampleTilesFew) : n_tiles;
+    // 128 of the top n among the sample, if that takes no more rows than the sample may have
+    const int most = L >= (1 << 16) ? kSampleTilesMax : kSampleTilesMax / 2;
+    const int enough = (int)(8.0f * (float)L / (float)n) + 1;
+    const int n_tiles = enough > most ? most : (enough < kSampleTilesMin ? kSampleTilesMin : enough);
     const int n_sample = n_tiles * 16;
     const int g = p.rgroup[rgi];
     const uint32_t hmask = p.rmask[g] & ((1u << c.group) - 1u);
@@ -471,41 +472,23 @@ __device__ __forceinline__ void score_row_unit(const Common &c, const LayerDesc 
     }
 }
 
-// The three sources of (ordered key, position) entries the select unit ranks.  for_each may
-// also hand out "no entry": key 0, below every real key, and position kNoEntry; for_window
-// hands out at least the entries of `count` positions from w0 on.  The visitors below fold
-// everything that decides whether an entry counts into one flag, with bitwise operators, and
-// guard a single LDS operation with it: short-circuit conditions made the compiler keep a lane
-// mask per entry and condition, spill them, and branch several times per entry.
-constexpr int kSelRegs = 40;     // entries one thread keeps in registers
-constexpr int kSelHead = 8;      // and those of them that it asks for first
+// (key, ~position) as one number: larger keys first, then lower positions.
+__device__ __forceinline__ unsigned long long ranked(uint32_t key, uint32_t pos)
+{
+    return ((unsigned long long)key << 32) | (uint32_t)~pos;
+}
+
+// Sources of (ordered key, position) entries.  for_each may also hand out "no entry": key 0, below
+// every real key, and position kNoEntry.  keep_from leaves the entries from a cutoff on, whose
+// positions for_kept hands out eight at a time (at least those of `count` positions from w0 on).  The visitors below fold everything that decides whether an entry counts
+// into one flag, with bitwise operators, and let an entry that does not count go to a word of its
+// lane's own: short-circuit conditions made the compiler keep a lane mask per entry and
+// condition, spill them, and branch several times per entry.
+constexpr int kSelRegs = 32;  // entries one thread keeps in registers
 struct RegEntries {           // up to kThreads * kSelRegs list entries, loaded once: beside a streaming
     uint32_t key[kSelRegs], pos[kSelRegs];  // launch every pass over memory costs a microsecond or two
     int tid;
     int left;                 // entries, uniform: whole groups of eight registers beyond them are skipped
-    unsigned long long head[kSelHead];
-    // The first entries of a list with room for `cap`, asked for before its length is known.
-    __device__ __forceinline__ void load_head(const unsigned long long *list, int cap, int tid_)
-    {
-        tid = tid_;
-#pragma unroll
-        for (int e = 0; e < kSelHead; ++e) {
-            const int i = e * kThreads + tid;
-            head[e] = gload(list + (i < cap ? i : cap - 1));
-        }
-    }
-    __device__ __forceinline__ void load(const unsigned long long *list, int total)
-    {
-        left = total;
-#pragma unroll
-        for (int e = 0; e < kSelRegs; ++e) {
-            if (e % 8 == 0 && e * kThreads >= left) break;
-            const int i = e * kThreads + tid;
-            const unsigned long long v = e < kSelHead ? head[e] : gload(list + (i < total ? i : total - 1));
-            key[e] = i < total ? real_key((uint32_t)v) : 0u;
-            pos[e] = i < total ? (uint32_t)(v >> 32) : kNoEntry;
-        }
-    }
     template <int kBatch = 8, typename F>
     __device__ __forceinline__ void for_each(F f) const
     {
@@ -515,10 +498,28 @@ struct RegEntries {           // up to kThreads * kSelRegs list entries, loaded 
             f(key[e], pos[e]);
         }
     }
+    __device__ __forceinline__ void keep_from(unsigned long long cutoff)
+    {
+#pragma unroll
+        for (int e = 0; e < kSelRegs; ++e) {
+            if (e % 8 == 0 && e * kThreads >= left) break;
+            pos[e] = ranked(key[e], pos[e]) >= cutoff ? pos[e] : kNoEntry;  // (the keys are dead from here on)
+        }
+    }
     template <typename F>
-    __device__ __forceinline__ void for_window(uint32_t, uint32_t, F f) const { for_each(f); }
+    __device__ __forceinline__ void for_kept(uint32_t, uint32_t, F f) const
+    {
+#pragma unroll
+        for (int e = 0; e < kSelRegs; e += 8) {
+            if (e * kThreads >= left) break;
+            uint32_t p[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) p[u] = pos[e + u];
+            f(p);
+        }
+    }
 };
-struct ListEntries {          // a longer list, read from memory on every pass
+struct ListEntries {          // a list too long to be held in LDS: read from memory on every pass
     const unsigned long long *list;
     int total;
     int tid;
@@ -542,18 +543,38 @@ struct ListEntries {          // a longer list, read from memory on every pass
             }
         }
     }
+    unsigned long long cutoff = 0;
+    __device__ __forceinline__ void keep_from(unsigned long long cut) { cutoff = cut; }
     template <typename F>
-    __device__ __forceinline__ void for_window(uint32_t, uint32_t, F f) const { for_each(f); }
+    __device__ __forceinline__ void for_kept(uint32_t, uint32_t, F f) const
+    {
+        for (int i0 = 0; i0 < total; i0 += 8 * kThreads) {
+            unsigned long long v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int i = i0 + u * kThreads + tid;
+                v[u] = gload(list + (i < total ? i : total - 1));
+            }
+            uint32_t p[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const uint32_t at = (uint32_t)(v[u] >> 32);
+                const bool ok = (i0 + u * kThreads + tid < total) & (ranked(real_key((uint32_t)v[u]), at) >= cutoff);
+                p[u] = ok ? at : kNoEntry;
+            }
+            f(p);
+        }
+    }
 };
 struct RowEntries {           // every row of the sequence, from its recomputed scores
     const float *sel;
     int total;
     int tid;
-    template <typename F>
-    __device__ __forceinline__ void for_window(uint32_t w0, uint32_t count, F f) const
+    template <int kBatch = 8, typename F>
+    __device__ __forceinline__ void for_each(F f) const
     {
-        const int end = (int)(count < (uint32_t)total - w0 ? w0 + count : (uint32_t)total);
-        for (int i0 = (int)w0 + tid; i0 < end; i0 += 8 * kThreads) {
+        const int end = total;
+        for (int i0 = tid; i0 < end; i0 += 8 * kThreads) {
             float v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
@@ -567,130 +588,182 @@ struct RowEntries {           // every row of the sequence, from its recomputed 
             }
         }
     }
-    template <int kBatch = 8, typename F>
-    __device__ __forceinline__ void for_each(F f) const { for_window(0u, (uint32_t)total, f); }
+    unsigned long long cutoff = 0;
+    __device__ __forceinline__ void keep_from(unsigned long long cut) { cutoff = cut; }
+    template <typename F>
+    __device__ __forceinline__ void for_kept(uint32_t w0, uint32_t count, F f) const
+    {
+        const int end = (int)(count < (uint32_t)total - w0 ? w0 + count : (uint32_t)total);
+        for (int i0 = (int)w0 + tid; i0 < end; i0 += 8 * kThreads) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int i = i0 + u * kThreads;
+                v[u] = gload(sel + (i < end ? i : end - 1));
+            }
+            uint32_t p[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int i = i0 + u * kThreads;
+                p[u] = (i < end) & (ranked(real_key(ordered_key(v[u])), (uint32_t)i) >= cutoff) ? (uint32_t)i : kNoEntry;
+            }
+            f(p);
+        }
+    }
 };
 
-// Exact top-n of the `total` entries by key, ties to the lower position (Eq. 2), written to dst in
-// ascending position order.  The entries may come in any order.  The range of keys is narrowed
-// around the n-th largest until it holds at most kFewKeys entries, which are then ranked against
-// one another by (key, position); equal keys that are more than that are cut at a position found
-// the same way.  The chosen positions are marked in an LDS bitmap, 131072 positions at a
-// time; a prefix sum over its words gives every chosen position its place, and each entry
-// writes itself there.
-//
-// One workgroup, a chain of LDS passes and barriers: latency bounds it.  Counting by fixed digits,
-// three passes always, with the positions read back by walking the bitmap's bits, took 15.7 us
-// from the loads to the last store for any row (7500 candidates, k = 4096: see the figures at
-// select_unit).
-template <typename Entries, typename Pool>
-__device__ __forceinline__ void select_from(const Entries &E, uint32_t floor_key, int total, int n, int L,
-                                            int32_t *dst, SharedSelect &sh, Pool &pool)
+// The smallest ranked() among the `need` largest of the entries in `cut`: the range of keys is
+// narrowed until it holds at most kLastKeys entries, which are then ranked against one another;
+// equal keys that are more than that are cut at a position found the same way.
+template <typename Entries>
+__device__ __forceinline__ unsigned long long cutoff_of(const Entries &E, Cut cut, int shift, int L, SharedSelect &sh)
+{
+    if (E.tid == 0) sh.n_last = 0;
+    __syncthreads();  // (a list of kLastKeys entries or fewer goes straight to its use)
+    cut = narrow(
+        E, cut, shift, (uint32_t)kLastKeys, [](uint32_t key, uint32_t) { return key; },
+        [](uint32_t, uint32_t) { return true; }, sh);
+    if (cut.need == cut.count) return (unsigned long long)cut.lo << 32;
+    if (cut.count > (uint32_t)kLastKeys) {
+        const uint32_t key_cut = cut.lo;
+        const Cut at = narrow(
+            E, Cut{~(uint32_t)(L - 1), 0xFFFFFFFFu, cut.need, cut.count}, level_shift((uint32_t)(L - 1)), 0u,
+            [](uint32_t, uint32_t pos) { return ~pos; }, [&](uint32_t key, uint32_t) { return key == key_cut; }, sh);
+        return ((unsigned long long)key_cut << 32) | at.lo;
+    }
+    E.for_each([&](uint32_t key, uint32_t pos) {
+        if (key - cut.lo <= cut.hi - cut.lo) sh.last[atomicAdd(&sh.n_last, 1u)] = ranked(key, pos);
+    });
+    __syncthreads();
+    if ((uint32_t)E.tid < cut.count) {
+        const unsigned long long mine = sh.last[E.tid];
+        uint32_t above = 0;
+        // (pairs, eight at a time: read one by one, each read waits for the one before it; what lies
+        // past the last entry is not counted)
+        for (uint32_t i0 = 0; i0 < cut.count; i0 += 16) {
+            ulonglong2 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = reinterpret_cast<const ulonglong2 *>(sh.last)[i0 / 2 + u];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                above += (uint32_t)((i0 + 2 * u < cut.count) & (v[u].x > mine));
+                above += (uint32_t)((i0 + 2 * u + 1 < cut.count) & (v[u].y > mine));
+            }
+        }
+        if (above + 1u == cut.need) sh.cutoff = mine;
+    }
+    __syncthreads();
+    return sh.cutoff;
+}
+
+// Writes the positions of the kept entries to dst in ascending order: they are marked in an LDS bitmap,
+// 131072 positions at a time, prefix sums over its words give every one its place, and each entry
+// stages itself there.
+template <typename Entries>
+__device__ __forceinline__ void write_ordered(const Entries &E, int L, int32_t *dst, SharedSelect &sh)
 {
     const int tid = E.tid;
     const int lane = tid & 63;
     const int wave = tid >> 6;
-    if (tid == 0) sh.n_few = 0;
-    __syncthreads();  // (a list of kFewKeys entries or fewer goes straight to its use)
-    // Rows that were sampled hold keys from their threshold up: the first level covers the eight
-    // octaves above it, 256 bins each.  Others (short rows, blocks, rows ranked whole) start from
-    // the range of all keys, four bins to the octave.
-    const uint32_t lo = floor_key > 1u ? floor_key : 1u;
-    const Cut cut = narrow(
-        E, Cut{lo, 0xFFFFFFFFu, (uint32_t)n, (uint32_t)total}, lo >= 0x80000000u ? 26 - kBinBits : 32 - kBinBits,
-        (uint32_t)kFewKeys, [](uint32_t key, uint32_t) { return key; }, [](uint32_t, uint32_t) { return true; }, sh);
-    const bool all = cut.need == cut.count;  // everything in the range is chosen
-    uint32_t my_few = kNoEntry;              // the position this thread ranked, if it is chosen
-    uint32_t pos_cut = 0;                    // entries of equal keys are chosen up to this position
-    bool by_pos = false;
-    if (!all && cut.count <= (uint32_t)kFewKeys) {
-        E.for_each([&](uint32_t key, uint32_t pos) {
-            const bool in = key - cut.lo <= cut.hi - cut.lo;
-            if (in) sh.few[atomicAdd(&sh.n_few, 1u)] = ((unsigned long long)key << 32) | (uint32_t)~pos;
-        });
-        __syncthreads();
-        if ((uint32_t)tid < cut.count) {
-            const unsigned long long mine = sh.few[tid];
-            uint32_t before = 0;
-            // (pairs, eight at a time: read one by one, each read waits for the one before it; what lies
-            // past the last entry is not counted)
-            for (uint32_t i0 = 0; i0 < cut.count; i0 += 16) {
-                ulonglong2 v[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = reinterpret_cast<const ulonglong2 *>(sh.few)[i0 / 2 + u];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    before += (uint32_t)((i0 + 2 * u < cut.count) & (v[u].x > mine));
-                    before += (uint32_t)((i0 + 2 * u + 1 < cut.count) & (v[u].y > mine));
-                }
-            }
-            if (before < cut.need) my_few = ~(uint32_t)mine;
-        }
-    } else if (!all) {
-        by_pos = true;
-        const Cut at = narrow(
-            E, Cut{~(uint32_t)(L - 1), 0xFFFFFFFFu, cut.need, cut.count}, level_shift((uint32_t)(L - 1)), 0u, [](uint32_t, uint32_t pos) { return ~pos; },
-            [&](uint32_t key, uint32_t) { return key == cut.lo; }, sh);
-        pos_cut = ~at.lo;
-    }
     constexpr uint32_t kWindow = kMapWords * 32u;
     uint32_t base = 0;  // positions chosen in earlier windows
     for (uint32_t w0 = 0; w0 < (uint32_t)L; w0 += kWindow) {
         const uint32_t span = (uint32_t)L - w0 < kWindow ? (uint32_t)L - w0 : kWindow;
-        const int rounds = (int)(span + 32 * kThreads - 1) / (32 * kThreads);  // words of a wavefront's share / 64
+        // wavefront w owns words w << (6 + lg) .. of the window, 64 << lg of them
+        const uint32_t per = (span + 32 * kThreads - 1) / (32 * kThreads);
+        const int lg = per > 1 ? 32 - __builtin_clz(per - 1) : 0;
+        const int rounds = 1 << lg;
         __syncthreads();
-        for (int r = 0; r < rounds; ++r) sh.map[r * kThreads + tid] = make_uint2(0, 0);
+        for (int r = 0; r < rounds; ++r) sh.bits[r * kThreads + tid] = 0;
         __syncthreads();
-        E.for_window(w0, span, [&](uint32_t key, uint32_t pos) {
-            const uint32_t rel = pos - w0;  // "no entry" lies outside every window
-            const bool in = key - cut.lo <= cut.hi - cut.lo;
-            const bool take = ((key > cut.hi) | (in & (all | (by_pos & (pos <= pos_cut))))) & (rel < span);
-            atomicOr(&sh.map[take ? rel >> 5 : (uint32_t)(kMapWords + lane)].x, 1u << (rel & 31u));
+        E.for_kept(w0, span, [&](const uint32_t (&pos)[8]) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const uint32_t rel = pos[u] - w0;  // "no entry" lies outside every window
+                atomicOr(&sh.bits[rel < span ? rel >> 5 : (uint32_t)(kMapWords + lane)], 1u << (rel & 31u));
+            }
         });
-        if (my_few - w0 < span) atomicOr(&sh.map[(my_few - w0) >> 5].x, 1u << ((my_few - w0) & 31u));
         __syncthreads();
-        // wavefront w counts words w * rounds * 64 .. of the window, then gives each its place
-        const uint2 *share = sh.map + wave * rounds * 64 + lane;
-        uint32_t cnt = 0;
-        for (int r = 0; r < rounds; ++r) cnt += (uint32_t)__builtin_popcount(share[r * 64].x);
-        cnt = wave_scan(cnt);
-        if (lane == 63) sh.wave_tot[wave] = cnt;
+        const int first = (wave << (6 + lg)) + lane;
+        uint32_t mine = 0;
+        for (int r = 0; r < rounds; ++r) {
+            const uint32_t c = (uint32_t)__builtin_popcount(sh.bits[first + r * 64]);
+            const uint32_t incl = wave_scan(c);
+            sh.before[first + r * 64] = (uint16_t)(mine + incl - c);  // (at most 1024 words of 32 before it)
+            mine += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        }
+        if (lane == 0) sh.wave_tot[wave] = mine;
         __syncthreads();
-        uint32_t at0 = base, tot = 0;
+        uint32_t at[kWaves], end = base;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) {
-            at0 += w < wave ? sh.wave_tot[w] : 0u;
-            tot += sh.wave_tot[w];
+            at[w] = end;
+            end += sh.wave_tot[w];
         }
-        for (int r = 0; r < rounds; ++r) {
-            const uint32_t c = (uint32_t)__builtin_popcount(share[r * 64].x);
-            const uint32_t incl = wave_scan(c);
-            sh.map[wave * rounds * 64 + lane + r * 64].y = at0 + incl - c;
-            at0 += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-        }
-        __syncthreads();
-        // The positions are put in order in LDS, kStage at a time, and copied out with coalesced
-        // write-through stores: the set is in device memory once the unit's stores have
-        // completed, whoever reads it next (a gather piece of the same launch, on another XCD,
-        // after an acquire).
-        constexpr uint32_t kStage = (uint32_t)(sizeof(sh.samp) / sizeof(sh.samp[0])) - 64u;
-        const uint32_t end = base + tot;
-        for (uint32_t c0 = base; c0 < end; c0 += kStage) {
-            E.for_window(w0, span, [&](uint32_t, uint32_t pos) {
-                const uint32_t rel = pos - w0;
-                const uint2 word = sh.map[rel < span ? rel >> 5 : 0];
-                const uint32_t bit = 1u << (rel & 31u);
-                const uint32_t at = word.y + (uint32_t)__builtin_popcount(word.x & (bit - 1u)) - c0;
-                const bool put = (rel < span) & ((word.x & bit) != 0) & (at < kStage);
-                sh.samp[put ? at : kStage + (uint32_t)lane] = pos;
+        // Staged in LDS and copied out with coalesced write-through stores: the set is in device
+        // memory once the unit's stores have completed, whoever reads it next (a gather piece of
+        // the same launch, on another XCD, after an acquire).
+        for (uint32_t c0 = base; c0 < end; c0 += (uint32_t)kStage) {
+            E.for_kept(w0, span, [&](const uint32_t (&pos)[8]) {
+                // (all lookups of a group before its first store: a lookup after a store waits for
+                // it, the compiler cannot tell their LDS words apart)
+                uint32_t put_at[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const uint32_t rel = pos[u] - w0;
+                    const uint32_t word_at = rel < span ? rel >> 5 : 0u;
+                    const uint32_t word = sh.bits[word_at];
+                    const uint32_t bit = 1u << (rel & 31u);
+                    const uint32_t owner = word_at >> (6 + lg);
+                    uint32_t place = owner == 0 ? at[0] : (owner == 1 ? at[1] : (owner == 2 ? at[2] : at[3]));
+                    place += sh.before[word_at] + (uint32_t)__builtin_popcount(word & (bit - 1u)) - c0;
+                    const bool put = (rel < span) & (place < (uint32_t)kStage);
+                    put_at[u] = put ? place : (uint32_t)(kStage + lane);
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) sh.stage[put_at[u]] = pos[u];
             });
             __syncthreads();
-            const uint32_t m = end - c0 < kStage ? end - c0 : kStage;
-            for (uint32_t i = tid; i < m; i += kThreads) gstore_through(dst + c0 + i, (int32_t)sh.samp[i]);
+            const uint32_t m = end - c0 < (uint32_t)kStage ? end - c0 : (uint32_t)kStage;
+            for (uint32_t i0 = 0; i0 < m; i0 += 8 * kThreads) {  // (eight reads, then eight stores)
+                int32_t v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = (int32_t)sh.stage[i0 + u * kThreads + tid];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const uint32_t i = i0 + u * kThreads + tid;
+                    if (i < m) gstore_through(dst + c0 + i, v[u]);
+                }
+            }
             __syncthreads();
         }
         base = end;
     }
+}
+
+// Where the first level's bins begin and how wide they are (as a power of two).  Rows that were
+// sampled hold keys from their threshold up: bins over the eight octaves above it, 256 to the
+// octave.  Others (short rows, blocks, rows ranked whole): the range of all keys, four to the octave.
+struct Level {
+    uint32_t lo;
+    int shift;
+};
+__device__ __forceinline__ Level first_level(uint32_t floor_key)
+{
+    return Level{floor_key > 1u ? floor_key : 1u, floor_key >= 0x80000000u ? 26 - kBinBits : 32 - kBinBits};
+}
+
+// Exact top-n of the `total` entries by key, ties to the lower position (Eq. 2), written to dst in
+// ascending position order.
+//
+// One workgroup, a chain of LDS passes and barriers: latency bounds it.
+template <typename Entries>
+__device__ __forceinline__ void select_from(Entries &E, uint32_t floor_key, int total, int n, int L, int32_t *dst,
+                                            SharedSelect &sh)
+{
+    const Level lv = first_level(floor_key);
+    E.keep_from(cutoff_of(E, Cut{lv.lo, 0xFFFFFFFFu, (uint32_t)n, (uint32_t)total}, lv.shift, L, sh));
+    write_ordered(E, L, dst, sh);
 }
 
 // A unit of one layer (Alg. 1, "C.append(k, v)"): the decoded token's key and value rows become
@@ -728,50 +801,42 @@ __device__ __forceinline__ unsigned long long mass_of(uint32_t key, float lse)
     return (unsigned long long)(fminf(p, 1.0f) * kMassOne);
 }
 
-// In a histogram of probability mass per digit, finds the highest digit d at which the mass
-// of the digits >= d reaches `need`; returns d and what is still needed inside d, or digit
-// 0xFFFFFFFF when all the mass together does not reach it.
-template <int kBins, typename Pool>
-__device__ __forceinline__ void find_digit_mass(const unsigned long long *hist, unsigned long long need,
-                                                Pool &pool, uint32_t &digit, unsigned long long &rest)
+// In the histogram of probability mass per bin, from the highest bin down, the one at which `need` is
+// reached, and what is still needed inside it; false when all the mass together does not reach it.
+template <typename Pool>
+__device__ __forceinline__ bool find_bin_mass(const unsigned long long *mass, unsigned long long need, Pool &pool,
+                                              SharedSelect &sh, int tid, uint32_t &bin, unsigned long long &left)
 {
-    constexpr int per = kBins / kThreads;
-    unsigned long long mine[per], sum = 0;
+    const int first = kBins - 8 - 8 * tid;
+    unsigned long long c[8], sum = 0, total;
 #pragma unroll
-    for (int j = 0; j < per; ++j) {
-        mine[j] = hist[kBins - 1 - (threadIdx.x * per + j)];  // bins taken from the top
-        sum += mine[j];
-    }
-    unsigned long long total;
+    for (int j = 0; j < 8; ++j) sum += c[j] = mass[first + 7 - j];
     unsigned long long above = block_scan64(sum, pool.scan64, total) - sum;
-    if (threadIdx.x == 0) {
-        pool.scan64[kWaves] = 0xFFFFFFFFull << 32;  // "not reached"
-    }
-    __syncthreads();
+    if (total < need) return false;  // (uniform)
 #pragma unroll
-    for (int j = 0; j < per; ++j) {
-        if (above < need && need <= above + mine[j]) {
-            // digit in the high word, the remaining need (< 2^41) cannot be packed with it: two words
-            pool.scan64[kWaves] = (unsigned long long)(uint32_t)(kBins - 1 - (threadIdx.x * per + j)) << 32;
-            pool.scan64[kWaves - 1] = need - above;
+    for (int j = 0; j < 8; ++j) {
+        if (above < need && need <= above + c[j]) {  // one thread
+            sh.found[0] = (uint32_t)(first + 7 - j);
+            sh.cutoff = need - above;
         }
-        above += mine[j];
+        above += c[j];
     }
     __syncthreads();
-    digit = (uint32_t)(pool.scan64[kWaves] >> 32);
-    rest = pool.scan64[kWaves - 1];
+    bin = uni(sh.found[0]);
+    left = sh.cutoff;
     __syncthreads();
+    return true;
 }
 
 // Entries the rule keeps, before the clamp to [1, n]: Threshold counts the entries whose
-// probability exceeds the parameter; Top-p finds, digit by digit, the key at which the
+// probability exceeds the parameter; Top-p finds, bin by bin, the key at which the
 // probability mass of the descending order reaches the parameter (all entries with that key
 // have the same mass, so a division says how many of them are needed).  `lse` is the
 // log-sum-exp of the pooled logits of the whole sequence.  The entries hold at least the n best
 // positions, and a rule that would go beyond them is capped at n anyway.
 template <typename Entries, typename Pool>
-__device__ __forceinline__ int rule_keeps(const Common &c, const Entries &E, int n, float lse, SharedSelect &sh,
-                                          Pool &pool)
+__device__ __forceinline__ int rule_keeps(const Common &c, const Entries &E, uint32_t floor_key, int n, float lse,
+                                          SharedSelect &sh, Pool &pool)
 {
     uint32_t want;
     if (c.prob_rule == 1) {
@@ -784,42 +849,63 @@ __device__ __forceinline__ int rule_keeps(const Common &c, const Entries &E, int
         unsigned long long *mh = sh.mass;
         unsigned long long need = (unsigned long long)((double)c.prob_param * (double)kMassOne);
         need = need < 1 ? 1 : need;
-        uint32_t prefix = 0, prefix_mask = 0;
-        bool reached = true;
-#pragma unroll
-        for (int pass = 0; pass < 3; ++pass) {
-            const int shift = pass == 0 ? 20 : (pass == 1 ? 10 : 0);
-            const int n_bins = pass == 0 ? 4096 : 1024;
-            const uint32_t digit_mask = (uint32_t)n_bins - 1u;
-            for (int i = threadIdx.x; i < n_bins; i += kThreads) mh[i] = 0;
+        // The range of keys is split into bins of mass as the select splits it into bins of entries, until the
+        // bin where the mass is reached holds few entries, which are looked at one by one.
+        const Level lv = first_level(floor_key);
+        uint32_t lo = lv.lo, hi = 0xFFFFFFFFu, above;
+        for (int shift = lv.shift;; shift = level_shift(hi - lo)) {
+            for (int i = E.tid; i < kBins; i += kThreads) mh[i] = 0;
+            if (E.tid == 0) sh.n_last = 0;
             __syncthreads();
-            E.template for_each<8>([&](uint32_t key, uint32_t pos) {
-                const bool in = (key != 0u) & ((key & prefix_mask) == prefix);
-                if (in) atomicAdd(&mh[(key >> shift) & digit_mask], mass_of(key, lse));
+            E.template for_each<8>([&](uint32_t key, uint32_t) {
+                const uint32_t at = key - lo;
+                if (at <= hi - lo) atomicAdd(&mh[min(at >> shift, (uint32_t)kBins - 1u)], mass_of(key, lse));
             });
             __syncthreads();
-            uint32_t digit;
-            unsigned long long left;
-            if (pass == 0)
-                find_digit_mass<4096, Pool>(mh, need, pool, digit, left);
-            else
-                find_digit_mass<1024, Pool>(mh, need, pool, digit, left);
-            if (digit == 0xFFFFFFFFu) {  // (uniform) not even all entries reach the mass: the cap decides
-                reached = false;
+            uint32_t bin;
+            if (!find_bin_mass(mh, need, pool, sh, E.tid, bin, need)) return n;  // not even all entries reach the mass: the cap decides
+            lo += bin << shift;
+            const uint32_t rest = hi - lo, width = (1u << shift) - 1u;
+            hi = bin == (uint32_t)kBins - 1u || rest < width ? hi : lo + width;
+            uint32_t mine = 0;
+            E.template for_each<8>([&](uint32_t key, uint32_t) {
+                mine += (uint32_t)(key > hi);
+                if (key - lo <= hi - lo) {
+                    const uint32_t at = atomicAdd(&sh.n_last, 1u);
+                    if (at < (uint32_t)kLastKeys) sh.last[at] = key;
+                }
+            });
+            (void)block_scan(mine, pool.scan, above);  // (its barriers publish the keys)
+            const uint32_t in_bin = uni(sh.n_last);
+            if (in_bin > (uint32_t)kLastKeys && hi != lo) {
+                __syncthreads();
+                continue;
+            }
+            // the key at which the mass is reached; all entries with that key have the same mass
+            if (in_bin > (uint32_t)kLastKeys) {  // (all equal)
+                const unsigned long long each = mass_of(lo, lse);
+                want = above + (uint32_t)((need + each - 1) / each);
                 break;
             }
-            prefix |= digit << shift;
-            prefix_mask |= digit_mask << shift;
-            need = left;
+            if ((uint32_t)E.tid < in_bin) {
+                const uint32_t key = (uint32_t)sh.last[E.tid];
+                unsigned long long sum = 0;
+                uint32_t larger = 0, equal = 0;
+                for (uint32_t i = 0; i < in_bin; ++i) {
+                    const uint32_t k = (uint32_t)sh.last[i];
+                    sum += k > key ? mass_of(k, lse) : 0ull;
+                    larger += (uint32_t)(k > key);
+                    equal += (uint32_t)(k == key);
+                }
+                const unsigned long long each = mass_of(key, lse);
+                if (sum < need && need <= sum + each * equal)  // (the same in every thread with this key)
+                    sh.found[0] = above + larger + (uint32_t)((need - sum + each - 1) / each);
+            }
+            __syncthreads();
+            want = uni(sh.found[0]);
+            __syncthreads();
+            break;
         }
-        if (!reached) return n;
-        const unsigned long long each = mass_of(prefix, lse);  // > 0: its digit held mass
-        const uint32_t of_last = (uint32_t)((need + each - 1) / each);
-        uint32_t mine = 0;
-        E.template for_each<8>([&](uint32_t key, uint32_t pos) { mine += (uint32_t)(key > prefix); });
-        uint32_t above;
-        (void)block_scan(mine, pool.scan, above);
-        want = above + of_last;
     }
     return want < 1u ? 1 : (want > (uint32_t)n ? n : (int)want);
 }
@@ -853,9 +939,12 @@ __device__ __forceinline__ void copy_set_unit(const Common &c, const LayerDesc &
 // S unit of KV head (b, g), whose group holds a retrieval head: the set the next layer's
 // sparse heads of the group inherit.  PROB: the build that knows the probability rules (their
 // 64-bit mass arithmetic over register-resident entries would cost the plain build registers).
+// flag, gen: the row's threshold word and the generation, when the launch that streams the row
+// also selects for it.
 template <bool PROB, typename Pool>
 __device__ __forceinline__ void select_unit(const Common &c, const LayerDesc &p, int b, int g,
-                                            SharedSelect &sh, Pool &pool)
+                                            SharedSelect &sh, Pool &pool, const unsigned long long *flag = nullptr,
+                                            uint32_t gen = 0)
 {
     const int64_t bg = (int64_t)b * c.n_kv_heads + g;
     int32_t *dst = p.idx_out + bg * c.k;
@@ -872,11 +961,29 @@ __device__ __forceinline__ void select_unit(const Common &c, const LayerDesc &p,
     }
     const int64_t row = (int64_t)b * p.n_rgroups + rgi;
     const unsigned long long *list = p.list + row * (int64_t)c.list_row;
-    RegEntries E;
-    E.load_head(list, c.list_row, fresh_tid());
+    // The first entries are asked for before the list's length is known.
+    const int tid = fresh_tid();
+    constexpr int kHead = 8;
+    unsigned long long head[kHead];
+#pragma unroll
+    for (int u = 0; u < kHead; ++u) {
+        const int i = u * kThreads + tid;
+        head[u] = gload(list + (i < c.list_row ? i : c.list_row - 1));
+    }
     // block-granular: the streaming left every block's score at its place in the list
     const int total = c.block_shift ? L : gload(p.list_count + row);
-    const uint32_t floor_key = c.block_shift ? 0u : gload(p.thr + row);  // no entry lies below it
+    // No entry lies below the row's threshold.  (A select of the launch that streamed the row takes it
+    // from where the row's pieces did; rows whose pieces asked nobody may not have one there yet.)
+    uint32_t floor_key = 0;
+    if (c.block_shift == 0 && !needs_no_sample(n, len)) {
+        if (flag != nullptr) {
+            const unsigned long long v = __hip_atomic_load((const LYCHEE_GLOBAL unsigned long long *)flag, __ATOMIC_RELAXED,
+                                                           __HIP_MEMORY_SCOPE_AGENT);
+            floor_key = (uint32_t)(v >> 32) == gen ? (uint32_t)v : 0u;
+        } else {
+            floor_key = gload(p.thr + row);
+        }
+    }
     // The select is the counter's only reader: it leaves it at zero for the next launch that
     // collects into it (a launch whose streaming runs beside its threshold units has nobody who
     // could clear it first).  Every thread has read it before any thread gets past the barriers
@@ -891,14 +998,31 @@ __device__ __forceinline__ void select_unit(const Common &c, const LayerDesc &p,
         lse = pooled_lse(c, p, row, count, pool);
     }
     int keep = n;  // what is selected in the end: n, or fewer under a probability rule
-    if (total >= n && total <= kThreads * kSelRegs && total <= c.list_row) {
-        E.load(list, total);
-        if (PROB && by_prob) keep = rule_keeps(c, E, n, lse, sh, pool);
-        select_from(E, floor_key, total, keep, L, dst, sh, pool);
-    } else if (total >= n && total <= c.list_row) {
-        const ListEntries M{list, total, fresh_tid()};
-        if (PROB && by_prob) keep = rule_keeps(c, M, n, lse, sh, pool);
-        select_from(M, floor_key, total, keep, L, dst, sh, pool);
+    const bool usable = total >= n && total <= c.list_row;
+    if (PROB && by_prob && usable) {
+        // (from memory, a few entries at a time: with the rules' 64-bit masses beside resident entries the
+        // whole kernel spilled, and its threshold units took four times as long)
+        ListEntries M;
+        M.list = list, M.total = total, M.tid = tid;
+        keep = rule_keeps(c, M, floor_key, n, lse, sh, pool);
+    }
+    if (usable && total <= kThreads * kSelRegs) {
+        RegEntries E;
+        E.tid = tid;
+        E.left = total;
+#pragma unroll
+        for (int e = 0; e < kSelRegs; ++e) {
+            if (e % 8 == 0 && e * kThreads >= total) break;  // (uniform)
+            const int i = e * kThreads + tid;
+            const unsigned long long v = e < kHead ? head[e] : gload(list + (i < total ? i : total - 1));
+            E.key[e] = i < total ? real_key((uint32_t)v) : 0u;
+            E.pos[e] = i < total ? (uint32_t)(v >> 32) : kNoEntry;
+        }
+        select_from(E, floor_key, total, keep, L, dst, sh);
+    } else if (usable) {
+        ListEntries M;
+        M.list = list, M.total = total, M.tid = tid;
+        select_from(M, floor_key, total, keep, L, dst, sh);
     } else {
         // too few candidates reached the threshold, or too many for the list: rank the row
         // (token-granular only: a block list is always complete)
@@ -912,9 +1036,10 @@ __device__ __forceinline__ void select_unit(const Common &c, const LayerDesc &p,
         }
         __threadfence();
         __syncthreads();  // the scores are read back by other threads of the workgroup
-        const RowEntries M{sel, len, fresh_tid()};
-        if (PROB && by_prob) keep = rule_keeps(c, M, n, lse, sh, pool);
-        select_from(M, 0u, len, keep, L, dst, sh, pool);
+        RowEntries M;
+        M.sel = sel, M.total = len, M.tid = tid;
+        if (PROB && by_prob) keep = rule_keeps(c, M, 0u, n, lse, sh, pool);
+        select_from(M, 0u, len, keep, L, dst, sh);
     }
     for (int i = keep + threadIdx.x; i < c.k; i += kThreads) gstore_through(dst + i, (int32_t)-1);
     if (clear_count && threadIdx.x == 0) gstore(p.list_count + row, (int32_t)0);

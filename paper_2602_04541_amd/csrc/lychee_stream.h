@@ -175,7 +175,7 @@ __device__ __forceinline__ void late_write(const Emit &em, SharedAttn &sh, int f
     for (int i = threadIdx.x; i < n_rows; i += kThreads) {
         const uint32_t key = sh.keys[i];
         if (key >= thr) {
-            if (at < em.cap) gstore(em.list + at, (unsigned long long)key | ((unsigned long long)(uint32_t)(first_row + i) << 32));
+            if (at < em.cap) gstore_through(em.list + at, (unsigned long long)key | ((unsigned long long)(uint32_t)(first_row + i) << 32));
             ++at;
         }
     }
@@ -302,7 +302,9 @@ __device__ __forceinline__ void stream_rows(const Common &c, const uint16_t *kba
             const int first = rb - 32;  // of the block, when this is its second span
             if ((span & 1) && first < r1 && lane == 0) {
                 const uint32_t blk = (uint32_t)(first >> 6);
-                gstore(em.list + blk, (unsigned long long)ordered_key(block_best) | ((unsigned long long)blk << 32));
+                const unsigned long long entry = (unsigned long long)ordered_key(block_best) | ((unsigned long long)blk << 32);
+                if (LATE) gstore_through(em.list + blk, entry);  // (a select of the same launch may read it)
+                else gstore(em.list + blk, entry);
             }
         } else if (!GATHER && em.list != nullptr) {
             // lane ch (< 8) of each row slot holds the score of row 16*(ch/4) + 4*(ch%4) + rs
@@ -532,7 +534,10 @@ __device__ __forceinline__ void run_piece(const Common &c, const uint16_t *q, co
                     gstore(part_ml + prow * 2 + 1, l);
                 }
             }
-            if (threadIdx.x == 0 && ends_segment) gstore(part_count + bh, (int32_t)(slot + 1));
+            if (threadIdx.x == 0 && ends_segment) {
+                if (LATE) gstore_through(part_count + bh, (int32_t)(slot + 1));
+                else gstore(part_count + bh, (int32_t)(slot + 1));
+            }
         }
     }
     if (pooled_lse && threadIdx.x == 0) {  // the piece's pooled log-sum-exp state, same slot
@@ -541,8 +546,13 @@ __device__ __forceinline__ void run_piece(const Common &c, const uint16_t *q, co
         for (int w = 0; w < kWaves; ++w) M = fmaxf(M, sh.pool_ml[2 * w]);
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) l = fmaf(fast_exp2((sh.pool_ml[2 * w] - M) * kLog2e), sh.pool_ml[2 * w + 1], l);
-        gstore(em.pool_ml + 2 * slot, M);
-        gstore(em.pool_ml + 2 * slot + 1, l);
+        if (LATE) {
+            gstore_through(em.pool_ml + 2 * slot, M);
+            gstore_through(em.pool_ml + 2 * slot + 1, l);
+        } else {
+            gstore(em.pool_ml + 2 * slot, M);
+            gstore(em.pool_ml + 2 * slot + 1, l);
+        }
     }
     if (LATE && collects) {
         __syncthreads();

@@ -61,7 +61,7 @@ template <int SELECTS>
 __global__ __launch_bounds__(kThreads, 2) void lychee_small_kernel(const LaunchPlan P)
 {
     __shared__ SharedUnit su;
-    __shared__ SharedPool pool;
+    __shared__ SharedSmall pool;
     __shared__ __align__(16) uint32_t small_desc[kDescWords];  // the current unit's layer descriptor
     const Common &c = P.c;
     const LayerDesc *layers = P.layers;
