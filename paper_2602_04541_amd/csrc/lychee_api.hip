@@ -82,8 +82,8 @@ namespace {
 constexpr size_t kSyncGen = 0, kSyncExit = 64;
 constexpr size_t kSyncRows = (size_t)kMaxBatch * kMaxKvHeads;  // (sequence, KV head) pairs a shape can have
 constexpr size_t kSyncThr = 4096;                               // uint64 [kSyncRows]
-constexpr size_t kSyncSet = kSyncThr + kSyncRows * 8;           // uint32 [kSyncRows]
-constexpr size_t kSyncSeg = kSyncSet + kSyncRows * 4;           // uint32 [kSyncRows][2]
+constexpr size_t kSyncSet = kSyncThr + kSyncRows * 8;           // uint32 [kSyncRows], kSetFlagStride apart
+constexpr size_t kSyncSeg = kSyncSet + kSyncRows * kSetFlagStride * 4;  // uint32 [kSyncRows][2]
 constexpr size_t kSyncCount = kSyncSeg + kSyncRows * 8;         // int32 [3][kSyncRows]
 constexpr size_t kSyncArrived = kSyncCount + 3 * kSyncRows * 4; // uint32 [kSyncRows]
 constexpr size_t kSyncBytes = kSyncArrived + kSyncRows * 4;
@@ -489,21 +489,23 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
     // layer, which waits for them; beside a long one as many units in turn, about 10 us each,
     // as fit a sixth of the streaming (5.5 ns a block of 64 rows at 6 TB/s; max_len bounds
     // the lengths, which are on the device).  A batch of 8 at 96K set 103 workgroups of 512 aside
-    // for 15 of its 140 us; now 26.
+    // for 15 of its 140 us; now 26.  Set copies alone (2 us) are done on the way to the pieces.
     const int wg = p.c.n_wg;
-    int64_t aside = units;
-    if (cur != nullptr) {
+    int64_t front = units;
+    const bool copies_only = !p.has_thr && (prev == nullptr || prev->n_rgroups == 0);
+    if (cur == nullptr || copies_only || wg < 8) {
+        front = front < wg ? front : wg;
+        p.n_aside = 0;
+    } else {
         const int64_t seg_blocks = (s.max_len + kBlockRows - 1) / kBlockRows;
         int64_t rounds = (int64_t)cur->n_rgroups * s.batch * seg_blocks * 11 / 2 / 60000;
         rounds = rounds < 1 ? 1 : rounds;
-        aside = (units + rounds - 1) / rounds;
-        const int64_t most = wg >= 8 ? wg / (rounds > 1 ? 16 : 4) : wg;
-        aside = aside < most ? aside : most;
-        if (aside < 1 && units > 0) aside = 1;
-    } else if (aside > wg) {
-        aside = wg;
+        front = (units + rounds - 1) / rounds;
+        const int64_t most = wg / (rounds > 1 && wg >= 16 ? 16 : 4);
+        front = front < most ? front : most;
+        p.n_aside = (int32_t)front;
     }
-    p.n_front = (int32_t)aside;
+    p.n_front = (int32_t)front;
     p.lead_blocks = ctx->select_lead;
     p.gen = reinterpret_cast<uint32_t *>(ctx->sync_dev + kSyncGen);
     p.exit_count = reinterpret_cast<uint32_t *>(ctx->sync_dev + kSyncExit);

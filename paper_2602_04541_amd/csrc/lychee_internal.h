@@ -26,6 +26,7 @@ constexpr int kDirectLen = 4096;         // sequences this short are ranked with
 constexpr int kCandBuf = 256;            // candidates a wavefront collects in LDS between flushes
 constexpr int kThrSplit = 4;             // units that share a score row's threshold sample in a layer launch
 constexpr int kKeyBuf = 4096;            // rows whose keys a piece buffers in LDS when its threshold comes late
+constexpr int kSetFlagStride = 32;        // words from one set flag to the next: a line each, hundreds of workgroups poll them
 constexpr float kMinusBig = -1.0e30f;    // "no score yet" sentinel of the running maximum
 
 constexpr int kMaxLayers = 128;          // layers one launch can cover
@@ -131,14 +132,15 @@ struct LayerLaunch {
     LayerDesc prev;        // the layer whose select is pending (has_prev)
     int32_t has_cur, has_prev;
     int32_t has_thr;       // the launch computes cur's selection thresholds
-    int32_t n_front;       // workgroups that run front units
+    int32_t n_front;       // workgroups that run front units (the first ones)
+    int32_t n_aside;       // and those of them that take no pieces afterwards
     int32_t lead_blocks;   // blocks of 64 rows the device streams while a select runs: how much
                            // later than the streaming the gated gathers can start
     uint64_t gate_mask;    // bit g: KV head g's inherited set is written by this launch's front units
     uint32_t *gen;         // the generation (read at the start, advanced at the end)
     uint32_t *exit_count;  // workgroups that have finished
     unsigned long long *thr_flags;  // [B * n_rgroups] {generation, threshold} of cur's score rows
-    uint32_t *set_flags;   // [B * H_kv] generation once the set of (sequence, KV head) is final
+    uint32_t *set_flags;   // [B * H_kv], kSetFlagStride apart: generation once the set of (sequence, KV head) is final
     uint32_t *seg_count;   // [B * H_kv * 2] partials written so far of each R / G segment (zero between launches)
     uint32_t *thr_arrived; // [B * n_rgroups] threshold units of a score row that have left their keys (likewise)
 };

@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                 const int b = j / n_rp;
                 const int g = prev.rgroup[j % n_rp];
                 if (SELECTS != 0 && !kNow) select_unit<SELECTS == 2>(c, prev, b, g, sh.unit.sel, pool);
-                publish_set(P.set_flags + b * c.n_kv_heads + g, gen);
+                publish_set(P.set_flags + (b * c.n_kv_heads + g) * kSetFlagStride, gen);
             } else if (j < nS + nC) {
                 const int u = j - nS;
                 const int b = u / n_keep;
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                 for (int gg = 0; gg < c.n_kv_heads; ++gg)
                     if (kept.rindex[gg] == 0xFF && want-- == 0) g = gg;
                 copy_set_unit(c, kept, b, g);
-                publish_set(P.set_flags + b * c.n_kv_heads + g, gen);
+                publish_set(P.set_flags + (b * c.n_kv_heads + g) * kSetFlagStride, gen);
             } else {
                 // a score row's sample is dealt to kThrSplit units: one round of loads each
                 const int u = (j - nS - nC) / kThrSplit;
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
         // (the totals are the same in every lane: scalar arithmetic from here on)
         const int64_t TR = (int64_t)uni((uint32_t)tot64) * n_rseg;
         const int64_t TG = (int64_t)uni((uint32_t)(tot64 >> 32)) * n_gseg;
-        const int first = W >= 8 ? P.n_front : 0;  // tiny grids: the front workgroups also take pieces
+        const int first = P.n_aside;
         const int Wn = W - first;
         int W_R = 0, W_G = 0;
         if (Wn < 2) {  // a single workgroup does both kinds, one after the other
@@ -347,6 +347,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                 float *d_part_o = desc_ptr<float>(dw, offsetof(LayerDesc, part_o));
                 float *d_part_ml = desc_ptr<float>(dw, offsetof(LayerDesc, part_ml));
                 int32_t *d_part_count = desc_ptr<int32_t>(dw, offsetof(LayerDesc, part_count));
+                uint16_t *alone = pc.pieces == 1 ? desc_ptr<uint16_t>(dw, offsetof(LayerDesc, out)) : nullptr;
                 const uint32_t my_gen = pool.gen;
                 if (!gather) {
                     const int n_rseg = uni(pool.role[0][2]);
@@ -369,15 +370,15 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                         em.timeouts = timeouts;
                     }
                     dispatch_piece<false, true>(__builtin_popcount(pc.hmask), c, dq, dk, dv, nullptr, em, d_part_o, d_part_ml,
-                                                d_part_count, pc.b, pc.g, pc.hmask, pc.len_b, pc.r0, pc.r1, pc.slot, pc.ends,
+                                                d_part_count, alone, pc.b, pc.g, pc.hmask, pc.len_b, pc.r0, pc.r1, pc.slot, pc.ends,
                                                 sh.attn, nothing);
                 } else {
                     if ((P.gate_mask >> pc.g) & 1ull)
-                        await_set(P.set_flags + pc.b * c.n_kv_heads + pc.g, my_gen, timeouts, pool);
+                        await_set(P.set_flags + (pc.b * c.n_kv_heads + pc.g) * kSetFlagStride, my_gen, timeouts, pool);
                     const int32_t *idx_src = desc_ptr<const int32_t>(dw, offsetof(LayerDesc, idx_src) + 8 * (size_t)pc.g) +
                                              ((int64_t)pc.b * c.n_kv_heads + pc.g) * c.k;
                     dispatch_piece<true, true>(__builtin_popcount(pc.hmask), c, dq, dk, dv, idx_src, Emit{}, d_part_o, d_part_ml,
-                                               d_part_count, pc.b, pc.g, pc.hmask, pc.len_b, pc.r0, pc.r1, pc.slot, pc.ends,
+                                               d_part_count, alone, pc.b, pc.g, pc.hmask, pc.len_b, pc.r0, pc.r1, pc.slot, pc.ends,
                                                sh.attn, nothing);
                 }
             }
@@ -400,8 +401,8 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             }
             __syncthreads();
             if (pool.flag) {
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-                switch (__builtin_popcount(pc.hmask)) {
+                if (pc.pieces > 1 || kNow) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                if (pc.pieces > 1) switch (__builtin_popcount(pc.hmask)) {
                 case 1: combine_segment<1>(c, cur, pc.b, pc.g, pc.hmask, pc.pieces, sh.unit.comb); break;
                 case 2: combine_segment<2>(c, cur, pc.b, pc.g, pc.hmask, pc.pieces, sh.unit.comb); break;
                 case 3: combine_segment<3>(c, cur, pc.b, pc.g, pc.hmask, pc.pieces, sh.unit.comb); break;

@@ -79,7 +79,7 @@ __device__ __forceinline__ void combine_segment(const Common &c, const LayerDesc
                                                 int count, SharedCombine &sh)
 {
     constexpr int kGrp = NH == 1 ? 8 : (NH == 2 ? 4 : 2);  // slot groups of a head
-    constexpr int kU = 16;                                 // slots a thread has in flight
+    constexpr int kU = 24;                                 // slots a thread has in flight
     const int tid = fresh_tid();
     const int lane = tid & 63;
     const int wave = tid >> 6;

@@ -366,12 +366,13 @@ __device__ __forceinline__ void stream_rows(const Common &c, const uint16_t *kba
 // segment also records how many slots the segment has.
 // LATE: the piece runs in a launch that also computes its thresholds and merges its partials
 // (lychee_layer_kernel): keys are filtered at the end of the piece, and the partial is written
-// through to device memory, complete when run_piece returns.
+// through to device memory, complete when run_piece returns.  alone_out: the piece is its segment's
+// only one and writes the heads' outputs at once (nullptr: it leaves a partial).
 template <int NH, bool GATHER, bool LATE, typename Hook>
 __device__ __forceinline__ void run_piece(const Common &c, const uint16_t *q, const uint16_t *k_cache,
                                           const uint16_t *v_cache, const int32_t *idx_src,
                                           const Emit &em, float *part_o, float *part_ml,
-                                          int32_t *part_count, int b, int g, uint32_t hmask, int L,
+                                          int32_t *part_count, uint16_t *alone_out, int b, int g, uint32_t hmask, int L,
                                           int r0, int r1, int slot, bool ends_segment,
                                           SharedAttn &sh, Hook &at_rows_done)
 {
@@ -521,7 +522,9 @@ __device__ __forceinline__ void run_piece(const Common &c, const uint16_t *q, co
             }
             const int64_t bh = (int64_t)b * c.n_q_heads + heads[h];
             const int64_t prow = bh * c.part_stride + slot;
-            if (LATE) {
+            if (LATE && alone_out != nullptr) {
+                gstore(alone_out + bh * kHeadDim + threadIdx.x, f32_to_bf16_rne(l > 0.0f ? o / l : 0.0f));
+            } else if (LATE) {
                 gstore_through(part_o + prow * kHeadDim + threadIdx.x, o);
                 if (threadIdx.x == 0) {
                     gstore_through(part_ml + prow * 2 + 0, M);
@@ -572,15 +575,15 @@ template <bool GATHER, bool LATE, typename Hook>
 __device__ __forceinline__ void dispatch_piece(int nh, const Common &c, const uint16_t *q,
                                                const uint16_t *k_cache, const uint16_t *v_cache,
                                                const int32_t *idx_src, const Emit &em, float *part_o,
-                                               float *part_ml, int32_t *part_count, int b, int g,
+                                               float *part_ml, int32_t *part_count, uint16_t *alone_out, int b, int g,
                                                uint32_t hmask, int L, int r0, int r1, int slot,
                                                bool ends_segment, SharedAttn &sh, Hook &at_rows_done)
 {
     switch (nh) {
-    case 1: run_piece<1, GATHER, LATE>(c, q, k_cache, v_cache, idx_src, em, part_o, part_ml, part_count, b, g, hmask, L, r0, r1, slot, ends_segment, sh, at_rows_done); break;
-    case 2: run_piece<2, GATHER, LATE>(c, q, k_cache, v_cache, idx_src, em, part_o, part_ml, part_count, b, g, hmask, L, r0, r1, slot, ends_segment, sh, at_rows_done); break;
-    case 3: run_piece<3, GATHER, LATE>(c, q, k_cache, v_cache, idx_src, em, part_o, part_ml, part_count, b, g, hmask, L, r0, r1, slot, ends_segment, sh, at_rows_done); break;
-    default: run_piece<4, GATHER, LATE>(c, q, k_cache, v_cache, idx_src, em, part_o, part_ml, part_count, b, g, hmask, L, r0, r1, slot, ends_segment, sh, at_rows_done); break;
+    case 1: run_piece<1, GATHER, LATE>(c, q, k_cache, v_cache, idx_src, em, part_o, part_ml, part_count, alone_out, b, g, hmask, L, r0, r1, slot, ends_segment, sh, at_rows_done); break;
+    case 2: run_piece<2, GATHER, LATE>(c, q, k_cache, v_cache, idx_src, em, part_o, part_ml, part_count, alone_out, b, g, hmask, L, r0, r1, slot, ends_segment, sh, at_rows_done); break;
+    case 3: run_piece<3, GATHER, LATE>(c, q, k_cache, v_cache, idx_src, em, part_o, part_ml, part_count, alone_out, b, g, hmask, L, r0, r1, slot, ends_segment, sh, at_rows_done); break;
+    default: run_piece<4, GATHER, LATE>(c, q, k_cache, v_cache, idx_src, em, part_o, part_ml, part_count, alone_out, b, g, hmask, L, r0, r1, slot, ends_segment, sh, at_rows_done); break;
     }
 }
 

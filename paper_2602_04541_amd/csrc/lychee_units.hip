@@ -363,14 +363,14 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_pool_kernel(const LaunchPl
                         em.pool_ml = desc_ptr<float>(dw, offsetof(LayerDesc, part_pool)) + row * (2 * (int64_t)c.part_stride);
                 }
                 dispatch_piece<false, false>(__builtin_popcount(hmask), c, dq, dk, dv, nullptr, em, d_part_o, d_part_ml,
-                                      d_part_count, b, g, hmask, len_b, r0, r1, slot, ends, sa, at_rows_done);
+                                      d_part_count, nullptr, b, g, hmask, len_b, r0, r1, slot, ends, sa, at_rows_done);
             } else {
                 const int g = (int)desc_u8(dw, offsetof(LayerDesc, sgroup) + gi);
                 const uint32_t hmask = ~desc_u8(dw, offsetof(LayerDesc, rmask) + g) & gmask;
                 const int32_t *idx_src = desc_ptr<const int32_t>(dw, offsetof(LayerDesc, idx_src) + 8 * (size_t)g) +
                                          ((int64_t)b * c.n_kv_heads + g) * c.k;
                 dispatch_piece<true, false>(__builtin_popcount(hmask), c, dq, dk, dv, idx_src, Emit{},
-                                     d_part_o, d_part_ml, d_part_count, b, g, hmask, len_b, r0, r1, slot, ends, sa,
+                                     d_part_o, d_part_ml, d_part_count, nullptr, b, g, hmask, len_b, r0, r1, slot, ends, sa,
                                      at_rows_done);
             }
             if (ahead_layer >= 0) {  // wave-uniform; readers of this buffer finished a piece ago
