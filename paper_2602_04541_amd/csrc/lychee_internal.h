@@ -27,6 +27,7 @@ constexpr int kCandBuf = 256;            // candidates a wavefront collects in L
 constexpr int kThrSplit = 4;             // units that share a score row's threshold sample in a layer launch
 constexpr int kKeyBuf = 4096;            // rows whose keys a piece buffers in LDS when its threshold comes late
 constexpr int kSetFlagStride = 32;        // words from one set flag to the next: a line each, hundreds of workgroups poll them
+constexpr int kPieceBlocks = 5;           // blocks of streaming or gathering that the fixed costs of a piece are worth
 constexpr float kMinusBig = -1.0e30f;    // "no score yet" sentinel of the running maximum
 
 constexpr int kMaxLayers = 128;          // layers one launch can cover

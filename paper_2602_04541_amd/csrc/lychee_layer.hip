@@ -45,6 +45,7 @@ struct SharedLayer {
     int32_t flag;
     int32_t role[2][4];            // per kind of piece: first workgroup, workgroups, segments per sequence, blocks
     uint32_t nb[2][kMaxBatch];     // per kind: blocks of one segment of every sequence
+    int32_t extra[2];              // per kind: blocks that a segment counts beyond those it has
     int32_t run[3];                // the piece loop: next block of this workgroup's run, blocks per run, padded
     uint32_t gen;                  // the generation of this launch's flags
     uint32_t wanted[kMaxBatch * kMaxKvHeads / 32];  // bit per score row: this workgroup selects its set
@@ -188,6 +189,14 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             nb_r = n_rseg ? (uint32_t)((L + kBlockRows - 1) / kBlockRows) : 0u;
             nb_g = n_gseg ? (uint32_t)((gather_rows(c, L) + gather_block(c) - 1) / gather_block(c)) : 0u;
         }
+        // Many segments: a run crosses several, and every piece costs its start-up, merge and hand-over
+        // (about 8 us, a block 1.2 to 1.7 us), so a segment counts kPieceBlocks blocks more than it has.
+        // (64 sequences of 61 to 3001 rows: a run of equal blocks held up to nine short
+        // segments, half the workgroups were done after 70 us and the last after 110.)
+        const int extra_r = 8ll * n_rseg * c.batch > W ? kPieceBlocks : 0;
+        const int extra_g = 8ll * n_gseg * c.batch > W ? kPieceBlocks : 0;
+        nb_r += nb_r ? extra_r : 0;
+        nb_g += nb_g ? extra_g : 0;
         unsigned long long tot64 = (unsigned long long)nb_r | ((unsigned long long)nb_g << 32);
         if (!single) (void)block_scan64(tot64, pool.scan64, tot64);
         // (the totals are the same in every lane: scalar arithmetic from here on)
@@ -238,6 +247,8 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             pool.role[1][1] = W_G;
             pool.role[1][2] = n_gseg;
             pool.role[1][3] = (int32_t)TG;
+            pool.extra[0] = extra_r;
+            pool.extra[1] = extra_g;
             pool.gen = gen;  // (its load, issued when the kernel started, has long arrived)
         }
         if (tid < c.batch) {
@@ -262,7 +273,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             // costs a second start-up and merge, which a launch this short cannot level out).
             int share = (T_real + role_n - 1) / role_n;
             int pad = 0;
-            if (8ll * nseg * c.batch <= role_n) {
+            if (uni(pool.extra[kind]) == 0 && 8ll * nseg * c.batch <= role_n) {
                 const int s_last = share + (share / 8 > 1 ? share / 8 : 1);
                 int s = share;
                 for (; s <= s_last; ++s) {
@@ -287,7 +298,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
 
         // One piece: where it lies, from the values in LDS alone.
         struct Piece {
-            int b, g, len_b, r0, r1, slot, pieces, len;
+            int b, g, len_b, r0, r1, slot, pieces, len, next_seg;
             uint32_t hmask;
             bool ends, padding;
         };
@@ -298,13 +309,14 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             pc.len_b = uni(pool.len[pc.b]);
             const int seg_rows = gather ? gather_rows(c, pc.len_b) : pc.len_b;
             const int nb = (seg_rows + brows - 1) / brows;
-            const int nbv = pad ? (nb + share - 1) / share * share : nb;
+            const int nbv = pad ? (nb + share - 1) / share * share : nb + uni(pool.extra[kind]);
             const int pre_b = uni(pool.pre[pc.b]);
             const int xo = x - pre_b;
             const int gi = xo / nbv;
             const int blk = xo % nbv;
-            pc.padding = blk >= nb;  // the run lies in a segment's padding
+            pc.padding = blk >= nb;  // the run goes on in what a segment counts beyond its blocks
             const int seg_start = pre_b + gi * nbv;
+            pc.next_seg = seg_start + nbv;
             int len = x1 - x;
             len = len < nb - blk ? len : nb - blk;
             pc.len = len;
@@ -339,7 +351,13 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             if (x >= x1) break;
             {
                 const Piece pc = piece_at(x, x1, share, pad);
-                if (pc.padding) break;
+                if (pc.padding) {  // (uniform) the next segment, if the run reaches it
+                    if (pc.next_seg >= x1) break;
+                    __syncthreads();
+                    if (tid == 0) pool.run[0] = pc.next_seg;
+                    __syncthreads();
+                    continue;
+                }
                 auto nothing = []() {};
                 const uint16_t *dq = desc_ptr<const uint16_t>(dw, offsetof(LayerDesc, q));
                 const uint16_t *dk = desc_ptr<const uint16_t>(dw, offsetof(LayerDesc, k_cache));
