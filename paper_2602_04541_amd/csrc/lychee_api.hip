@@ -31,7 +31,7 @@ struct lychee_ctx {
     int32_t wg_per_cu = 2;
     int32_t n_wg = 0;          // 0 = n_cu * wg_per_cu
     int32_t step_mode = LYCHEE_STEP_PHASED;
-    int32_t g_block_rows = 48;
+    int32_t g_block_rows = 0;  // 0: by the context's length, see fill_common
     int32_t tail_permille = 250;
     int32_t select_margin = 60;  // tenths of a standard deviation, see LYCHEE_OPT_SELECT_MARGIN
     int32_t select_lead = 3000;  // blocks of 64 rows streamed while a select runs, see LYCHEE_OPT_SELECT_LEAD
@@ -82,8 +82,8 @@ namespace {
 constexpr size_t kSyncGen = 0, kSyncExit = 64;
 constexpr size_t kSyncRows = (size_t)kMaxBatch * kMaxKvHeads;  // (sequence, KV head) pairs a shape can have
 constexpr size_t kSyncThr = 4096;                               // uint64 [kSyncRows]
-constexpr size_t kSyncSet = kSyncThr + kSyncRows * 8;           // uint32 [kSyncRows], kSetFlagStride apart
-constexpr size_t kSyncSeg = kSyncSet + kSyncRows * kSetFlagStride * 4;  // uint32 [kSyncRows][2]
+constexpr size_t kSyncSet = kSyncThr + kSyncRows * 8;           // uint32 [kSetFlagWords]
+constexpr size_t kSyncSeg = kSyncSet + kSetFlagWords * 4;  // uint32 [kSyncRows][2]
 constexpr size_t kSyncCount = kSyncSeg + kSyncRows * 8;         // int32 [3][kSyncRows]
 constexpr size_t kSyncArrived = kSyncCount + 3 * kSyncRows * 4; // uint32 [kSyncRows]
 constexpr size_t kSyncBytes = kSyncArrived + kSyncRows * 4;
@@ -327,15 +327,21 @@ void fill_common(Common &c, const lychee_ctx *ctx, const lychee_shape &s, const 
     c.list_row = w.list_row;
     c.n_wg = n_wg;
     c.part_stride = kPartSlots;
-    c.g_block_rows = ctx->g_block_rows;
+    // Unless the caller chose it: a gathered row costs a third more than a streamed one where the launch
+    // is bound by memory (contexts of 96K and more: 56.4 us a 128K layer, 57.7 with 64 rows); a
+    // shorter launch is bound by its pieces' chains of latencies, and fewer, longer pieces are
+    // faster (model loop at 32K 35.1 -> 32.5 us a layer, at 16K 32.2 -> 28.8; 64 short sequences 75.2 -> 73.4).
+    c.g_block_rows = ctx->g_block_rows > 0 ? ctx->g_block_rows : (s.max_len >= 98304 ? 48 : 64);
     c.tickets = reinterpret_cast<uint32_t *>(ctx->arena_dev);
     c.stats = reinterpret_cast<uint32_t *>(ctx->arena_dev + kArenaStats);
     c.tail_permille = ctx->tail_permille;
-    // chunks small enough to level the finish times, large enough that a segment
-    // never has more than ~192 of them (partial slots per head are limited)
+    // chunks small enough to level the finish times, large enough that a segment never has more than
+    // ~192 of them (partial slots per head are limited) and that a chunk outweighs its piece's
+    // start-up and merge, about five blocks (36 layers of 33333 rows, chunks of 3 and of 8 blocks: the
+    // step 464 and 424 us, its gather launch 137 and 111; 12 layers of 8 x 3K-16K: 406 and 363)
     const int64_t seg_blocks = (s.max_len + kBlockRows - 1) / kBlockRows;
     c.chunk_blocks = (int32_t)((seg_blocks + 191) / 192);
-    if (c.chunk_blocks < 2) c.chunk_blocks = 2;
+    if (c.chunk_blocks < 8) c.chunk_blocks = 8;
     c.sel_margin = 0.1f * (float)ctx->select_margin;
     c.scale = (float)(1.0 / sqrt((double)kHeadDim));
     c.scale_log2e = (float)(1.4426950408889634 / sqrt((double)kHeadDim));

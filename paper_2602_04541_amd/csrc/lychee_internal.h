@@ -26,7 +26,14 @@ constexpr int kDirectLen = 4096;         // sequences this short are ranked with
 constexpr int kCandBuf = 256;            // candidates a wavefront collects in LDS between flushes
 constexpr int kThrSplit = 4;             // units that share a score row's threshold sample in a layer launch
 constexpr int kKeyBuf = 4096;            // rows whose keys a piece buffers in LDS when its threshold comes late
-constexpr int kSetFlagStride = 32;        // words from one set flag to the next: a line each, hundreds of workgroups poll them
+// Set flags: one per (sequence, KV head).  Those of the first sequence lie in lines of their own (beside a
+// single sequence hundreds of workgroups poll eight of them), the others side by side.
+constexpr int kSetFlagStride = 32;
+constexpr int kSetFlagWords = kMaxKvHeads * kSetFlagStride + kMaxBatch * kMaxKvHeads;
+__host__ __device__ constexpr int set_flag_at(int b, int g, int n_kv_heads)
+{
+    return b == 0 ? g * kSetFlagStride : kMaxKvHeads * kSetFlagStride + b * n_kv_heads + g;
+}
 constexpr int kPieceBlocks = 5;           // blocks of streaming or gathering that the fixed costs of a piece are worth
 constexpr float kMinusBig = -1.0e30f;    // "no score yet" sentinel of the running maximum
 
@@ -141,7 +148,7 @@ struct LayerLaunch {
     uint32_t *gen;         // the generation (read at the start, advanced at the end)
     uint32_t *exit_count;  // workgroups that have finished
     unsigned long long *thr_flags;  // [B * n_rgroups] {generation, threshold} of cur's score rows
-    uint32_t *set_flags;   // [B * H_kv], kSetFlagStride apart: generation once the set of (sequence, KV head) is final
+    uint32_t *set_flags;   // (set_flag_at) generation once the set of (sequence, KV head) is final
     uint32_t *seg_count;   // [B * H_kv * 2] partials written so far of each R / G segment (zero between launches)
     uint32_t *thr_arrived; // [B * n_rgroups] threshold units of a score row that have left their keys (likewise)
 };

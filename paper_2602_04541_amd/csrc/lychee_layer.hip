@@ -138,7 +138,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                 const int b = j / n_rp;
                 const int g = prev.rgroup[j % n_rp];
                 if (SELECTS != 0 && !kNow) select_unit<SELECTS == 2>(c, prev, b, g, sh.unit.sel, pool);
-                publish_set(P.set_flags + (b * c.n_kv_heads + g) * kSetFlagStride, gen);
+                publish_set(P.set_flags + set_flag_at(b, g, c.n_kv_heads), gen);
             } else if (j < nS + nC) {
                 const int u = j - nS;
                 const int b = u / n_keep;
@@ -146,7 +146,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                 for (int gg = 0; gg < c.n_kv_heads; ++gg)
                     if (kept.rindex[gg] == 0xFF && want-- == 0) g = gg;
                 copy_set_unit(c, kept, b, g);
-                publish_set(P.set_flags + (b * c.n_kv_heads + g) * kSetFlagStride, gen);
+                publish_set(P.set_flags + set_flag_at(b, g, c.n_kv_heads), gen);
             } else {
                 // a score row's sample is dealt to kThrSplit units: one round of loads each
                 const int u = (j - nS - nC) / kThrSplit;
@@ -392,7 +392,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                                                 sh.attn, nothing);
                 } else {
                     if ((P.gate_mask >> pc.g) & 1ull)
-                        await_set(P.set_flags + (pc.b * c.n_kv_heads + pc.g) * kSetFlagStride, my_gen, timeouts, pool);
+                        await_set(P.set_flags + set_flag_at(pc.b, pc.g, c.n_kv_heads), my_gen, timeouts, pool);
                     const int32_t *idx_src = desc_ptr<const int32_t>(dw, offsetof(LayerDesc, idx_src) + 8 * (size_t)pc.g) +
                                              ((int64_t)pc.b * c.n_kv_heads + pc.g) * c.k;
                     dispatch_piece<true, true>(__builtin_popcount(pc.hmask), c, dq, dk, dv, idx_src, Emit{}, d_part_o, d_part_ml,

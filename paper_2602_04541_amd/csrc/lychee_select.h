@@ -9,68 +9,13 @@ namespace {
 
 // ------------------------------------------------------------------------------ C
 // out = (sum_s w_s o_s) / (sum_s w_s l_s),  w_s = 2^((m_s - M) log2(e)/sqrt(d)),  M = max_s m_s,
-// over the head's partial slots in ascending order (a fixed summation tree).
-// `known_count` >= 0: the number of partial slots, known to the caller; else it is read from part_count.
-template <typename Pool>
-__device__ __forceinline__ void combine_unit(const Common &c, const LayerDesc &p, int bh, SharedCombine &sh,
-                                             Pool &pool, int known_count = -1)
-{
-    int count = known_count >= 0 ? known_count : gload(p.part_count + bh);
-    count = count < 0 ? 0 : (count > c.part_stride ? c.part_stride : count);
-    const float *ml = p.part_ml + (int64_t)bh * c.part_stride * 2;
-    const float *po = p.part_o + (int64_t)bh * c.part_stride * kHeadDim;
-    float m_loc = kMinusBig;
-    for (int s = threadIdx.x; s < count; s += kThreads)
-        if (gload(ml + 2 * s + 1) > 0.0f) m_loc = fmaxf(m_loc, gload(ml + 2 * s));
-    const float M = block_max(m_loc, pool.fred);
-    float l_loc = 0.0f;
-    for (int s = threadIdx.x; s < count; s += kThreads) {
-        const float ls = gload(ml + 2 * s + 1);
-        const float w = ls > 0.0f ? fast_exp2((gload(ml + 2 * s) - M) * c.scale_log2e) : 0.0f;
-        sh.w[0][s] = w;
-        l_loc = fmaf(w, ls, l_loc);
-    }
-    const float lsum = block_sum(l_loc, pool.fred);  // also publishes sh.w
-    constexpr int kLanes = kThreads / 32;  // interleaved slot subsets
-    const int lane8 = threadIdx.x >> 5;
-    const int c4 = threadIdx.x & 31;       // which 4 columns
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int s0 = lane8; s0 < count; s0 += 8 * kLanes) {
-        // 8 slots per thread and round, all loads issued before the first use
-        float wv[8];
-        float4 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int s = s0 + kLanes * u;
-            wv[u] = s < count ? sh.w[0][s] : 0.0f;
-            v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (wv[u] > 0.0f) v[u] = gload_f4(po + (int64_t)s * kHeadDim + c4 * 4);
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            acc.x = fmaf(wv[u], v[u].x, acc.x);
-            acc.y = fmaf(wv[u], v[u].y, acc.y);
-            acc.z = fmaf(wv[u], v[u].z, acc.z);
-            acc.w = fmaf(wv[u], v[u].w, acc.w);
-        }
-    }
-    reinterpret_cast<float4 *>(sh.red + lane8 * kHeadDim)[c4] = acc;
-    __syncthreads();
-    if (threadIdx.x < kHeadDim) {
-        float o = 0.0f;
-#pragma unroll
-        for (int i = 0; i < kLanes; ++i) o += sh.red[i * kHeadDim + threadIdx.x];
-        const float r = lsum > 0.0f ? o / lsum : 0.0f;
-        gstore(p.out + (int64_t)bh * kHeadDim + threadIdx.x, f32_to_bf16_rne(r));
-    }
-    __syncthreads();
-}
-
-// The same merge for all NH heads of a segment at once, by the workgroup that has just written the
-// segment's last partial.  It stands at the end of the layer's chain and is latency, not bytes: the
-// partial outputs of up to kGrp * kU slots are asked for before anything else; meanwhile wavefront
-// h turns head h's (m, l) pairs into weights (in LDS); then thread (head, group, column quad)
-// sums its group's slots, and the groups are added in a fixed order.  (With every wavefront
+// over a head's partial slots in ascending order (a fixed summation tree), for all NH heads of a
+// segment at once (in a layer launch by the workgroup that has just written the segment's last
+// partial, in a phased step one head per unit).
+// It stands at the end of the layer's chain and is latency, not bytes: the partial outputs of up to
+// kGrp * kU slots are asked for before anything else; meanwhile wavefront h turns head h's (m, l)
+// pairs into weights (in LDS); then thread (head, group, column quad) sums its group's slots, and
+// the groups are added in a fixed order.  (With every wavefront
 // keeping every head's running maximum and fetching each weight through the LDS crossbar, 12
 // exchanges per head and round and one more per slot, the merge took 6.0 us for 4 heads of 43
 // slots, loads in the L2 or not.)
@@ -349,9 +294,10 @@ __device__ __forceinline__ void threshold_unit(const Common &c, const LayerDesc 
         if (split.sub == 0) emit(n == L && c.prob_rule == 0 ? 0xFFFFFFFFu : 0u);
         return;
     }
-    // 128 of the top n among the sample, if that takes no more rows than the sample may have
-    const int most = L >= (1 << 16) ? kSampleTilesMax : kSampleTilesMax / 2;
-    const int enough = (int)(8.0f * (float)L / (float)n) + 1;
+    // 128 of the top n among the sample, if that takes no more rows than the sample may have; whole rounds
+    // of loads of an undivided unit, which takes 2048 rows at most (eight rounds took it 50 us)
+    const int most = L >= (1 << 16) && split.n_sub > 1 ? kSampleTilesMax : kSampleTilesMax / 2;
+    const int enough = (int)(8.0f * (float)L / (float)n) & ~31;
     const int n_tiles = enough > most ? most : (enough < kSampleTilesMin ? kSampleTilesMin : enough);
     const int n_sample = n_tiles * 16;
     const int g = p.rgroup[rgi];
