@@ -187,21 +187,21 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
         if (tid < c.batch || single) {
             const int L = pool.len[single ? 0 : tid];
             nb_r = n_rseg ? (uint32_t)((L + kBlockRows - 1) / kBlockRows) : 0u;
-            nb_g = n_gseg ? (uint32_t)((gather_rows(c, L) + gather_block(c) - 1) / gather_block(c)) : 0u;
+            nb_g = n_gseg ? (uint32_t)quot(gather_rows(c, L) + gather_block(c) - 1, gather_block(c)) : 0u;
         }
         // Many segments: a run crosses several, and every piece costs its start-up, merge and hand-over
         // (about 8 us, a block 1.2 to 1.7 us), so a segment counts kPieceBlocks blocks more than it has.
         // (64 sequences of 61 to 3001 rows: a run of equal blocks held up to nine short
         // segments, half the workgroups were done after 70 us and the last after 110.)
-        const int extra_r = 8ll * n_rseg * c.batch > W ? kPieceBlocks : 0;
-        const int extra_g = 8ll * n_gseg * c.batch > W ? kPieceBlocks : 0;
+        const int extra_r = 8 * n_rseg * c.batch > W ? kPieceBlocks : 0;
+        const int extra_g = 8 * n_gseg * c.batch > W ? kPieceBlocks : 0;
         nb_r += nb_r ? extra_r : 0;
         nb_g += nb_g ? extra_g : 0;
         unsigned long long tot64 = (unsigned long long)nb_r | ((unsigned long long)nb_g << 32);
         if (!single) (void)block_scan64(tot64, pool.scan64, tot64);
         // (the totals are the same in every lane: scalar arithmetic from here on)
-        const int64_t TR = (int64_t)uni((uint32_t)tot64) * n_rseg;
-        const int64_t TG = (int64_t)uni((uint32_t)(tot64 >> 32)) * n_gseg;
+        const int TR = uni((int)(uint32_t)tot64) * n_rseg;  // (below 2^31, checked before the launch)
+        const int TG = uni((int)(uint32_t)(tot64 >> 32)) * n_gseg;
         const int first = P.n_aside;
         const int Wn = W - first;
         int W_R = 0, W_G = 0;
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             int wg = u - a > 0.0f ? (int)(tg * __builtin_amdgcn_rcpf(u - a) + 0.5f) : Wn;
             // a gather piece is a chain of latencies (flag, set entries, rows, merge) of about 10 us
             // whatever its size: few gather blocks get a workgroup each rather than a queue on two
-            const int floor_wg = TG < Wn / 8 ? (int)TG : Wn / 8;
+            const int floor_wg = TG < (Wn >> 3) ? TG : Wn >> 3;
             wg = wg < floor_wg ? floor_wg : wg;
             // and the streaming keeps at least a third of the workgroups its share of the blocks would give it
             const int most = Wn - (int)(wn * tr * __builtin_amdgcn_rcpf(3.0f * (tr + tg)));
@@ -242,11 +242,11 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             pool.role[0][0] = first;
             pool.role[0][1] = W_R;
             pool.role[0][2] = n_rseg;
-            pool.role[0][3] = (int32_t)TR;
+            pool.role[0][3] = TR;
             pool.role[1][0] = Wn < 2 ? first : first + W_R;
             pool.role[1][1] = W_G;
             pool.role[1][2] = n_gseg;
-            pool.role[1][3] = (int32_t)TG;
+            pool.role[1][3] = TG;
             pool.extra[0] = extra_r;
             pool.extra[1] = extra_g;
             pool.gen = gen;  // (its load, issued when the kernel started, has long arrived)
@@ -271,19 +271,19 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             // Equal contiguous runs of blocks; when the segments are few, every segment is padded to
             // a whole number of runs, so that each workgroup has exactly one piece (a second piece
             // costs a second start-up and merge, which a launch this short cannot level out).
-            int share = (T_real + role_n - 1) / role_n;
+            int share = quot(T_real + role_n - 1, role_n);
             int pad = 0;
-            if (uni(pool.extra[kind]) == 0 && 8ll * nseg * c.batch <= role_n) {
-                const int s_last = share + (share / 8 > 1 ? share / 8 : 1);
+            if (uni(pool.extra[kind]) == 0 && 8 * nseg * c.batch <= role_n) {
+                const int s_last = share + (share >= 16 ? share >> 3 : 1);
                 int s = share;
                 for (; s <= s_last; ++s) {
-                    uint32_t runs = nseg * ((nb_mine + s - 1) / s), all = runs;
+                    uint32_t runs = nseg * (uint32_t)quot((int)nb_mine + s - 1, s), all = runs;
                     if (!single) (void)block_scan(runs, pool.scan, all);
                     if ((int)all <= role_n) break;
                 }
                 if (s <= s_last) share = s, pad = 1;
             }
-            const uint32_t mine = pad ? nseg * ((nb_mine + share - 1) / share) * share : nseg * nb_mine;
+            const uint32_t mine = pad ? nseg * (uint32_t)(quot((int)nb_mine + share - 1, share) * share) : nseg * nb_mine;
             uint32_t all;
             const uint32_t incl = single ? mine : block_scan(mine, pool.scan, all);
             if (tid < c.batch) pool.pre[tid + 1] = (int32_t)incl;
@@ -308,12 +308,12 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             pc.b = uni(find_item(pool.pre, c.batch, x));
             pc.len_b = uni(pool.len[pc.b]);
             const int seg_rows = gather ? gather_rows(c, pc.len_b) : pc.len_b;
-            const int nb = (seg_rows + brows - 1) / brows;
-            const int nbv = pad ? (nb + share - 1) / share * share : nb + uni(pool.extra[kind]);
+            const int nb = quot(seg_rows + brows - 1, brows);
+            const int nbv = pad ? quot(nb + share - 1, share) * share : nb + uni(pool.extra[kind]);
             const int pre_b = uni(pool.pre[pc.b]);
             const int xo = x - pre_b;
-            const int gi = xo / nbv;
-            const int blk = xo % nbv;
+            const int gi = quot(xo, nbv);
+            const int blk = xo - gi * nbv;
             pc.padding = blk >= nb;  // the run goes on in what a segment counts beyond its blocks
             const int seg_start = pre_b + gi * nbv;
             pc.next_seg = seg_start + nbv;
@@ -323,8 +323,9 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             pc.r0 = blk * brows;
             const int r1 = (blk + len) * brows;
             pc.r1 = r1 < seg_rows ? r1 : seg_rows;
-            pc.slot = x / share - seg_start / share;
-            pc.pieces = (seg_start + nb - 1) / share - seg_start / share + 1;
+            const int run0 = quot(seg_start, share);
+            pc.slot = quot(x, share) - run0;
+            pc.pieces = quot(seg_start + nb - 1, share) - run0 + 1;
             pc.ends = blk + len == nb;
             const uint32_t gmask = (1u << c.group) - 1u;
             if (!gather) {
