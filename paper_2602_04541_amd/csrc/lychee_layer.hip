@@ -19,7 +19,10 @@
 //   G pieces     Eq. 3 over the inherited set, on the last workgroups of the grid; a piece polls
 //                until the front unit that writes its KV head's set has published it
 //   combine      every piece writes its partial through to device memory and counts itself in;
-//                the piece that completes a segment merges the segment's partials into `out`
+//                the piece that completes a segment merges the segment's partials into `out` (a
+//                segment of one piece writes `out` itself)
+//   own select   in the build for calls that want their sets at once: the workgroup that completed a
+//                segment selects its set after its last piece
 //
 // Waiting is safe because every wait is for a front unit, front units never wait, and they run
 // on the lowest workgroup indices, which are dispatched first; waits are bounded all the same.

@@ -7,7 +7,7 @@
 //   R  retrieval streaming   Eq. 1, o = A V; rows whose pooled score reaches the threshold
 //                            are collected as candidates of Eq. 2's top-k (block-granular
 //                            sets, App. C: every block's best score is written in place)
-//   S  select                exact radix select over the candidates (ties to the lower
+//   S  select                exact select over the candidates (ties to the lower
 //                            position), ascending write of the set; verbatim copy for groups
 //                            that keep theirs; the Ratio, Threshold and Top-p rules of
 //                            Sec. 4.4.1 decide here how many are kept

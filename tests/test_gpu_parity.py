@@ -527,6 +527,55 @@ def test_select_routes_give_the_same_sets(ctx, margin, route):
     assert (few - few0, many - many0) == {60: (0, 0), 1250: (0, 0), -1000: (n_rows, 0), 100000: (0, n_rows)}[margin]
 
 
+@pytest.mark.parametrize("L,k,copies", [
+    (4096, 1, 0), (4096, 64, 63), (4096, 65, 70),   # every row a candidate; 64 and more equal keys at the cut
+    (8191, 4096, 0), (8192, 4096, 500),             # the last list that is held in registers
+    (8193, 4097, 500),                              # the first one that is read from memory
+    (16500, 8250, 100),                             # more positions than are staged at a time
+    (40000, 4096, 300), (65537, 2048, 0),           # sampled rows: the smaller and the larger sample
+    (131072, 96, 0), (131073, 96, 70),              # the last row of a bitmap window, the first of the next
+])
+def test_select_at_the_edges_of_its_routes(ctx, L, k, copies):
+    """The same sets from a plain call (which selects in its one launch) and from a deferred one (a later
+    launch selects), against the oracle, with no position allowed to differ."""
+    lb = H.binding()
+    w = wl.scaled(wl.WORKLOADS["c1"], max_len=L, k=k, planted=16)
+    inp = wl.make_layer(w, l_cap=L)
+    ones = np.ones(w.n_q_heads, np.uint8)
+    if copies:
+        _, _, sel0 = H.oracle_layer(inp, ones, k, None)
+        src = np.zeros((1, w.n_kv_heads, 1), np.int64)
+        for g in range(w.n_kv_heads):
+            src[0, g, 0] = np.argsort(-sel0[0, g, :L], kind="stable")[k - 1]  # rows equal to the last one in
+        wl.plant_ties(inp, copies, src)
+    _say("select edge: L=%d k=%d copies=%d" % (L, k, copies))
+    dl, _, idx, _, _, _ = H.check_layer(ctx, inp, ones, k, None, "L=%d k=%d" % (L, k), exact_sets=True)
+    ws = lb.alloc_workspace(dl.shape, "cuda", n_layers=2)
+    ws.fill_(0xFF)
+    dl.idx_out.fill_(-7)
+    ctx.decode_attn_deferred(dl.shape, dl.q, dl.k_cache, dl.v_cache, ones, None, dl.out, dl.idx_out, dl.lengths, ws)
+    ctx.select_flush()
+    torch.cuda.synchronize()
+    assert (dl.idx_out.cpu().numpy() == idx).all()
+
+
+@pytest.mark.parametrize("lens,k,block", [
+    ([61, 3001, 200, 1] * 20, 300, 1),       # runs that cross many short segments; set copies by every workgroup
+    ([61, 3001, 200, 1] * 20, 5, 64),
+    ([9000, 4097, 20000, 64] * 6, 1024, 1),  # front units in turn on few workgroups beside a long stream
+])
+def test_layer_calls_of_batches_whose_runs_cross_segments(ctx, lens, k, block):
+    """Ragged batches in one launch each, sets included: heads that keep theirs, single-piece segments that
+    write their output directly, and rows whose set is selected by the workgroup that completes them."""
+    w = wl.scaled(wl.WORKLOADS["c1"], batch=len(lens), max_len=max(lens), k=k, planted=1)
+    mask = np.zeros(w.n_q_heads, np.uint8)
+    mask[1] = 1                                   # the second KV head keeps its sets
+    inp = wl.make_layer(w, mask=mask, lens=np.array(lens, np.int32), l_cap=max(lens) + 3)
+    idx_in = H.previous_layer_sets(inp, k, block=block)
+    _say("batch of %d, longest %d, k=%d, block %d" % (len(lens), max(lens), k, block))
+    H.check_layer(ctx, inp, mask, k, idx_in, "batch", exact_sets=True, block=block)
+
+
 def test_sequence_longer_than_one_bitmap_window(ctx):
     """The ordered write marks positions in windows of 131072: a longer sequence needs two."""
     w = wl.scaled(wl.WORKLOADS["c1"], n_q_heads=2, n_kv_heads=1, max_len=150000, k=700, planted=32)
