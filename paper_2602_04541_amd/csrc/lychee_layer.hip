@@ -51,11 +51,17 @@ struct SharedLayer {
     int32_t extra[2];              // per kind: blocks that a segment counts beyond those it has
     int32_t run[3];                // the piece loop: next block of this workgroup's run, blocks per run, padded
     uint32_t gen;                  // the generation of this launch's flags
-    uint32_t wanted[kMaxBatch * kMaxKvHeads / 32];  // bit per score row: this workgroup selects its set
 };
+template <bool kUnits>
 union SharedRole {
-    SharedAttn attn;  // a piece
-    SharedUnit unit;  // a front unit, or the combine that follows a piece
+    SharedAttn attn;     // a piece
+    SharedCombine comb;  // the merge that follows a piece
+    SharedSelect sel;    // a front unit, or the launch's own select
+};
+template <>
+union SharedRole<false> {  // (the dense build selects nothing: a workgroup with less LDS is placed sooner)
+    SharedAttn attn;
+    SharedCombine comb;
 };
 
 __device__ __forceinline__ uint32_t load_agent(const uint32_t *p)
@@ -98,7 +104,9 @@ template <bool COLLECT, int SELECTS>
 __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLaunch P)
 {
     constexpr bool kNow = SELECTS == 3;
-    __shared__ SharedRole sh;
+    __shared__ __align__(16) SharedRole<COLLECT> sh;
+    SharedSelect &sel = reinterpret_cast<SharedSelect &>(sh);  // (never touched in the dense build)
+    __shared__ uint32_t wanted[SELECTS == 3 ? kMaxBatch * kMaxKvHeads / 32 : 1];  // bit per score row: this workgroup selects its set
     __shared__ SharedLayer pool;
     // Both layer descriptors are staged in LDS, one word per thread, and read from there.  (The
     // kernel argument is never indexed with a run-time value: for `idx_src[g]` the compiler
@@ -116,7 +124,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
     const uint32_t gen = tid == 0 ? load_agent(P.gen) : 0u;
     if (tid < c.batch) pool.len[tid] = clamp_len(c.lengths[tid], c.max_len);
     if (SELECTS == 3)
-        for (int i = tid; i < kMaxBatch * kMaxKvHeads / 32; i += kThreads) pool.wanted[i] = 0;
+        for (int i = tid; i < kMaxBatch * kMaxKvHeads / 32; i += kThreads) wanted[i] = 0;
     if (tid < kDescWords) {
         desc_cur[tid] = reinterpret_cast<const uint32_t *>(&P.cur)[tid];
         desc_prev[tid] = reinterpret_cast<const uint32_t *>(&P.prev)[tid];
@@ -140,7 +148,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             if (j < nS) {
                 const int b = j / n_rp;
                 const int g = prev.rgroup[j % n_rp];
-                if (SELECTS != 0 && !kNow) select_unit<SELECTS == 2>(c, prev, b, g, sh.unit.sel, pool);
+                if (SELECTS != 0 && !kNow) select_unit<SELECTS == 2>(c, prev, b, g, sel, pool);
                 publish_set(P.set_flags + set_flag_at(b, g, c.n_kv_heads), gen);
             } else if (j < nS + nC) {
                 const int u = j - nS;
@@ -163,10 +171,10 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                 split.keys = reinterpret_cast<uint32_t *>(cur.sel + row * c.sel_stride);  // (free until a select ranks this row whole)
                 split.arrived = P.thr_arrived + row;
                 switch (__builtin_popcount(cur.rmask[cur.rgroup[rgi]] & ((1u << c.group) - 1u))) {
-                case 1: threshold_unit<1>(c, cur, b, rgi, sh.unit.sel, pool, flag, gen, split); break;
-                case 2: threshold_unit<2>(c, cur, b, rgi, sh.unit.sel, pool, flag, gen, split); break;
-                case 3: threshold_unit<3>(c, cur, b, rgi, sh.unit.sel, pool, flag, gen, split); break;
-                default: threshold_unit<4>(c, cur, b, rgi, sh.unit.sel, pool, flag, gen, split); break;
+                case 1: threshold_unit<1>(c, cur, b, rgi, sel, pool, flag, gen, split); break;
+                case 2: threshold_unit<2>(c, cur, b, rgi, sel, pool, flag, gen, split); break;
+                case 3: threshold_unit<3>(c, cur, b, rgi, sel, pool, flag, gen, split); break;
+                default: threshold_unit<4>(c, cur, b, rgi, sel, pool, flag, gen, split); break;
                 }
             }
             __syncthreads();
@@ -425,14 +433,14 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             if (pool.flag) {
                 if (pc.pieces > 1 || kNow) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                 if (pc.pieces > 1) switch (__builtin_popcount(pc.hmask)) {
-                case 1: combine_segment<1>(c, cur, pc.b, pc.g, pc.hmask, pc.pieces, sh.unit.comb); break;
-                case 2: combine_segment<2>(c, cur, pc.b, pc.g, pc.hmask, pc.pieces, sh.unit.comb); break;
-                case 3: combine_segment<3>(c, cur, pc.b, pc.g, pc.hmask, pc.pieces, sh.unit.comb); break;
-                default: combine_segment<4>(c, cur, pc.b, pc.g, pc.hmask, pc.pieces, sh.unit.comb); break;
+                case 1: combine_segment<1>(c, cur, pc.b, pc.g, pc.hmask, pc.pieces, sh.comb); break;
+                case 2: combine_segment<2>(c, cur, pc.b, pc.g, pc.hmask, pc.pieces, sh.comb); break;
+                case 3: combine_segment<3>(c, cur, pc.b, pc.g, pc.hmask, pc.pieces, sh.comb); break;
+                default: combine_segment<4>(c, cur, pc.b, pc.g, pc.hmask, pc.pieces, sh.comb); break;
                 }
                 if (kNow && !gather && tid == 0) {  // every candidate of the row is in its list: its set can be selected
                     const int row = pc.b * uni(pool.role[0][2]) + (int)desc_u8(dw, offsetof(LayerDesc, rindex) + pc.g);
-                    pool.wanted[row >> 5] |= 1u << (row & 31);
+                    wanted[row >> 5] |= 1u << (row & 31);
                 }
             }
             __syncthreads();
@@ -446,9 +454,9 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
         const int n_rseg = uni(pool.role[0][2]);
         const int n_rows = c.batch * n_rseg;
         for (int i = 0; i < n_rows; i += 32) {
-            for (uint32_t rows = uni(pool.wanted[i >> 5]); rows != 0; rows &= rows - 1u) {
+            for (uint32_t rows = uni(wanted[i >> 5]); rows != 0; rows &= rows - 1u) {
                 const int row = i + __builtin_ctz(rows);
-                select_unit<false>(c, cur, row / n_rseg, cur.rgroup[row % n_rseg], sh.unit.sel, pool, P.thr_flags + row,
+                select_unit<false>(c, cur, row / n_rseg, cur.rgroup[row % n_rseg], sel, pool, P.thr_flags + row,
                                    pool.gen);
                 __syncthreads();
             }
