@@ -427,9 +427,11 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                     if (last) store_agent(counter, 0u);  // as every launch finds it
                 }
                 pool.flag = last;
-                pool.run[0] = x + pc.len;
             }
             __syncthreads();
+            // (only now: until the barrier a slower wavefront may still be reading where this piece lay, and
+            // one that saw the next piece's place would merge, or not merge, another segment than the others)
+            if (tid == 0) pool.run[0] = x + pc.len;
             if (pool.flag) {
                 if (pc.pieces > 1 || kNow) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                 if (pc.pieces > 1) switch (__builtin_popcount(pc.hmask)) {
@@ -445,6 +447,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             }
             __syncthreads();
         }
+        __syncthreads();  // (a workgroup that does both kinds sets up the second: every wavefront has read that the first is done)
     }
 
     // ------------------------------------------------------------------ this layer's own sets

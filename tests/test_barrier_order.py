@@ -1,0 +1,47 @@
+"""Where the kernels' barriers stand, read off the sources (no GPU needed): a word in LDS that one thread
+rewrites is only rewritten after a barrier that every reader of its old value has passed.  A wavefront that
+reads the new value takes another branch than the others, and the branches hold barriers of their own: the
+workgroup falls out of step.  That cannot be shown by running it, so the order itself is checked."""
+import os
+import re
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2602_04541_amd", "csrc")
+
+
+def source(name: str) -> str:
+    text = open(os.path.join(CSRC, name)).read()
+    return re.sub(r"//[^\n]*", "", re.sub(r"/\*.*?\*/", "", text, flags=re.S))
+
+
+def block_after(text: str, head: str) -> str:
+    """The braced block that follows the (only) occurrence of `head`, braces included."""
+    assert text.count(head) == 1, head
+    at = text.index("{", text.index(head) + len(head))
+    depth = 0
+    for i in range(at, len(text)):
+        depth += {"{": 1, "}": -1}.get(text[i], 0)
+        if depth == 0:
+            return text[at:i + 1]
+    raise AssertionError("unbalanced braces after " + head)
+
+
+def events(text: str, **patterns: str) -> list:
+    """Names of the patterns in the order in which they occur; "barrier" is always among them."""
+    patterns = dict(patterns, barrier=r"__syncthreads\(\)")
+    joined = "|".join("(?P<%s>%s)" % kv for kv in patterns.items())
+    return [m.lastgroup for m in re.finditer(joined, text)]
+
+
+def test_the_place_of_a_piece_is_rewritten_between_barriers():
+    kinds = block_after(source("lychee_layer.hip"), "for (int kind = 0; kind < 2; ++kind)")
+    loop = block_after(kinds, "for (;;)")
+    # where() reads the words of pool.run that thread 0 writes
+    seen = events(kinds.replace("auto where = [&]", ""), read=r"\bwhere\(\);", write=r"pool\.run\[\d\] = ")
+    assert seen.count("read") == 2 and seen.count("write") == 5, seen
+    order = [e for i, e in enumerate(seen) if i == 0 or e != seen[i - 1]]  # (runs of one event are one)
+    for a, b in zip(order, order[1:]):
+        assert {a, b} != {"read", "write"}, "no barrier between a %s and the %s after it: %s" % (a, b, order)
+    # the loop is left right after its first read, and the next kind's set-up writes
+    after = kinds[kinds.index(loop) + len(loop):]
+    assert events(after) == ["barrier"], "no barrier between the loop's last read and the next kind's set-up"
