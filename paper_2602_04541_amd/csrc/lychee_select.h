@@ -828,10 +828,8 @@ __device__ __forceinline__ int rule_keeps(const Common &c, const Entries &E, uin
             });
             (void)block_scan(mine, pool.scan, above);  // (its barriers publish the keys)
             const uint32_t in_bin = uni(sh.n_last);
-            if (in_bin > (uint32_t)kLastKeys && hi != lo) {
-                __syncthreads();
-                continue;
-            }
+            __syncthreads();  // (the next level, or the select that follows, counts in n_last anew)
+            if (in_bin > (uint32_t)kLastKeys && hi != lo) continue;
             // the key at which the mass is reached; all entries with that key have the same mass
             if (in_bin > (uint32_t)kLastKeys) {  // (all equal)
                 const unsigned long long each = mass_of(lo, lse);

@@ -45,3 +45,11 @@ def test_the_place_of_a_piece_is_rewritten_between_barriers():
     # the loop is left right after its first read, and the next kind's set-up writes
     after = kinds[kinds.index(loop) + len(loop):]
     assert events(after) == ["barrier"], "no barrier between the loop's last read and the next kind's set-up"
+
+
+def test_the_count_of_the_last_entries_is_read_before_it_is_reset():
+    rule = block_after(source("lychee_select.h"), "__device__ __forceinline__ int rule_keeps")
+    read = r"uni\(sh\.n_last\)"
+    assert len(re.findall(read, rule)) == 1
+    # (right after the read, ahead of every branch: the ways out of the loop differ in what they do next)
+    assert re.match(r";\s*__syncthreads\(\);", rule[re.search(read, rule).end():]), "no barrier right after the read"

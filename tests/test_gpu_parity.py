@@ -1012,6 +1012,36 @@ def test_probability_rules_on_short_and_ragged_sequences(ctx, rule, param):
     H.check_prob_rule_layer(ctx, inp, np.ones(w.n_q_heads, np.uint8), w.k, rule, param, "ragged rule %d" % rule)
 
 
+@pytest.mark.parametrize("L,k", [(3000, 2000), (9000, 5000), (50000, 2000)])
+def test_top_p_crosses_its_mass_among_equal_keys(ctx, L, k):
+    """More equal keys than are looked at one by one hold the position where the mass is reached: the rest of
+    it is counted in whole positions.  Rows of 3000 and of 9000 candidates (the first list fits registers, the
+    second does not), and a sampled row."""
+    copies = 400
+    w = wl.scaled(wl.WORKLOADS["c1"], max_len=L, k=k, planted=4)
+    inp = wl.make_layer(w, l_cap=L)
+    ones = np.ones(w.n_q_heads, np.uint8)
+    _, _, sel0 = H.oracle_layer(inp, ones, w.k, None)
+    src = np.zeros((1, w.n_kv_heads, 1), np.int64)
+    for g in range(w.n_kv_heads):
+        src[0, g, 0] = np.argsort(-sel0[0, g, :L], kind="stable")[6]  # (below the planted rows)
+    wl.plant_ties(inp, copies, src)
+    _, _, sel = H.oracle_layer(inp, ones, w.k, None)
+    s = sel[0, :, :L]
+    s = s - s.max(axis=1, keepdims=True)
+    prob = np.exp(s) / np.exp(s).sum(axis=1, keepdims=True)
+    tied = [s[g] == s[g, src[0, g, 0]] for g in range(w.n_kv_heads)]
+    assert all(t.sum() > copies for t in tied)
+    # the middle of the tied rows' share of the first KV head's mass
+    above = prob[0][s[0] > s[0, src[0, 0, 0]]].sum()
+    param = float(np.float32(above + 0.5 * prob[0][tied[0]].sum()))
+    _say("top-p %g: L=%d, %d equal keys where the mass is reached" % (param, L, int(tied[0].sum())))
+    sizes = H.check_prob_rule_layer(ctx, inp, ones, w.k, 2, param, "ties L=%d" % L)
+    # (the mass the smaller of two sets may lack, as in check_prob_rule_layer, in positions of this probability)
+    slack = 1 + 1e-4 * param / prob[0][src[0, 0, 0]]
+    assert abs(int(sizes[0, 0]) - int((s[0] > s[0, src[0, 0, 0]]).sum()) - copies // 2) <= slack
+
+
 def test_probability_rule_step_feeds_variable_sets_to_the_next_layers(ctx):
     lb = H.binding()
     n_layers, k = 4, 1500
