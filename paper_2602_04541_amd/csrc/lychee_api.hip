@@ -465,20 +465,20 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
     const int W = grid_of(ctx);
     fill_common(p.c, ctx, s, w, lengths, W);
     const bool blocks = s.block_size == 64;
-    int64_t units = 0;
+    int64_t selects = 0, copies = 0, thresholds = 0;  // front units
     if (prev != nullptr) {
         p.prev = *prev;
         p.has_prev = 1;
-        units += (int64_t)s.batch * prev->n_rgroups;
-        if (prev->copy_keep) units += (int64_t)s.batch * (s.n_kv_heads - prev->n_rgroups);
+        selects = (int64_t)s.batch * prev->n_rgroups;
+        if (prev->copy_keep) copies = (int64_t)s.batch * (s.n_kv_heads - prev->n_rgroups);
     }
     if (cur != nullptr) {
         p.cur = *cur;
         p.has_cur = 1;
         // (pieces know the thresholds of rows this short themselves; the units also keep a copy of the queries)
         p.has_thr = cur->emit_sel && !blocks && (s.max_len > kDirectLen || cur->q_keep != nullptr);
-        if (p.has_thr) units += (int64_t)s.batch * cur->n_rgroups * kThrSplit;
-        if (select_now && cur->copy_keep) units += (int64_t)s.batch * (s.n_kv_heads - cur->n_rgroups);
+        if (p.has_thr) thresholds = (int64_t)s.batch * cur->n_rgroups * kThrSplit;
+        if (select_now && cur->copy_keep) copies = (int64_t)s.batch * (s.n_kv_heads - cur->n_rgroups);
         if (prev != nullptr)
             for (int g = 0; g < s.n_kv_heads; ++g)
                 if (cur->idx_src[g] != nullptr && cur->idx_src[g] == prev->idx_out &&
@@ -486,32 +486,17 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
                     p.gate_mask |= 1ull << g;
         const int rc = check_layer_space(s, *cur);
         if (rc != LYCHEE_OK) return rc;
+        // (max_len bounds the lengths, which are on the device)
+        const int64_t seg_blocks = (s.max_len + kBlockRows - 1) / kBlockRows;
+        const FrontPlan front = front_plan((int32_t)selects, (int32_t)copies, (int32_t)thresholds, p.gate_mask != 0,
+                                           (int64_t)cur->n_rgroups * s.batch * seg_blocks, W);
+        p.n_front = front.n_front;
+        p.n_aside = front.n_aside;
     } else {
         // only front units: one workgroup each, up to the usual grid
-        p.c.n_wg = (int32_t)(units < 1 ? 1 : (units > W ? W : units));
+        const int64_t units = selects + copies;
+        p.c.n_wg = p.n_front = (int32_t)(units < 1 ? 1 : (units > W ? W : units));
     }
-    // The front units get workgroups to themselves, which then have nothing else to do (a grid too small
-    // to set workgroups aside lets them take pieces afterwards): one unit each beside a short
-    // layer, which waits for them; beside a long one as many units in turn, about 10 us each,
-    // as fit a sixth of the streaming (5.5 ns a block of 64 rows at 6 TB/s; max_len bounds
-    // the lengths, which are on the device).  A batch of 8 at 96K set 103 workgroups of 512 aside
-    // for 15 of its 140 us; now 26.  Set copies alone (2 us) are done on the way to the pieces.
-    const int wg = p.c.n_wg;
-    int64_t front = units;
-    const bool copies_only = !p.has_thr && (prev == nullptr || prev->n_rgroups == 0);
-    if (cur == nullptr || copies_only || wg < 8) {
-        front = front < wg ? front : wg;
-        p.n_aside = 0;
-    } else {
-        const int64_t seg_blocks = (s.max_len + kBlockRows - 1) / kBlockRows;
-        int64_t rounds = (int64_t)cur->n_rgroups * s.batch * seg_blocks * 11 / 2 / 60000;
-        rounds = rounds < 1 ? 1 : rounds;
-        front = (units + rounds - 1) / rounds;
-        const int64_t most = wg / (rounds > 1 && wg >= 16 ? 16 : 4);
-        front = front < most ? front : most;
-        p.n_aside = (int32_t)front;
-    }
-    p.n_front = (int32_t)front;
     p.lead_blocks = ctx->select_lead;
     p.gen = reinterpret_cast<uint32_t *>(ctx->sync_dev + kSyncGen);
     p.exit_count = reinterpret_cast<uint32_t *>(ctx->sync_dev + kSyncExit);
@@ -519,9 +504,8 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
     p.set_flags = reinterpret_cast<uint32_t *>(ctx->sync_dev + kSyncSet);
     p.seg_count = reinterpret_cast<uint32_t *>(ctx->sync_dev + kSyncSeg);
     p.thr_arrived = reinterpret_cast<uint32_t *>(ctx->sync_dev + kSyncArrived);
-    const bool selects = prev != nullptr && prev->n_rgroups > 0;
     const bool collects = cur != nullptr && cur->emit_sel;
-    const int build = !(selects || collects) ? 0 : (s.prob_rule != 0 ? 2 : (select_now ? 3 : 1));
+    const int build = !(selects > 0 || collects) ? 0 : (s.prob_rule != 0 ? 2 : (select_now ? 3 : 1));
     if (!ctx->timing) return launch_layer(p, build, stream) == hipSuccess ? LYCHEE_OK : LYCHEE_EHIP;
     lychee_ctx::Rec rec{cur != nullptr ? LYCHEE_KERNEL_STREAM : LYCHEE_KERNEL_SELECT, take_event(ctx), take_event(ctx)};
     if (rec.start == nullptr || rec.stop == nullptr) return LYCHEE_EHIP;

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "lychee_plan.h"
+
 namespace lychee {
 
 constexpr int kHeadDim = 128;
@@ -123,7 +125,7 @@ struct LaunchPlan {
 // side and with hand-offs inside the launch, everything the layer's output needs and the select
 // that the previous layer call left pending:
 //   front units   the pending select (and set copies) of `prev`, the selection thresholds of `cur`;
-//                 they run first, on the first n_front workgroups, and wait for nothing
+//                 they run first, on the first n_front workgroups (front_plan), and wait for nothing
 //   R pieces      cur's retrieval streaming; a piece polls for its row's threshold when it ends
 //   G pieces      cur's sparse gathers; a piece of a KV head in gate_mask polls until the front
 //                 unit that writes that head's inherited set has published it

@@ -24,8 +24,9 @@
 //   own select   in the build for calls that want their sets at once: the workgroup that completed a
 //                segment selects its set after its last piece
 //
-// Waiting is safe because every wait is for a front unit, front units never wait, and they run
-// on the lowest workgroup indices, which are dispatched first; waits are bounded all the same.
+// Waiting is safe because every wait is for a front unit, front units never wait, and where anything
+// waits they have the lowest workgroup indices, which are dispatched first, to themselves
+// (front_plan); waits are bounded all the same.
 // Partials cross from one XCD's L2 to another's without the agent-scope release fence (its
 // write-back of the whole L2, executed by every workgroup, costs more than the layer): they are
 // written with write-through stores, the writer waits until those have completed before it

@@ -1,0 +1,47 @@
+// How a launch is laid out: functions of sizes alone, in plain C++ (host, device and tests include them).
+#pragma once
+
+#include <stdint.h>
+
+#ifdef __HIP__
+#define LYCHEE_HD __host__ __device__
+#else
+#define LYCHEE_HD
+#endif
+
+namespace lychee {
+
+// The front units of a layer launch: workgroup w < n_front runs units w, w + n_front, ... before anything
+// else, and takes pieces afterwards unless w < n_aside.
+struct FrontPlan {
+    int32_t n_front, n_aside;
+};
+
+// selects, copies, thresholds: how many units of each kind; gated: gather pieces of the launch wait for sets
+// that its selects and copies write; r_blocks: blocks of 64 rows that the launch streams.
+//
+// Pieces wait for thresholds and for gated sets, and nothing else in a launch waits.  Workgroups start in
+// index order, and not all of them at once if the grid is larger than what fits the chip beside
+// whatever else runs there.  So where something waits, the front units have workgroups to themselves,
+// the lowest: those never wait, so that whatever a piece waits for has started before it and will end.
+// (Copies dealt over the whole grid, whose workgroups then went on to gated gathers, needed every
+// workgroup of the grid resident at once: the started ones would wait for copies of the others.)
+// Fewer than eight workgroups are always resident together, and too few to set any aside.
+// Copies alone (2 us) that nothing waits for are done on the way to the pieces.
+//
+// How many: one workgroup per unit beside a short layer, which waits for them; beside a long one as many
+// units in turn, about 10 us each, as fit a sixth of the streaming (5.5 ns a block at 6 TB/s).  A batch
+// of 8 at 96K set 103 workgroups of 512 aside for 15 of its 140 us; now 26.
+LYCHEE_HD inline FrontPlan front_plan(int32_t selects, int32_t copies, int32_t thresholds, bool gated, int64_t r_blocks,
+                                      int32_t n_wg)
+{
+    const int32_t units = selects + copies + thresholds;
+    if ((selects == 0 && thresholds == 0 && !gated) || n_wg < 8) return FrontPlan{units < n_wg ? units : n_wg, 0};
+    int64_t rounds = r_blocks * 11 / 2 / 60000;
+    rounds = rounds < 1 ? 1 : rounds;
+    const int32_t front = (int32_t)((units + rounds - 1) / rounds);
+    const int32_t most = n_wg / (rounds > 1 && n_wg >= 16 ? 16 : 4);
+    return front < most ? FrontPlan{front, front} : FrontPlan{most, most};
+}
+
+}  // namespace lychee

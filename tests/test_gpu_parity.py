@@ -1228,6 +1228,34 @@ def test_deferred_layer_calls_on_tiny_grids(ctx, n_wg):
             assert (got[0, g] == refs[-1][1][0, g]).all()
 
 
+def test_deferred_calls_of_layers_without_a_retrieval_head(ctx):
+    """Every piece is a gather and every gather waits for a set that the same launch copies: 300 copies,
+    written by workgroups that take no pieces."""
+    lb = H.binding()
+    n_seq, k = 150, 12
+    lens_h = np.array([64, 700, 3001] * 50, np.int32)
+    w = wl.scaled(wl.WORKLOADS["c1"], batch=n_seq, max_len=3001, k=k, planted=1)
+    mask = np.zeros(w.n_q_heads, np.uint8)
+    inp = wl.make_layer(w, mask=mask, lens=lens_h, l_cap=3001)
+    idx_in = H.previous_layer_sets(inp, k, block=64)
+    out_ref, _, _ = H.oracle_layer(inp, mask, k, idx_in, block=64)
+    dl = H.DeviceLayer(inp, k, idx_in, block=64)
+    ws = lb.alloc_workspace(dl.shape, "cuda", n_layers=2)
+    ws.fill_(0xFF)
+    sets = [dl.idx_in] + [torch.full_like(dl.idx_in, -7) for _ in range(3)]
+    outs = [torch.full_like(dl.out, float("nan")) for _ in range(3)]
+    waits0 = ctx.wait_timeouts()
+    _say("three all-sparse layers, %d sequences, block-granular sets" % n_seq)
+    for l in range(3):
+        ctx.decode_attn_deferred(dl.shape, dl.q, dl.k_cache, dl.v_cache, mask, sets[l], outs[l], sets[l + 1], dl.lengths, ws)
+    ctx.select_flush()
+    torch.cuda.synchronize()
+    assert ctx.wait_timeouts() == waits0
+    for l in range(3):
+        H.assert_outputs_close(H.bf16_tensor_to_f64(outs[l]), out_ref, "all-sparse layer %d" % l)
+        assert torch.equal(sets[l + 1], dl.idx_in)
+
+
 def test_two_contexts_on_two_streams_run_layer_calls_side_by_side():
     """Two contexts, each on a stream of its own, run deferred layer chains at the same time (two
     model replicas on one GPU).  The launches share the GPU's workgroup slots; every wait inside a

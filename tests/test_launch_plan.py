@@ -1,0 +1,77 @@
+"""How launches are laid out (csrc/lychee_plan.h), compiled for the host (no GPU needed)."""
+import ctypes
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2602_04541_amd", "csrc")
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="no C++ compiler")
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("plan") / "plan.so")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-shared", "-fPIC", "-I", CSRC,
+                           os.path.join(ROOT, "tests", "c", "plan.cpp"), "-o", lib])
+    dll = ctypes.CDLL(lib)
+    dll.front_plan.argtypes = [ctypes.c_int32] * 4 + [ctypes.c_int64, ctypes.c_int32, ctypes.c_void_p]
+    return dll
+
+
+def front_plan(plan, selects, copies, thresholds, gated, r_blocks, n_wg):
+    out = (ctypes.c_int32 * 2)()
+    plan.front_plan(selects, copies, thresholds, int(gated), r_blocks, n_wg, out)
+    return out[0], out[1]
+
+
+def gets_stuck(n_front, n_aside, n_wg, resident):
+    """Workgroups start in index order as places come free.  One below n_front runs its units first; one below
+    n_aside leaves then, every other one takes pieces that wait (the worst case) until all units are done."""
+    started, waiting = 0, 0
+    while started < n_wg:
+        if waiting == resident and started < n_front:
+            return True                 # every place is held by a workgroup that waits for one not started
+        if waiting == resident:
+            return False                # all units are done or running: the waiting ones go on
+        started += 1
+        if started > n_aside:
+            waiting += 1
+    return False
+
+
+def layers(rng):
+    """What consecutive layers of a call bring: (selects, copies, thresholds, gated, blocks streamed)."""
+    batch = rng.choice([1, 2, 3, 8, 64, 100, 256])
+    kv = rng.choice([1, 2, 8, 64])
+    prev_r, cur_r = rng.randint(0, kv), rng.randint(0, kv)
+    blocks = sum((rng.choice([1, 64, 3001, 32768, 131072]) + 63) // 64 for _ in range(batch))
+    selects, copies = rng.choice([(batch * prev_r, batch * (kv - prev_r)), (0, batch * kv), (0, 0)])
+    thresholds = rng.choice([0, 4 * batch * cur_r])
+    return selects, copies, thresholds, bool(selects + copies) and rng.random() < 0.7, cur_r * blocks
+
+
+def test_no_piece_waits_for_a_workgroup_that_may_not_have_started(plan):
+    rng = random.Random(5)
+    cases = [(0, 800, 0, True, 0)] + [layers(rng) for _ in range(400)]   # (copies alone, every piece a gated gather)
+    for case in cases:
+        selects, copies, thresholds, gated, _ = case
+        for n_wg in (1, 2, 7, 8, 9, 37, 256, 512, 513, 768):
+            n_front, n_aside = front_plan(plan, *case, n_wg)
+            assert 0 <= n_aside <= n_front <= n_wg
+            assert n_front > 0 or selects + copies + thresholds == 0
+            assert n_aside < n_wg            # somebody takes the pieces
+            if not (gated or thresholds):
+                continue
+            for resident in {min(n_wg, r) for r in (7, 8, 100, 256, 512)}:
+                assert not gets_stuck(n_front, n_aside, n_wg, resident), (case, n_wg, resident, n_front, n_aside)
+
+
+def test_copies_that_nothing_waits_for_are_done_on_the_way(plan):
+    assert front_plan(plan, 0, 800, 0, False, 4096, 512) == (512, 0)
+    assert front_plan(plan, 0, 5, 0, False, 4096, 512) == (5, 0)
+    assert front_plan(plan, 0, 800, 0, True, 4096, 512) == (128, 128)    # gated: a quarter of the grid, to themselves
