@@ -94,19 +94,6 @@ constexpr int kPartSlots = 1024;  // partial slots per head in the workspace: st
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 inline bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
-// Capacity of one score row's candidate list.  A threshold unit aims at n = min(k, L)
-// candidates plus six standard deviations of its sample (a few thousand at the usual sizes),
-// and makes every row a candidate when L <= kDirectLen or L <= 2k.  A list that still
-// overflows is not an error: the select unit then ranks the whole row itself.
-int32_t list_row_entries(int32_t max_len, int32_t k)
-{
-    int64_t cap = 4ll * k;
-    if (cap < (int64_t)k + 16384) cap = (int64_t)k + 16384;
-    if (cap < max_len / 64) cap = max_len / 64;
-    const int64_t all = round_up(max_len, 64);
-    return (int32_t)(cap < all ? cap : all);
-}
-
 // Per-layer scratch, laid out layer after layer.
 struct Workspace {
     size_t sel, part_o, part_ml, part_count, part_pool, list, list_count, thr, idx_set, q_keep;  // offsets inside a layer
@@ -118,7 +105,7 @@ Workspace carve(const lychee_shape &s, int n_layers)
 {
     Workspace w;
     w.sel_stride = (int32_t)round_up(s.max_len, 64);
-    w.list_row = list_row_entries(s.max_len, s.k);
+    w.list_row = list_row_entries(s.max_len, s.k, s.block_size == 64);
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t at = off;

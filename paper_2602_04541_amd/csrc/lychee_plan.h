@@ -11,6 +11,22 @@
 
 namespace lychee {
 
+// Capacity, in entries, of one score row's candidate list.  A threshold unit aims at n = min(k, L)
+// candidates plus six standard deviations of its sample (a few thousand at the usual sizes),
+// and makes every row a candidate when L <= kDirectLen or L <= 2k.  A list that still
+// overflows is not an error: the select unit then ranks the whole row itself.  Block-granular lists
+// hold an entry for every block of 64 rows, the last, partial one included, each written at its place
+// unasked: they must not overflow.
+LYCHEE_HD inline int32_t list_row_entries(int32_t max_len, int32_t k, bool blocks)
+{
+    int64_t cap = 4ll * k;
+    if (cap < (int64_t)k + 16384) cap = (int64_t)k + 16384;
+    const int64_t per_64 = blocks ? ((int64_t)max_len + 63) / 64 : max_len / 64;
+    if (cap < per_64) cap = per_64;
+    const int64_t all = ((int64_t)max_len + 63) / 64 * 64;
+    return (int32_t)(cap < all ? cap : all);
+}
+
 // The front units of a layer launch: workgroup w < n_front runs units w, w + n_front, ... before anything
 // else, and takes pieces afterwards unless w < n_aside.
 struct FrontPlan {

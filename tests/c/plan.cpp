@@ -8,3 +8,8 @@ extern "C" void front_plan(int32_t selects, int32_t copies, int32_t thresholds, 
     out[0] = p.n_front;
     out[1] = p.n_aside;
 }
+
+extern "C" int32_t list_row_entries(int32_t max_len, int32_t k, int32_t blocks)
+{
+    return lychee::list_row_entries(max_len, k, blocks != 0);
+}

@@ -740,6 +740,17 @@ def test_block_granular_decode_step(ctx, mode):
 
 
 # ------------------------------------------------------------------ the cache append of Alg. 1
+def test_block_granular_set_of_a_row_with_a_partial_last_block(ctx):
+    """More blocks than the list of a smaller row holds, and the last of them a single position."""
+    L, k = 2000001, 204
+    w = wl.scaled(wl.WORKLOADS["c1"], n_q_heads=1, n_kv_heads=1, max_len=L, k=k, planted=8, retrieval_heads=(0,))
+    inp = wl.make_layer(w, mask=np.ones(1, np.uint8), l_cap=L, device="cuda")
+    inp.k_cache[0, 0, L - 1] = inp.k_cache[0, 0, int(inp.planted_pos[0, 0, 0])]
+    _say("block-granular sets: %d positions in %d blocks" % (L, -(-L // 64)))
+    _, _, idx_gpu, _, _, _ = H.check_layer(ctx, inp, inp.mask, k, None, "L=%d" % L, exact_sets=True, block=64)
+    assert idx_gpu[0, 0].max() == (L - 1) // 64
+
+
 @pytest.mark.parametrize("token_major", [False, True])
 def test_append_kv_writes_exactly_the_new_rows(ctx, token_major):
     lb = H.binding()

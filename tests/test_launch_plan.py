@@ -20,6 +20,7 @@ def plan(tmp_path_factory):
                            os.path.join(ROOT, "tests", "c", "plan.cpp"), "-o", lib])
     dll = ctypes.CDLL(lib)
     dll.front_plan.argtypes = [ctypes.c_int32] * 4 + [ctypes.c_int64, ctypes.c_int32, ctypes.c_void_p]
+    dll.list_row_entries.argtypes = [ctypes.c_int32] * 3
     return dll
 
 
@@ -75,3 +76,16 @@ def test_copies_that_nothing_waits_for_are_done_on_the_way(plan):
     assert front_plan(plan, 0, 800, 0, False, 4096, 512) == (512, 0)
     assert front_plan(plan, 0, 5, 0, False, 4096, 512) == (5, 0)
     assert front_plan(plan, 0, 800, 0, True, 4096, 512) == (128, 128)    # gated: a quarter of the grid, to themselves
+
+
+def test_a_block_granular_list_holds_every_block(plan):
+    rng = random.Random(6)
+    for _ in range(2000):
+        k = rng.choice([1, 5, 204, 4096, 131072])
+        n = int(2 ** rng.uniform(0, 24))
+        for max_len in {n, n // 64 * 64 + 1, 64 * (k + 16384) + rng.choice([0, 1, 63, 64, 65]), 2000001, 1 << 24}:
+            if 1 <= max_len <= 1 << 24:
+                assert plan.list_row_entries(max_len, k, 1) >= (max_len + 63) // 64, (max_len, k)
+                # lists of positions may overflow: their size, and with it the workspace's, is what it was
+                assert plan.list_row_entries(max_len, k, 0) == min(max(4 * k, k + 16384, max_len // 64),
+                                                                   (max_len + 63) // 64 * 64)
