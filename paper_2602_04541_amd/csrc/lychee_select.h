@@ -19,7 +19,10 @@ namespace {
 // keeping every head's running maximum and fetching each weight through the LDS crossbar, 12
 // exchanges per head and round and one more per slot, the merge took 6.0 us for 4 heads of 43
 // slots, loads in the L2 or not.)
-template <int NH>
+// SKIP: a slot of weight 0 adds nothing whatever it holds (a piece without a valid row re-reads some row
+// in its place, and 0 times that row's infinity or NaN is NaN).  C units; in a layer launch such a slot
+// shows in the output.
+template <int NH, bool SKIP = false>
 __device__ __forceinline__ void combine_segment(const Common &c, const LayerDesc &p, int b, int g, uint32_t hmask,
                                                 int count, SharedCombine &sh)
 {
@@ -79,6 +82,7 @@ __device__ __forceinline__ void combine_segment(const Common &c, const LayerDesc
                 if (u % 4 == 0 && s0 + kGrp * u >= count) break;
                 const int s = s0 + kGrp * u + grp;
                 const float w = s < count ? sh.w[h][s] : 0.0f;
+                if (SKIP && !(w > 0.0f)) continue;
                 acc.x = fmaf(w, v[u].x, acc.x);
                 acc.y = fmaf(w, v[u].y, acc.y);
                 acc.z = fmaf(w, v[u].z, acc.z);

@@ -132,7 +132,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_small_kernel(const LaunchP
                 const int b = bh / c.n_q_heads, h = bh % c.n_q_heads;
                 int count = uni(gload(L.part_count + bh));  // at least 1: every head has a piece
                 count = count < 1 ? 1 : (count > c.part_stride ? c.part_stride : count);
-                combine_segment<1>(c, L, b, h / c.group, 1u << (h % c.group), count, su.comb);
+                combine_segment<1, true>(c, L, b, h / c.group, 1u << (h % c.group), count, su.comb);
             } else if ((u -= (int)tot[1]) < (int)tot[2]) {
                 const int li = find_item(pool.upre[2], P.t_count, u);
                 const LayerDesc &L = stage(P.t_first + li);

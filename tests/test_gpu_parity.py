@@ -309,6 +309,33 @@ def test_decode_step_with_given_sets_and_ragged_batch(ctx):
         H.assert_outputs_close(H.bf16_tensor_to_f64(outs[l]), refs[l][0], "ragged step layer %d" % l)
 
 
+def test_phased_step_skips_partials_without_a_row(ctx):
+    """A piece whose set entries are all -1 has no row and weight 0.  The rows it re-reads in their place hold
+    an infinity, and must not reach the output of heads whose sets do not name them."""
+    lb = H.binding()
+    n_layers, L, k, used = 2, 3000, 1024, 256
+    w = wl.scaled(wl.WORKLOADS["c1"], max_len=L, k=k, n_layers=n_layers, planted=8)
+    mask = np.zeros(w.n_q_heads, np.uint8)
+    inp = wl.make_layer(w, mask=mask, l_cap=L)
+    idx = np.full((1, w.n_kv_heads, k), -1, np.int32)
+    rng = np.random.default_rng(4)
+    for g in range(w.n_kv_heads):
+        idx[0, g, :used] = np.sort(rng.choice(np.arange(1, L), size=used, replace=False))
+    out_ref, _, _ = H.oracle_layer(inp, mask, used, np.ascontiguousarray(idx[:, :, :used]))
+    dl = H.DeviceLayer(inp, k, idx)
+    dl.v_cache[:, :, 0, ::3] = float("inf")
+    ws = lb.alloc_workspace(dl.shape, n_layers=n_layers)
+    ws.fill_(0xFF)
+    outs = [torch.full_like(dl.out, float("nan")) for _ in range(n_layers)]
+    _say("phased step: sets of %d entries of which %d name a row" % (k, used))
+    ctx.set_option(lb.OPT_GATHER_BLOCK, 128)      # (whole spans: the pieces with rows re-read nothing)
+    ctx.decode_step(dl.shape, [dl.q] * n_layers, [dl.k_cache] * n_layers, [dl.v_cache] * n_layers,
+                    np.stack([mask] * n_layers), dl.idx_in, outs, None, dl.lengths, ws)
+    torch.cuda.synchronize()
+    for l in range(n_layers):
+        H.assert_outputs_close(H.bf16_tensor_to_f64(outs[l]), out_ref, "layer %d" % l)
+
+
 # ------------------------------------------------------------------ boundary behaviour
 def test_error_codes_and_index_validator(ctx):
     lb = H.binding()
