@@ -452,20 +452,19 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
     const int W = grid_of(ctx);
     fill_common(p.c, ctx, s, w, lengths, W);
     const bool blocks = s.block_size == 64;
-    int64_t selects = 0, copies = 0, thresholds = 0;  // front units
     if (prev != nullptr) {
         p.prev = *prev;
         p.has_prev = 1;
-        selects = (int64_t)s.batch * prev->n_rgroups;
-        if (prev->copy_keep) copies = (int64_t)s.batch * (s.n_kv_heads - prev->n_rgroups);
+        p.n_selects = s.batch * prev->n_rgroups;
+        if (prev->copy_keep) p.n_copies = s.batch * (s.n_kv_heads - prev->n_rgroups);
     }
     if (cur != nullptr) {
         p.cur = *cur;
         p.has_cur = 1;
         // (pieces know the thresholds of rows this short themselves; the units also keep a copy of the queries)
-        p.has_thr = cur->emit_sel && !blocks && (s.max_len > kDirectLen || cur->q_keep != nullptr);
-        if (p.has_thr) thresholds = (int64_t)s.batch * cur->n_rgroups * kThrSplit;
-        if (select_now && cur->copy_keep) copies = (int64_t)s.batch * (s.n_kv_heads - cur->n_rgroups);
+        if (cur->emit_sel && !blocks && (s.max_len > kDirectLen || cur->q_keep != nullptr))
+            p.n_thresholds = s.batch * cur->n_rgroups * kThrSplit;
+        if (select_now && cur->copy_keep) p.n_copies = s.batch * (s.n_kv_heads - cur->n_rgroups);
         if (prev != nullptr)
             for (int g = 0; g < s.n_kv_heads; ++g)
                 if (cur->idx_src[g] != nullptr && cur->idx_src[g] == prev->idx_out &&
@@ -473,16 +472,17 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
                     p.gate_mask |= 1ull << g;
         const int rc = check_layer_space(s, *cur);
         if (rc != LYCHEE_OK) return rc;
-        // (max_len bounds the lengths, which are on the device)
-        const int64_t seg_blocks = (s.max_len + kBlockRows - 1) / kBlockRows;
-        const FrontPlan front = front_plan((int32_t)selects, (int32_t)copies, (int32_t)thresholds, p.gate_mask != 0,
-                                           (int64_t)cur->n_rgroups * s.batch * seg_blocks, W);
-        p.n_front = front.n_front;
-        p.n_aside = front.n_aside;
+        // The lengths are on the device; where even sequences of max_len make no difference (a single
+        // sequence's few units) the kernel is spared the question.
+        const int32_t r_blocks = cur->n_rgroups * s.batch * ((s.max_len + kBlockRows - 1) / kBlockRows);
+        p.front = front_plan(p.n_selects, p.n_copies, p.n_thresholds, p.gate_mask != 0, r_blocks, W);
+        if (p.front.n_front != front_plan(p.n_selects, p.n_copies, p.n_thresholds, p.gate_mask != 0, 0, W).n_front)
+            p.front.n_front = -1;
     } else {
         // only front units: one workgroup each, up to the usual grid
-        const int64_t units = selects + copies;
-        p.c.n_wg = p.n_front = (int32_t)(units < 1 ? 1 : (units > W ? W : units));
+        const int32_t units = p.n_selects + p.n_copies;
+        p.c.n_wg = units < 1 ? 1 : (units > W ? W : units);
+        p.front = FrontPlan{p.c.n_wg, 0};
     }
     p.lead_blocks = ctx->select_lead;
     p.gen = reinterpret_cast<uint32_t *>(ctx->sync_dev + kSyncGen);
@@ -492,7 +492,7 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
     p.seg_count = reinterpret_cast<uint32_t *>(ctx->sync_dev + kSyncSeg);
     p.thr_arrived = reinterpret_cast<uint32_t *>(ctx->sync_dev + kSyncArrived);
     const bool collects = cur != nullptr && cur->emit_sel;
-    const int build = !(selects > 0 || collects) ? 0 : (s.prob_rule != 0 ? 2 : (select_now ? 3 : 1));
+    const int build = !(p.n_selects > 0 || collects) ? 0 : (s.prob_rule != 0 ? 2 : (select_now ? 3 : 1));
     if (!ctx->timing) return launch_layer(p, build, stream) == hipSuccess ? LYCHEE_OK : LYCHEE_EHIP;
     lychee_ctx::Rec rec{cur != nullptr ? LYCHEE_KERNEL_STREAM : LYCHEE_KERNEL_SELECT, take_event(ctx), take_event(ctx)};
     if (rec.start == nullptr || rec.stop == nullptr) return LYCHEE_EHIP;

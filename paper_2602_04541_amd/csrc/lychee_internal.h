@@ -141,9 +141,8 @@ struct LayerLaunch {
     LayerDesc cur;         // the layer whose rows are streamed and gathered (has_cur)
     LayerDesc prev;        // the layer whose select is pending (has_prev)
     int32_t has_cur, has_prev;
-    int32_t has_thr;       // the launch computes cur's selection thresholds
-    int32_t n_front;       // workgroups that run front units (the first ones)
-    int32_t n_aside;       // and those of them that take no pieces afterwards
+    FrontPlan front;       // who runs front units; n_front < 0: front_plan says with the sequences' lengths, of
+    int32_t n_selects, n_copies, n_thresholds;  // so many units of each kind
     int32_t lead_blocks;   // blocks of 64 rows the device streams while a select runs: how much
                            // later than the streaming the gated gathers can start
     uint64_t gate_mask;    // bit g: KV head g's inherited set is written by this launch's front units

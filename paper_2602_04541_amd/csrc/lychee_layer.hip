@@ -6,7 +6,7 @@
 // a prologue and a tail) shows.  This kernel therefore runs the whole layer in ONE launch and
 // hands results from workgroup to workgroup inside it:
 //
-//   front units  (the first n_front workgroups, before anything else; they wait for nothing)
+//   front units  (the first workgroups, as many as front_plan says, before anything else; they wait for nothing)
 //       S  the select of the PREVIOUS layer call (Eq. 2), left pending by that call: its set is
 //          read again only by this layer's sparse heads (Sec. 3.1), so it runs beside this
 //          layer's streaming instead of after the previous layer's; copies of the sets of KV
@@ -51,6 +51,7 @@ struct SharedLayer {
     uint32_t nb[2][kMaxBatch];     // per kind: blocks of one segment of every sequence
     int32_t extra[2];              // per kind: blocks that a segment counts beyond those it has
     int32_t run[3];                // the piece loop: next block of this workgroup's run, blocks per run, padded
+    FrontPlan front;               // who runs front units
     uint32_t gen;                  // the generation of this launch's flags
 };
 template <bool kUnits>
@@ -72,6 +73,14 @@ __device__ __forceinline__ uint32_t load_agent(const uint32_t *p)
 __device__ __forceinline__ void store_agent(uint32_t *p, uint32_t v)
 {
     __hip_atomic_store((LYCHEE_GLOBAL uint32_t *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Blocks of 64 rows of all sequences of a batch, the same in every lane.
+__device__ __forceinline__ int all_blocks(const int32_t *len, int batch)
+{
+    uint32_t n = 0;
+    for (int b = threadIdx.x & 63; b < batch; b += 64) n += (uint32_t)(len[b] + kBlockRows - 1) / kBlockRows;
+    return __builtin_amdgcn_readlane((int)wave_scan(n), 63);
 }
 
 // A front unit has written the set of (b, g), with write-through stores: once every wavefront's
@@ -137,15 +146,20 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
     uint32_t *timeouts = c.stats + 2;
 
     // ------------------------------------------------------------------ front units
-    if (w < P.n_front) {
+    FrontPlan front = P.front;
+    if (__builtin_expect(front.n_front < 0, 0))
+        front = front_plan(P.n_selects, P.n_copies, P.n_thresholds, P.gate_mask != 0,
+                           P.cur.n_rgroups * all_blocks(pool.len, c.batch), W);
+    pool.front = front;  // (read again for the split; every thread writes the same, so that none waits for another's)
+    if (w < front.n_front) {
         __builtin_amdgcn_s_setprio(3);  // (the launch waits for these; a streaming workgroup shares the CU)
         const int n_rp = P.has_prev ? prev.n_rgroups : 0;
         const int nS = SELECTS && !kNow ? c.batch * n_rp : 0;
         const LayerDesc &kept = kNow ? cur : prev;  // whose kept sets are copied
         const int n_keep = c.n_kv_heads - kept.n_rgroups;
         const int nC = (kNow || P.has_prev) && kept.copy_keep ? c.batch * n_keep : 0;
-        const int nT = COLLECT && P.has_thr ? c.batch * cur.n_rgroups * kThrSplit : 0;
-        for (int j = w; j < nS + nC + nT; j += P.n_front) {
+        const int nT = COLLECT && P.n_thresholds ? c.batch * cur.n_rgroups * kThrSplit : 0;
+        for (int j = w; j < nS + nC + nT; j += front.n_front) {
             if (j < nS) {
                 const int b = j / n_rp;
                 const int g = prev.rgroup[j % n_rp];
@@ -214,7 +228,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
         // (the totals are the same in every lane: scalar arithmetic from here on)
         const int TR = uni((int)(uint32_t)tot64) * n_rseg;  // (below 2^31, checked before the launch)
         const int TG = uni((int)(uint32_t)(tot64 >> 32)) * n_gseg;
-        const int first = P.n_aside;
+        const int first = uni(pool.front.n_aside);
         const int Wn = W - first;
         int W_R = 0, W_G = 0;
         if (Wn < 2) {  // a single workgroup does both kinds, one after the other
@@ -483,7 +497,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
 
 hipError_t launch_layer(const LayerLaunch &plan, int build, hipStream_t stream)
 {
-    if (plan.c.n_wg < 1 || plan.c.n_wg > kMaxWg || plan.n_front > plan.c.n_wg) return hipErrorInvalidValue;
+    if (plan.c.n_wg < 1 || plan.c.n_wg > kMaxWg) return hipErrorInvalidValue;
     const dim3 grid(plan.c.n_wg), block(kThreads);
     switch (build) {
     case 0: hipLaunchKernelGGL((lychee_layer_kernel<false, 0>), grid, block, 0, stream, plan); break;

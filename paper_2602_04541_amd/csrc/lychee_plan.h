@@ -34,7 +34,8 @@ struct FrontPlan {
 };
 
 // selects, copies, thresholds: how many units of each kind; gated: gather pieces of the launch wait for sets
-// that its selects and copies write; r_blocks: blocks of 64 rows that the launch streams.
+// that its selects and copies write; r_blocks: blocks of 64 rows that the launch streams, by the sequences'
+// lengths (a capacity far above the lengths says nothing about them).
 //
 // Pieces wait for thresholds and for gated sets, and nothing else in a launch waits.  Workgroups start in
 // index order, and not all of them at once if the grid is larger than what fits the chip beside
@@ -45,19 +46,27 @@ struct FrontPlan {
 // Fewer than eight workgroups are always resident together, and too few to set any aside.
 // Copies alone (2 us) that nothing waits for are done on the way to the pieces.
 //
-// How many: one workgroup per unit beside a short layer, which waits for them; beside a long one as many
-// units in turn, about 10 us each, as fit a sixth of the streaming (5.5 ns a block at 6 TB/s).  A batch
-// of 8 at 96K set 103 workgroups of 512 aside for 15 of its 140 us; now 26.
-LYCHEE_HD inline FrontPlan front_plan(int32_t selects, int32_t copies, int32_t thresholds, bool gated, int64_t r_blocks,
+// How many: one workgroup per unit, but never more than a quarter of the grid; and beyond a sixteenth of it
+// (which a launch does not notice) only as many as run the units in turn, about 8 us each, in half of the
+// time that the streaming takes (5.5 ns a block at 6 TB/s), since the pieces need the thresholds when
+// they end.  On 512 workgroups, us a layer with 32, 64 and 128 in front: 8 sequences of 16411 to 98304 rows
+// 153, 153, 163; 64 of 8192: 336, 236, 203; 64 of 16384: 426, 351, 384.  (By the cache's capacity, and on a
+// sixteenth of the grid beside anything longer than 120 us, 64 sequences of 2000 to 5056 rows took 165 us in
+// a cache of 65536 rows and 125 in one of 5056, and 64 of 8192 took 340 a layer of the model loop.)
+LYCHEE_HD inline FrontPlan front_plan(int32_t selects, int32_t copies, int32_t thresholds, bool gated, int32_t r_blocks,
                                       int32_t n_wg)
 {
     const int32_t units = selects + copies + thresholds;
     if ((selects == 0 && thresholds == 0 && !gated) || n_wg < 8) return FrontPlan{units < n_wg ? units : n_wg, 0};
-    int64_t rounds = r_blocks * 11 / 2 / 60000;
-    rounds = rounds < 1 ? 1 : rounds;
-    const int32_t front = (int32_t)((units + rounds - 1) / rounds);
-    const int32_t most = n_wg / (rounds > 1 && n_wg >= 16 ? 16 : 4);
-    return front < most ? FrontPlan{front, front} : FrontPlan{most, most};
+    const uint32_t turns = (uint32_t)r_blocks / (8000u * 2u * 2u / 11u);  // 8000 ns in half of 5.5 ns a block
+    const int32_t few = n_wg / 16, most = n_wg / 4;
+    int32_t front = units;
+    if (turns > 1 && units > few) {
+        front = (int32_t)(((uint32_t)units + turns - 1) / turns);
+        front = front < few ? few : front;
+    }
+    front = front < most ? front : most;
+    return FrontPlan{front, front};
 }
 
 }  // namespace lychee

@@ -1,7 +1,7 @@
 /* The library's layout functions behind C names, for tests/test_launch_plan.py. */
 #include "lychee_plan.h"
 
-extern "C" void front_plan(int32_t selects, int32_t copies, int32_t thresholds, int32_t gated, int64_t r_blocks, int32_t n_wg,
+extern "C" void front_plan(int32_t selects, int32_t copies, int32_t thresholds, int32_t gated, int32_t r_blocks, int32_t n_wg,
                            int32_t *out)
 {
     const lychee::FrontPlan p = lychee::front_plan(selects, copies, thresholds, gated != 0, r_blocks, n_wg);

@@ -603,6 +603,27 @@ def test_layer_calls_of_batches_whose_runs_cross_segments(ctx, lens, k, block):
     H.check_layer(ctx, inp, mask, k, idx_in, "batch", exact_sets=True, block=block)
 
 
+def test_a_layer_call_in_a_cache_far_larger_than_its_sequences(ctx):
+    """Which workgroups run the front units follows from the lengths on the device: the same batch, in a cache
+    with room for ten times its rows, gives the same sets, and outputs that another split may round otherwise."""
+    lens = [5000, 9000, 4097, 300] * 10
+    w = wl.scaled(wl.WORKLOADS["c1"], batch=len(lens), n_q_heads=8, n_kv_heads=4, max_len=max(lens), k=700, planted=4,
+                  retrieval_heads=(0, 2, 4))
+    inp = wl.make_layer(w, lens=np.array(lens, np.int32), l_cap=max(lens), device="cuda")
+    idx_in = H.previous_layer_sets(inp, w.k)
+    _say("batch of %d in caches of %d and %d rows" % (len(lens), max(lens), 10 * max(lens)))
+    _, out, idx, _, _, _ = H.check_layer(ctx, inp, inp.mask, w.k, idx_in, "snug", exact_sets=True)
+    for name in ("k_cache", "v_cache"):
+        rows = getattr(inp, name)
+        roomy = torch.full((w.batch, w.n_kv_heads, 10 * max(lens), 128), 50.0, dtype=torch.bfloat16, device="cuda")
+        roomy[:, :, :max(lens)] = rows
+        setattr(inp, name, roomy)
+    dl = H.DeviceLayer(inp, w.k, idx_in)
+    out2, idx2 = H.run_hybrid(ctx, dl, inp.mask)
+    assert (idx2 == idx).all()
+    H.assert_outputs_close(out2, out, "roomy")
+
+
 def test_sequence_longer_than_one_bitmap_window(ctx):
     """The ordered write marks positions in windows of 131072: a longer sequence needs two."""
     w = wl.scaled(wl.WORKLOADS["c1"], n_q_heads=2, n_kv_heads=1, max_len=150000, k=700, planted=32)

@@ -19,7 +19,7 @@ def plan(tmp_path_factory):
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-shared", "-fPIC", "-I", CSRC,
                            os.path.join(ROOT, "tests", "c", "plan.cpp"), "-o", lib])
     dll = ctypes.CDLL(lib)
-    dll.front_plan.argtypes = [ctypes.c_int32] * 4 + [ctypes.c_int64, ctypes.c_int32, ctypes.c_void_p]
+    dll.front_plan.argtypes = [ctypes.c_int32] * 6 + [ctypes.c_void_p]
     dll.list_row_entries.argtypes = [ctypes.c_int32] * 3
     return dll
 
@@ -89,3 +89,17 @@ def test_a_block_granular_list_holds_every_block(plan):
                 # lists of positions may overflow: their size, and with it the workspace's, is what it was
                 assert plan.list_row_entries(max_len, k, 0) == min(max(4 * k, k + 16384, max_len // 64),
                                                                    (max_len + 63) // 64 * 64)
+
+
+def test_front_units_do_not_outlast_half_of_the_streaming(plan):
+    """Units run in turn (about 8 us each) on fewer workgroups than they could have only where that takes no
+    longer than half of the streaming (5.5 ns a block of 64 rows), or where a sixteenth of the grid is in front."""
+    rng = random.Random(7)
+    for case in [(256, 256, 1024, True, 64 * 4 * 128)] + [layers(rng) for _ in range(400)]:
+        units = sum(case[:3])
+        for n_wg in (16, 37, 256, 512, 768):
+            n_front, n_aside = front_plan(plan, *case, n_wg)
+            if n_aside == 0 or n_front in (units, n_wg // 4):
+                continue
+            turns = -(-units // n_front)
+            assert turns <= 1 + case[4] * 5.5e-3 / 2 / 8, (case, n_wg, n_front)
