@@ -287,8 +287,8 @@ const char *lychee_strerror(int code);
  *                 launches too short to hold several chunks per workgroup use none); it levels out
  *                 compute units that stream at different speeds
  *   GATHER_BLOCK  set entries whose gather is balanced against 64 streamed rows (a multiple
- *                 of 16 in [16, 128]; the default is 48 for max_len of 96K and more, where a
- *                 gathered row costs more than a streamed one, and 64 below)
+ *                 of 16 in [16, 128]; the default is 64, and 48 for deferred calls and
+ *                 layer-after-layer steps of long sequences or many rows in all)
  *   SELECT_MARGIN tenths of a standard deviation by which the sampled selection threshold is
  *                 lowered below its estimate of the k-th score (-10000..100000, default 60).
  *                 A larger margin makes more rows candidates of the exact select; a margin so

@@ -314,11 +314,7 @@ void fill_common(Common &c, const lychee_ctx *ctx, const lychee_shape &s, const 
     c.list_row = w.list_row;
     c.n_wg = n_wg;
     c.part_stride = kPartSlots;
-    // Unless the caller chose it: a gathered row costs a third more than a streamed one where the launch
-    // is bound by memory (contexts of 96K and more: 56.4 us a 128K layer, 57.7 with 64 rows); a
-    // shorter launch is bound by its pieces' chains of latencies, and fewer, longer pieces are
-    // faster (model loop at 32K 35.1 -> 32.5 us a layer, at 16K 32.2 -> 28.8; 64 short sequences 75.2 -> 73.4).
-    c.g_block_rows = ctx->g_block_rows > 0 ? ctx->g_block_rows : (s.max_len >= 98304 ? 48 : 64);
+    c.g_block_rows = ctx->g_block_rows > 0 ? ctx->g_block_rows : kGatherRows;
     c.tickets = reinterpret_cast<uint32_t *>(ctx->arena_dev);
     c.stats = reinterpret_cast<uint32_t *>(ctx->arena_dev + kArenaStats);
     c.tail_permille = ctx->tail_permille;
@@ -478,6 +474,8 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
         p.front = front_plan(p.n_selects, p.n_copies, p.n_thresholds, p.gate_mask != 0, r_blocks, W);
         if (p.front.n_front != front_plan(p.n_selects, p.n_copies, p.n_thresholds, p.gate_mask != 0, 0, W).n_front)
             p.front.n_front = -1;
+        const int32_t g_blocks = cur->n_sgroups * s.batch * (((s.k < s.max_len ? s.k : s.max_len) + 63) / 64);
+        if (ctx->g_block_rows == 0 && !select_now) p.c.g_block_rows = gather_block_rows(r_blocks, g_blocks, s.max_len, W);
     } else {
         // only front units: one workgroup each, up to the usual grid
         const int32_t units = p.n_selects + p.n_copies;

@@ -69,4 +69,21 @@ LYCHEE_HD inline FrontPlan front_plan(int32_t selects, int32_t copies, int32_t t
     return FrontPlan{front, front};
 }
 
+// Set entries per block of gather work, unless the caller chose it (blocks are dealt like blocks of 64
+// streamed rows).  64 makes the fewest pieces, whose chains of latencies bound a short launch: the faster one
+// for phased steps (12 layers of 1 to 64 sequences of 1K to 128K: 0.82 to 1.01 of the time with 48, 0.97 at
+// most sizes) and for calls that select for themselves (one layer of the same: 0.98 on average).
+constexpr int32_t kGatherRows = 64;
+// In launches whose gathers follow a select of the same launch (deferred calls, layer-after-layer steps) they
+// start late and should have more workgroups than as many streamed rows, but only where rows and not
+// latencies fill the launch: beyond 12 blocks per workgroup, by the cache's capacity, and for the longest
+// sequences.  Model loop, time with 64 over time with 48: two sequences (blocks per workgroup) at 48K (12) 0.98,
+// 64K (16) 1.05; four at 16K (9) 0.96, 32K (18) 0.99, 64K (33) 1.06 to 1.11; eight at 8K (9) 1.01, 16K (18) 1.00, 64K
+// (66) 1.07; 64 at 1K (9) 0.94, 3K (26) 1.09, 8K (72) 1.06.  One sequence of 1 to 5 retrieval heads: 64K 0.91 to 0.99,
+// 96K 0.96 to 1.02, 112K 0.98 to 1.02, 128K 0.95 to 1.08, and 1.04 over the 36 layers of a step.
+LYCHEE_HD inline int32_t gather_block_rows(int32_t r_blocks, int32_t g_blocks, int32_t max_len, int32_t n_wg)
+{
+    return (int64_t)r_blocks + g_blocks > 12ll * n_wg || max_len >= 7 << 14 ? 48 : kGatherRows;
+}
+
 }  // namespace lychee

@@ -13,3 +13,8 @@ extern "C" int32_t list_row_entries(int32_t max_len, int32_t k, int32_t blocks)
 {
     return lychee::list_row_entries(max_len, k, blocks != 0);
 }
+
+extern "C" int32_t gather_block_rows(int32_t r_blocks, int32_t g_blocks, int32_t max_len, int32_t n_wg)
+{
+    return lychee::gather_block_rows(r_blocks, g_blocks, max_len, n_wg);
+}

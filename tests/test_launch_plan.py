@@ -103,3 +103,10 @@ def test_front_units_do_not_outlast_half_of_the_streaming(plan):
                 continue
             turns = -(-units // n_front)
             assert turns <= 1 + case[4] * 5.5e-3 / 2 / 8, (case, n_wg, n_front)
+
+
+def test_gather_blocks_are_shorter_where_rows_fill_the_launch(plan):
+    for r, g, max_len, n_wg, rows in ((6144, 0, 4096, 512, 64), (6144, 1, 4096, 512, 48), (0, 12, 768, 1, 64),
+                                      (0, 13, 832, 1, 48), (2 ** 30, 2 ** 30, 1 << 24, 768, 48), (0, 0, 1, 512, 64),
+                                      (0, 512, 114687, 512, 64), (0, 512, 114688, 512, 48)):
+        assert plan.gather_block_rows(r, g, max_len, n_wg) == rows
