@@ -15,7 +15,7 @@ constexpr int kMaxBatch = 256;
 #ifndef LYCHEE_THREADS
 #define LYCHEE_THREADS 256
 #endif
-constexpr int kThreads = LYCHEE_THREADS;  // threads of every workgroup (256 or 512)
+constexpr int kThreads = LYCHEE_THREADS;  // threads of every workgroup (the layouts below fit 256)
 constexpr int kWaves = kThreads / 64;
 constexpr int kTileRows = 16;            // rows one wavefront handles per iteration
 constexpr int kBlockRows = kWaves * kTileRows;  // cache rows per block of the pooled row space

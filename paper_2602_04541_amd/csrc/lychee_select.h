@@ -228,8 +228,8 @@ __device__ __forceinline__ float tile_pooled_score(const uint4 (&kr)[4], const u
 }
 
 // T unit of score row (b, rgi): the ordered key that a row's pooled score has to reach to
-// become a candidate.  The key is the target-th largest of a sample of the row's scores,
-// to 22 bits, where target is the number of sampled rows expected among the top n = min(k, L)
+// become a candidate.  The key is the target-th largest of a sample of the row's scores, or the lower end
+// of a range of keys that holds it and at most one more, where target is the number of sampled rows expected among the top n = min(k, L)
 // plus sel_margin (six, unless the caller changes it) standard deviations; the streamed rows
 // that reach it are then very likely at least n and a few thousand more at most.  Whatever the sample yields, the select unit
 // checks the candidate count and ranks the whole row itself when the list cannot be used.
