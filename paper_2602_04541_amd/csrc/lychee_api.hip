@@ -437,12 +437,14 @@ int check_layer_space(const lychee_shape &s, const LayerDesc &d)
 
 // One launch of lychee_layer_kernel: everything `cur`'s output needs (cur may be null: only the
 // pending select), with the select and set copies of `prev` (may be null) among its front units.
-// select_now: `cur`'s own sets are wanted from this launch (then `prev` is null; no probability rule).
+// plain: `cur`'s own sets are wanted with the call (then `prev` is null): from this launch, or under a
+// probability rule from one that the caller enqueues behind it.
 // Every check happens before the launch; nothing else is enqueued.
 int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, const int32_t *lengths,
-                 const LayerDesc *cur, const LayerDesc *prev, hipStream_t stream, bool select_now = false)
+                 const LayerDesc *cur, const LayerDesc *prev, hipStream_t stream, bool plain = false)
 {
     if (cur == nullptr && prev == nullptr) return LYCHEE_OK;
+    const bool select_now = plain && s.prob_rule == 0;
     LayerLaunch p;
     memset(&p, 0, sizeof p);
     const int W = grid_of(ctx);
@@ -475,7 +477,7 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
         if (p.front.n_front != front_plan(p.n_selects, p.n_copies, p.n_thresholds, p.gate_mask != 0, 0, W).n_front)
             p.front.n_front = -1;
         const int32_t g_blocks = cur->n_sgroups * s.batch * (((s.k < s.max_len ? s.k : s.max_len) + 63) / 64);
-        if (ctx->g_block_rows == 0 && !select_now) p.c.g_block_rows = gather_block_rows(r_blocks, g_blocks, s.max_len, W);
+        if (ctx->g_block_rows == 0 && !plain) p.c.g_block_rows = gather_block_rows(r_blocks, g_blocks, s.max_len, W);
     } else {
         // only front units: one workgroup each, up to the usual grid
         const int32_t units = p.n_selects + p.n_copies;
@@ -683,8 +685,7 @@ int decode_attn(lychee_ctx *ctx, const lychee_shape *shape, const void *q, const
     // idx_out is complete when the call's work is: the launch selects as its segments complete.  (The
     // probability rules select in a launch of their own: inside the streaming one their registers
     // spilled and cost it more than a launch: 95.7 against 85.7 us for Top-p at 128K.)
-    if (shape->prob_rule == 0) return layer_launch(ctx, *shape, w, lengths, &d, nullptr, stream, true);
-    if ((rc = layer_launch(ctx, *shape, w, lengths, &d, nullptr, stream)) != LYCHEE_OK) return rc;
+    if ((rc = layer_launch(ctx, *shape, w, lengths, &d, nullptr, stream, true)) != LYCHEE_OK || shape->prob_rule == 0) return rc;
     return layer_launch(ctx, *shape, w, lengths, nullptr, &d, stream);
 }
 
