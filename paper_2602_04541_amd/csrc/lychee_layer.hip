@@ -150,9 +150,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
     if (__builtin_expect(front.n_front < 0, 0))
         front = front_plan(P.n_selects, P.n_copies, P.n_thresholds, P.gate_mask != 0,
                            P.cur.n_rgroups * all_blocks(pool.len, c.batch), W);
-    // (Read again for the split, in the build that spilled when it kept it across the front units; every thread
-    // writes the same, so that none waits for another's.  In the others the LDS read cost 0.1 us a launch.)
-    if (SELECTS == 2) pool.front = front;
+    pool.front = front;  // (read again for the split; every thread writes the same, so that none waits for another's)
     if (w < front.n_front) {
         __builtin_amdgcn_s_setprio(3);  // (the launch waits for these; a streaming workgroup shares the CU)
         const int n_rp = P.has_prev ? prev.n_rgroups : 0;
@@ -230,7 +228,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
         // (the totals are the same in every lane: scalar arithmetic from here on)
         const int TR = uni((int)(uint32_t)tot64) * n_rseg;  // (below 2^31, checked before the launch)
         const int TG = uni((int)(uint32_t)(tot64 >> 32)) * n_gseg;
-        const int first = SELECTS == 2 ? uni(pool.front.n_aside) : front.n_aside;
+        const int first = uni(pool.front.n_aside);
         const int Wn = W - first;
         int W_R = 0, W_G = 0;
         if (Wn < 2) {  // a single workgroup does both kinds, one after the other
