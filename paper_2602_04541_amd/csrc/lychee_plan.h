@@ -72,7 +72,7 @@ LYCHEE_HD inline FrontPlan front_plan(int32_t selects, int32_t copies, int32_t t
 // Set entries per block of gather work, unless the caller chose it (blocks are dealt like blocks of 64
 // streamed rows).  64 makes the fewest pieces, whose chains of latencies bound a short launch: the faster one
 // for phased steps (12 layers of 1 to 64 sequences of 1K to 128K: 0.82 to 1.01 of the time with 48, 0.97 at
-// most sizes) and for calls that select for themselves (one layer of the same: 0.98 on average).
+// most sizes) and for plain layer calls (one layer of the same: 0.98 on average).
 constexpr int32_t kGatherRows = 64;
 // In launches whose gathers follow a select of the same launch (deferred calls, layer-after-layer steps) they
 // start late and should have more workgroups than as many streamed rows, but only where rows and not
