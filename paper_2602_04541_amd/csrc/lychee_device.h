@@ -19,9 +19,6 @@ struct SharedAttn {
     };                                              //     filtered once the row's threshold is known
     int32_t cand_left[kWaves];                  // what each wavefront still holds when a piece ends
     int32_t cand_base;                          // where the workgroup's last candidates go
-    uint32_t late_thr;                          // the row's threshold, once a piece has fetched it
-    int32_t late_have;
-    uint32_t scan[kWaves + 1];                  // block_scan scratch of the key filter
 };
 constexpr int kBinBits = 11;               // a level of the select splits its range of keys into 2048 bins
 constexpr int kBins = 1 << kBinBits;
@@ -184,6 +181,21 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float x)
     return (uint16_t)(u >> 16);
 }
 
+// The kernel arguments are read through a pointer of their own address space (scalar loads, from the scalar
+// cache after the first), and every unit of work starts from a pointer that is opaque to the compiler
+// (arg_of).  Read through the kernel's parameter, a few dozen of the fields and what derives from them were
+// loaded once at the top, kept across every unit and spilled: 220 scalar registers in lanes of vector
+// registers, whose reads and writes made up a third of the instructions between two units.
+#define LYCHEE_CONSTANT __attribute__((address_space(4)))
+typedef const LYCHEE_CONSTANT Common ArgCommon;
+template <typename T>
+__device__ __forceinline__ const LYCHEE_CONSTANT T *arg_of()
+{
+    const LYCHEE_CONSTANT T *p = (const LYCHEE_CONSTANT T *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
 // Every buffer the units touch is device global memory, but most pointers reach the kernel
 // through the descriptor table, where the compiler can no longer see that.  Generic-address
 // ("flat") accesses make it wait for *all* outstanding loads before each use, which breaks the
@@ -259,7 +271,7 @@ __device__ __forceinline__ int clamp_len(int L, int max_len) { return L < 1 ? 1 
 
 // Selectable units of a sequence of L rows: its positions, or its blocks of 64 positions
 // (the last one may be short) in the block-granular variant (App. C).
-__device__ __forceinline__ int units_of(const Common &c, int L)
+__device__ __forceinline__ int units_of(ArgCommon &c, int L)
 {
     return (L + (1 << c.block_shift) - 1) >> c.block_shift;
 }
@@ -267,7 +279,7 @@ __device__ __forceinline__ int units_of(const Common &c, int L)
 // Units selected for a sequence of L units: Eq. 2's fixed budget, min(k, L), or under the
 // Ratio rule (Sec. 4.4.1: a budget proportional to the sequence length) the rounded-up share
 // keep_ppm / 10^6 of L, at least 1 and at most the fixed budget.
-__device__ __forceinline__ int budget_of(const Common &c, int L)
+__device__ __forceinline__ int budget_of(ArgCommon &c, int L)
 {
     int n = c.k < L ? c.k : L;
     if (c.keep_ppm > 0) {
@@ -320,12 +332,25 @@ __device__ __forceinline__ T *desc_ptr(const uint32_t *dw, size_t off)
     return reinterpret_cast<T *>(lo | (hi << 32));
 }
 
-// a / b for a >= 0, b > 0.  A workgroup divides a dozen times before its first load; the compiler's 32-bit
-// division is about 25 dependent instructions.  Below 2^22 the rounded product is at most one off.
+// a / b for 0 <= a < 2^31 - b, 0 < b < 2^24.  A workgroup divides a dozen times before its first load; the compiler's
+// 32-bit division is about 25 dependent instructions.  The rounded product is off by at most 2^-22 of itself,
+// so the remainder's quotient, below 2^10 either way, is at most one off.  No branches.
 __device__ __forceinline__ int quot(int a, int b)
 {
-    if (a >= (1 << 22)) return (int)((uint32_t)a / (uint32_t)b);
-    int q = (int)((float)a * __builtin_amdgcn_rcpf((float)b));
+    const float inv = __builtin_amdgcn_rcpf((float)b);
+    int q = (int)((float)a * inv);
+    q += (int)((float)(a - q * b) * inv);
+    const int r = a - q * b;
+    q += r >= b ? 1 : 0;
+    q -= r < 0 ? 1 : 0;
+    return q;
+}
+// The same of values that are the same in every lane: scalar arithmetic but for the product.
+__device__ __forceinline__ int quot_uni(int a, int b)
+{
+    const float inv = __builtin_amdgcn_rcpf((float)b);
+    int q = __builtin_amdgcn_readfirstlane((int)((float)a * inv));
+    q += __builtin_amdgcn_readfirstlane((int)((float)(a - q * b) * inv));
     const int r = a - q * b;
     q += r >= b ? 1 : 0;
     q -= r < 0 ? 1 : 0;
@@ -345,12 +370,12 @@ __device__ __forceinline__ int find_item(const int32_t *pre, int n, int x)
 
 // Rows a sparse KV head gathers for a sequence of L cache rows (set entries that are -1 or
 // name rows past L are skipped one by one), and how many of them make one pooled block.
-__device__ __forceinline__ int gather_rows(const Common &c, int L)
+__device__ __forceinline__ int gather_rows(ArgCommon &c, int L)
 {
     const int units = units_of(c, L);
     return (c.k < units ? c.k : units) << c.block_shift;
 }
-__device__ __forceinline__ int gather_block(const Common &c)
+__device__ __forceinline__ int gather_block(ArgCommon &c)
 {
     return c.block_shift ? (1 << c.block_shift) : c.g_block_rows;  // whole blocks stream like R rows
 }
@@ -358,16 +383,11 @@ __device__ __forceinline__ int gather_block(const Common &c)
 // Inclusive prefix sum over the 256 threads of the workgroup; `total` = sum of all.
 __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *wave_tot, uint32_t &total)
 {
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    uint32_t x = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t y = __shfl_up(x, d);
-        if (lane >= d) x += y;
-    }
+    const int tid = fresh_tid();
+    const int wave = tid >> 6;
+    const uint32_t x = wave_scan(v);
     __syncthreads();  // wave_tot may still be read by the previous call
-    if (lane == 63) wave_tot[wave] = x;
+    if ((tid & 63) == 63) wave_tot[wave] = x;
     __syncthreads();
     uint32_t before = 0, all = 0;
 #pragma unroll
@@ -380,12 +400,35 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *wave_tot, u
     return x + before;
 }
 
-// The same for four 16-bit counts packed in 64 bits (no field may overflow).
+// The same for two 32-bit counts packed in 64 bits (neither may overflow).
+__device__ __forceinline__ unsigned long long block_scan_pair(unsigned long long v, unsigned long long *wave_tot,
+                                                              unsigned long long &total)
+{
+    const int tid = fresh_tid();
+    const int wave = tid >> 6;
+    const unsigned long long x = (unsigned long long)wave_scan((uint32_t)v) |
+                                 ((unsigned long long)wave_scan((uint32_t)(v >> 32)) << 32);
+    __syncthreads();
+    if ((tid & 63) == 63) wave_tot[wave] = x;
+    __syncthreads();
+    unsigned long long before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        const unsigned long long t = wave_tot[w];
+        before += (w < wave) ? t : 0ull;
+        all += t;
+    }
+    total = all;
+    return x + before;
+}
+
+// The same for 64-bit numbers.
 __device__ __forceinline__ unsigned long long block_scan64(unsigned long long v, unsigned long long *wave_tot,
                                                            unsigned long long &total)
 {
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int tid = fresh_tid();
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
     unsigned long long x = v;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
@@ -411,7 +454,7 @@ __device__ __forceinline__ float block_max(float v, float *scratch)
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) v = fmaxf(v, __shfl_xor(v, d));
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
+    if ((fresh_tid() & 63) == 0) scratch[fresh_tid() >> 6] = v;
     __syncthreads();
     float r = scratch[0];
 #pragma unroll
@@ -424,7 +467,7 @@ __device__ __forceinline__ float block_sum(float v, float *scratch)
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
+    if ((fresh_tid() & 63) == 0) scratch[fresh_tid() >> 6] = v;
     __syncthreads();
     float r = scratch[0];
 #pragma unroll

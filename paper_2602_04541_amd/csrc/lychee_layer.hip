@@ -50,7 +50,8 @@ struct SharedLayer {
     int32_t role[2][4];            // per kind of piece: first workgroup, workgroups, segments per sequence, blocks
     uint32_t nb[2][kMaxBatch];     // per kind: blocks of one segment of every sequence
     int32_t extra[2];              // per kind: blocks that a segment counts beyond those it has
-    int32_t run[3];                // the piece loop: next block of this workgroup's run, blocks per run, padded
+    int32_t run[3];                // the piece loop: next block of this workgroup's run, blocks per run, padded (2: `at` holds the only piece)
+    __align__(16) int32_t at[8];   // the piece in hand: sequence, KV head, heads, blocks; pieces of its segment, first and end row, slot
     FrontPlan front;               // who runs front units
     uint32_t gen;                  // the generation of this launch's flags
 };
@@ -79,7 +80,7 @@ __device__ __forceinline__ void store_agent(uint32_t *p, uint32_t v)
 __device__ __forceinline__ int all_blocks(const int32_t *len, int batch)
 {
     uint32_t n = 0;
-    for (int b = threadIdx.x & 63; b < batch; b += 64) n += (uint32_t)(len[b] + kBlockRows - 1) / kBlockRows;
+    for (int b = fresh_tid() & 63; b < batch; b += 64) n += (uint32_t)(len[b] + kBlockRows - 1) / kBlockRows;
     return __builtin_amdgcn_readlane((int)wave_scan(n), 63);
 }
 
@@ -89,13 +90,13 @@ __device__ __forceinline__ void publish_set(uint32_t *flag, uint32_t gen)
 {
     wait_stores();
     __syncthreads();
-    if (threadIdx.x == 0) store_agent(flag, gen);
+    if (fresh_tid() == 0) store_agent(flag, gen);
 }
 
 // Before a gather piece reads a set that a front unit of this launch writes.
 __device__ __forceinline__ void await_set(const uint32_t *flag, uint32_t gen, uint32_t *timeouts, SharedLayer &pool)
 {
-    if (threadIdx.x == 0) {
+    if (fresh_tid() == 0) {
         int spin = 0;
         for (; spin < kSpinMax; ++spin) {
             if (load_agent(flag) == gen) break;
@@ -124,47 +125,49 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
     // held `7 g` - only their sum is a multiple of 4 -, and the scalar memory unit drops the
     // low bits of each, so that the load returned the halves of two neighbouring pointers.)
     __shared__ __align__(16) uint32_t desc_cur[kDescWords], desc_prev[kDescWords];
-    const Common &c = P.c;
+    const LYCHEE_CONSTANT LayerLaunch *A = arg_of<LayerLaunch>();
+    ArgCommon &c = A->c;
     const int w = blockIdx.x;
     const int W = c.n_wg;
-    const int tid = threadIdx.x;
+    const int tid = fresh_tid();
 
     // The generation is only ever used by thread 0 (it sets, polls and advances the flags), which
     // keeps it in a register: the load is not waited for before its first use, late in the launch.
-    const uint32_t gen = tid == 0 ? load_agent(P.gen) : 0u;
-    if (tid < c.batch) pool.len[tid] = clamp_len(c.lengths[tid], c.max_len);
+    const uint32_t gen = tid == 0 ? load_agent(A->gen) : 0u;
+    if (tid < c.batch) pool.len[tid] = clamp_len(gload(c.lengths + tid), c.max_len);
     if (SELECTS == 3)
         for (int i = tid; i < kMaxBatch * kMaxKvHeads / 32; i += kThreads) wanted[i] = 0;
     if (tid < kDescWords) {
-        desc_cur[tid] = reinterpret_cast<const uint32_t *>(&P.cur)[tid];
-        desc_prev[tid] = reinterpret_cast<const uint32_t *>(&P.prev)[tid];
+        desc_cur[tid] = reinterpret_cast<const LYCHEE_CONSTANT uint32_t *>(&A->cur)[tid];
+        desc_prev[tid] = reinterpret_cast<const LYCHEE_CONSTANT uint32_t *>(&A->prev)[tid];
     }
     __syncthreads();
     const LayerDesc &cur = *reinterpret_cast<const LayerDesc *>(desc_cur);
     const LayerDesc &prev = *reinterpret_cast<const LayerDesc *>(desc_prev);
     const uint32_t *dw = desc_cur;
-    uint32_t *timeouts = c.stats + 2;
 
     // ------------------------------------------------------------------ front units
-    FrontPlan front = P.front;
+    FrontPlan front{A->front.n_front, A->front.n_aside};
     if (__builtin_expect(front.n_front < 0, 0))
-        front = front_plan(P.n_selects, P.n_copies, P.n_thresholds, P.gate_mask != 0,
-                           P.cur.n_rgroups * all_blocks(pool.len, c.batch), W);
+        front = front_plan(A->n_selects, A->n_copies, A->n_thresholds, A->gate_mask != 0,
+                           A->cur.n_rgroups * all_blocks(pool.len, c.batch), W);
     pool.front = front;  // (read again for the split; every thread writes the same, so that none waits for another's)
     if (w < front.n_front) {
         __builtin_amdgcn_s_setprio(3);  // (the launch waits for these; a streaming workgroup shares the CU)
-        const int n_rp = P.has_prev ? prev.n_rgroups : 0;
+        const int n_rp = A->has_prev ? prev.n_rgroups : 0;
         const int nS = SELECTS && !kNow ? c.batch * n_rp : 0;
         const LayerDesc &kept = kNow ? cur : prev;  // whose kept sets are copied
         const int n_keep = c.n_kv_heads - kept.n_rgroups;
-        const int nC = (kNow || P.has_prev) && kept.copy_keep ? c.batch * n_keep : 0;
-        const int nT = COLLECT && P.n_thresholds ? c.batch * cur.n_rgroups * kThrSplit : 0;
+        const int nC = (kNow || A->has_prev) && kept.copy_keep ? c.batch * n_keep : 0;
+        const int nT = COLLECT && A->n_thresholds ? c.batch * cur.n_rgroups * kThrSplit : 0;
         for (int j = w; j < nS + nC + nT; j += front.n_front) {
+            const LYCHEE_CONSTANT LayerLaunch *A = arg_of<LayerLaunch>();
+            ArgCommon &c = A->c;
             if (j < nS) {
                 const int b = j / n_rp;
                 const int g = prev.rgroup[j % n_rp];
                 if (SELECTS != 0 && !kNow) select_unit<SELECTS == 2>(c, prev, b, g, sel, pool);
-                publish_set(P.set_flags + set_flag_at(b, g, c.n_kv_heads), gen);
+                publish_set(A->set_flags + set_flag_at(b, g, c.n_kv_heads), gen);
             } else if (j < nS + nC) {
                 const int u = j - nS;
                 const int b = u / n_keep;
@@ -172,19 +175,19 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                 for (int gg = 0; gg < c.n_kv_heads; ++gg)
                     if (kept.rindex[gg] == 0xFF && want-- == 0) g = gg;
                 copy_set_unit(c, kept, b, g);
-                publish_set(P.set_flags + set_flag_at(b, g, c.n_kv_heads), gen);
+                publish_set(A->set_flags + set_flag_at(b, g, c.n_kv_heads), gen);
             } else {
                 // a score row's sample is dealt to kThrSplit units: one round of loads each
                 const int u = (j - nS - nC) / kThrSplit;
                 const int n_rc = cur.n_rgroups;
                 const int b = u / n_rc, rgi = u % n_rc;
                 const int64_t row = (int64_t)b * n_rc + rgi;
-                unsigned long long *flag = P.thr_flags + row;
+                unsigned long long *flag = A->thr_flags + row;
                 ThrSplit split;
                 split.sub = (j - nS - nC) % kThrSplit;
                 split.n_sub = kThrSplit;
                 split.keys = reinterpret_cast<uint32_t *>(cur.sel + row * c.sel_stride);  // (free until a select ranks this row whole)
-                split.arrived = P.thr_arrived + row;
+                split.arrived = A->thr_arrived + row;
                 switch (__builtin_popcount(cur.rmask[cur.rgroup[rgi]] & ((1u << c.group) - 1u))) {
                 case 1: threshold_unit<1>(c, cur, b, rgi, sel, pool, flag, gen, split); break;
                 case 2: threshold_unit<2>(c, cur, b, rgi, sel, pool, flag, gen, split); break;
@@ -205,10 +208,18 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
     // across it was spilled to scratch memory by all workgroups (a launch with a scratch
     // segment also starts its wavefronts more slowly).
     // (A single sequence needs no scans over the batch: every thread evaluates it for itself.)
+    // Everything from here to the first piece's loads is a chain of latencies that every workgroup of the
+    // launch goes through: a dozen divisions and as many LDS round trips took 3.4 us of a 20-us launch, and
+    // a barrier a wavefront waits at in it costs more than the arithmetic between two of them.  So the
+    // values that the first piece is found from stay in registers (`kd`, `next`), a single sequence's
+    // run length has a closed form, and its piece follows from the workgroup's number alone.
     const bool single = c.batch == 1;
+    struct Kind {
+        int first, n_wg, segs, blocks, nb, extra;  // nb: of a single sequence's segment
+    } kd, next;
     {
-        const int n_rseg = P.has_cur ? (int)desc_u32(dw, offsetof(LayerDesc, n_rgroups)) : 0;
-        const int n_gseg = P.has_cur ? (int)desc_u32(dw, offsetof(LayerDesc, n_sgroups)) : 0;
+        const int n_rseg = A->has_cur ? (int)desc_u32(dw, offsetof(LayerDesc, n_rgroups)) : 0;
+        const int n_gseg = A->has_cur ? (int)desc_u32(dw, offsetof(LayerDesc, n_sgroups)) : 0;
         uint32_t nb_r = 0, nb_g = 0;
         if (tid < c.batch || single) {
             const int L = pool.len[single ? 0 : tid];
@@ -224,7 +235,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
         nb_r += nb_r ? extra_r : 0;
         nb_g += nb_g ? extra_g : 0;
         unsigned long long tot64 = (unsigned long long)nb_r | ((unsigned long long)nb_g << 32);
-        if (!single) (void)block_scan64(tot64, pool.scan64, tot64);
+        if (!single) (void)block_scan_pair(tot64, pool.scan64, tot64);
         // (the totals are the same in every lane: scalar arithmetic from here on)
         const int TR = uni((int)(uint32_t)tot64) * n_rseg;  // (below 2^31, checked before the launch)
         const int TG = uni((int)(uint32_t)(tot64 >> 32)) * n_gseg;
@@ -242,7 +253,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             // valid one), and every workgroup evaluates the same operations on the same values, so
             // all agree on it.
             const float tr = (float)TR, tg = (float)TG, wn = (float)Wn;
-            const float lead = P.has_prev && P.gate_mask != 0 ? (float)P.lead_blocks : 0.0f;
+            const float lead = A->has_prev && A->gate_mask != 0 ? (float)A->lead_blocks : 0.0f;
             const float inv_wn = __builtin_amdgcn_rcpf(wn);
             const float a = lead * inv_wn;
             const float half_b = 0.5f * (lead + tr + tg);
@@ -257,7 +268,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             // and the streaming keeps at least a third of the workgroups its share of the blocks would give it
             const int most = Wn - (int)(wn * tr * __builtin_amdgcn_rcpf(3.0f * (tr + tg)));
             wg = wg > most ? most : wg;
-            W_G = wg < 1 ? 1 : (wg > Wn - 1 ? Wn - 1 : wg);
+            W_G = uni(wg < 1 ? 1 : (wg > Wn - 1 ? Wn - 1 : wg));
             W_R = Wn - W_G;
         } else if (TG > 0) {
             W_G = Wn;
@@ -277,39 +288,86 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             pool.extra[1] = extra_g;
             pool.gen = gen;  // (its load, issued when the kernel started, has long arrived)
         }
+        kd = Kind{first, W_R, n_rseg, TR, uni((int)nb_r), extra_r};
+        next = Kind{Wn < 2 ? first : first + W_R, W_G, n_gseg, TG, uni((int)nb_g), extra_g};
         if (tid < c.batch) {
             pool.nb[0][tid] = nb_r;
             pool.nb[1][tid] = nb_g;
         }
     }
-    __syncthreads();
 
     for (int kind = 0; kind < 2; ++kind) {
         const bool gather = kind == 1;
+        const int tid = fresh_tid();
+        const LYCHEE_CONSTANT LayerLaunch *A = arg_of<LayerLaunch>();
+        ArgCommon &c = A->c;
+        auto head_at = [&](int gi) {  // KV head of a sequence's gi-th segment, and the query heads it works for
+            return (int)desc_u8(dw, (gather ? offsetof(LayerDesc, sgroup) : offsetof(LayerDesc, rgroup)) + gi);
+        };
+        auto heads_of = [&](int g) {
+            const uint32_t r = desc_u8(dw, offsetof(LayerDesc, rmask) + g);
+            return (gather ? ~r : r) & ((1u << c.group) - 1u);
+        };
         {
-            const int role_n = uni(pool.role[kind][1]);
-            const int wl = w - uni(pool.role[kind][0]);
-            if (role_n <= 0 || wl < 0 || wl >= role_n) continue;  // (uniform in the workgroup)
-            const int nseg = uni(pool.role[kind][2]);
-            const int T_real = uni(pool.role[kind][3]);
-            const uint32_t nb_mine = single ? pool.nb[kind][0] : (tid < c.batch ? pool.nb[kind][tid] : 0u);
+            const int wl = w - kd.first;
+            const int role_n = kd.n_wg;
+            if (role_n <= 0 || wl < 0 || wl >= role_n) {  // (uniform in the workgroup)
+                kd = next;
+                continue;
+            }
+            const int nseg = kd.segs;
+            const uint32_t nb_mine = single ? (uint32_t)kd.nb : (tid < c.batch ? pool.nb[kind][tid] : 0u);
 
             // Equal contiguous runs of blocks; when the segments are few, every segment is padded to
             // a whole number of runs, so that each workgroup has exactly one piece (a second piece
             // costs a second start-up and merge, which a launch this short cannot level out).
-            int share = quot(T_real + role_n - 1, role_n);
+            int share = quot_uni(kd.blocks + role_n - 1, role_n);
             int pad = 0;
-            if (uni(pool.extra[kind]) == 0 && 8 * nseg * c.batch <= role_n) {
+            uint32_t mine = nseg * nb_mine;
+            if (kd.extra == 0 && 8 * nseg * c.batch <= role_n) {
                 const int s_last = share + (share >= 16 ? share >> 3 : 1);
-                int s = share;
-                for (; s <= s_last; ++s) {
-                    uint32_t runs = nseg * (uint32_t)quot((int)nb_mine + s - 1, s), all = runs;
-                    if (!single) (void)block_scan(runs, pool.scan, all);
-                    if ((int)all <= role_n) break;
+                if (single) {  // (the shortest run of which a segment takes no more than its part of the workgroups)
+                    const int most = quot_uni(role_n, nseg);
+                    const int s = quot_uni(kd.nb + most - 1, most);
+                    if (s <= s_last) {
+                        // the workgroup's one piece is run `ri` of segment `gi`: worked out here, read back below
+                        share = s, pad = 2;
+                        const int runs = quot_uni(kd.nb + s - 1, s);
+                        mine = (uint32_t)(nseg * runs * s);
+                        const int gi = quot_uni(wl, runs);
+                        const int ri = wl - gi * runs;
+                        if (gi < nseg) {
+                            const int brows = gather ? gather_block(c) : kBlockRows;
+                            const int len = pool.len[0];
+                            const int seg_rows = gather ? gather_rows(c, len) : len;
+                            const int r1 = (ri + 1) * s * brows;
+                            const int g = head_at(gi);
+                            const uint32_t hmask = heads_of(g);
+                            if (tid == 0) {
+                                pool.at[0] = 0;
+                                pool.at[1] = g;
+                                pool.at[2] = (int32_t)hmask;
+                                pool.at[3] = s;
+                                pool.at[4] = runs;
+                                pool.at[5] = ri * s * brows;
+                                pool.at[6] = r1 < seg_rows ? r1 : seg_rows;
+                                pool.at[7] = ri;
+                            }
+                        }
+                    }
+                } else {
+                    int s = share;
+                    for (; s <= s_last; ++s) {
+                        uint32_t need = nseg * (uint32_t)quot((int)nb_mine + s - 1, s), all;
+                        (void)block_scan(need, pool.scan, all);
+                        if ((int)all <= role_n) break;
+                    }
+                    if (s <= s_last) {
+                        share = s, pad = 1;
+                        mine = nseg * (uint32_t)(quot((int)nb_mine + s - 1, s) * s);
+                    }
                 }
-                if (s <= s_last) share = s, pad = 1;
             }
-            const uint32_t mine = pad ? nseg * (uint32_t)(quot((int)nb_mine + share - 1, share) * share) : nseg * nb_mine;
             uint32_t all;
             const uint32_t incl = single ? mine : block_scan(mine, pool.scan, all);
             if (tid < c.batch) pool.pre[tid + 1] = (int32_t)incl;
@@ -328,17 +386,17 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             uint32_t hmask;
             bool ends, padding;
         };
-        auto piece_at = [&](int x, int x1, int share, int pad) {
+        auto piece_at = [&](ArgCommon &c, int x, int x1, int share, int pad) {
             Piece pc;
             const int brows = gather ? gather_block(c) : kBlockRows;
             pc.b = uni(find_item(pool.pre, c.batch, x));
             pc.len_b = uni(pool.len[pc.b]);
             const int seg_rows = gather ? gather_rows(c, pc.len_b) : pc.len_b;
-            const int nb = quot(seg_rows + brows - 1, brows);
-            const int nbv = pad ? quot(nb + share - 1, share) * share : nb + uni(pool.extra[kind]);
+            const int nb = quot_uni(seg_rows + brows - 1, brows);
+            const int nbv = pad ? quot_uni(nb + share - 1, share) * share : nb + uni(pool.extra[kind]);
             const int pre_b = uni(pool.pre[pc.b]);
             const int xo = x - pre_b;
-            const int gi = quot(xo, nbv);
+            const int gi = quot_uni(xo, nbv);
             const int blk = xo - gi * nbv;
             pc.padding = blk >= nb;  // the run goes on in what a segment counts beyond its blocks
             const int seg_start = pre_b + gi * nbv;
@@ -349,22 +407,19 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             pc.r0 = blk * brows;
             const int r1 = (blk + len) * brows;
             pc.r1 = r1 < seg_rows ? r1 : seg_rows;
-            const int run0 = quot(seg_start, share);
-            pc.slot = quot(x, share) - run0;
-            pc.pieces = quot(seg_start + nb - 1, share) - run0 + 1;
+            const int run0 = quot_uni(seg_start, share);
+            pc.slot = quot_uni(x, share) - run0;
+            pc.pieces = quot_uni(seg_start + nb - 1, share) - run0 + 1;
             pc.ends = blk + len == nb;
-            const uint32_t gmask = (1u << c.group) - 1u;
-            if (!gather) {
-                pc.g = (int)desc_u8(dw, offsetof(LayerDesc, rgroup) + gi);
-                pc.hmask = desc_u8(dw, offsetof(LayerDesc, rmask) + pc.g) & gmask;
-            } else {
-                pc.g = (int)desc_u8(dw, offsetof(LayerDesc, sgroup) + gi);
-                pc.hmask = ~desc_u8(dw, offsetof(LayerDesc, rmask) + pc.g) & gmask;
-            }
+            pc.g = head_at(gi);
+            pc.hmask = heads_of(pc.g);
             return pc;
         };
 
         for (;;) {
+            const int tid = fresh_tid();
+            const LYCHEE_CONSTANT LayerLaunch *A = arg_of<LayerLaunch>();
+            ArgCommon &c = A->c;
             int x, x1, share, pad;
             auto where = [&]() {
                 x = uni(pool.run[0]);
@@ -377,13 +432,34 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             where();
             if (x >= x1) break;
             {
-                const Piece pc = piece_at(x, x1, share, pad);
+                Piece pc;
+                if (pad == 2) {
+                    pc.b = 0;
+                    pc.len_b = uni(pool.len[0]);
+                    pc.g = uni(pool.at[1]);
+                    pc.hmask = (uint32_t)uni(pool.at[2]);
+                    pc.pieces = uni(pool.at[4]);
+                    pc.r0 = uni(pool.at[5]);
+                    pc.r1 = uni(pool.at[6]);
+                    pc.slot = uni(pool.at[7]);
+                    pc.ends = pc.slot == pc.pieces - 1;
+                    pc.padding = false;
+                } else {
+                    pc = piece_at(c, x, x1, share, pad);
+                }
                 if (pc.padding) {  // (uniform) the next segment, if the run reaches it
                     if (pc.next_seg >= x1) break;
                     __syncthreads();
                     if (tid == 0) pool.run[0] = pc.next_seg;
                     __syncthreads();
                     continue;
+                }
+                if (pad != 2 && tid == 0) {  // (what follows the piece reads this instead of working it out again)
+                    pool.at[0] = pc.b;
+                    pool.at[1] = pc.g;
+                    pool.at[2] = (int32_t)pc.hmask;
+                    pool.at[3] = pc.len;
+                    pool.at[4] = pc.pieces;
                 }
                 auto nothing = []() {};
                 const uint16_t *dq = desc_ptr<const uint16_t>(dw, offsetof(LayerDesc, q));
@@ -410,16 +486,16 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                         const int n = budget_of(c, pc.len_b);
                         em.thr_known = needs_no_sample(n, pc.len_b);
                         em.thr = n == pc.len_b && c.prob_rule == 0 ? 0xFFFFFFFFu : 0u;
-                        em.thr_flag = P.thr_flags + row;
+                        em.thr_flag = A->thr_flags + row;
                         em.gen = my_gen;
-                        em.timeouts = timeouts;
+                        em.timeouts = c.stats + 2;
                     }
                     dispatch_piece<false, true>(__builtin_popcount(pc.hmask), c, dq, dk, dv, nullptr, em, d_part_o, d_part_ml,
                                                 d_part_count, alone, pc.b, pc.g, pc.hmask, pc.len_b, pc.r0, pc.r1, pc.slot, pc.ends,
                                                 sh.attn, nothing);
                 } else {
-                    if ((P.gate_mask >> pc.g) & 1ull)
-                        await_set(P.set_flags + set_flag_at(pc.b, pc.g, c.n_kv_heads), my_gen, timeouts, pool);
+                    if ((A->gate_mask >> pc.g) & 1ull)
+                        await_set(A->set_flags + set_flag_at(pc.b, pc.g, c.n_kv_heads), my_gen, c.stats + 2, pool);
                     const int32_t *idx_src = desc_ptr<const int32_t>(dw, offsetof(LayerDesc, idx_src) + 8 * (size_t)pc.g) +
                                              ((int64_t)pc.b * c.n_kv_heads + pc.g) * c.k;
                     dispatch_piece<true, true>(__builtin_popcount(pc.hmask), c, dq, dk, dv, idx_src, Emit{}, d_part_o, d_part_ml,
@@ -430,15 +506,18 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             // The piece's partials are in device memory.  Count it in; whoever completes the
             // segment merges its partials (slots 0 .. pieces-1 of every head of the segment).
             __syncthreads();
+            A = arg_of<LayerLaunch>();
+            ArgCommon &cc = A->c;
             where();
-            const Piece pc = piece_at(x, x1, share, pad);
+            const int b = uni(pool.at[0]), g = uni(pool.at[1]), pieces = uni(pool.at[4]);
+            const uint32_t hmask = (uint32_t)uni(pool.at[2]);
             if (tid == 0) {
                 int last = 1;
-                if (pc.pieces > 1) {
-                    uint32_t *counter = P.seg_count + (((int64_t)pc.b * c.n_kv_heads + pc.g) * 2 + kind);
+                if (pieces > 1) {
+                    uint32_t *counter = A->seg_count + (((int64_t)b * cc.n_kv_heads + g) * 2 + kind);
                     const uint32_t old = __hip_atomic_fetch_add((LYCHEE_GLOBAL uint32_t *)counter, 1u, __ATOMIC_RELAXED,
                                                                 __HIP_MEMORY_SCOPE_AGENT);
-                    last = old == (uint32_t)pc.pieces - 1u;
+                    last = old == (uint32_t)pieces - 1u;
                     if (last) store_agent(counter, 0u);  // as every launch finds it
                 }
                 pool.flag = last;
@@ -446,35 +525,40 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             __syncthreads();
             // (only now: until the barrier a slower wavefront may still be reading where this piece lay, and
             // one that saw the next piece's place would merge, or not merge, another segment than the others)
-            if (tid == 0) pool.run[0] = x + pc.len;
+            if (tid == 0) pool.run[0] = x + uni(pool.at[3]);
             if (pool.flag) {
-                if (pc.pieces > 1 || kNow) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-                if (pc.pieces > 1) switch (__builtin_popcount(pc.hmask)) {
-                case 1: combine_segment<1>(c, cur, pc.b, pc.g, pc.hmask, pc.pieces, sh.comb); break;
-                case 2: combine_segment<2>(c, cur, pc.b, pc.g, pc.hmask, pc.pieces, sh.comb); break;
-                case 3: combine_segment<3>(c, cur, pc.b, pc.g, pc.hmask, pc.pieces, sh.comb); break;
-                default: combine_segment<4>(c, cur, pc.b, pc.g, pc.hmask, pc.pieces, sh.comb); break;
+                if (pieces > 1 || kNow) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                if (pieces > 1) switch (__builtin_popcount(hmask)) {
+                case 1: combine_segment<1>(cc, cur, b, g, hmask, pieces, sh.comb); break;
+                case 2: combine_segment<2>(cc, cur, b, g, hmask, pieces, sh.comb); break;
+                case 3: combine_segment<3>(cc, cur, b, g, hmask, pieces, sh.comb); break;
+                default: combine_segment<4>(cc, cur, b, g, hmask, pieces, sh.comb); break;
                 }
                 if (kNow && !gather && tid == 0) {  // every candidate of the row is in its list: its set can be selected
-                    const int row = pc.b * uni(pool.role[0][2]) + (int)desc_u8(dw, offsetof(LayerDesc, rindex) + pc.g);
+                    const int row = b * uni(pool.role[0][2]) + (int)desc_u8(dw, offsetof(LayerDesc, rindex) + g);
                     wanted[row >> 5] |= 1u << (row & 31);
                 }
             }
             __syncthreads();
         }
         __syncthreads();  // (a workgroup that does both kinds sets up the second: every wavefront has read that the first is done)
+        kd = Kind{uni(pool.role[1][0]), uni(pool.role[1][1]), uni(pool.role[1][2]), uni(pool.role[1][3]),
+                  uni((int)pool.nb[1][0]), uni(pool.extra[1])};
     }
 
     // ------------------------------------------------------------------ this layer's own sets
     // The rows of the segments that this workgroup completed, after its last piece.  (Selected inside
     // the piece loop they took registers from the streaming, which spilled.)
     if (kNow) {
+        __syncthreads();  // (a workgroup without pieces has passed no barrier since thread 0 left the roles)
+        const LYCHEE_CONSTANT LayerLaunch *A = arg_of<LayerLaunch>();
+        ArgCommon &c = A->c;
         const int n_rseg = uni(pool.role[0][2]);
         const int n_rows = c.batch * n_rseg;
         for (int i = 0; i < n_rows; i += 32) {
             for (uint32_t rows = uni(wanted[i >> 5]); rows != 0; rows &= rows - 1u) {
                 const int row = i + __builtin_ctz(rows);
-                select_unit<false>(c, cur, row / n_rseg, cur.rgroup[row % n_rseg], sel, pool, P.thr_flags + row,
+                select_unit<false>(c, cur, row / n_rseg, cur.rgroup[row % n_rseg], sel, pool, A->thr_flags + row,
                                    pool.gen);
                 __syncthreads();
             }
@@ -482,12 +566,13 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
     }
 
     // ------------------------------------------------------------------ the generation moves on
-    if (tid == 0) {
-        const uint32_t old = __hip_atomic_fetch_add((LYCHEE_GLOBAL uint32_t *)P.exit_count, 1u, __ATOMIC_RELAXED,
+    if (fresh_tid() == 0) {
+        const LYCHEE_CONSTANT LayerLaunch *A = arg_of<LayerLaunch>();
+        const uint32_t old = __hip_atomic_fetch_add((LYCHEE_GLOBAL uint32_t *)A->exit_count, 1u, __ATOMIC_RELAXED,
                                                     __HIP_MEMORY_SCOPE_AGENT);
         if (old == (uint32_t)W - 1u) {
-            store_agent(P.exit_count, 0u);
-            store_agent(P.gen, pool.gen + 1u);
+            store_agent(A->exit_count, 0u);
+            store_agent(A->gen, pool.gen + 1u);
         }
     }
 }

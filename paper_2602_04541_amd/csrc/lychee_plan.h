@@ -69,6 +69,25 @@ LYCHEE_HD inline FrontPlan front_plan(int32_t selects, int32_t copies, int32_t t
     return FrontPlan{front, front};
 }
 
+// Rows one threshold unit samples in one round of loads.
+constexpr int32_t kAloneSample = 512;
+// Whether a score row's threshold is taken by one unit from one round of loads (512 rows) instead of by four from
+// 1024 to 4096.  r_blocks: blocks of 64 rows that the launch streams.
+// The four hand their keys to the one that ranks them through device memory: stores, a counter, loads, each of which takes about
+// 2 us beside the streaming's first loads, so that the threshold is out after 14 us, and a piece of a short
+// launch is done with its rows after 12.  From fewer samples the threshold lets more rows through for the same
+// safety: with f of the n best among 512 rows, (f + 6 sqrt f + 6) / f times n.  So: where the streaming takes less
+// than the hand-over (five blocks per workgroup), and what is let through (n, or L if no more are) still fits the
+// select's registers with a tenth to spare.  The pieces' filter of a 32K layer of 3 retrieval heads, k = 2048: 18.0
+// us after the launch with four units, 15.9 with one.
+LYCHEE_HD inline float threshold_target(float f, float margin) { return f + margin * __builtin_sqrtf(f) + 6.0f; }
+LYCHEE_HD inline bool threshold_alone(int32_t n, int32_t L, int32_t r_blocks, int32_t n_wg, float margin, int32_t fits)
+{
+    if (r_blocks > 5 * n_wg) return false;
+    const float per_sample = (float)L / (float)kAloneSample;
+    return 10.0f * threshold_target((float)n / per_sample, margin) * per_sample <= 9.0f * (float)fits;
+}
+
 // Set entries per block of gather work, unless the caller chose it (blocks are dealt like blocks of 64
 // streamed rows).  64 makes the fewest pieces, whose chains of latencies bound a short launch: the faster one
 // for phased steps (12 layers of 1 to 64 sequences of 1K to 128K: 0.82 to 1.01 of the time with 48, 0.97 at

@@ -23,7 +23,7 @@ namespace {
 // in its place, and 0 times that row's infinity or NaN is NaN).  C units; in a layer launch such a slot
 // shows in the output.
 template <int NH, bool SKIP = false>
-__device__ __forceinline__ void combine_segment(const Common &c, const LayerDesc &p, int b, int g, uint32_t hmask,
+__device__ __forceinline__ void combine_segment(ArgCommon &c, const LayerDesc &p, int b, int g, uint32_t hmask,
                                                 int count, SharedCombine &sh)
 {
     constexpr int kGrp = NH == 1 ? 8 : (NH == 2 ? 4 : 2);  // slot groups of a head
@@ -197,10 +197,10 @@ __device__ __forceinline__ Cut narrow(const Entries &E, Cut cut, int shift, uint
 }
 
 template <int NH>
-__device__ __forceinline__ void load_q(const Common &c, const uint16_t *q, int b, int g, uint32_t hmask,
+__device__ __forceinline__ void load_q(ArgCommon &c, const uint16_t *q, int b, int g, uint32_t hmask,
                                        uint4 (&qf)[NH])
 {
-    const int ch = threadIdx.x & 15;
+    const int ch = fresh_tid() & 15;
     uint32_t mk = hmask;
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
@@ -215,7 +215,7 @@ __device__ __forceinline__ void load_q(const Common &c, const uint16_t *q, int b
 template <int NH>
 __device__ __forceinline__ float tile_pooled_score(const uint4 (&kr)[4], const uint4 (&qf)[NH], float sel_mul)
 {
-    const int ch = threadIdx.x & 15;
+    const int ch = fresh_tid() & 15;
     float mine = 0.0f;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -229,7 +229,7 @@ __device__ __forceinline__ float tile_pooled_score(const uint4 (&kr)[4], const u
 
 // T unit of score row (b, rgi): the ordered key that a row's pooled score has to reach to
 // become a candidate.  The key is the target-th largest of a sample of the row's scores, or the lower end
-// of a range of keys that holds it and at most one more, where target is the number of sampled rows expected among the top n = min(k, L)
+// of a range of keys that holds it and at most seven more, where target is the number of sampled rows expected among the top n = min(k, L)
 // plus sel_margin (six, unless the caller changes it) standard deviations; the streamed rows
 // that reach it are then very likely at least n and a few thousand more at most.  Whatever the sample yields, the select unit
 // checks the candidate count and ranks the whole row itself when the list cannot be used.
@@ -246,7 +246,9 @@ __device__ __forceinline__ float tile_pooled_score(const uint4 (&kr)[4], const u
 // `split` (launches whose streaming waits for the threshold): the row's sample is dealt to n_sub
 // units, each of which reads its share of the rows in one round of loads and leaves the keys in
 // device memory; the unit that arrives last ranks them.  Nobody waits for anybody.
+constexpr int kSelRegs = 32;  // entries of a candidate list that a thread of the select keeps in registers
 constexpr int kSampleRegs = kSampleTilesMax * 16 / kThreads;
+constexpr int kThrNear = 8;  // sampled keys that the threshold may lie below the one that was aimed at
 struct SampleEntries {  // the sample's keys, in registers (0: none)
     uint32_t key[kSampleRegs];
     int tid;
@@ -267,9 +269,9 @@ struct ThrSplit {
     uint32_t *arrived = nullptr;  // units of this row that have left their keys (zero between launches)
 };
 template <int NH, typename Pool>
-__device__ __forceinline__ void threshold_unit(const Common &c, const LayerDesc &p, int b, int rgi,
+__device__ __forceinline__ void threshold_unit(ArgCommon &c, const LayerDesc &p, int b, int rgi,
                                                SharedSelect &sh, Pool &pool, unsigned long long *publish = nullptr,
-                                               uint32_t gen = 0, const ThrSplit split = ThrSplit())
+                                               uint32_t gen = 0, ThrSplit split = ThrSplit())
 {
     const int tid = fresh_tid();
     const int lane = tid & 63;
@@ -298,11 +300,18 @@ __device__ __forceinline__ void threshold_unit(const Common &c, const LayerDesc 
         if (split.sub == 0) emit(n == L && c.prob_rule == 0 ? 0xFFFFFFFFu : 0u);
         return;
     }
+    // Short launches: the row's first unit takes one round of loads for itself
+    if (split.n_sub > 1 && threshold_alone(n, L, c.batch * p.n_rgroups * ((L + kBlockRows - 1) / kBlockRows), c.n_wg, c.sel_margin,
+                                           kThreads * kSelRegs)) {
+        if (split.sub > 0) return;
+        split = ThrSplit();
+    }
+    const bool alone = publish != nullptr && split.n_sub == 1;
     // 128 of the top n among the sample, if that takes no more rows than the sample may have; whole rounds
     // of loads of an undivided unit, which takes 2048 rows at most (eight rounds took it 50 us)
     const int most = L >= (1 << 16) && split.n_sub > 1 ? kSampleTilesMax : kSampleTilesMax / 2;
     const int enough = (int)(8.0f * (float)L / (float)n) & ~31;
-    const int n_tiles = enough > most ? most : (enough < kSampleTilesMin ? kSampleTilesMin : enough);
+    const int n_tiles = alone ? kAloneSample / 16 : enough > most ? most : (enough < kSampleTilesMin ? kSampleTilesMin : enough);
     const int n_sample = n_tiles * 16;
     const int g = p.rgroup[rgi];
     const uint32_t hmask = p.rmask[g] & ((1u << c.group) - 1u);
@@ -316,18 +325,22 @@ __device__ __forceinline__ void threshold_unit(const Common &c, const LayerDesc 
     // row may be being appended in this very launch).  Row by row, not tile by tile: scores
     // come in runs (a passage that matters is hundreds of consecutive rows), and a sample of
     // contiguous tiles would over- or under-count such runs far beyond its nominal deviation.
-    const int stratum = (L - 1) / n_sample;  // >= 2
+    const int stratum = quot_uni(L - 1, n_sample);  // >= 2
     const int t_lo = n_tiles * split.sub / split.n_sub, t_hi = n_tiles * (split.sub + 1) / split.n_sub;
-    for (int t0 = t_lo + wave * kBatch; t0 < t_hi; t0 += kWaves * kBatch) {
+    // (sample i of a row lies at i * stratum + umulhi(i * A + row * B, stratum); what is the same in a wavefront
+    // is multiplied in scalar registers: two vector multiplications less per load, of 32 before the first is used)
+    constexpr uint32_t kHashA = 2654435761u * 2246822519u, kHashB = 40503u * 2246822519u;
+    const uint32_t h_lane = (uint32_t)rs * kHashA + (uint32_t)row * kHashB;
+    const int p_lane = rs * stratum;
+    for (int t0 = t_lo + uni(wave) * kBatch; t0 < t_hi; t0 += kWaves * kBatch) {
         uint4 kr[kBatch][4];
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
             const int t = t0 + u < t_hi ? t0 + u : t_hi - 1;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const int i = t * 16 + 4 * j + rs;  // sample number
-                const uint32_t hsh = ((uint32_t)i * 2654435761u + (uint32_t)row * 40503u) * 2246822519u;
-                const int pos = i * stratum + (int)__umulhi(hsh, (uint32_t)stratum);
+                const int i = t * 16 + 4 * j;  // sample number, less rs
+                const int pos = i * stratum + p_lane + (int)__umulhi(h_lane + (uint32_t)i * kHashA, (uint32_t)stratum);
                 kr[u][j] = gload_u4(kbase + (int64_t)pos * c.stride_t + ch * 8);
             }
         }
@@ -373,14 +386,35 @@ __device__ __forceinline__ void threshold_unit(const Common &c, const LayerDesc 
         E.key[e] = i < n_sample ? real_key(key) : 0u;
     }
     const float f = (float)n_sample * (float)n / (float)L;
-    const float want = f + c.sel_margin * sqrtf(f) + 6.0f;
+    const float want = threshold_target(f, c.sel_margin);
     const uint32_t target = want < 1.0f ? 1u : (want > (float)n_sample ? (uint32_t)n_sample : (uint32_t)want);
     uint32_t t_key = 0;
     if (target < (uint32_t)n_sample) {
-        // the lower end of a narrow range of keys around the sample's target-th largest
-        t_key = narrow(
-            E, Cut{1u, 0xFFFFFFFFu, target, (uint32_t)n_sample}, 32 - kBinBits, 2u, [](uint32_t key, uint32_t) { return key; },
-            [](uint32_t, uint32_t) { return true; }, sh).lo;
+        // The lower end of a narrow range of keys around the sample's target-th largest.  The first level's
+        // bins, 128 to the octave, cover the 16 octaves below the largest key; what lies lower shares
+        // the first bin.  So one level is normally enough.  (Over the range of all keys, four bins to the
+        // octave, it took two or three, a microsecond each.)
+        uint32_t top = 0;
+#pragma unroll
+        for (int e = 0; e < kSampleRegs; ++e) {
+            if (e % 4 == 0 && e * kThreads >= n_sample) break;
+            top = E.key[e] > top ? E.key[e] : top;
+        }
+        top = wave_max(top);
+        if (lane == 0) sh.wave_tot[wave] = top;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) top = sh.wave_tot[w] > top ? sh.wave_tot[w] : top;
+        top = uni(top);
+        const uint32_t low = top > (16u << 23) ? top - (16u << 23) : 0u;
+        auto all = [](uint32_t, uint32_t) { return true; };
+        const uint32_t above = narrow(
+            E, Cut{0u, top - low, target, (uint32_t)n_sample}, 16, (uint32_t)kThrNear,
+            [low](uint32_t key, uint32_t) { return key > low ? key - low : 0u; }, all, sh).lo;
+        t_key = low + above;
+        if (above == 0 && low > 0)  // further down
+            t_key = narrow(E, Cut{1u, low, target, (uint32_t)n_sample}, 32 - kBinBits, (uint32_t)kThrNear,
+                           [low](uint32_t key, uint32_t) { return key < low ? key : low; }, all, sh).lo;
     }
     emit(t_key);
 }
@@ -388,7 +422,7 @@ __device__ __forceinline__ void threshold_unit(const Common &c, const LayerDesc 
 // Writes the pooled score of every row of (b, g) into sel[0 .. L): what the select unit falls
 // back on when a row's candidate list is short of n entries or has overflowed.
 template <int NH>
-__device__ __forceinline__ void score_row_unit(const Common &c, const LayerDesc &p, int b, int g, int L, float *sel)
+__device__ __forceinline__ void score_row_unit(ArgCommon &c, const LayerDesc &p, int b, int g, int L, float *sel)
 {
     const int tid = fresh_tid();
     const int lane = tid & 63;
@@ -434,7 +468,6 @@ __device__ __forceinline__ unsigned long long ranked(uint32_t key, uint32_t pos)
 // into one flag, with bitwise operators, and let an entry that does not count go to a word of its
 // lane's own: short-circuit conditions made the compiler keep a lane mask per entry and
 // condition, spill them, and branch several times per entry.
-constexpr int kSelRegs = 32;  // entries one thread keeps in registers
 struct RegEntries {           // up to kThreads * kSelRegs list entries, loaded once: beside a streaming
     uint32_t key[kSelRegs], pos[kSelRegs];  // launch every pass over memory costs a microsecond or two
     int tid;
@@ -723,15 +756,15 @@ __device__ __forceinline__ void select_from(Entries &E, uint32_t floor_key, int 
 
 // A unit of one layer (Alg. 1, "C.append(k, v)"): the decoded token's key and value rows become
 // row L_b - 1 of every KV head's cache.  16 lanes move one 256-byte row.
-__device__ __forceinline__ void append_unit(const Common &c, const LayerDesc &p)
+__device__ __forceinline__ void append_unit(ArgCommon &c, const LayerDesc &p)
 {
-    const int ch = threadIdx.x & 15;
+    const int ch = fresh_tid() & 15;
     const int n_rows = c.batch * c.n_kv_heads * 2;  // K rows, then V rows
-    for (int r = threadIdx.x >> 4; r < n_rows; r += kThreads >> 4) {
+    for (int r = fresh_tid() >> 4; r < n_rows; r += kThreads >> 4) {
         const int which = r / (c.batch * c.n_kv_heads);
         const int bg = r % (c.batch * c.n_kv_heads);
         const int b = bg / c.n_kv_heads, g = bg % c.n_kv_heads;
-        const int L = clamp_len(c.lengths[b], c.max_len);
+        const int L = clamp_len(gload(c.lengths + b), c.max_len);
         const uint16_t *src = (which ? p.v_new : p.k_new) + (int64_t)bg * kHeadDim + ch * 8;
         const uint16_t *dst = (which ? p.v_cache : p.k_cache) + (int64_t)b * c.stride_b +
                               (int64_t)g * c.stride_h + (int64_t)(L - 1) * c.stride_t + ch * 8;
@@ -790,7 +823,7 @@ __device__ __forceinline__ bool find_bin_mass(const unsigned long long *mass, un
 // log-sum-exp of the pooled logits of the whole sequence.  The entries hold at least the n best
 // positions, and a rule that would go beyond them is capped at n anyway.
 template <typename Entries, typename Pool>
-__device__ __forceinline__ int rule_keeps(const Common &c, const Entries &E, uint32_t floor_key, int n, float lse,
+__device__ __forceinline__ int rule_keeps(ArgCommon &c, const Entries &E, uint32_t floor_key, int n, float lse,
                                           SharedSelect &sh, Pool &pool)
 {
     uint32_t want;
@@ -865,15 +898,15 @@ __device__ __forceinline__ int rule_keeps(const Common &c, const Entries &E, uin
 
 // Log-sum-exp of the pooled logits of score row `row`: the pieces' states, merged.
 template <typename Pool>
-__device__ __forceinline__ float pooled_lse(const Common &c, const LayerDesc &p, int64_t row, int count,
+__device__ __forceinline__ float pooled_lse(ArgCommon &c, const LayerDesc &p, int64_t row, int count,
                                             Pool &pool)
 {
     const float *ml = p.part_pool + row * (2 * (int64_t)c.part_stride);
     float m_loc = kMinusBig;
-    for (int s = threadIdx.x; s < count; s += kThreads) m_loc = fmaxf(m_loc, gload(ml + 2 * s));
+    for (int s = fresh_tid(); s < count; s += kThreads) m_loc = fmaxf(m_loc, gload(ml + 2 * s));
     const float M = block_max(m_loc, pool.fred);
     float l_loc = 0.0f;
-    for (int s = threadIdx.x; s < count; s += kThreads)
+    for (int s = fresh_tid(); s < count; s += kThreads)
         l_loc = fmaf(fast_exp2((gload(ml + 2 * s) - M) * kLog2e), gload(ml + 2 * s + 1), l_loc);
     const float l = block_sum(l_loc, pool.fred);
     return M + __logf(l);
@@ -881,12 +914,12 @@ __device__ __forceinline__ float pooled_lse(const Common &c, const LayerDesc &p,
 
 // The set of a KV head (b, g) whose group holds no retrieval head is handed on unchanged
 // (Sec. 3.1): a verbatim copy.
-__device__ __forceinline__ void copy_set_unit(const Common &c, const LayerDesc &p, int b, int g)
+__device__ __forceinline__ void copy_set_unit(ArgCommon &c, const LayerDesc &p, int b, int g)
 {
     const int64_t bg = (int64_t)b * c.n_kv_heads + g;
     int32_t *dst = p.idx_out + bg * c.k;
     const int32_t *src = p.idx_src[g] + bg * c.k;
-    for (int i = threadIdx.x; i < c.k; i += kThreads) gstore_through(dst + i, gload(src + i));
+    for (int i = fresh_tid(); i < c.k; i += kThreads) gstore_through(dst + i, gload(src + i));
 }
 
 // S unit of KV head (b, g), whose group holds a retrieval head: the set the next layer's
@@ -895,7 +928,7 @@ __device__ __forceinline__ void copy_set_unit(const Common &c, const LayerDesc &
 // flag, gen: the row's threshold word and the generation, when the launch that streams the row
 // also selects for it.
 template <bool PROB, typename Pool>
-__device__ __forceinline__ void select_unit(const Common &c, const LayerDesc &p, int b, int g,
+__device__ __forceinline__ void select_unit(ArgCommon &c, const LayerDesc &p, int b, int g,
                                             SharedSelect &sh, Pool &pool, const unsigned long long *flag = nullptr,
                                             uint32_t gen = 0)
 {
@@ -907,8 +940,8 @@ __device__ __forceinline__ void select_unit(const Common &c, const LayerDesc &p,
     const int n = budget_of(c, L);
     const bool by_prob = PROB && c.prob_rule != 0;
     if (n == L && !by_prob) {  // everything is selected
-        for (int i = threadIdx.x; i < c.k; i += kThreads) gstore_through(dst + i, (int32_t)(i < L ? i : -1));
-        if (threadIdx.x == 0 && c.block_shift == 0 && rgi != 0xFF)
+        for (int i = fresh_tid(); i < c.k; i += kThreads) gstore_through(dst + i, (int32_t)(i < L ? i : -1));
+        if (fresh_tid() == 0 && c.block_shift == 0 && rgi != 0xFF)
             gstore(p.list_count + ((int64_t)b * p.n_rgroups + rgi), (int32_t)0);  // (nothing was collected; see below)
         return;
     }
@@ -979,7 +1012,7 @@ __device__ __forceinline__ void select_unit(const Common &c, const LayerDesc &p,
     } else {
         // too few candidates reached the threshold, or too many for the list: rank the row
         // (token-granular only: a block list is always complete)
-        if (threadIdx.x == 0) atomicAdd(c.stats + (total < n ? 0 : 1), 1u);
+        if (fresh_tid() == 0) (void)__hip_atomic_fetch_add((LYCHEE_GLOBAL uint32_t *)c.stats + (total < n ? 0 : 1), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         float *sel = p.sel + row * c.sel_stride;
         switch (__builtin_popcount(p.rmask[g] & ((1u << c.group) - 1u))) {
         case 1: score_row_unit<1>(c, p, b, g, len, sel); break;
@@ -994,8 +1027,8 @@ __device__ __forceinline__ void select_unit(const Common &c, const LayerDesc &p,
         if (PROB && by_prob) keep = rule_keeps(c, M, 0u, n, lse, sh, pool);
         select_from(M, 0u, len, keep, L, dst, sh);
     }
-    for (int i = keep + threadIdx.x; i < c.k; i += kThreads) gstore_through(dst + i, (int32_t)-1);
-    if (clear_count && threadIdx.x == 0) gstore(p.list_count + row, (int32_t)0);
+    for (int i = keep + fresh_tid(); i < c.k; i += kThreads) gstore_through(dst + i, (int32_t)-1);
+    if (clear_count && fresh_tid() == 0) gstore(p.list_count + row, (int32_t)0);
 }
 
 

@@ -135,49 +135,57 @@ __device__ __forceinline__ uint32_t wait_word(const unsigned long long *flag, ui
         if ((uint32_t)(v >> 32) == gen) return (uint32_t)v;
         __builtin_amdgcn_s_sleep(2);
     }
-    atomicAdd(timeouts, 1u);
+    if ((fresh_tid() & 63) == 0) atomicAdd(timeouts, 1u);
     return fail;
 }
 
-// The threshold of a LATE piece's score row, the same in every thread (one thread polls).
-__device__ __forceinline__ uint32_t late_threshold(const Emit &em, SharedAttn &sh)
+// LATE pieces: lists the rows of a window of n_rows keys in sh.keys that reach the threshold; row i of the window is
+// position first_row + i.  Each wavefront filters 1024 rows for itself, the last one first: it asks for the
+// threshold, counts by ballots, reserves list space, writes.  At the end of a piece of up to 2048
+// rows that leaves the first two wavefronts to the partial.  (Counted and scanned by the whole workgroup
+// ahead of the partial, four barriers and the answer of the one reservation stood between the last row and the
+// partial, and a piece that ended before its threshold was out held its partial back.)
+constexpr int kFilterRows = kKeyBuf / kWaves;
+__device__ __forceinline__ void late_filter(const Emit &em, const SharedAttn &sh, int first_row, int n_rows)
 {
-    if (threadIdx.x == 0 && sh.late_have == 0) {
-        // on a time-out nothing is collected; the select then ranks the whole row itself
-        sh.late_thr = wait_word(em.thr_flag, em.gen, 0xFFFFFFFFu, em.timeouts);
-        sh.late_have = 1;
+    const int tid = fresh_tid();
+    const int lane = tid & 63;
+    const int i0 = uni(kWaves - 1 - (tid >> 6)) * kFilterRows;
+    if (i0 >= n_rows) return;  // (uniform in the wavefront)
+    const int i1 = n_rows < i0 + kFilterRows ? n_rows : i0 + kFilterRows;
+    // (on a time-out nothing is collected; the select then ranks the whole row itself)
+    const uint32_t thr = em.thr_known ? em.thr : uni(wait_word(em.thr_flag, em.gen, 0xFFFFFFFFu, em.timeouts));
+    constexpr int kRounds = kFilterRows / 64;
+    uint32_t key[kRounds];
+    uint32_t n = 0;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        if (r % 4 == 0 && i0 + r * 64 >= i1) break;
+        const int i = i0 + r * 64 + lane;
+        key[r] = sh.keys[i];
     }
-    __syncthreads();
-    return sh.late_thr;
-}
-
-// LATE pieces, first half of a filter over the n_rows keys in sh.keys: counts this thread's
-// rows that reach the threshold (`mine`), their rank among the workgroup's (`incl`, inclusive),
-// and has the last thread reserve list space for all of them; the reservation's answer, which
-// takes a microsecond or two, is only needed by late_write.
-__device__ __forceinline__ void late_count(const Emit &em, SharedAttn &sh, int n_rows, uint32_t thr,
-                                           uint32_t &mine, uint32_t &incl, int &base)
-{
-    mine = 0;
-    for (int i = threadIdx.x; i < n_rows; i += kThreads) mine += (uint32_t)(sh.keys[i] >= thr);
-    uint32_t total;
-    incl = block_scan(mine, sh.scan, total);
-    base = 0;
-    if (threadIdx.x == kThreads - 1 && total > 0)
-        base = __hip_atomic_fetch_add((LYCHEE_GLOBAL int32_t *)em.count, (int32_t)total, __ATOMIC_RELAXED,
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        if (r % 4 == 0 && i0 + r * 64 >= i1) break;
+        const int i = i0 + r * 64 + lane;
+        n += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64((i < i1) & (key[r] >= thr)));
+    }
+    if (n == 0) return;
+    int base = 0;
+    if (lane == 0)
+        base = __hip_atomic_fetch_add((LYCHEE_GLOBAL int32_t *)em.count, (int32_t)n, __ATOMIC_RELAXED,
                                       __HIP_MEMORY_SCOPE_AGENT);
-}
-// Second half: sh.cand_base holds the reservation; row i of the window is position first_row + i.
-__device__ __forceinline__ void late_write(const Emit &em, SharedAttn &sh, int first_row, int n_rows, uint32_t thr,
-                                           uint32_t mine, uint32_t incl)
-{
-    int at = sh.cand_base + (int)(incl - mine);
-    for (int i = threadIdx.x; i < n_rows; i += kThreads) {
-        const uint32_t key = sh.keys[i];
-        if (key >= thr) {
-            if (at < em.cap) gstore_through(em.list + at, (unsigned long long)key | ((unsigned long long)(uint32_t)(first_row + i) << 32));
-            ++at;
-        }
+    base = uni(base);
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        if (r % 4 == 0 && i0 + r * 64 >= i1) break;
+        const int i = i0 + r * 64 + lane;
+        const bool hit = (i < i1) & (key[r] >= thr);
+        const unsigned long long hits = __builtin_amdgcn_ballot_w64(hit);
+        const int at = base + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hits, 0u));
+        if (hit && at < em.cap)
+            gstore_through(em.list + at, (unsigned long long)key[r] | ((unsigned long long)(uint32_t)(first_row + i) << 32));
+        base += __builtin_popcountll(hits);
     }
 }
 
@@ -189,7 +197,7 @@ __device__ __forceinline__ void late_write(const Emit &em, SharedAttn &sh, int f
 // counter are served one after the other.)
 __device__ __forceinline__ void flush_candidates(const unsigned long long *buf, int n, const Emit &em)
 {
-    const int lane = threadIdx.x & 63;
+    const int lane = fresh_tid() & 63;
     int base = 0;
     if (lane == 0)
         base = __hip_atomic_fetch_add((LYCHEE_GLOBAL int32_t *)em.count, (int32_t)n, __ATOMIC_RELAXED,
@@ -208,15 +216,16 @@ __device__ __forceinline__ void flush_candidates(const unsigned long long *buf, 
 // a span the wavefront compares its 32 pooled scores with the threshold and puts the rows
 // that reach it into its LDS buffer, which goes to the list in bursts.
 template <int NH, bool GATHER, bool LATE>
-__device__ __forceinline__ void stream_rows(const Common &c, const uint16_t *kbase,
+__device__ __forceinline__ void stream_rows(ArgCommon &c, const uint16_t *kbase,
                                             const uint16_t *vbase, const uint4 (&qf)[NH],
                                             Acc<NH> &acc, int L, int r0, int r1,
                                             const int32_t *idx_s, const Emit &em, float sel_mul,
                                             unsigned long long *cand_buf, int &cand_left,
                                             float &pool_m, float &pool_l, SharedAttn &sh)
 {
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int tid = fresh_tid();
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
     const int rs = lane >> 4;  // row slot: which of the 4 rows of a load this lane is in
     const int ch = lane & 15;  // 16-byte chunk of the 256-byte row
     constexpr int kSpan = 32 * kWaves;
@@ -333,13 +342,7 @@ __device__ __forceinline__ void stream_rows(const Common &c, const uint16_t *kba
                 if (ch < 8) sh.keys[(r - r0) & (kKeyBuf - 1)] = key;
                 if (((span + 1) & (kWindowSpans - 1)) == 0 && span + 1 < n_spans) {  // uniform in the workgroup
                     __syncthreads();
-                    const uint32_t thr = late_threshold(em, sh);
-                    uint32_t mine, incl;
-                    int base;
-                    late_count(em, sh, kKeyBuf, thr, mine, incl, base);
-                    if (threadIdx.x == kThreads - 1) sh.cand_base = base;
-                    __syncthreads();
-                    late_write(em, sh, r0 + (span + 1) * kSpan - kKeyBuf, kKeyBuf, thr, mine, incl);
+                    late_filter(em, sh, r0 + (span + 1) * kSpan - kKeyBuf, kKeyBuf);
                     __syncthreads();
                 }
                 continue;
@@ -369,7 +372,7 @@ __device__ __forceinline__ void stream_rows(const Common &c, const uint16_t *kba
 // through to device memory, complete when run_piece returns.  alone_out: the piece is its segment's
 // only one and writes the heads' outputs at once (nullptr: it leaves a partial).
 template <int NH, bool GATHER, bool LATE, typename Hook>
-__device__ __forceinline__ void run_piece(const Common &c, const uint16_t *q, const uint16_t *k_cache,
+__device__ __forceinline__ void run_piece(ArgCommon &c, const uint16_t *q, const uint16_t *k_cache,
                                           const uint16_t *v_cache, const int32_t *idx_src,
                                           const Emit &em, float *part_o, float *part_ml,
                                           int32_t *part_count, uint16_t *alone_out, int b, int g, uint32_t hmask, int L,
@@ -379,10 +382,9 @@ __device__ __forceinline__ void run_piece(const Common &c, const uint16_t *q, co
     // The thread index is made opaque here: the LDS addresses below that derive from it were
     // otherwise computed once per kernel, for every variant of this function, kept across
     // everything and spilled.
-    uint32_t tix = threadIdx.x;
-    asm volatile("" : "+v"(tix));
-    const int lane = (int)(tix & 63u);
-    const int wave = (int)(tix >> 6);
+    const int tid = fresh_tid();
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
     const int rs = lane >> 4;
     const int ch = lane & 15;
 
@@ -414,10 +416,6 @@ __device__ __forceinline__ void run_piece(const Common &c, const uint16_t *q, co
     const float sel_mul = c.scale / (float)NH;
     float pool_m = kMinusBig, pool_l = 0.0f;  // per lane: log-sum-exp state of the pooled logits
     int cand_left = 0;                        // candidates still in this wavefront's LDS buffer
-    if (LATE && !GATHER && threadIdx.x == 0) {  // (barriers lie between this and the first use)
-        sh.late_have = em.thr_known;
-        sh.late_thr = em.thr;
-    }
 
     if (GATHER) {
         // rows r0 .. r1-1 of the gathered sequence are row (r mod 2^shift) of set entry r >> shift
@@ -427,7 +425,7 @@ __device__ __forceinline__ void run_piece(const Common &c, const uint16_t *q, co
             const int e1 = e0 + chunk_rows < r1 ? e0 + chunk_rows : r1;
             const int n_entries = (e1 - e0 + (1 << shift) - 1) >> shift;
             __syncthreads();  // the previous chunk's readers are done
-            for (int i = threadIdx.x; i < n_entries; i += kThreads) sh.idx_s[i] = gload(idx_src + (e0 >> shift) + i);
+            for (int i = tid; i < n_entries; i += kThreads) sh.idx_s[i] = gload(idx_src + (e0 >> shift) + i);
             __syncthreads();
             stream_rows<NH, true, LATE>(c, kbase, vbase, qf, acc, L, e0, e1, sh.idx_s, em, 0.0f, nullptr, cand_left, pool_m, pool_l, sh);
         }
@@ -483,14 +481,9 @@ __device__ __forceinline__ void run_piece(const Common &c, const uint16_t *q, co
         }
     }
     int cand_base = 0;
-    uint32_t late_thr = 0, late_mine = 0, late_incl = 0;
     // the piece's last window of keys: rows late_first .. r1 - 1
     const int late_first = r0 + (r1 - r0 > 0 ? (r1 - r0 - 1) / kKeyBuf * kKeyBuf : 0);
-    if (LATE && collects) {
-        late_thr = late_threshold(em, sh);
-        late_count(em, sh, r1 - late_first, late_thr, late_mine, late_incl, cand_base);
-    }
-    if (!LATE && collects && threadIdx.x == kThreads - 1) {
+    if (!LATE && collects && tid == kThreads - 1) {
         // room for the workgroup's last candidates, asked for by a thread that writes no
         // partial, as early as every wavefront's count is known: the answer is on its way
         // while the others merge
@@ -506,8 +499,8 @@ __device__ __forceinline__ void run_piece(const Common &c, const uint16_t *q, co
         sh.pool_ml[2 * wave + 1] = pool_l;
     }
     __syncthreads();
-    if (collects && threadIdx.x == kThreads - 1) sh.cand_base = cand_base;
-    if (threadIdx.x < kHeadDim) {
+    if (!LATE && collects && tid == kThreads - 1) sh.cand_base = cand_base;
+    if (tid < kHeadDim) {
 #pragma unroll
         for (int h = 0; h < NH; ++h) {
             float M = kMinusBig;
@@ -517,33 +510,33 @@ __device__ __forceinline__ void run_piece(const Common &c, const uint16_t *q, co
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) {
                 const float a = fast_exp2((sh.red_ml[(w * kMaxGroup + h) * 2] - M) * c_log2e);
-                o = fmaf(a, sh.red_o[(w * kMaxGroup + h) * kHeadDim + threadIdx.x], o);
+                o = fmaf(a, sh.red_o[(w * kMaxGroup + h) * kHeadDim + tid], o);
                 l = fmaf(a, sh.red_ml[(w * kMaxGroup + h) * 2 + 1], l);
             }
             const int64_t bh = (int64_t)b * c.n_q_heads + heads[h];
             const int64_t prow = bh * c.part_stride + slot;
             if (LATE && alone_out != nullptr) {
-                gstore(alone_out + bh * kHeadDim + threadIdx.x, f32_to_bf16_rne(l > 0.0f ? o / l : 0.0f));
+                gstore(alone_out + bh * kHeadDim + tid, f32_to_bf16_rne(l > 0.0f ? o / l : 0.0f));
             } else if (LATE) {
-                gstore_through(part_o + prow * kHeadDim + threadIdx.x, o);
-                if (threadIdx.x == 0) {
+                gstore_through(part_o + prow * kHeadDim + tid, o);
+                if (tid == 0) {
                     gstore_through(part_ml + prow * 2 + 0, M);
                     gstore_through(part_ml + prow * 2 + 1, l);
                 }
             } else {
-                gstore(part_o + prow * kHeadDim + threadIdx.x, o);
-                if (threadIdx.x == 0) {
+                gstore(part_o + prow * kHeadDim + tid, o);
+                if (tid == 0) {
                     gstore(part_ml + prow * 2 + 0, M);
                     gstore(part_ml + prow * 2 + 1, l);
                 }
             }
-            if (threadIdx.x == 0 && ends_segment) {
+            if (tid == 0 && ends_segment) {
                 if (LATE) gstore_through(part_count + bh, (int32_t)(slot + 1));
                 else gstore(part_count + bh, (int32_t)(slot + 1));
             }
         }
     }
-    if (pooled_lse && threadIdx.x == 0) {  // the piece's pooled log-sum-exp state, same slot
+    if (pooled_lse && tid == 0) {  // the piece's pooled log-sum-exp state, same slot
         float M = kMinusBig, l = 0.0f;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) M = fmaxf(M, sh.pool_ml[2 * w]);
@@ -558,8 +551,7 @@ __device__ __forceinline__ void run_piece(const Common &c, const uint16_t *q, co
         }
     }
     if (LATE && collects) {
-        __syncthreads();
-        late_write(em, sh, late_first, r1 - late_first, late_thr, late_mine, late_incl);
+        late_filter(em, sh, late_first, r1 - late_first);
     } else if (collects) {
         __syncthreads();
         int base = sh.cand_base;
@@ -572,7 +564,7 @@ __device__ __forceinline__ void run_piece(const Common &c, const uint16_t *q, co
 }
 
 template <bool GATHER, bool LATE, typename Hook>
-__device__ __forceinline__ void dispatch_piece(int nh, const Common &c, const uint16_t *q,
+__device__ __forceinline__ void dispatch_piece(int nh, ArgCommon &c, const uint16_t *q,
                                                const uint16_t *k_cache, const uint16_t *v_cache,
                                                const int32_t *idx_src, const Emit &em, float *part_o,
                                                float *part_ml, int32_t *part_count, uint16_t *alone_out, int b, int g,

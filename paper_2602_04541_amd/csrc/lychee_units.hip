@@ -63,13 +63,13 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_small_kernel(const LaunchP
     __shared__ SharedUnit su;
     __shared__ SharedSmall pool;
     __shared__ __align__(16) uint32_t small_desc[kDescWords];  // the current unit's layer descriptor
-    const Common &c = P.c;
+    ArgCommon &c = arg_of<LaunchPlan>()->c;
     const LayerDesc *layers = P.layers;
     const int w = blockIdx.x;
     const int W = c.n_wg;
-    if (w == 0 && (int)threadIdx.x < c.n_clear) c.tickets[c.clear_slot[threadIdx.x]] = 0u;
+    if (w == 0 && (int)threadIdx.x < c.n_clear) gstore(c.tickets + P.c.clear_slot[threadIdx.x], 0u);
     // the sequence lengths: asked for now, in LDS by the time the unit tables below are built
-    if ((int)threadIdx.x < c.batch) pool.len[threadIdx.x] = clamp_len(c.lengths[threadIdx.x], c.max_len);
+    if ((int)threadIdx.x < c.batch) pool.len[threadIdx.x] = clamp_len(gload(c.lengths + threadIdx.x), c.max_len);
 
     // Kinds in a fixed order (S on retrieval groups, C, T, S set copies, A); within a kind
     // layer by layer.
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_small_kernel(const LaunchP
         if (t < P.t_count) cnt_t = (uint32_t)(c.batch * P.n_rseg[P.t_first + t]);
         uint32_t tot[5];
         unsigned long long tot_s;
-        const unsigned long long incl_s = block_scan64(cnt_s, pool.scan64, tot_s);
+        const unsigned long long incl_s = block_scan_pair(cnt_s, pool.scan64, tot_s);
         const uint32_t incl_t = block_scan(cnt_t, pool.scan, tot[2]);
         tot[0] = (uint32_t)tot_s;
         tot[3] = (uint32_t)(tot_s >> 32);
@@ -117,6 +117,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_small_kernel(const LaunchP
             return *reinterpret_cast<const LayerDesc *>(small_desc);
         };
         for (int j = w; j < n_small; j += W) {
+            ArgCommon &c = arg_of<LaunchPlan>()->c;
             int u = j;
             if (u < (int)tot[0]) {
                 const int li = find_item(pool.upre[0], P.s_count, u);
@@ -172,7 +173,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_pool_kernel(const LaunchPl
     __shared__ SharedAttn sa;
     __shared__ SharedPool pool;
     __shared__ uint32_t desc_s[2][kDescWords];
-    const Common &c = P.c;
+    ArgCommon &c = arg_of<LaunchPlan>()->c;
     const LayerDesc *layers = P.layers;
     const int w = blockIdx.x;
     const int W = c.n_wg;
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_pool_kernel(const LaunchPl
     // one segment per retrieval (sparse) KV head of the layer
     // (the sequence lengths go to LDS for the pieces; the item sizes below read them from memory
     // themselves, so that those loads are not behind a barrier)
-    if (threadIdx.x < c.batch) pool.len[threadIdx.x] = clamp_len(c.lengths[threadIdx.x], c.max_len);
+    if (threadIdx.x < c.batch) pool.len[threadIdx.x] = clamp_len(gload(c.lengths + threadIdx.x), c.max_len);
     // Most of the pooled blocks are dealt statically, an equal contiguous run per workgroup;
     // the last tail_permille/1000 of them are cut into chunks that workgroups claim through
     // a counter as they finish, which evens out CUs that stream at different speeds.  Runs
@@ -206,7 +207,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_pool_kernel(const LaunchPl
             nseg[i] = nb[i] = 0;
             if (it < n_items) {
                 const int li = it / c.batch;
-                const int L = clamp_len(c.lengths[it % c.batch], c.max_len);
+                const int L = clamp_len(gload(c.lengths + it % c.batch), c.max_len);
                 if (li < P.r_count) {
                     nseg[i] = (uint32_t)P.n_rseg[P.r_first + li];
                     nb[i] = (uint32_t)((L + kBlockRows - 1) / kBlockRows);
@@ -219,7 +220,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_pool_kernel(const LaunchPl
             sum += ((unsigned long long)nseg[i] << 32) | (unsigned long long)(nseg[i] * nb[i]);
         }
         unsigned long long total64;
-        uint32_t at = (uint32_t)(block_scan64(sum, pool.scan64, total64) - sum);
+        uint32_t at = (uint32_t)(block_scan_pair(sum, pool.scan64, total64) - sum);
         const int T_real = (int)(uint32_t)total64;
         const int n_segs = (int)(total64 >> 32);
         const int tail = (int64_t)T_real >= 8ll * c.chunk_blocks * W ? c.tail_permille : 0;
@@ -267,7 +268,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_pool_kernel(const LaunchPl
     // of the launch were served one after the other, and the first barrier waited for it.)
     uint32_t next_ticket = (uint32_t)w;
     if (threadIdx.x == 0) {
-        if (w == 0) c.tickets[(c.ticket_slot + kTicketRing / 2) % kTicketRing] = 0u;
+        if (w == 0) gstore(c.tickets + (c.ticket_slot + kTicketRing / 2) % kTicketRing, 0u);
     }
 
     // A piece needs its layer's descriptor before it can issue its first load.  Read through
@@ -289,6 +290,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_pool_kernel(const LaunchPl
     x1 = x1 < T_static ? x1 : T_static;
     for (;;) {
         while (x < x1) {
+            ArgCommon &c = arg_of<LaunchPlan>()->c;
             const int it = find_item(pool.ipre, n_items, x);
             const int li = it / c.batch;
             const int b = it % c.batch;

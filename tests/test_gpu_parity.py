@@ -586,6 +586,34 @@ def test_select_at_the_edges_of_its_routes(ctx, L, k, copies):
     assert (dl.idx_out.cpu().numpy() == idx).all()
 
 
+@pytest.mark.parametrize("n_wg,L,k", [
+    (0, 4097, 2048), (0, 20000, 1), (0, 32768, 3900), (0, 32768, 4100),  # thresholds by one unit and by four
+    (0, 65, 3), (0, 129, 40),                       # pieces of one block and of a part of one
+    (18, 8193, 100), (18, 16384, 700),              # pieces around 1024 and 2048 rows: one or two wavefronts filter
+    (12, 16700, 900), (10, 33000, 300),             # around 4096: the last window of keys full, short, the second one
+])
+def test_pieces_filter_their_keys_at_the_edges_of_a_wavefronts_share(ctx, n_wg, L, k):
+    """Plain and deferred calls of one sequence whose pieces end at the edges of what a wavefront filters, on grids
+    that make them so long: the oracle's sets, with no position allowed to differ."""
+    lb = H.binding()
+    w = wl.scaled(wl.WORKLOADS["c1"], max_len=L, k=k, planted=1)
+    mask = np.zeros(w.n_q_heads, np.uint8)
+    mask[[0, 5]] = 1
+    inp = wl.make_layer(w, mask=mask, l_cap=L)
+    idx_in = H.previous_layer_sets(inp, k)
+    _say("filter edge: n_wg=%d L=%d k=%d" % (n_wg, L, k))
+    ctx.set_option(lb.OPT_N_WG, n_wg)
+    dl, _, idx, _, _, _ = H.check_layer(ctx, inp, mask, k, idx_in, "L=%d k=%d" % (L, k), exact_sets=True)
+    ws = lb.alloc_workspace(dl.shape, "cuda", n_layers=2)
+    ws.fill_(0xFF)
+    dl.idx_out.fill_(-7)
+    ctx.decode_attn_deferred(dl.shape, dl.q, dl.k_cache, dl.v_cache, mask, dl.idx_in, dl.out, dl.idx_out, dl.lengths, ws)
+    ctx.select_flush()
+    torch.cuda.synchronize()
+    assert (dl.idx_out.cpu().numpy() == idx).all()
+    assert ctx.wait_timeouts() == 0
+
+
 @pytest.mark.parametrize("lens,k,block", [
     ([61, 3001, 200, 1] * 20, 300, 1),       # runs that cross many short segments; set copies by every workgroup
     ([61, 3001, 200, 1] * 20, 5, 64),
