@@ -476,6 +476,7 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
         p.front = front_plan(p.n_selects, p.n_copies, p.n_thresholds, p.gate_mask != 0, r_blocks, W);
         if (p.front.n_front != front_plan(p.n_selects, p.n_copies, p.n_thresholds, p.gate_mask != 0, 0, W).n_front)
             p.front.n_front = -1;
+        if (select_now) p.n_tail = tail_selects(s.batch * cur->n_rgroups, r_blocks, W);
         const int32_t g_blocks = cur->n_sgroups * s.batch * (((s.k < s.max_len ? s.k : s.max_len) + 63) / 64);
         if (ctx->g_block_rows == 0 && !plain) p.c.g_block_rows = gather_block_rows(r_blocks, g_blocks, s.max_len, W);
     } else {

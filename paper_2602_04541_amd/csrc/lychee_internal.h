@@ -130,9 +130,9 @@ struct LaunchPlan {
 //   G pieces      cur's sparse gathers; a piece of a KV head in gate_mask polls until the front
 //                 unit that writes that head's inherited set has published it
 //   combine       the workgroup that writes the last partial of a (sequence, KV head, kind)
-//                 segment merges the segment's partials into `out`; in the build that selects for
-//                 its own layer it then selects the segment's set, and cur's kept sets are
-//                 copied by front units
+//                 segment merges the segment's partials into `out`
+//   own select    in the build that selects for its own layer: by the last n_tail workgroups, a score row each,
+//                 or by whoever completed the row's segment; cur's kept sets are copied by front units
 // Flags carry the launch's generation, a counter in device memory that the last workgroup to
 // finish advances: a flag of an earlier launch, or of an earlier replay of a captured launch,
 // never matches.
@@ -143,6 +143,7 @@ struct LayerLaunch {
     int32_t has_cur, has_prev;
     FrontPlan front;       // who runs front units; n_front < 0: front_plan says with the sequences' lengths, of
     int32_t n_selects, n_copies, n_thresholds;  // so many units of each kind
+    int32_t n_tail;        // the last workgroups, which wait for cur's score rows and select them (tail_selects)
     int32_t lead_blocks;   // blocks of 64 rows the device streams while a select runs: how much
                            // later than the streaming the gated gathers can start
     uint64_t gate_mask;    // bit g: KV head g's inherited set is written by this launch's front units
@@ -150,7 +151,7 @@ struct LayerLaunch {
     uint32_t *exit_count;  // workgroups that have finished
     unsigned long long *thr_flags;  // [B * n_rgroups] {generation, threshold} of cur's score rows
     uint32_t *set_flags;   // (set_flag_at) generation once the set of (sequence, KV head) is final
-    uint32_t *seg_count;   // [B * H_kv * 2] partials written so far of each R / G segment (zero between launches)
+    uint32_t *seg_count;   // [B * H_kv * 2] blocks done so far of each R / G segment (zero between launches)
     uint32_t *thr_arrived; // [B * n_rgroups] threshold units of a score row that have left their keys (likewise)
 };
 // 0: no selection anywhere in the launch (the dense baseline); 1: the hybrid build; 2: the one

@@ -21,12 +21,14 @@
 //   combine      every piece writes its partial through to device memory and counts itself in;
 //                the piece that completes a segment merges the segment's partials into `out` (a
 //                segment of one piece writes `out` itself)
-//   own select   in the build for calls that want their sets at once: the workgroup that completed a
-//                segment selects its set after its last piece
+//   own select   in the build for calls that want their sets at once: the last workgroups of the grid
+//                select, one score row each, as soon as the row's pieces have counted themselves in and
+//                beside the merge that follows (tail_selects); where the rows are too many for that, the
+//                workgroup that completed a segment selects its set after its last piece
 //
-// Waiting is safe because every wait is for a front unit, front units never wait, and where anything
-// waits they have the lowest workgroup indices, which are dispatched first, to themselves
-// (front_plan); waits are bounded all the same.
+// Waiting is safe because workgroups are dispatched in index order and every wait is for lower ones: pieces
+// wait for front units, which never wait and have, where anything waits, the lowest indices to themselves
+// (front_plan); selects at the end of the grid wait for pieces.  Waits are bounded all the same.
 // Partials cross from one XCD's L2 to another's without the agent-scope release fence (its
 // write-back of the whole L2, executed by every workgroup, costs more than the layer): they are
 // written with write-through stores, the writer waits until those have completed before it
@@ -51,7 +53,7 @@ struct SharedLayer {
     uint32_t nb[2][kMaxBatch];     // per kind: blocks of one segment of every sequence
     int32_t extra[2];              // per kind: blocks that a segment counts beyond those it has
     int32_t run[3];                // the piece loop: next block of this workgroup's run, blocks per run, padded (2: `at` holds the only piece)
-    __align__(16) int32_t at[8];   // the piece in hand: sequence, KV head, heads, blocks; pieces of its segment, first and end row, slot
+    __align__(16) int32_t at[12];  // the piece in hand: sequence, KV head, heads, blocks of the run; pieces of its segment, first and end row, slot; its blocks, its segment's
     FrontPlan front;               // who runs front units
     uint32_t gen;                  // the generation of this launch's flags
 };
@@ -108,9 +110,35 @@ __device__ __forceinline__ void await_set(const uint32_t *flag, uint32_t gen, ui
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
 }
 
+// Before a workgroup at the end of the grid selects a row: until the row's pieces have counted in all of its
+// blocks.  Whether they have (false: it gave up).  The counter goes back to zero: here, or, marked by the
+// highest bit, by the piece that completes it later.
+constexpr uint32_t kNobodyWaits = 0x80000000u;
+__device__ __forceinline__ bool await_rows(uint32_t *counter, uint32_t blocks, uint32_t *timeouts, SharedLayer &pool)
+{
+    if (fresh_tid() == 0) {
+        int spin = 0;
+        for (; spin < kSpinMax; ++spin) {
+            if (load_agent(counter) == blocks) break;
+            __builtin_amdgcn_s_sleep(2);
+        }
+        if (spin == kSpinMax) {
+            const uint32_t old = __hip_atomic_fetch_add((LYCHEE_GLOBAL uint32_t *)counter, kNobodyWaits, __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT);
+            if (old == blocks) spin = 0;  // (just in time)
+            else atomicAdd(timeouts, 1u);
+        }
+        if (spin != kSpinMax) store_agent(counter, 0u);
+        pool.flag = spin != kSpinMax;
+    }
+    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    return uni(pool.flag) != 0;
+}
+
 // SELECTS: 0 no selection in the launch; 1 the select that an earlier call left pending; 2 the same with the
-// probability rules; 3 this layer's own, by whoever completes a segment (nothing pends then: with
-// one select in it every build keeps its registers).
+// probability rules; 3 this layer's own, by workgroups at the end of the grid or whoever completes a segment
+// (nothing pends then: with one select in it every build keeps its registers).
 template <bool COLLECT, int SELECTS>
 __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLaunch P)
 {
@@ -240,7 +268,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
         const int TR = uni((int)(uint32_t)tot64) * n_rseg;  // (below 2^31, checked before the launch)
         const int TG = uni((int)(uint32_t)(tot64 >> 32)) * n_gseg;
         const int first = uni(pool.front.n_aside);
-        const int Wn = W - first;
+        const int Wn = W - first - (kNow ? A->n_tail : 0);
         int W_R = 0, W_G = 0;
         if (Wn < 2) {  // a single workgroup does both kinds, one after the other
             W_R = TR > 0;
@@ -352,6 +380,8 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                                 pool.at[5] = ri * s * brows;
                                 pool.at[6] = r1 < seg_rows ? r1 : seg_rows;
                                 pool.at[7] = ri;
+                                pool.at[8] = kd.nb - ri * s < s ? kd.nb - ri * s : s;
+                                pool.at[9] = kd.nb;
                             }
                         }
                     }
@@ -382,7 +412,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
 
         // One piece: where it lies, from the values in LDS alone.
         struct Piece {
-            int b, g, len_b, r0, r1, slot, pieces, len, next_seg;
+            int b, g, len_b, r0, r1, slot, pieces, len, nb, next_seg;
             uint32_t hmask;
             bool ends, padding;
         };
@@ -404,6 +434,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             int len = x1 - x;
             len = len < nb - blk ? len : nb - blk;
             pc.len = len;
+            pc.nb = nb;
             pc.r0 = blk * brows;
             const int r1 = (blk + len) * brows;
             pc.r1 = r1 < seg_rows ? r1 : seg_rows;
@@ -460,6 +491,8 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                     pool.at[2] = (int32_t)pc.hmask;
                     pool.at[3] = pc.len;
                     pool.at[4] = pc.pieces;
+                    pool.at[8] = pc.len;
+                    pool.at[9] = pc.nb;
                 }
                 auto nothing = []() {};
                 const uint16_t *dq = desc_ptr<const uint16_t>(dw, offsetof(LayerDesc, q));
@@ -503,7 +536,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                                                sh.attn, nothing);
                 }
             }
-            // The piece's partials are in device memory.  Count it in; whoever completes the
+            // The piece's partials are in device memory.  Count its blocks in; whoever completes the
             // segment merges its partials (slots 0 .. pieces-1 of every head of the segment).
             __syncthreads();
             A = arg_of<LayerLaunch>();
@@ -513,12 +546,14 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             const uint32_t hmask = (uint32_t)uni(pool.at[2]);
             if (tid == 0) {
                 int last = 1;
-                if (pieces > 1) {
+                const bool awaited = kNow && !gather && A->n_tail > 0;  // by the workgroup that selects the row
+                if (pieces > 1 || awaited) {
                     uint32_t *counter = A->seg_count + (((int64_t)b * cc.n_kv_heads + g) * 2 + kind);
-                    const uint32_t old = __hip_atomic_fetch_add((LYCHEE_GLOBAL uint32_t *)counter, 1u, __ATOMIC_RELAXED,
+                    const uint32_t mine = (uint32_t)pool.at[8];
+                    const uint32_t old = __hip_atomic_fetch_add((LYCHEE_GLOBAL uint32_t *)counter, mine, __ATOMIC_RELAXED,
                                                                 __HIP_MEMORY_SCOPE_AGENT);
-                    last = old == (uint32_t)pieces - 1u;
-                    if (last) store_agent(counter, 0u);  // as every launch finds it
+                    last = (old & ~kNobodyWaits) + mine == (uint32_t)pool.at[9];
+                    if (last && (!awaited || old >= kNobodyWaits)) store_agent(counter, 0u);  // as every launch finds it
                 }
                 pool.flag = last;
             }
@@ -527,14 +562,14 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             // one that saw the next piece's place would merge, or not merge, another segment than the others)
             if (tid == 0) pool.run[0] = x + uni(pool.at[3]);
             if (pool.flag) {
-                if (pieces > 1 || kNow) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                if (pieces > 1 || (kNow && A->n_tail == 0)) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                 if (pieces > 1) switch (__builtin_popcount(hmask)) {
                 case 1: combine_segment<1>(cc, cur, b, g, hmask, pieces, sh.comb); break;
                 case 2: combine_segment<2>(cc, cur, b, g, hmask, pieces, sh.comb); break;
                 case 3: combine_segment<3>(cc, cur, b, g, hmask, pieces, sh.comb); break;
                 default: combine_segment<4>(cc, cur, b, g, hmask, pieces, sh.comb); break;
                 }
-                if (kNow && !gather && tid == 0) {  // every candidate of the row is in its list: its set can be selected
+                if (kNow && !gather && A->n_tail == 0 && tid == 0) {  // every candidate of the row is in its list: its set can be selected
                     const int row = b * uni(pool.role[0][2]) + (int)desc_u8(dw, offsetof(LayerDesc, rindex) + g);
                     wanted[row >> 5] |= 1u << (row & 31);
                 }
@@ -547,19 +582,28 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
     }
 
     // ------------------------------------------------------------------ this layer's own sets
-    // The rows of the segments that this workgroup completed, after its last piece.  (Selected inside
-    // the piece loop they took registers from the streaming, which spilled.)
+    // The row of a workgroup at the end of the grid, or those of the segments that this one completed, after
+    // its last piece.  (Selected inside the piece loop they took registers from the streaming, which spilled.)
     if (kNow) {
         __syncthreads();  // (a workgroup without pieces has passed no barrier since thread 0 left the roles)
         const LYCHEE_CONSTANT LayerLaunch *A = arg_of<LayerLaunch>();
         ArgCommon &c = A->c;
         const int n_rseg = uni(pool.role[0][2]);
         const int n_rows = c.batch * n_rseg;
+        const int own = A->n_tail > 0 ? w - (W - A->n_tail) : -1;
+        if (own >= 0) {
+            if (tid == 0) wanted[own >> 5] = 1u << (own & 31);
+            __syncthreads();
+        }
         for (int i = 0; i < n_rows; i += 32) {
             for (uint32_t rows = uni(wanted[i >> 5]); rows != 0; rows &= rows - 1u) {
                 const int row = i + __builtin_ctz(rows);
-                select_unit<false>(c, cur, row / n_rseg, cur.rgroup[row % n_rseg], sel, pool, A->thr_flags + row,
-                                   pool.gen);
+                const int b = row / n_rseg, g = cur.rgroup[row % n_rseg];
+                bool complete = true;
+                if (own >= 0)
+                    complete = await_rows(A->seg_count + ((int64_t)b * c.n_kv_heads + g) * 2,
+                                          (uint32_t)(pool.len[b] + kBlockRows - 1) / kBlockRows, c.stats + 2, pool);
+                select_unit<false>(c, cur, b, g, sel, pool, A->thr_flags + row, pool.gen, complete);
                 __syncthreads();
             }
         }

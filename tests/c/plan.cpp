@@ -18,3 +18,8 @@ extern "C" int32_t gather_block_rows(int32_t r_blocks, int32_t g_blocks, int32_t
 {
     return lychee::gather_block_rows(r_blocks, g_blocks, max_len, n_wg);
 }
+
+extern "C" int32_t tail_selects(int32_t rows, int32_t r_blocks, int32_t n_wg)
+{
+    return lychee::tail_selects(rows, r_blocks, n_wg);
+}

@@ -614,6 +614,29 @@ def test_pieces_filter_their_keys_at_the_edges_of_a_wavefronts_share(ctx, n_wg, 
     assert ctx.wait_timeouts() == 0
 
 
+@pytest.mark.parametrize("lens,Hkv,k,block,n_wg", [
+    ([4099], 4, 300, 1, 64), ([4099], 5, 300, 1, 64), ([4099], 4, 300, 1, 63),  # rows beside the grid: selected at its end or not
+    ([700, 65, 1, 64], 8, 40, 1, 0), ([700, 65, 1] * 11, 1, 40, 1, 0),          # 32 and 33 rows; segments of one piece
+    ([40000] * 2, 4, 900, 1, 64), ([40000], 1, 900, 1, 64),                     # streaming too long for four rows' workgroups
+    ([65], 8, 200, 1, 0), ([9000, 63, 130], 2, 9, 64, 0),                       # the set is everything; blocks
+])
+def test_layer_calls_whose_rows_are_selected_at_the_end_of_the_grid(ctx, lens, Hkv, k, block, n_wg):
+    """On both sides of the rule that gives a launch's score rows workgroups of their own: the oracle's sets, twice
+    in a row (the second call finds the counters as the first left them)."""
+    lb = H.binding()
+    w = wl.scaled(wl.WORKLOADS["c1"], batch=len(lens), n_q_heads=2 * Hkv, n_kv_heads=Hkv, max_len=max(lens), k=k, planted=1)
+    inp = wl.make_layer(w, mask=np.tile(np.array([1, 0], np.uint8), Hkv), lens=np.asarray(lens, np.int32), l_cap=max(lens))
+    idx_in = H.previous_layer_sets(inp, k, block=block)
+    _say("selects at the end: B%d rows=%d k=%d block=%d n_wg=%d" % (len(lens), len(lens) * Hkv, k, block, n_wg))
+    ctx.set_option(lb.OPT_N_WG, n_wg)
+    dl, out, idx, _, _, _ = H.check_layer(ctx, inp, inp.mask, k, idx_in, exact_sets=True, block=block)
+    dl.out.fill_(float("nan"))
+    dl.idx_out.fill_(-7)
+    out2, idx2 = H.run_hybrid(ctx, dl, inp.mask)
+    assert (out2 == out).all() and (idx2 == idx).all()
+    assert ctx.wait_timeouts() == 0
+
+
 @pytest.mark.parametrize("lens,k,block", [
     ([61, 3001, 200, 1] * 20, 300, 1),       # runs that cross many short segments; set copies by every workgroup
     ([61, 3001, 200, 1] * 20, 5, 64),
