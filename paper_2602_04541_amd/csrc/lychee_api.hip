@@ -437,14 +437,12 @@ int check_layer_space(const lychee_shape &s, const LayerDesc &d)
 
 // One launch of lychee_layer_kernel: everything `cur`'s output needs (cur may be null: only the
 // pending select), with the select and set copies of `prev` (may be null) among its front units.
-// plain: `cur`'s own sets are wanted with the call (then `prev` is null): from this launch, or under a
-// probability rule from one that the caller enqueues behind it.
+// select_now: `cur`'s own sets are wanted with the call (then `prev` is null).
 // Every check happens before the launch; nothing else is enqueued.
 int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, const int32_t *lengths,
-                 const LayerDesc *cur, const LayerDesc *prev, hipStream_t stream, bool plain = false)
+                 const LayerDesc *cur, const LayerDesc *prev, hipStream_t stream, bool select_now = false)
 {
     if (cur == nullptr && prev == nullptr) return LYCHEE_OK;
-    const bool select_now = plain && s.prob_rule == 0;
     LayerLaunch p;
     memset(&p, 0, sizeof p);
     const int W = grid_of(ctx);
@@ -478,7 +476,7 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
             p.front.n_front = -1;
         if (select_now) p.n_tail = tail_selects(s.batch * cur->n_rgroups, r_blocks, W);
         const int32_t g_blocks = cur->n_sgroups * s.batch * (((s.k < s.max_len ? s.k : s.max_len) + 63) / 64);
-        if (ctx->g_block_rows == 0 && !plain) p.c.g_block_rows = gather_block_rows(r_blocks, g_blocks, s.max_len, W);
+        if (ctx->g_block_rows == 0 && !select_now) p.c.g_block_rows = gather_block_rows(r_blocks, g_blocks, s.max_len, W);
     } else {
         // only front units: one workgroup each, up to the usual grid
         const int32_t units = p.n_selects + p.n_copies;
@@ -493,7 +491,7 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
     p.seg_count = reinterpret_cast<uint32_t *>(ctx->sync_dev + kSyncSeg);
     p.thr_arrived = reinterpret_cast<uint32_t *>(ctx->sync_dev + kSyncArrived);
     const bool collects = cur != nullptr && cur->emit_sel;
-    const int build = !(p.n_selects > 0 || collects) ? 0 : (s.prob_rule != 0 ? 2 : (select_now ? 3 : 1));
+    const int build = !(p.n_selects > 0 || collects) ? 0 : (select_now ? 3 : (s.prob_rule != 0 ? 2 : 1));
     if (!ctx->timing) return launch_layer(p, build, stream) == hipSuccess ? LYCHEE_OK : LYCHEE_EHIP;
     lychee_ctx::Rec rec{cur != nullptr ? LYCHEE_KERNEL_STREAM : LYCHEE_KERNEL_SELECT, take_event(ctx), take_event(ctx)};
     if (rec.start == nullptr || rec.stop == nullptr) return LYCHEE_EHIP;
@@ -683,11 +681,8 @@ int decode_attn(lychee_ctx *ctx, const lychee_shape *shape, const void *q, const
     d.copy_keep = 1;
     d.list_count = count_bank(ctx, 2);
     if ((rc = check_layer_space(*shape, d)) != LYCHEE_OK) return rc;
-    // idx_out is complete when the call's work is: the launch selects as its segments complete.  (The
-    // probability rules select in a launch of their own: inside the streaming one their registers
-    // spilled and cost it more than a launch: 95.7 against 85.7 us for Top-p at 128K.)
-    if ((rc = layer_launch(ctx, *shape, w, lengths, &d, nullptr, stream, true)) != LYCHEE_OK || shape->prob_rule == 0) return rc;
-    return layer_launch(ctx, *shape, w, lengths, nullptr, &d, stream);
+    // idx_out is complete when the call's work is: the launch selects as its segments complete.
+    return layer_launch(ctx, *shape, w, lengths, &d, nullptr, stream, true);
 }
 
 }  // namespace

@@ -155,7 +155,7 @@ struct LayerLaunch {
     uint32_t *thr_arrived; // [B * n_rgroups] threshold units of a score row that have left their keys (likewise)
 };
 // 0: no selection anywhere in the launch (the dense baseline); 1: the hybrid build; 2: the one
-// that also knows the probability rules; 3: the hybrid build that selects for `cur` instead of `prev`
+// that also knows the probability rules; 3: the one, rules included, that selects for `cur` instead of `prev`
 hipError_t launch_layer(const LayerLaunch &plan, int build, hipStream_t stream);
 
 hipError_t launch_units(const LaunchPlan &plan, hipStream_t stream);

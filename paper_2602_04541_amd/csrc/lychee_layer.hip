@@ -603,7 +603,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                 if (own >= 0)
                     complete = await_rows(A->seg_count + ((int64_t)b * c.n_kv_heads + g) * 2,
                                           (uint32_t)(pool.len[b] + kBlockRows - 1) / kBlockRows, c.stats + 2, pool);
-                select_unit<false>(c, cur, b, g, sel, pool, A->thr_flags + row, pool.gen, complete);
+                select_unit<true>(c, cur, b, g, sel, pool, A->thr_flags + row, pool.gen, complete);
                 __syncthreads();
             }
         }
