@@ -435,14 +435,28 @@ int check_layer_space(const lychee_shape &s, const LayerDesc &d)
     return LYCHEE_OK;
 }
 
+// Blocks of 64 rows that a layer's streaming takes, by the cache's capacity.
+int32_t streamed_blocks(const lychee_shape &s, const LayerDesc &d)
+{
+    return d.n_rgroups * s.batch * ((s.max_len + kBlockRows - 1) / kBlockRows);
+}
+
+// Whether a plain layer call under a probability rule selects in a launch of its own.
+bool selects_apart(const lychee_ctx *ctx, const lychee_shape &s, const LayerDesc &d)
+{
+    return s.prob_rule != 0 && rules_apart(s.batch * d.n_rgroups, streamed_blocks(s, d), grid_of(ctx));
+}
+
 // One launch of lychee_layer_kernel: everything `cur`'s output needs (cur may be null: only the
 // pending select), with the select and set copies of `prev` (may be null) among its front units.
-// select_now: `cur`'s own sets are wanted with the call (then `prev` is null).
+// plain: `cur`'s own sets are wanted with the call (then `prev` is null): from this launch, or, where
+// selects_apart says so, from one that the caller enqueues behind it.
 // Every check happens before the launch; nothing else is enqueued.
 int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, const int32_t *lengths,
-                 const LayerDesc *cur, const LayerDesc *prev, hipStream_t stream, bool select_now = false)
+                 const LayerDesc *cur, const LayerDesc *prev, hipStream_t stream, bool plain = false)
 {
     if (cur == nullptr && prev == nullptr) return LYCHEE_OK;
+    const bool select_now = plain && !selects_apart(ctx, s, *cur);
     LayerLaunch p;
     memset(&p, 0, sizeof p);
     const int W = grid_of(ctx);
@@ -470,13 +484,13 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
         if (rc != LYCHEE_OK) return rc;
         // The lengths are on the device; where even sequences of max_len make no difference (a single
         // sequence's few units) the kernel is spared the question.
-        const int32_t r_blocks = cur->n_rgroups * s.batch * ((s.max_len + kBlockRows - 1) / kBlockRows);
+        const int32_t r_blocks = streamed_blocks(s, *cur);
         p.front = front_plan(p.n_selects, p.n_copies, p.n_thresholds, p.gate_mask != 0, r_blocks, W);
         if (p.front.n_front != front_plan(p.n_selects, p.n_copies, p.n_thresholds, p.gate_mask != 0, 0, W).n_front)
             p.front.n_front = -1;
         if (select_now) p.n_tail = tail_selects(s.batch * cur->n_rgroups, r_blocks, W);
         const int32_t g_blocks = cur->n_sgroups * s.batch * (((s.k < s.max_len ? s.k : s.max_len) + 63) / 64);
-        if (ctx->g_block_rows == 0 && !select_now) p.c.g_block_rows = gather_block_rows(r_blocks, g_blocks, s.max_len, W);
+        if (ctx->g_block_rows == 0 && !plain) p.c.g_block_rows = gather_block_rows(r_blocks, g_blocks, s.max_len, W);
     } else {
         // only front units: one workgroup each, up to the usual grid
         const int32_t units = p.n_selects + p.n_copies;
@@ -681,8 +695,10 @@ int decode_attn(lychee_ctx *ctx, const lychee_shape *shape, const void *q, const
     d.copy_keep = 1;
     d.list_count = count_bank(ctx, 2);
     if ((rc = check_layer_space(*shape, d)) != LYCHEE_OK) return rc;
-    // idx_out is complete when the call's work is: the launch selects as its segments complete.
-    return layer_launch(ctx, *shape, w, lengths, &d, nullptr, stream, true);
+    // idx_out is complete when the call's work is: the launch selects as its segments complete, or a
+    // second one selects all of its rows.
+    if ((rc = layer_launch(ctx, *shape, w, lengths, &d, nullptr, stream, true)) != LYCHEE_OK) return rc;
+    return selects_apart(ctx, *shape, d) ? layer_launch(ctx, *shape, w, lengths, nullptr, &d, stream) : LYCHEE_OK;
 }
 
 }  // namespace

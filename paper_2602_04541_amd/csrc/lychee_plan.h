@@ -83,6 +83,17 @@ LYCHEE_HD inline int32_t tail_selects(int32_t rows, int32_t r_blocks, int32_t n_
     return 64 * rows <= n_wg || (16 * rows <= n_wg && r_blocks <= 8 * n_wg) ? rows : 0;
 }
 
+// Whether a plain layer call under a probability rule selects in a second launch, a workgroup per row, instead of in
+// its own.  A select with a rule takes up to 15 us, and of more rows than a quarter of the workgroups some complete
+// several and select them in turn; a streaming of more than 32 blocks a workgroup hides that.  us a call
+// in one launch and in two, 64 sequences of four retrieval heads, Top-p: of 1/3 to 1024 rows 66 and 57, 61 to 3001 rows
+// (in 4096) 106 and 92, 1/3 to 6000 142 and 165; a Threshold, 61 to 1001 rows 58 and 51; 32 sequences of 1/3 to
+// 1000 rows, Top-p, 41 and 44.
+LYCHEE_HD inline bool rules_apart(int32_t rows, int32_t r_blocks, int32_t n_wg)
+{
+    return 4 * rows > n_wg && r_blocks <= 32 * n_wg;
+}
+
 // Rows one threshold unit samples in one round of loads.
 constexpr int32_t kAloneSample = 512;
 // Whether a score row's threshold is taken by one unit from one round of loads (512 rows) instead of by four from

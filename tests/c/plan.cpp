@@ -23,3 +23,8 @@ extern "C" int32_t tail_selects(int32_t rows, int32_t r_blocks, int32_t n_wg)
 {
     return lychee::tail_selects(rows, r_blocks, n_wg);
 }
+
+extern "C" int32_t rules_apart(int32_t rows, int32_t r_blocks, int32_t n_wg)
+{
+    return lychee::rules_apart(rows, r_blocks, n_wg);
+}

@@ -1122,6 +1122,21 @@ def test_probability_rules_on_short_and_ragged_sequences(ctx, rule, param):
     H.check_prob_rule_layer(ctx, inp, np.ones(w.n_q_heads, np.uint8), w.k, rule, param, "ragged rule %d" % rule)
 
 
+@pytest.mark.parametrize("rule,param", [(1, 1e-3), (2, 0.8)])
+@pytest.mark.parametrize("lens,n_wg", [([300, 65, 1, 64, 129, 1000], 24), ([300, 65, 1, 64, 129, 1000], 25), ([2000, 4100], 64)])
+def test_probability_rules_beside_the_lines_between_their_routes(ctx, lens, n_wg, rule, param):
+    """Twelve rows select in a second launch on 24 and 25 workgroups, as their segments complete on 48 and 50; four
+    rows on 64 and 128 workgroups are selected at the end of the grid."""
+    w = wl.scaled(wl.WORKLOADS["c1"], batch=len(lens), max_len=max(lens), k=100, planted=1)
+    mask = np.tile(np.array([1, 0, 1, 0], np.uint8), w.n_q_heads // 4)
+    inp = wl.make_layer(w, mask=mask, lens=np.asarray(lens, np.int32), l_cap=max(lens))
+    idx_in = H.previous_layer_sets(inp, w.k)
+    for n in (n_wg, 2 * n_wg):
+        _say("rule routes: %d rows, rule=%d n_wg=%d" % (len(lens) * w.n_kv_heads, rule, n))
+        ctx.set_option(H.binding().OPT_N_WG, n)
+        H.check_prob_rule_layer(ctx, inp, mask, w.k, rule, param, "n_wg=%d" % n, idx_in)
+
+
 @pytest.mark.parametrize("L,k", [(3000, 2000), (9000, 5000), (50000, 2000)])
 def test_top_p_crosses_its_mass_among_equal_keys(ctx, L, k):
     """More equal keys than are looked at one by one hold the position where the mass is reached: the rest of

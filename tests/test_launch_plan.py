@@ -118,3 +118,9 @@ def test_selects_at_the_end_of_the_grid_leave_the_pieces_their_workgroups(plan):
         assert plan.tail_selects(rows, r_blocks, n_wg) == tail
         front, aside = front_plan(plan, 0, 8 * rows, 4 * rows, False, r_blocks, n_wg)
         assert n_wg - aside - tail >= n_wg // 2
+
+
+def test_rules_select_apart_where_many_rows_end_a_short_streaming(plan):
+    for rows, r_blocks, n_wg, apart in ((128, 64, 512, 0), (129, 129, 512, 1), (129, 16384, 512, 1), (129, 16385, 512, 0),
+                                        (16384, 2 ** 30, 512, 0), (1, 1, 4, 0), (1, 1, 3, 1)):
+        assert plan.rules_apart(rows, r_blocks, n_wg) == apart
