@@ -254,12 +254,17 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             nb_r = n_rseg ? (uint32_t)((L + kBlockRows - 1) / kBlockRows) : 0u;
             nb_g = n_gseg ? (uint32_t)quot(gather_rows(c, L) + gather_block(c) - 1, gather_block(c)) : 0u;
         }
-        // Many segments: a run crosses several, and every piece costs its start-up, merge and hand-over
-        // (about 8 us, a block 1.2 to 1.7 us), so a segment counts kPieceBlocks blocks more than it has.
+        // A run may cross segments, and every piece costs its start-up, merge and hand-over (about 8 us, a
+        // block 1.2 to 1.7 us), so a segment counts kPieceBlocks blocks more than it has.
         // (64 sequences of 61 to 3001 rows: a run of equal blocks held up to nine short
-        // segments, half the workgroups were done after 70 us and the last after 110.)
-        const int extra_r = 8 * n_rseg * c.batch > W ? kPieceBlocks : 0;
-        const int extra_g = 8 * n_gseg * c.batch > W ? kPieceBlocks : 0;
+        // segments, half the workgroups were done after 70 us and the last after 110.  Few segments of
+        // a batch, us without and with: model loop of 8 x 2000-5000 rows, 4 layers, 142.6 and 129.1, of
+        // 5 x 6000-24000 197.8 and 185.8; a layer call of 8 x 3000-8192 30.1 and 23.8.)
+        // Not the few gathers of a launch that selects its own rows: the blocks also weigh the split of the
+        // grid, and there the streaming, which the select follows, should end first (8 x 3000-8192, four retrieval heads:
+        // 32.8, with them 35.5).  A single sequence's segments end with a run.
+        const int extra_r = !single || 8 * n_rseg > W ? kPieceBlocks : 0;
+        const int extra_g = (!single && !kNow) || 8 * n_gseg * c.batch > W ? kPieceBlocks : 0;
         nb_r += nb_r ? extra_r : 0;
         nb_g += nb_g ? extra_g : 0;
         unsigned long long tot64 = (unsigned long long)nb_r | ((unsigned long long)nb_g << 32);
@@ -352,8 +357,10 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             int share = quot_uni(kd.blocks + role_n - 1, role_n);
             int pad = 0;
             uint32_t mine = nseg * nb_mine;
-            if (kd.extra == 0 && 8 * nseg * c.batch <= role_n) {
-                const int s_last = share + (share >= 16 ? share >> 3 : 1);
+            if (8 * nseg * c.batch <= role_n) {
+                // (of the blocks the segments have: a single sequence's count none beyond them here)
+                const int s_min = single ? share : quot_uni(kd.blocks - kd.extra * nseg * c.batch + role_n - 1, role_n);
+                const int s_last = s_min + (s_min >= 16 ? s_min >> 3 : 1);
                 if (single) {  // (the shortest run of which a segment takes no more than its part of the workgroups)
                     const int most = quot_uni(role_n, nseg);
                     const int s = quot_uni(kd.nb + most - 1, most);
@@ -386,15 +393,16 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                         }
                     }
                 } else {
-                    int s = share;
+                    const uint32_t nb_have = nb_mine - (nb_mine ? (uint32_t)kd.extra : 0u);
+                    int s = s_min;
                     for (; s <= s_last; ++s) {
-                        uint32_t need = nseg * (uint32_t)quot((int)nb_mine + s - 1, s), all;
+                        uint32_t need = nseg * (uint32_t)quot((int)nb_have + s - 1, s), all;
                         (void)block_scan(need, pool.scan, all);
                         if ((int)all <= role_n) break;
                     }
                     if (s <= s_last) {
                         share = s, pad = 1;
-                        mine = nseg * (uint32_t)(quot((int)nb_mine + s - 1, s) * s);
+                        mine = nseg * (uint32_t)(quot((int)nb_have + s - 1, s) * s);
                     }
                 }
             }
