@@ -73,14 +73,14 @@ LYCHEE_HD inline FrontPlan front_plan(int32_t selects, int32_t copies, int32_t t
 // (the workgroup that completes a segment then selects its set after its last piece).  They wait for the
 // rows' pieces, which lie on lower workgroups, so whatever they wait for has started.
 // Selecting there begins when a row's last piece has counted itself in, beside the merge of its partials, which
-// takes 4 us.  What it costs is the streaming that these workgroups would have done: 1/64 of it, or up to
-// 1/16 where a workgroup streams no more than eight blocks (about 15 us).  us a call, selected after the
+// takes 4 us.  What it costs is the streaming that these workgroups would have done, rows / n_wg of 5.5 ns a
+// block: up to 1/64 of it at any length, or up to 1/16 where that is no more than 1.5 us.  us a call, selected after the
 // merge and at the end of the grid: two KV heads at 4K 25.1 and 21.8, four retrieval heads of eight KV heads at
 // 32K 34.9 and 31.2, at 100K with k = 8192 70.7 and 64.8.
 LYCHEE_HD inline int32_t tail_selects(int32_t rows, int32_t r_blocks, int32_t n_wg)
 {
     if (n_wg < 64) return 0;
-    return 64 * rows <= n_wg || (16 * rows <= n_wg && r_blocks <= 8 * n_wg) ? rows : 0;
+    return 64 * rows <= n_wg || (16 * rows <= n_wg && (int64_t)rows * r_blocks <= 256ll * n_wg) ? rows : 0;
 }
 
 // Whether a plain layer call under a probability rule selects in a second launch, a workgroup per row, instead of in

@@ -113,8 +113,9 @@ def test_gather_blocks_are_shorter_where_rows_fill_the_launch(plan):
 
 
 def test_selects_at_the_end_of_the_grid_leave_the_pieces_their_workgroups(plan):
-    for rows, r_blocks, n_wg, tail in ((8, 2 ** 30, 512, 8), (9, 4097, 512, 0), (9, 4096, 512, 9), (32, 4096, 512, 32),
-                                       (33, 64, 512, 0), (1, 64, 63, 0), (1, 2 ** 30, 64, 1), (5, 5, 64, 0), (0, 0, 512, 0)):
+    for rows, r_blocks, n_wg, tail in ((8, 2 ** 30, 512, 8), (16, 8193, 512, 0), (16, 8192, 512, 16), (9, 2 ** 30, 512, 0),
+                                       (32, 4096, 512, 32), (32, 4097, 512, 0), (33, 64, 512, 0), (1, 64, 63, 0),
+                                       (1, 2 ** 30, 64, 1), (5, 5, 64, 0), (0, 0, 512, 0)):
         assert plan.tail_selects(rows, r_blocks, n_wg) == tail
         front, aside = front_plan(plan, 0, 8 * rows, 4 * rows, False, r_blocks, n_wg)
         assert n_wg - aside - tail >= n_wg // 2
