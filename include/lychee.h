@@ -19,8 +19,8 @@
  *     never read device memory from the host.  The layer calls (lychee_decode_attn,
  *     lychee_decode_attn_static, lychee_decode_attn_deferred, lychee_select_flush,
  *     lychee_dense_decode_attn) and the layer-after-layer steps enqueue kernel launches only,
- *     one per layer (two for a plain or static layer call under a probability rule, whose sets
- *     are selected behind the layer's launch), and never wait.  The phased steps and the cache append keep their layer
+ *     one per layer (two for a layer call of many short sequences under a probability rule, whose
+ *     sets are selected behind the layer's launch), and never wait.  The phased steps and the cache append keep their layer
  *     descriptors in the arena: they enqueue one small asynchronous host-to-device copy when the
  *     call's pointers differ from those of earlier calls, and once the arena has seen about
  *     4 MiB of distinct tables such a call waits for the stream once and starts the arena over
