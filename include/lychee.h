@@ -275,7 +275,8 @@ const char *lychee_strerror(int code);
 
 /* ==========================================================================================
  * Tuning and diagnostics.  Nothing below is needed to run the path; results never depend on any
- * of it beyond the fp32 rounding order of the split merge (index sets do not depend on it at all).
+ * of it beyond the fp32 rounding order of the split merge (index sets do not depend on it at all),
+ * except on WAIT_POLLS in calls with a pending selection (see there).
  * ========================================================================================== */
 
 /* Options of a context.
@@ -298,7 +299,10 @@ const char *lychee_strerror(int code);
  *                 never changes a result
  *   SELECT_LEAD   layer launches: blocks of 64 rows the device streams while a pending select
  *                 runs (default 3000); the gathers that wait for that select get workgroups for
- *                 the work that is left by then */
+ *                 the work that is left by then
+ *   WAIT_POLLS    polls of a flag after which a wait inside a layer launch gives up (0 .. 1048576, the
+ *                 default: seconds).  Fewer are for tests of what a launch does then (see
+ *                 lychee_wait_timeouts) */
 #define LYCHEE_OPT_DEFAULTS     0
 #define LYCHEE_OPT_WG_PER_CU    1
 #define LYCHEE_OPT_STEP_MODE    2
@@ -307,6 +311,7 @@ const char *lychee_strerror(int code);
 #define LYCHEE_OPT_TAIL_PERMILLE 8
 #define LYCHEE_OPT_SELECT_MARGIN 9
 #define LYCHEE_OPT_SELECT_LEAD  10
+#define LYCHEE_OPT_WAIT_POLLS   11
 #define LYCHEE_STEP_PHASED      1
 #define LYCHEE_STEP_LAYERWISE   0
 int lychee_set_option(lychee_ctx *ctx, int32_t option, int32_t value);

@@ -22,6 +22,7 @@ KERNEL_STREAM, KERNEL_GATHER, KERNEL_THRESHOLD, KERNEL_SELECT, KERNEL_COMBINE = 
 N_KERNEL_CLASSES = 5
 OPT_DEFAULTS = 0
 OPT_SELECT_LEAD = 10
+OPT_WAIT_POLLS = 11
 STATIC_SCRATCH_BYTES = 32 << 20
 OPT_WG_PER_CU, OPT_STEP_MODE, OPT_GATHER_BLOCK, OPT_N_WG, OPT_TAIL_PERMILLE, OPT_SELECT_MARGIN = 1, 2, 6, 7, 8, 9
 STEP_PHASED, STEP_LAYERWISE = 1, 0

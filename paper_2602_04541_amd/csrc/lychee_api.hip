@@ -35,6 +35,7 @@ struct lychee_ctx {
     int32_t tail_permille = 250;
     int32_t select_margin = 60;  // tenths of a standard deviation, see LYCHEE_OPT_SELECT_MARGIN
     int32_t select_lead = 3000;  // blocks of 64 rows streamed while a select runs, see LYCHEE_OPT_SELECT_LEAD
+    int32_t wait_polls = kWaitPolls;
     uint32_t launch_seq = 0;   // pooled launches so far: picks the chunk counter
     std::vector<int32_t> used_slots;  // counters of pooled launches that no later launch has reset yet
     bool timing = false;
@@ -325,6 +326,7 @@ void fill_common(Common &c, const lychee_ctx *ctx, const lychee_shape &s, const 
     const int64_t seg_blocks = (s.max_len + kBlockRows - 1) / kBlockRows;
     c.chunk_blocks = (int32_t)((seg_blocks + 191) / 192);
     if (c.chunk_blocks < 8) c.chunk_blocks = 8;
+    c.wait_polls = ctx->wait_polls;
     c.sel_margin = 0.1f * (float)ctx->select_margin;
     c.scale = (float)(1.0 / sqrt((double)kHeadDim));
     c.scale_log2e = (float)(1.4426950408889634 / sqrt((double)kHeadDim));
@@ -1067,6 +1069,7 @@ int lychee_set_option(lychee_ctx *ctx, int32_t option, int32_t value)
         ctx->tail_permille = fresh.tail_permille;
         ctx->select_margin = fresh.select_margin;
         ctx->select_lead = fresh.select_lead;
+        ctx->wait_polls = fresh.wait_polls;
         return LYCHEE_OK;
     }
     case LYCHEE_OPT_WG_PER_CU:
@@ -1092,6 +1095,10 @@ int lychee_set_option(lychee_ctx *ctx, int32_t option, int32_t value)
     case LYCHEE_OPT_SELECT_LEAD:
         if (value < 0 || value > (1 << 24)) return LYCHEE_EINVAL;
         ctx->select_lead = value;
+        return LYCHEE_OK;
+    case LYCHEE_OPT_WAIT_POLLS:
+        if (value < 0 || value > kWaitPolls) return LYCHEE_EINVAL;
+        ctx->wait_polls = value;
         return LYCHEE_OK;
     case LYCHEE_OPT_GATHER_BLOCK:
         if (value < 16 || value > 128 || value % 16) return LYCHEE_EINVAL;

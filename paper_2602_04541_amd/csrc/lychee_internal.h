@@ -42,6 +42,7 @@ constexpr float kMinusBig = -1.0e30f;    // "no score yet" sentinel of the runni
 constexpr int kMaxLayers = 128;          // layers one launch can cover
 constexpr int kMaxItems = 2048;          // (layer, sequence) pairs of one launch's pooled rows
 constexpr int kTicketRing = 64;          // chunk counters; one is cleared 32 launches before its use
+constexpr int kWaitPolls = 1 << 20;      // polls before a wait inside a launch gives up (seconds; see LYCHEE_OPT_WAIT_POLLS)
 
 // What every part of a launch shares.
 struct Common {
@@ -66,6 +67,7 @@ struct Common {
     int32_t chunk_blocks; //   chunk_blocks blocks, to whichever workgroup asks next
     int32_t g_block_rows; // set entries per pooled block of gather work (fewer than kBlockRows:
                           // a gathered row costs more than a streamed one)
+    int32_t wait_polls;   // polls of a flag or counter before a wait inside the launch gives up
     float sel_margin;     // standard deviations the threshold sample's target rank is raised by
     float scale;          // 1 / sqrt(head_dim)
     float scale_log2e;    // log2(e) / sqrt(head_dim)
@@ -89,7 +91,7 @@ struct LayerDesc {
                            // pooled selection logits, per piece (Threshold / Top-p rules only)
     unsigned long long *list;  // [B*n_rgroups][list_row] candidates in no particular order:
                                // ordered key in the low 32 bits, position in the high 32 bits
-    int32_t *list_count;   // [B*n_rgroups] candidates found (may exceed list_row: list unusable)
+    int32_t *list_count;   // [B*n_rgroups] candidates found (may exceed list_row: list unusable; kListUnusable)
     uint32_t *thr;         // [B*n_rgroups] ordered key a score must reach to be a candidate
     int32_t *idx_out;      // [B][H_kv][k] where this layer's sets are written
     const int32_t *idx_src[kMaxKvHeads];  // per KV head: base of the [B][H_kv][k] array that

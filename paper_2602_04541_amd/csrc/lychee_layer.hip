@@ -96,15 +96,16 @@ __device__ __forceinline__ void publish_set(uint32_t *flag, uint32_t gen)
 }
 
 // Before a gather piece reads a set that a front unit of this launch writes.
-__device__ __forceinline__ void await_set(const uint32_t *flag, uint32_t gen, uint32_t *timeouts, SharedLayer &pool)
+__device__ __forceinline__ void await_set(ArgCommon &c, const uint32_t *flag, uint32_t gen, SharedLayer &pool)
 {
     if (fresh_tid() == 0) {
+        const int polls = c.wait_polls;
         int spin = 0;
-        for (; spin < kSpinMax; ++spin) {
+        for (; spin < polls; ++spin) {
             if (load_agent(flag) == gen) break;
             __builtin_amdgcn_s_sleep(2);
         }
-        if (spin == kSpinMax) atomicAdd(timeouts, 1u);  // (the piece then reads whatever the array holds; entries are range-checked)
+        if (spin == polls) atomicAdd(c.stats + 2, 1u);  // (the piece then reads whatever the array holds; entries are range-checked)
     }
     __syncthreads();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
@@ -114,22 +115,23 @@ __device__ __forceinline__ void await_set(const uint32_t *flag, uint32_t gen, ui
 // blocks.  Whether they have (false: it gave up).  The counter goes back to zero: here, or, marked by the
 // highest bit, by the piece that completes it later.
 constexpr uint32_t kNobodyWaits = 0x80000000u;
-__device__ __forceinline__ bool await_rows(uint32_t *counter, uint32_t blocks, uint32_t *timeouts, SharedLayer &pool)
+__device__ __forceinline__ bool await_rows(ArgCommon &c, uint32_t *counter, uint32_t blocks, SharedLayer &pool)
 {
     if (fresh_tid() == 0) {
+        const int polls = c.wait_polls;
         int spin = 0;
-        for (; spin < kSpinMax; ++spin) {
+        for (; spin < polls; ++spin) {
             if (load_agent(counter) == blocks) break;
             __builtin_amdgcn_s_sleep(2);
         }
-        if (spin == kSpinMax) {
+        if (spin == polls) {
             const uint32_t old = __hip_atomic_fetch_add((LYCHEE_GLOBAL uint32_t *)counter, kNobodyWaits, __ATOMIC_RELAXED,
                                                         __HIP_MEMORY_SCOPE_AGENT);
-            if (old == blocks) spin = 0;  // (just in time)
-            else atomicAdd(timeouts, 1u);
+            if (old == blocks) spin = -1;  // (just in time)
+            else atomicAdd(c.stats + 2, 1u);
         }
-        if (spin != kSpinMax) store_agent(counter, 0u);
-        pool.flag = spin != kSpinMax;
+        if (spin != polls) store_agent(counter, 0u);
+        pool.flag = spin != polls;
     }
     __syncthreads();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
@@ -536,7 +538,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                                                 sh.attn, nothing);
                 } else {
                     if ((A->gate_mask >> pc.g) & 1ull)
-                        await_set(A->set_flags + set_flag_at(pc.b, pc.g, c.n_kv_heads), my_gen, c.stats + 2, pool);
+                        await_set(c, A->set_flags + set_flag_at(pc.b, pc.g, c.n_kv_heads), my_gen, pool);
                     const int32_t *idx_src = desc_ptr<const int32_t>(dw, offsetof(LayerDesc, idx_src) + 8 * (size_t)pc.g) +
                                              ((int64_t)pc.b * c.n_kv_heads + pc.g) * c.k;
                     dispatch_piece<true, true>(__builtin_popcount(pc.hmask), c, dq, dk, dv, idx_src, Emit{}, d_part_o, d_part_ml,
@@ -609,8 +611,8 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                 const int b = row / n_rseg, g = cur.rgroup[row % n_rseg];
                 bool complete = true;
                 if (own >= 0)
-                    complete = await_rows(A->seg_count + ((int64_t)b * c.n_kv_heads + g) * 2,
-                                          (uint32_t)(pool.len[b] + kBlockRows - 1) / kBlockRows, c.stats + 2, pool);
+                    complete = await_rows(c, A->seg_count + ((int64_t)b * c.n_kv_heads + g) * 2,
+                                          (uint32_t)(pool.len[b] + kBlockRows - 1) / kBlockRows, pool);
                 select_unit<true>(c, cur, b, g, sel, pool, A->thr_flags + row, pool.gen, complete);
                 __syncthreads();
             }

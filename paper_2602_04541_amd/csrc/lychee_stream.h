@@ -120,23 +120,28 @@ struct Emit {
     uint32_t *timeouts;        // counts waits that gave up
 };
 
-constexpr int kSpinMax = 1 << 20;  // polls of a flag before a wait gives up (seconds; never reached in a working launch)
+// A bit of a row's candidate counter, above every count of rows: some candidates are missing from the list.
+// (Set, not added: any number of wavefronts may give up on one row.)
+constexpr int32_t kListUnusable = 1 << 30;
 
-// Waits until the 64-bit word at `flag` carries this launch's generation in its upper half and
-// returns the lower half; `fail` if that does not happen within kSpinMax polls.  The producer
-// is a unit that runs on a workgroup with a lower index, started before this one, and waits for
-// nothing itself.
-__device__ __forceinline__ uint32_t wait_word(const unsigned long long *flag, uint32_t gen, uint32_t fail,
-                                              uint32_t *timeouts)
+// Waits until the score row's threshold word carries this launch's generation in its upper half and
+// returns the lower half.  The producer is a unit that runs on a workgroup with a lower index, started
+// before this one, and waits for nothing itself.  If that does not happen within `polls` polls nothing is
+// to be collected, and the list is marked: what the other pieces list may well be as many as the select
+// needs, but it lacks this one's rows, so that the select has to rank the whole row.
+__device__ __forceinline__ uint32_t wait_threshold(const Emit &em, int polls)
 {
-    for (int spin = 0; spin < kSpinMax; ++spin) {
-        const unsigned long long v = __hip_atomic_load((const LYCHEE_GLOBAL unsigned long long *)flag,
+    for (int spin = 0; spin < polls; ++spin) {
+        const unsigned long long v = __hip_atomic_load((const LYCHEE_GLOBAL unsigned long long *)em.thr_flag,
                                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if ((uint32_t)(v >> 32) == gen) return (uint32_t)v;
+        if ((uint32_t)(v >> 32) == em.gen) return (uint32_t)v;
         __builtin_amdgcn_s_sleep(2);
     }
-    if ((fresh_tid() & 63) == 0) atomicAdd(timeouts, 1u);
-    return fail;
+    if ((fresh_tid() & 63) == 0) {
+        (void)__hip_atomic_fetch_or((LYCHEE_GLOBAL int32_t *)em.count, kListUnusable, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        atomicAdd(em.timeouts, 1u);
+    }
+    return 0xFFFFFFFFu;
 }
 
 // LATE pieces: lists the rows of a window of n_rows keys in sh.keys that reach the threshold; row i of the window is
@@ -146,15 +151,14 @@ __device__ __forceinline__ uint32_t wait_word(const unsigned long long *flag, ui
 // ahead of the partial, four barriers and the answer of the one reservation stood between the last row and the
 // partial, and a piece that ended before its threshold was out held its partial back.)
 constexpr int kFilterRows = kKeyBuf / kWaves;
-__device__ __forceinline__ void late_filter(const Emit &em, const SharedAttn &sh, int first_row, int n_rows)
+__device__ __forceinline__ void late_filter(ArgCommon &c, const Emit &em, const SharedAttn &sh, int first_row, int n_rows)
 {
     const int tid = fresh_tid();
     const int lane = tid & 63;
     const int i0 = uni(kWaves - 1 - (tid >> 6)) * kFilterRows;
     if (i0 >= n_rows) return;  // (uniform in the wavefront)
     const int i1 = n_rows < i0 + kFilterRows ? n_rows : i0 + kFilterRows;
-    // (on a time-out nothing is collected; the select then ranks the whole row itself)
-    const uint32_t thr = em.thr_known ? em.thr : uni(wait_word(em.thr_flag, em.gen, 0xFFFFFFFFu, em.timeouts));
+    const uint32_t thr = em.thr_known ? em.thr : uni(wait_threshold(em, c.wait_polls));
     constexpr int kRounds = kFilterRows / 64;
     uint32_t key[kRounds];
     uint32_t n = 0;
@@ -342,7 +346,7 @@ __device__ __forceinline__ void stream_rows(ArgCommon &c, const uint16_t *kbase,
                 if (ch < 8) sh.keys[(r - r0) & (kKeyBuf - 1)] = key;
                 if (((span + 1) & (kWindowSpans - 1)) == 0 && span + 1 < n_spans) {  // uniform in the workgroup
                     __syncthreads();
-                    late_filter(em, sh, r0 + (span + 1) * kSpan - kKeyBuf, kKeyBuf);
+                    late_filter(c, em, sh, r0 + (span + 1) * kSpan - kKeyBuf, kKeyBuf);
                     __syncthreads();
                 }
                 continue;
@@ -551,7 +555,7 @@ __device__ __forceinline__ void run_piece(ArgCommon &c, const uint16_t *q, const
         }
     }
     if (LATE && collects) {
-        late_filter(em, sh, late_first, r1 - late_first);
+        late_filter(c, em, sh, late_first, r1 - late_first);
     } else if (collects) {
         __syncthreads();
         int base = sh.cand_base;

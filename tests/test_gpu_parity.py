@@ -637,6 +637,45 @@ def test_layer_calls_whose_rows_are_selected_at_the_end_of_the_grid(ctx, lens, H
     assert ctx.wait_timeouts() == 0
 
 
+@pytest.mark.parametrize("call", ["plain", "deferred"])
+def test_a_list_that_a_piece_gave_up_on_is_not_selected_from(ctx, call):
+    """One of a row's pieces gives up on the row's threshold, the others do not: what they list is more than the
+    budget, but the best rows are the ones that are missing.  Nine workgroups take runs of 64 blocks of two segments of
+    257 and 309 (and five each for a piece's fixed cost); the first segment's last block is a run's first piece,
+    over long before the threshold is out, and the 40 rows in it are the highest-scoring ones."""
+    lb = H.binding()
+    lens, k = [256 * 64 + 40, 309 * 64], 300
+    w = wl.scaled(wl.WORKLOADS["c1"], batch=2, n_q_heads=2, n_kv_heads=1, max_len=max(lens), k=k, planted=1)
+    mask = np.ones(2, np.uint8)
+    inp = wl.make_layer(w, mask=mask, lens=np.asarray(lens, np.int32), l_cap=max(lens))
+    best = slice(256 * 64, lens[0])
+    inp.k_cache[0, 0, best] = inp.q[0].float().sum(0).to(inp.k_cache.dtype)
+    ref = H.oracle_layer(inp, mask, k, None)
+    assert np.isin(np.arange(best.start, best.stop), ref[1][0, 0]).all()
+    dl = H.DeviceLayer(inp, k, None)
+    ws = lb.alloc_workspace(dl.shape, "cuda", n_layers=2)
+    before = ctx.wait_timeouts()
+    ctx.set_option(lb.OPT_N_WG, 12)
+    for polls in (1, 1 << 20):
+        _say("a piece without its threshold: %s polls=%d" % (call, polls))
+        ctx.set_option(lb.OPT_WAIT_POLLS, polls)
+        ws.fill_(0xFF)
+        dl.out.fill_(float("nan"))
+        dl.idx_out.fill_(-7)
+        fallbacks = sum(ctx.select_stats())
+        f = ctx.decode_attn_deferred if call == "deferred" else ctx.decode_attn
+        f(dl.shape, dl.q, dl.k_cache, dl.v_cache, mask, None, dl.out, dl.idx_out, dl.lengths, ws)
+        ctx.select_flush()
+        torch.cuda.synchronize()
+        H.assert_outputs_close(H.bf16_tensor_to_f64(dl.out), ref[0], "polls=%d" % polls)
+        assert (dl.idx_out.cpu().numpy() == ref[1]).all(), "polls=%d" % polls
+        if polls == 1:
+            gave_up = ctx.wait_timeouts()
+            assert gave_up > before and sum(ctx.select_stats()) > fallbacks
+        else:  # (the counter is back at zero, whatever was left in it)
+            assert ctx.wait_timeouts() == gave_up and sum(ctx.select_stats()) == fallbacks
+
+
 @pytest.mark.parametrize("lens,k,block", [
     ([61, 3001, 200, 1] * 20, 300, 1),       # runs that cross many short segments; set copies by every workgroup
     ([61, 3001, 200, 1] * 20, 5, 64),
