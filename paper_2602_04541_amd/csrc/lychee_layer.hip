@@ -112,8 +112,10 @@ __device__ __forceinline__ void await_set(ArgCommon &c, const uint32_t *flag, ui
 }
 
 // Before a workgroup at the end of the grid selects a row: until the row's pieces have counted in all of its
-// blocks.  Whether they have (false: it gave up).  The counter goes back to zero: here, or, marked by the
-// highest bit, by the piece that completes it later.
+// blocks.  Whether they have.  If it gives up it leaves the row, marked in the counter's highest bit, to the piece
+// that completes it, whose workgroup then selects it: whatever the select reads and puts back to zero (the
+// list and its counter, the pieces' log-sum-exps) is complete by then.  The counter goes back to zero here, or
+// there.
 constexpr uint32_t kNobodyWaits = 0x80000000u;
 __device__ __forceinline__ bool await_rows(ArgCommon &c, uint32_t *counter, uint32_t blocks, SharedLayer &pool)
 {
@@ -555,7 +557,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             const int b = uni(pool.at[0]), g = uni(pool.at[1]), pieces = uni(pool.at[4]);
             const uint32_t hmask = (uint32_t)uni(pool.at[2]);
             if (tid == 0) {
-                int last = 1;
+                int last = 1, selects = 1;
                 const bool awaited = kNow && !gather && A->n_tail > 0;  // by the workgroup that selects the row
                 if (pieces > 1 || awaited) {
                     uint32_t *counter = A->seg_count + (((int64_t)b * cc.n_kv_heads + g) * 2 + kind);
@@ -563,23 +565,25 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                     const uint32_t old = __hip_atomic_fetch_add((LYCHEE_GLOBAL uint32_t *)counter, mine, __ATOMIC_RELAXED,
                                                                 __HIP_MEMORY_SCOPE_AGENT);
                     last = (old & ~kNobodyWaits) + mine == (uint32_t)pool.at[9];
-                    if (last && (!awaited || old >= kNobodyWaits)) store_agent(counter, 0u);  // as every launch finds it
+                    selects = !awaited || old >= kNobodyWaits;
+                    if (last && selects) store_agent(counter, 0u);  // as every launch finds it
                 }
-                pool.flag = last;
+                // 2: and the row's set is this workgroup's (every candidate of the row is in its list)
+                pool.flag = !last ? 0 : (kNow && !gather && selects ? 2 : 1);
             }
             __syncthreads();
             // (only now: until the barrier a slower wavefront may still be reading where this piece lay, and
             // one that saw the next piece's place would merge, or not merge, another segment than the others)
             if (tid == 0) pool.run[0] = x + uni(pool.at[3]);
             if (pool.flag) {
-                if (pieces > 1 || (kNow && A->n_tail == 0)) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                if (pieces > 1 || (kNow && pool.flag == 2)) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                 if (pieces > 1) switch (__builtin_popcount(hmask)) {
                 case 1: combine_segment<1>(cc, cur, b, g, hmask, pieces, sh.comb); break;
                 case 2: combine_segment<2>(cc, cur, b, g, hmask, pieces, sh.comb); break;
                 case 3: combine_segment<3>(cc, cur, b, g, hmask, pieces, sh.comb); break;
                 default: combine_segment<4>(cc, cur, b, g, hmask, pieces, sh.comb); break;
                 }
-                if (kNow && !gather && A->n_tail == 0 && tid == 0) {  // every candidate of the row is in its list: its set can be selected
+                if (kNow && tid == 0 && pool.flag == 2) {
                     const int row = b * uni(pool.role[0][2]) + (int)desc_u8(dw, offsetof(LayerDesc, rindex) + g);
                     wanted[row >> 5] |= 1u << (row & 31);
                 }
@@ -592,8 +596,9 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
     }
 
     // ------------------------------------------------------------------ this layer's own sets
-    // The row of a workgroup at the end of the grid, or those of the segments that this one completed, after
-    // its last piece.  (Selected inside the piece loop they took registers from the streaming, which spilled.)
+    // The row of a workgroup at the end of the grid, or those of the segments that this one completed and that no
+    // such workgroup waits for, after its last piece.  (Selected inside the piece loop they took registers from the
+    // streaming, which spilled.)
     if (kNow) {
         __syncthreads();  // (a workgroup without pieces has passed no barrier since thread 0 left the roles)
         const LYCHEE_CONSTANT LayerLaunch *A = arg_of<LayerLaunch>();
@@ -609,11 +614,10 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             for (uint32_t rows = uni(wanted[i >> 5]); rows != 0; rows &= rows - 1u) {
                 const int row = i + __builtin_ctz(rows);
                 const int b = row / n_rseg, g = cur.rgroup[row % n_rseg];
-                bool complete = true;
-                if (own >= 0)
-                    complete = await_rows(c, A->seg_count + ((int64_t)b * c.n_kv_heads + g) * 2,
-                                          (uint32_t)(pool.len[b] + kBlockRows - 1) / kBlockRows, pool);
-                select_unit<true>(c, cur, b, g, sel, pool, A->thr_flags + row, pool.gen, complete);
+                if (own >= 0 && !await_rows(c, A->seg_count + ((int64_t)b * c.n_kv_heads + g) * 2,
+                                            (uint32_t)(pool.len[b] + kBlockRows - 1) / kBlockRows, pool))
+                    break;
+                select_unit<true>(c, cur, b, g, sel, pool, A->thr_flags + row, pool.gen);
                 __syncthreads();
             }
         }

@@ -926,11 +926,11 @@ __device__ __forceinline__ void copy_set_unit(ArgCommon &c, const LayerDesc &p, 
 // sparse heads of the group inherit.  PROB: the build that knows the probability rules (their
 // 64-bit mass arithmetic over register-resident entries would cost the plain build registers).
 // flag, gen: the row's threshold word and the generation, when the launch that streams the row
-// also selects for it.  complete: the row's list holds all of its candidates.
+// also selects for it.
 template <bool PROB, typename Pool>
 __device__ __forceinline__ void select_unit(ArgCommon &c, const LayerDesc &p, int b, int g,
                                             SharedSelect &sh, Pool &pool, const unsigned long long *flag = nullptr,
-                                            uint32_t gen = 0, bool complete = true)
+                                            uint32_t gen = 0)
 {
     const int64_t bg = (int64_t)b * c.n_kv_heads + g;
     int32_t *dst = p.idx_out + bg * c.k;
@@ -984,7 +984,7 @@ __device__ __forceinline__ void select_unit(ArgCommon &c, const LayerDesc &p, in
         lse = pooled_lse(c, p, row, count, pool);
     }
     int keep = n;  // what is selected in the end: n, or fewer under a probability rule
-    const bool usable = total >= n && total <= c.list_row && (complete || c.block_shift != 0);
+    const bool usable = total >= n && total <= c.list_row;
     if (PROB && by_prob && usable) {
         // (from memory, a few entries at a time: with the rules' 64-bit masses beside resident entries the
         // whole kernel spilled, and its threshold units took four times as long)

@@ -683,6 +683,35 @@ def test_a_list_that_a_piece_gave_up_on_is_not_selected_from(own_ctx, call):
             assert ctx.wait_timeouts() == gave_up and sum(ctx.select_stats()) == fallbacks
 
 
+@pytest.mark.parametrize("lens,k,block,rule,param", [
+    ([4096, 3000, 4000, 2500], 200, 1, 0, 0.0),      # rows whose threshold is known
+    ([20000, 9000], 500, 1, 0, 0.0),                 # and rows whose pieces give up on it too
+    ([4096, 3000, 4000, 2500], 200, 1, 1, 1e-3), ([20000, 9000], 500, 1, 2, 0.8),
+    ([20000, 9000, 131, 4096], 30, 64, 0, 0.0),
+])
+def test_rows_that_the_end_of_the_grid_gives_up_on(own_ctx, lens, k, block, rule, param):
+    """The workgroups at the end of the grid give up on their rows at once, and the pieces that complete the rows select
+    them: the oracle's sets, and the same from the next call, whose waits last, with nothing ranked whole in it."""
+    lb, ctx = H.binding(), own_ctx
+    w = wl.scaled(wl.WORKLOADS["c1"], batch=len(lens), n_q_heads=2, n_kv_heads=1, max_len=max(lens), k=k, planted=1)
+    mask = np.array([1, 0], np.uint8)
+    inp = wl.make_layer(w, mask=mask, lens=np.asarray(lens, np.int32), l_cap=max(lens))
+    idx_in = H.previous_layer_sets(inp, k, block=block)
+    ctx.set_option(lb.OPT_N_WG, 64)
+    for polls in (0, 1 << 20):
+        _say("rows given up on: B%d k=%d block=%d rule=%d polls=%d" % (len(lens), k, block, rule, polls))
+        ctx.set_option(lb.OPT_WAIT_POLLS, polls)
+        fallbacks = sum(ctx.select_stats())
+        if rule:
+            H.check_prob_rule_layer(ctx, inp, mask, k, rule, param, "polls=%d" % polls, idx_in)
+        else:
+            H.check_layer(ctx, inp, mask, k, idx_in, "polls=%d" % polls, exact_sets=True, block=block)
+        if polls == 0:
+            gave_up = ctx.wait_timeouts()
+            assert gave_up > 0
+    assert ctx.wait_timeouts() == gave_up and sum(ctx.select_stats()) == fallbacks
+
+
 @pytest.mark.parametrize("lens,k,block", [
     ([61, 3001, 200, 1] * 20, 300, 1),       # runs that cross many short segments; set copies by every workgroup
     ([61, 3001, 200, 1] * 20, 5, 64),
