@@ -19,11 +19,12 @@
  *     never read device memory from the host.  The layer calls (lychee_decode_attn,
  *     lychee_decode_attn_static, lychee_decode_attn_deferred, lychee_select_flush,
  *     lychee_dense_decode_attn) and the layer-after-layer steps enqueue kernel launches only,
- *     one per layer (two for a layer call of many short sequences under a probability rule, whose
- *     sets are selected behind the layer's launch), and never wait.  The phased steps and the cache append keep their layer
- *     descriptors in the arena: they enqueue one small asynchronous host-to-device copy when the
- *     call's pointers differ from those of earlier calls, and once the arena has seen about
- *     4 MiB of distinct tables such a call waits for the stream once and starts the arena over
+ *     one per layer (two for a layer call under a probability rule with more sets to select than a
+ *     quarter of the launch's workgroups: the second selects where the sequences are short or of
+ *     very unequal lengths, and else does nothing), and never wait.  The phased steps and the cache
+ *     append keep their layer descriptors in the arena: they enqueue one small asynchronous
+ *     host-to-device copy when the call's pointers differ from those of earlier calls, and once
+ *     the arena has seen about 4 MiB of distinct tables such a call waits for the stream once and starts the arena over
  *     - unless a stream capture has seen the arena: a captured graph keeps pointing into it, so
  *     its tables are never recycled and the call returns LYCHEE_EARENA instead.
  *   - bf16 means the upper 16 bits of an IEEE fp32.  Scores and accumulation are fp32;

@@ -80,7 +80,7 @@ struct lychee_ctx {
 namespace {
 
 // Layout of lychee_ctx::sync_dev
-constexpr size_t kSyncGen = 0, kSyncExit = 64;
+constexpr size_t kSyncGen = 0, kSyncExit = 64, kSyncApart = 128;
 constexpr size_t kSyncRows = (size_t)kMaxBatch * kMaxKvHeads;  // (sequence, KV head) pairs a shape can have
 constexpr size_t kSyncThr = 4096;                               // uint64 [kSyncRows]
 constexpr size_t kSyncSet = kSyncThr + kSyncRows * 8;           // uint32 [kSetFlagWords]
@@ -443,22 +443,25 @@ int32_t streamed_blocks(const lychee_shape &s, const LayerDesc &d)
     return d.n_rgroups * s.batch * ((s.max_len + kBlockRows - 1) / kBlockRows);
 }
 
-// Whether a plain layer call under a probability rule selects in a launch of its own.
-bool selects_apart(const lychee_ctx *ctx, const lychee_shape &s, const LayerDesc &d)
+// Whether a plain layer call under a probability rule selects in a launch of its own: 0 no, 1 yes, 2 on the
+// device it will turn out.
+int selects_apart(const lychee_ctx *ctx, const lychee_shape &s, const LayerDesc &d)
 {
-    return s.prob_rule != 0 && rules_apart(s.batch * d.n_rgroups, streamed_blocks(s, d), grid_of(ctx));
+    if (s.prob_rule == 0 || !rules_apart(s.batch * d.n_rgroups, 0, grid_of(ctx))) return 0;
+    return rules_apart(s.batch * d.n_rgroups, streamed_blocks(s, d), grid_of(ctx)) ? 1 : 2;
 }
 
 // One launch of lychee_layer_kernel: everything `cur`'s output needs (cur may be null: only the
 // pending select), with the select and set copies of `prev` (may be null) among its front units.
 // plain: `cur`'s own sets are wanted with the call (then `prev` is null): from this launch, or, where
-// selects_apart says so, from one that the caller enqueues behind it.
+// selects_apart says so, from one that the caller enqueues behind it.  pair: one of two launches of which the
+// first decides who selects.
 // Every check happens before the launch; nothing else is enqueued.
 int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, const int32_t *lengths,
-                 const LayerDesc *cur, const LayerDesc *prev, hipStream_t stream, bool plain = false)
+                 const LayerDesc *cur, const LayerDesc *prev, hipStream_t stream, bool plain = false, bool pair = false)
 {
     if (cur == nullptr && prev == nullptr) return LYCHEE_OK;
-    const bool select_now = plain && !selects_apart(ctx, s, *cur);
+    const bool select_now = plain && selects_apart(ctx, s, *cur) != 1;
     LayerLaunch p;
     memset(&p, 0, sizeof p);
     const int W = grid_of(ctx);
@@ -500,6 +503,7 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
         p.front = FrontPlan{p.c.n_wg, 0};
     }
     p.lead_blocks = ctx->select_lead;
+    if (pair) p.apart = reinterpret_cast<uint32_t *>(ctx->sync_dev + kSyncApart);
     p.gen = reinterpret_cast<uint32_t *>(ctx->sync_dev + kSyncGen);
     p.exit_count = reinterpret_cast<uint32_t *>(ctx->sync_dev + kSyncExit);
     p.thr_flags = reinterpret_cast<unsigned long long *>(ctx->sync_dev + kSyncThr);
@@ -699,8 +703,10 @@ int decode_attn(lychee_ctx *ctx, const lychee_shape *shape, const void *q, const
     if ((rc = check_layer_space(*shape, d)) != LYCHEE_OK) return rc;
     // idx_out is complete when the call's work is: the launch selects as its segments complete, or a
     // second one selects all of its rows.
-    if ((rc = layer_launch(ctx, *shape, w, lengths, &d, nullptr, stream, true)) != LYCHEE_OK) return rc;
-    return selects_apart(ctx, *shape, d) ? layer_launch(ctx, *shape, w, lengths, nullptr, &d, stream) : LYCHEE_OK;
+    const int apart = selects_apart(ctx, *shape, d);
+    if ((rc = layer_launch(ctx, *shape, w, lengths, &d, nullptr, stream, true, apart == 2)) != LYCHEE_OK || apart == 0) return rc;
+    if (apart == 2) d.copy_keep = 0;  // (copied by the first launch)
+    return layer_launch(ctx, *shape, w, lengths, nullptr, &d, stream, false, apart == 2);
 }
 
 }  // namespace

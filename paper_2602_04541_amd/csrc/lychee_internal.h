@@ -149,6 +149,8 @@ struct LayerLaunch {
     int32_t lead_blocks;   // blocks of 64 rows the device streams while a select runs: how much
                            // later than the streaming the gated gathers can start
     uint64_t gate_mask;    // bit g: KV head g's inherited set is written by this launch's front units
+    uint32_t *apart;       // nullptr, or the launch is one of a pair: the first leaves here whether it leaves its
+                           // rows to the second (rows_in_turn)
     uint32_t *gen;         // the generation (read at the start, advanced at the end)
     uint32_t *exit_count;  // workgroups that have finished
     unsigned long long *thr_flags;  // [B * n_rgroups] {generation, threshold} of cur's score rows

@@ -86,6 +86,14 @@ __device__ __forceinline__ int all_blocks(const int32_t *len, int batch)
     return __builtin_amdgcn_readlane((int)wave_scan(n), 63);
 }
 
+// Whether the rows of this launch are left to the launch behind it (rows_in_turn).
+__device__ __forceinline__ bool selects_apart(const SharedLayer &pool, int batch)
+{
+    uint32_t least = ~0u;
+    for (int b = fresh_tid() & 63; b < batch; b += 64) least = min(least, pool.nb[0][b]);
+    return rows_in_turn(uni(pool.role[0][3]), uni(pool.role[0][1]), uni((int)wave_min(least)));
+}
+
 // A front unit has written the set of (b, g), with write-through stores: once every wavefront's
 // stores have completed the set is in device memory, and the flag says so.
 __device__ __forceinline__ void publish_set(uint32_t *flag, uint32_t gen)
@@ -162,6 +170,9 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
     const int w = blockIdx.x;
     const int W = c.n_wg;
     const int tid = fresh_tid();
+    // The second launch of a pair whose first one selected its rows itself: nothing is left to do, and as it
+    // leaves no flags the generation may stay.
+    if (SELECTS == 2 && A->apart != nullptr && uni(load_agent(A->apart)) == 0u) return;
 
     // The generation is only ever used by thread 0 (it sets, polls and advances the flags), which
     // keeps it in a register: the load is not waited for before its first use, late in the launch.
@@ -606,11 +617,16 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
         const int n_rseg = uni(pool.role[0][2]);
         const int n_rows = c.batch * n_rseg;
         const int own = A->n_tail > 0 ? w - (W - A->n_tail) : -1;
+        bool apart = false;
+        if (A->apart != nullptr) {
+            apart = selects_apart(pool, c.batch);
+            if (w == 0 && tid == 0) store_agent(A->apart, apart ? 1u : 0u);
+        }
         if (own >= 0) {
             if (tid == 0) wanted[own >> 5] = 1u << (own & 31);
             __syncthreads();
         }
-        for (int i = 0; i < n_rows; i += 32) {
+        for (int i = 0; i < n_rows && !apart; i += 32) {
             for (uint32_t rows = uni(wanted[i >> 5]); rows != 0; rows &= rows - 1u) {
                 const int row = i + __builtin_ctz(rows);
                 const int b = row / n_rseg, g = cur.rgroup[row % n_rseg];

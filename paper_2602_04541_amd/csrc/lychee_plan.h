@@ -84,14 +84,29 @@ LYCHEE_HD inline int32_t tail_selects(int32_t rows, int32_t r_blocks, int32_t n_
 }
 
 // Whether a plain layer call under a probability rule selects in a second launch, a workgroup per row, instead of in
-// its own.  A select with a rule takes up to 15 us, and of more rows than a quarter of the workgroups some complete
+// its own.  r_blocks: blocks of 64 rows that the launch streams at most, by the cache's capacity.  A select with a rule takes up to 15 us, and of more rows than a quarter of the workgroups some complete
 // several and select them in turn; a streaming of more than 32 blocks a workgroup hides that.  us a call
 // in one launch and in two, 64 sequences of four retrieval heads, Top-p: of 1/3 to 1024 rows 66 and 57, 61 to 3001 rows
 // (in 4096) 106 and 92, 1/3 to 6000 142 and 165; a Threshold, 61 to 1001 rows 58 and 51; 32 sequences of 1/3 to
-// 1000 rows, Top-p, 41 and 44.
+// 1000 rows, Top-p, 41 and 44.  (Not the faster side everywhere: 64 of 1000 to 3000 in 3000 95 and 102.)
 LYCHEE_HD inline bool rules_apart(int32_t rows, int32_t r_blocks, int32_t n_wg)
 {
     return 4 * rows > n_wg && r_blocks <= 32 * n_wg;
+}
+
+// The same where the cache's capacity does not bound the streaming (r_blocks above is by the capacity, which says
+// nothing about what lies far below it): both launches are enqueued, the first one decides by the sequences'
+// lengths, and the second returns at once if nothing is left to it (2 us).  r_blocks: what the n_wg streaming
+// workgroups take; shortest: blocks of the shortest segment; both with the blocks that a segment counts beyond
+// those it has.  Rows are selected in turn where a workgroup's run holds several segments, so: where it holds more
+// than two of the shortest.  us a call selected by the first launch and by the second, Top-p, three score rows a
+// sequence (blocks of a run over the shortest segment's): 64 sequences of 2000 to 5000 rows (1.3) 121 and 138, 1000
+// to 3000 (1.7) 98 and 111, 800 to 2400 (1.8) 96 and 104, 500 to 2000 (2.3) 100 and 95, 61 to 3001 (5) 116 and
+// 103, 61 to 6000 (7) 130 and 131, 61 to 12000 (11) 208 and 185; 128 of 300 to 1000 (4) 123 and 110; 256 of 61 to
+// 1000 (12) 228 and 187; 128 of 1000 to 3000 (3.4) 178 and 186.
+LYCHEE_HD inline bool rows_in_turn(int32_t r_blocks, int32_t n_wg, int32_t shortest)
+{
+    return r_blocks > 2 * shortest * n_wg;
 }
 
 // Rows one threshold unit samples in one round of loads.

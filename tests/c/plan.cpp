@@ -28,3 +28,8 @@ extern "C" int32_t rules_apart(int32_t rows, int32_t r_blocks, int32_t n_wg)
 {
     return lychee::rules_apart(rows, r_blocks, n_wg);
 }
+
+extern "C" int32_t rows_in_turn(int32_t r_blocks, int32_t n_wg, int32_t shortest)
+{
+    return lychee::rows_in_turn(r_blocks, n_wg, shortest);
+}

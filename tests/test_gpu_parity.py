@@ -1212,6 +1212,27 @@ def test_probability_rules_beside_the_lines_between_their_routes(ctx, lens, n_wg
         H.check_prob_rule_layer(ctx, inp, mask, w.k, rule, param, "n_wg=%d" % n, idx_in)
 
 
+@pytest.mark.parametrize("lens,rule,param", [([1000, 1, 900, 1000, 64, 950], 2, 0.8), ([1000, 1, 900, 1000, 64, 950], 1, 1e-3),
+                                             ([5000, 4097, 4700, 5000, 4999, 4160], 2, 0.8)])
+def test_where_a_rules_rows_are_selected_in_a_cache_of_many_times_their_length(own_ctx, lens, rule, param):
+    """Twelve rows on 24 workgroups in a cache whose capacity says nothing about them.  Of the first lengths a workgroup's
+    run holds several segments, and the second launch selects; of the other ones the first does, and the second
+    finds nothing to do.  The same launches, and the oracle's sets, twice with either."""
+    lb, ctx = H.binding(), own_ctx
+    ctx.set_option(lb.OPT_N_WG, 24)
+    ctx.timing_enable(True)
+    w = wl.scaled(wl.WORKLOADS["c1"], batch=len(lens), max_len=9000, k=100, planted=1)
+    mask = np.tile(np.array([1, 0, 1, 0], np.uint8), w.n_q_heads // 4)
+    inp = wl.make_layer(w, mask=mask, lens=np.asarray(lens, np.int32), l_cap=w.max_len)
+    idx_in = H.previous_layer_sets(inp, w.k)
+    for i in range(2):
+        _say("rule %d, up to %d rows in a cache of %d" % (rule, max(lens), w.max_len))
+        H.check_prob_rule_layer(ctx, inp, mask, w.k, rule, param, "call %d" % i, idx_in)
+        n = ctx.timing_read()[1]
+        assert (n[lb.KERNEL_STREAM], n[lb.KERNEL_SELECT], sum(n)) == (1, 1, 2), n
+    assert ctx.wait_timeouts() == 0
+
+
 @pytest.mark.parametrize("L,k", [(3000, 2000), (9000, 5000), (50000, 2000)])
 def test_top_p_crosses_its_mass_among_equal_keys(ctx, L, k):
     """More equal keys than are looked at one by one hold the position where the mass is reached: the rest of

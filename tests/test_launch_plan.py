@@ -125,3 +125,9 @@ def test_rules_select_apart_where_many_rows_end_a_short_streaming(plan):
     for rows, r_blocks, n_wg, apart in ((128, 64, 512, 0), (129, 129, 512, 1), (129, 16384, 512, 1), (129, 16385, 512, 0),
                                         (16384, 2 ** 30, 512, 0), (1, 1, 4, 0), (1, 1, 3, 1)):
         assert plan.rules_apart(rows, r_blocks, n_wg) == apart
+
+
+def test_rules_select_behind_a_launch_whose_runs_hold_several_short_rows(plan):
+    for r_blocks, n_wg, shortest, apart in ((188, 13, 6, 1), (156, 13, 6, 0), (157, 13, 6, 1), (942, 17, 70, 0), (0, 1, 6, 0),
+                                            (2 ** 31 - 1, 768, 2 ** 18 + 5, 1), (2 * 768 * (2 ** 18 + 5), 768, 2 ** 18 + 5, 0)):
+        assert plan.rows_in_turn(r_blocks, n_wg, shortest) == apart
