@@ -332,29 +332,16 @@ __device__ __forceinline__ T *desc_ptr(const uint32_t *dw, size_t off)
     return reinterpret_cast<T *>(lo | (hi << 32));
 }
 
-// a / b for 0 <= a < 2^31 - b, 0 < b < 2^24.  A workgroup divides a dozen times before its first load; the compiler's
-// 32-bit division is about 25 dependent instructions.  The rounded product is off by at most 2^-22 of itself,
-// so the remainder's quotient, below 2^10 either way, is at most one off.  No branches.
+// a / b (quot_by).  A workgroup divides a dozen times before its first load; the compiler's 32-bit division is about
+// 25 dependent instructions.
 __device__ __forceinline__ int quot(int a, int b)
 {
-    const float inv = __builtin_amdgcn_rcpf((float)b);
-    int q = (int)((float)a * inv);
-    q += (int)((float)(a - q * b) * inv);
-    const int r = a - q * b;
-    q += r >= b ? 1 : 0;
-    q -= r < 0 ? 1 : 0;
-    return q;
+    return quot_by(a, b, __builtin_amdgcn_rcpf((float)b), [](uint32_t v) { return v; });
 }
 // The same of values that are the same in every lane: scalar arithmetic but for the product.
 __device__ __forceinline__ int quot_uni(int a, int b)
 {
-    const float inv = __builtin_amdgcn_rcpf((float)b);
-    int q = __builtin_amdgcn_readfirstlane((int)((float)a * inv));
-    q += __builtin_amdgcn_readfirstlane((int)((float)(a - q * b) * inv));
-    const int r = a - q * b;
-    q += r >= b ? 1 : 0;
-    q -= r < 0 ? 1 : 0;
-    return q;
+    return quot_by(a, b, __builtin_amdgcn_rcpf((float)b), [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); });
 }
 
 // Largest i in [0, n) with pre[i] <= x, for a non-decreasing pre[0..n] with pre[0] <= x < pre[n].

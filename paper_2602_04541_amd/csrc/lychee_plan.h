@@ -11,6 +11,19 @@
 
 namespace lychee {
 
+// a / b for 0 <= a < 2^31 - b, 0 < b < 2^24, from `inv`, the reciprocal of b to one unit in its last place.  The
+// product is off by at most 2^-22 of itself, so the remainder lies within 512 + b of zero, and what its
+// quotient adds is at most one off.  (Unsigned up to there: q * b may pass 2^31.)  No branches.  u: what the
+// caller does with a value that was computed in single precision.
+template <typename U>
+LYCHEE_HD inline int32_t quot_by(int32_t a, int32_t b, float inv, U u)
+{
+    uint32_t q = u((uint32_t)((float)a * inv));
+    q += u((uint32_t)(int32_t)((float)(int32_t)((uint32_t)a - q * (uint32_t)b) * inv));
+    const int32_t r = (int32_t)((uint32_t)a - q * (uint32_t)b);
+    return (int32_t)(q + (r >= b ? 1u : 0u) - (r < 0 ? 1u : 0u));
+}
+
 // Capacity, in entries, of one score row's candidate list.  A threshold unit aims at n = min(k, L)
 // candidates plus six standard deviations of its sample (a few thousand at the usual sizes),
 // and makes every row a candidate when L <= kDirectLen or L <= 2k.  A list that still

@@ -1,4 +1,6 @@
 /* The library's layout functions behind C names, for tests/test_launch_plan.py. */
+#include <cmath>
+
 #include "lychee_plan.h"
 
 extern "C" void front_plan(int32_t selects, int32_t copies, int32_t thresholds, int32_t gated, int32_t r_blocks, int32_t n_wg,
@@ -32,4 +34,12 @@ extern "C" int32_t rules_apart(int32_t rows, int32_t r_blocks, int32_t n_wg)
 extern "C" int32_t rows_in_turn(int32_t r_blocks, int32_t n_wg, int32_t shortest)
 {
     return lychee::rows_in_turn(r_blocks, n_wg, shortest);
+}
+
+// (ulps: how far the reciprocal is off)
+extern "C" int32_t quot(int32_t a, int32_t b, int32_t ulps)
+{
+    float inv = 1.0f / (float)b;
+    if (ulps) inv = std::nextafter(inv, ulps > 0 ? 2.0f : 0.0f);
+    return lychee::quot_by(a, b, inv, [](uint32_t v) { return v; });
 }

@@ -131,3 +131,19 @@ def test_rules_select_behind_a_launch_whose_runs_hold_several_short_rows(plan):
     for r_blocks, n_wg, shortest, apart in ((188, 13, 6, 1), (156, 13, 6, 0), (157, 13, 6, 1), (942, 17, 70, 0), (0, 1, 6, 0),
                                             (2 ** 31 - 1, 768, 2 ** 18 + 5, 1), (2 * 768 * (2 ** 18 + 5), 768, 2 ** 18 + 5, 0)):
         assert plan.rows_in_turn(r_blocks, n_wg, shortest) == apart
+
+
+def test_quotients_are_exact_over_their_whole_range(plan):
+    """Around multiples of the divisor, where a rounded quotient goes wrong first, and at the top of the range, where the
+    product of quotient and divisor passes 2^31; with reciprocals that are one unit in the last place off either way."""
+    rng = random.Random(8)
+    divisors = [1, 2, 3, 5, 7, 48, 64, 511, 512, 1000, 4097, 65535, 2 ** 20 + 1, 2 ** 23 - 1, 2 ** 24 - 1]
+    divisors += [int(2 ** rng.uniform(0, 24)) for _ in range(150)]
+    for b in divisors:
+        top = 2 ** 31 - b - 1
+        near = [0, b, 2 ** 22, 2 ** 24, 2 ** 30, top] + [int(2 ** rng.uniform(0, 31)) for _ in range(20)]
+        for n in near:
+            for a in (n - n % b - 1, n - n % b, n - n % b + 1, n - n % b + b - 1, n):
+                if 0 <= a <= top:
+                    for ulps in (-1, 0, 1):
+                        assert plan.quot(a, b, ulps) == a // b, (a, b, ulps)
