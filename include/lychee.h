@@ -330,10 +330,12 @@ int lychee_validate_idx(lychee_ctx *ctx, const lychee_shape *shape, const int32_
 int lychee_select_stats(lychee_ctx *ctx, int64_t *too_few, int64_t *too_many, void *hip_stream);
 
 /* Debug helper (synchronous): how many bounded waits inside layer launches have given up since the
- * context was created (a piece waiting for its row's threshold, a gather waiting for its set).
- * It stays 0 unless the device cannot keep a launch's workgroups resident together; a piece that
- * gives up on a threshold costs time only (its row is ranked whole), a gather that gives up on a
- * set reads the set as it is. */
+ * context was created (a piece waiting for its row's threshold, a gather waiting for its set, a
+ * workgroup at the end of the grid waiting for the row it selects).
+ * It stays 0 unless the device cannot keep a launch's workgroups resident together.  A piece that
+ * gives up on a threshold costs time only (its row is ranked whole, and counted as too_many above),
+ * and so does a workgroup that gives up on its row (the piece that completes the row selects it); a
+ * gather that gives up on a set reads the set as it is. */
 int lychee_wait_timeouts(lychee_ctx *ctx, int64_t *timeouts, void *hip_stream);
 
 /* Per-launch timing with HIP events on the caller's stream.  While enabled, every launch of

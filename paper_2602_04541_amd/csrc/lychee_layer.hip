@@ -26,9 +26,11 @@
 //                beside the merge that follows (tail_selects); where the rows are too many for that, the
 //                workgroup that completed a segment selects its set after its last piece
 //
-// Waiting is safe because workgroups are dispatched in index order and every wait is for lower ones: pieces
-// wait for front units, which never wait and have, where anything waits, the lowest indices to themselves
-// (front_plan); selects at the end of the grid wait for pieces.  Waits are bounded all the same.
+// Waiting is safe because every XCD starts its workgroups in index order and every wait is for a kind of workgroup
+// that comes earlier on all of them: pieces wait for front units, which never wait and have, where anything waits,
+// the lowest indices to themselves (front_plan); selects at the end of the grid wait for pieces.  That holds for a
+// launch by itself; launches of several streams that start at the same time share the places in an order that
+// nothing here fixes.  Waits are bounded: one that gives up on a threshold or on a row costs time only.
 // Partials cross from one XCD's L2 to another's without the agent-scope release fence (its
 // write-back of the whole L2, executed by every workgroup, costs more than the layer): they are
 // written with write-through stores, the writer waits until those have completed before it

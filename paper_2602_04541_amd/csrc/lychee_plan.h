@@ -50,10 +50,12 @@ struct FrontPlan {
 // that its selects and copies write; r_blocks: blocks of 64 rows that the launch streams, by the sequences'
 // lengths (a capacity far above the lengths says nothing about them).
 //
-// Pieces wait for thresholds and for gated sets, and nothing else in a launch waits.  Workgroups start in
+// Pieces wait for thresholds and for gated sets, selects at the end of the grid (tail_selects) for pieces, and
+// nothing else in a launch waits.  Workgroups are dealt to the XCDs in turn, every XCD starts its own in
 // index order, and not all of them at once if the grid is larger than what fits the chip beside
 // whatever else runs there.  So where something waits, the front units have workgroups to themselves,
-// the lowest: those never wait, so that whatever a piece waits for has started before it and will end.
+// the lowest: those never wait, so that they end on every XCD whatever holds its other places; then
+// the pieces, ahead of the selects on every XCD, do.
 // (Copies dealt over the whole grid, whose workgroups then went on to gated gathers, needed every
 // workgroup of the grid resident at once: the started ones would wait for copies of the others.)
 // Fewer than eight workgroups are always resident together, and too few to set any aside.
@@ -84,7 +86,7 @@ LYCHEE_HD inline FrontPlan front_plan(int32_t selects, int32_t copies, int32_t t
 
 // Workgroups at the end of a grid of n_wg that select the launch's own score rows, one each: `rows`, or 0
 // (the workgroup that completes a segment then selects its set after its last piece).  They wait for the
-// rows' pieces, which lie on lower workgroups, so whatever they wait for has started.
+// rows' pieces, which lie on lower workgroups: on every XCD those have started before one of these does.
 // Selecting there begins when a row's last piece has counted itself in, beside the merge of its partials, which
 // takes 4 us.  What it costs is the streaming that these workgroups would have done, rows / n_wg of 5.5 ns a
 // block: up to 1/64 of it at any length, or up to 1/16 where that is no more than 1.5 us.  us a call, selected after the
@@ -125,7 +127,10 @@ LYCHEE_HD inline bool rows_in_turn(int32_t r_blocks, int32_t n_wg, int32_t short
 // Rows one threshold unit samples in one round of loads.
 constexpr int32_t kAloneSample = 512;
 // Whether a score row's threshold is taken by one unit from one round of loads (512 rows) instead of by four from
-// 1024 to 4096.  r_blocks: blocks of 64 rows that the launch streams.
+// 1024 to 4096.  r_blocks: blocks of 64 rows that the launch would stream if every sequence were as long as this one
+// (what it does stream would take a sum over the batch in every unit; in a ragged batch a short row's
+// threshold may so be taken by one unit behind a long streaming, from fewer samples, which costs the select up to
+// what its registers hold).
 // The four hand their keys to the one that ranks them through device memory: stores, a counter, loads, each of which takes about
 // 2 us beside the streaming's first loads, so that the threshold is out after 14 us, and a piece of a short
 // launch is done with its rows after 12.  From fewer samples the threshold lets more rows through for the same

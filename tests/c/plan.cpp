@@ -43,3 +43,8 @@ extern "C" int32_t quot(int32_t a, int32_t b, int32_t ulps)
     if (ulps) inv = std::nextafter(inv, ulps > 0 ? 2.0f : 0.0f);
     return lychee::quot_by(a, b, inv, [](uint32_t v) { return v; });
 }
+
+extern "C" int32_t threshold_alone(int32_t n, int32_t L, int32_t r_blocks, int32_t n_wg, float margin, int32_t fits)
+{
+    return lychee::threshold_alone(n, L, r_blocks, n_wg, margin, fits);
+}

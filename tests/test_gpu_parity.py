@@ -9,6 +9,7 @@ import torch
 from oracle import lychee_oracle as lo
 from paper_2602_04541_amd import workloads as wl
 from tests import gpu_harness as H
+from tests.test_launch_plan import plan  # noqa: F401  (a fixture: the rules that lay out a launch)
 
 pytestmark = pytest.mark.gpu
 
@@ -622,13 +623,19 @@ def test_pieces_filter_their_keys_at_the_edges_of_a_wavefronts_share(ctx, n_wg, 
     assert ctx.wait_timeouts() == 0
 
 
-@pytest.mark.parametrize("lens,Hkv,k,block,n_wg", [
-    ([4099], 4, 300, 1, 64), ([4099], 5, 300, 1, 64), ([4099], 4, 300, 1, 63),  # rows beside the grid: selected at its end or not
-    ([700, 65, 1, 64], 8, 40, 1, 0), ([700, 65, 1] * 11, 1, 40, 1, 0),          # 32 and 33 rows; segments of one piece
-    ([40000] * 2, 4, 900, 1, 64), ([40000], 1, 900, 1, 64),                     # streaming too long for four rows' workgroups
-    ([65], 8, 200, 1, 0), ([9000, 63, 130], 2, 9, 64, 0),                       # the set is everything; blocks
+@pytest.mark.parametrize("lens,Hkv,k,block,n_wg,tail", [
+    # four and five rows on 64 workgroups, four on 63
+    ([4099], 4, 300, 1, 64, 4), ([4099], 5, 300, 1, 64, 0), ([4099], 4, 300, 1, 63, 0),
+    # 32 and 33 rows; segments of one piece
+    ([700, 65, 1, 64], 8, 40, 1, 0, 32), ([700, 65, 1] * 11, 1, 40, 1, 0, 0),
+    # too many rows; one row, at any length
+    ([40000] * 2, 4, 900, 1, 64, 0), ([40000], 1, 900, 1, 64, 1),
+    # four rows whose streaming is short enough for that, and one block too long
+    ([65536], 4, 900, 1, 64, 4), ([65537], 4, 900, 1, 64, 0),
+    # the set is everything; blocks
+    ([65], 8, 200, 1, 0, 8), ([9000, 63, 130], 2, 9, 64, 0, 6),
 ])
-def test_layer_calls_whose_rows_are_selected_at_the_end_of_the_grid(ctx, lens, Hkv, k, block, n_wg):
+def test_layer_calls_whose_rows_are_selected_at_the_end_of_the_grid(ctx, plan, lens, Hkv, k, block, n_wg, tail):
     """On both sides of the rule that gives a launch's score rows workgroups of their own: the oracle's sets, twice
     in a row (the second call finds the counters as the first left them)."""
     lb = H.binding()
@@ -636,6 +643,9 @@ def test_layer_calls_whose_rows_are_selected_at_the_end_of_the_grid(ctx, lens, H
     inp = wl.make_layer(w, mask=np.tile(np.array([1, 0], np.uint8), Hkv), lens=np.asarray(lens, np.int32), l_cap=max(lens))
     idx_in = H.previous_layer_sets(inp, k, block=block)
     _say("selects at the end: B%d rows=%d k=%d block=%d n_wg=%d" % (len(lens), len(lens) * Hkv, k, block, n_wg))
+    rows = len(lens) * Hkv   # (the default grid is two workgroups per compute unit)
+    grid = n_wg or 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    assert plan.tail_selects(rows, rows * -(-max(lens) // 64), grid) == tail
     ctx.set_option(lb.OPT_N_WG, n_wg)
     dl, out, idx, _, _, _ = H.check_layer(ctx, inp, inp.mask, k, idx_in, exact_sets=True, block=block)
     dl.out.fill_(float("nan"))

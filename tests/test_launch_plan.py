@@ -45,6 +45,31 @@ def gets_stuck(n_front, n_aside, n_wg, resident):
     return False
 
 
+def gets_stuck_on_xcds(n_aside, n_tail, n_wg, resident, n_xcd):
+    """The workgroups are dealt to the XCDs in turn, and every XCD starts its own in index order as its places come free,
+    however far the others are.  Those below n_aside run their units and leave; the last n_tail wait until all
+    pieces are done; the others have the pieces, which wait (the worst case) until all units are done."""
+    queue = [list(range(x, n_wg, n_xcd)) for x in range(n_xcd)]
+    held = [[] for _ in range(n_xcd)]
+    units, pieces = n_aside, n_wg - n_aside - n_tail      # workgroups of each kind that have not ended
+    while True:
+        moved = False
+        for x in range(n_xcd):
+            while queue[x] and len(held[x]) < resident:
+                held[x].append(queue[x].pop(0))
+            for w in list(held[x]):
+                if w < n_aside:
+                    units -= 1
+                elif w < n_wg - n_tail and units == 0:
+                    pieces -= 1
+                elif w < n_wg - n_tail or pieces:
+                    continue
+                held[x].remove(w)
+                moved = True
+        if not moved:
+            return any(queue) or any(held)
+
+
 def layers(rng):
     """What consecutive layers of a call bring: (selects, copies, thresholds, gated, blocks streamed)."""
     batch = rng.choice([1, 2, 3, 8, 64, 100, 256])
@@ -70,6 +95,23 @@ def test_no_piece_waits_for_a_workgroup_that_may_not_have_started(plan):
                 continue
             for resident in {min(n_wg, r) for r in (7, 8, 100, 256, 512)}:
                 assert not gets_stuck(n_front, n_aside, n_wg, resident), (case, n_wg, resident, n_front, n_aside)
+
+
+def test_no_workgroup_waits_for_one_that_its_xcd_cannot_start(plan):
+    """Units in front, pieces, and selects at the end of the grid that wait for all pieces, also where the XCDs hold far
+    fewer workgroups than the grid has."""
+    rng = random.Random(9)
+    with_tail = 0
+    for case in [layers(rng) for _ in range(60)]:
+        _, _, thresholds, _, r_blocks = case
+        for n_wg in (8, 37, 64, 512, 768):
+            tail = plan.tail_selects(thresholds // 4, r_blocks, n_wg)
+            with_tail += tail > 0
+            _, n_aside = front_plan(plan, 0, case[1], thresholds, False, r_blocks, n_wg)
+            assert n_aside + tail < n_wg and (n_aside > 0 or thresholds == 0)   # (what pieces wait for waits for nothing)
+            for n_xcd, resident in ((8, 1), (8, 2), (8, 64), (1, 1), (1, 100)):
+                assert not gets_stuck_on_xcds(n_aside, tail, n_wg, resident, n_xcd), (case, n_wg, n_xcd, resident)
+    assert with_tail > 20
 
 
 def test_copies_that_nothing_waits_for_are_done_on_the_way(plan):
@@ -147,3 +189,17 @@ def test_quotients_are_exact_over_their_whole_range(plan):
                 if 0 <= a <= top:
                     for ulps in (-1, 0, 1):
                         assert plan.quot(a, b, ulps) == a // b, (a, b, ulps)
+
+
+def test_one_unit_takes_a_threshold_where_the_launch_is_short_and_the_rest_fits_registers(plan):
+    fits = 32 * 256
+    for n, L, r_blocks, n_wg, margin, alone in ((2048, 32768, 1536, 512, 6.0, 1), (2048, 32768, 2560, 512, 6.0, 1),
+                                                (2048, 32768, 2561, 512, 6.0, 0), (3900, 32768, 1536, 512, 6.0, 1),
+                                                (4000, 32768, 1536, 512, 6.0, 0), (3900, 32768, 1536, 512, 60.0, 0),
+                                                (1, 20000, 320, 64, 6.0, 1), (1, 20000, 321, 64, 6.0, 0),
+                                                (1, 1 << 24, 0, 512, 6.0, 0)):
+        got = plan.threshold_alone(n, L, r_blocks, n_wg, ctypes.c_float(margin), fits)
+        assert got == alone, (n, L, r_blocks, n_wg, margin)
+        if got:   # what reaches the threshold, for f of the n best among 512 sampled rows, with a tenth to spare
+            f = n * 512 / L
+            assert (f + margin * f ** 0.5 + 6) * L / 512 <= 0.9 * fits * (1 + 1e-5)
