@@ -134,7 +134,7 @@ struct LaunchPlan {
 //   combine       the workgroup that writes the last partial of a (sequence, KV head, kind)
 //                 segment merges the segment's partials into `out`
 //   own select    in the build that selects for its own layer: by the last n_tail workgroups, a score row each,
-//                 or by whoever completed the row's segment; cur's kept sets are copied by front units
+//                 or by whoever completed the row's segment (see `apart`); cur's kept sets are copied by front units
 // Flags carry the launch's generation, a counter in device memory that the last workgroup to
 // finish advances: a flag of an earlier launch, or of an earlier replay of a captured launch,
 // never matches.

@@ -24,7 +24,8 @@
 //   own select   in the build for calls that want their sets at once: the last workgroups of the grid
 //                select, one score row each, as soon as the row's pieces have counted themselves in and
 //                beside the merge that follows (tail_selects); where the rows are too many for that, the
-//                workgroup that completed a segment selects its set after its last piece
+//                workgroup that completed a segment selects its set after its last piece, or, under a
+//                probability rule, the launch behind this one does (rules_apart, rows_in_turn)
 //
 // Waiting is safe because every XCD starts its workgroups in index order and every wait is for a kind of workgroup
 // that comes earlier on all of them: pieces wait for front units, which never wait and have, where anything waits,

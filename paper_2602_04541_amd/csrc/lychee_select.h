@@ -235,10 +235,12 @@ __device__ __forceinline__ float tile_pooled_score(const uint4 (&kr)[4], const u
 // checks the candidate count and ranks the whole row itself when the list cannot be used.
 // The sample is one row at a hashed offset inside each of 1024 to 4096 equal strata, as many as let 128
 // sampled rows be expected among the top n: the threshold then lets through about 1.6 n rows,
-// which a select of n = 4096 holds in registers.
+// which a select of n = 4096 holds in registers.  (512 strata where one unit takes the threshold of a short
+// launch for itself, see threshold_alone: more rows get through.)
 //
 // Latency bounds it (the row's streaming pieces wait for it at the end of their rows): one round
-// of row loads, a hand-over, one round of key loads, two levels of bins.
+// of row loads, a hand-over (but for threshold_alone), one round of key loads, one level of bins (two or more where
+// the target lies 16 octaves below the largest key).
 // `publish` != nullptr (launches whose streaming runs beside this unit): the threshold goes, with
 // the launch's generation `gen` in the upper half, into *publish by one 64-bit atomic store, which
 // the row's pieces poll; the candidate counter is not touched (it is zero between uses, and the
