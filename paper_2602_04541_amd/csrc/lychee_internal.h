@@ -107,7 +107,7 @@ struct LayerDesc {
 
 // Kernel argument: the layer ranges [first, first + count) of each unit kind.
 struct LaunchPlan {
-    Common c;
+    Common c;              // (first: the units read it without knowing which launch they are in)
     const LayerDesc *layers;
     int32_t r_first, r_count;    // retrieval streaming
     int32_t g_first, g_count;    // sparse gather
@@ -139,7 +139,7 @@ struct LaunchPlan {
 // finish advances: a flag of an earlier launch, or of an earlier replay of a captured launch,
 // never matches.
 struct LayerLaunch {
-    Common c;
+    Common c;              // (first, as above)
     LayerDesc cur;         // the layer whose rows are streamed and gathered (has_cur)
     LayerDesc prev;        // the layer whose select is pending (has_prev)
     int32_t has_cur, has_prev;

@@ -126,11 +126,12 @@ constexpr int32_t kListUnusable = 1 << 30;
 
 // Waits until the score row's threshold word carries this launch's generation in its upper half and
 // returns the lower half.  The producer is a unit that runs on a workgroup with a lower index, started
-// before this one, and waits for nothing itself.  If that does not happen within `polls` polls nothing is
+// before this one, and waits for nothing itself.  If that does not happen within wait_polls polls nothing is
 // to be collected, and the list is marked: what the other pieces list may well be as many as the select
 // needs, but it lacks this one's rows, so that the select has to rank the whole row.
-__device__ __forceinline__ uint32_t wait_threshold(const Emit &em, int polls)
+__device__ __forceinline__ uint32_t wait_threshold(const Emit &em)
 {
+    const int polls = arg_of<Common>()->wait_polls;  // (read here: kept through a piece it cost 20 spilled scalar registers)
     for (int spin = 0; spin < polls; ++spin) {
         const unsigned long long v = __hip_atomic_load((const LYCHEE_GLOBAL unsigned long long *)em.thr_flag,
                                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -151,14 +152,14 @@ __device__ __forceinline__ uint32_t wait_threshold(const Emit &em, int polls)
 // ahead of the partial, four barriers and the answer of the one reservation stood between the last row and the
 // partial, and a piece that ended before its threshold was out held its partial back.)
 constexpr int kFilterRows = kKeyBuf / kWaves;
-__device__ __forceinline__ void late_filter(ArgCommon &c, const Emit &em, const SharedAttn &sh, int first_row, int n_rows)
+__device__ __forceinline__ void late_filter(const Emit &em, const SharedAttn &sh, int first_row, int n_rows)
 {
     const int tid = fresh_tid();
     const int lane = tid & 63;
     const int i0 = uni(kWaves - 1 - (tid >> 6)) * kFilterRows;
     if (i0 >= n_rows) return;  // (uniform in the wavefront)
     const int i1 = n_rows < i0 + kFilterRows ? n_rows : i0 + kFilterRows;
-    const uint32_t thr = em.thr_known ? em.thr : uni(wait_threshold(em, c.wait_polls));
+    const uint32_t thr = em.thr_known ? em.thr : uni(wait_threshold(em));
     constexpr int kRounds = kFilterRows / 64;
     uint32_t key[kRounds];
     uint32_t n = 0;
@@ -346,7 +347,7 @@ __device__ __forceinline__ void stream_rows(ArgCommon &c, const uint16_t *kbase,
                 if (ch < 8) sh.keys[(r - r0) & (kKeyBuf - 1)] = key;
                 if (((span + 1) & (kWindowSpans - 1)) == 0 && span + 1 < n_spans) {  // uniform in the workgroup
                     __syncthreads();
-                    late_filter(c, em, sh, r0 + (span + 1) * kSpan - kKeyBuf, kKeyBuf);
+                    late_filter(em, sh, r0 + (span + 1) * kSpan - kKeyBuf, kKeyBuf);
                     __syncthreads();
                 }
                 continue;
@@ -555,7 +556,7 @@ __device__ __forceinline__ void run_piece(ArgCommon &c, const uint16_t *q, const
         }
     }
     if (LATE && collects) {
-        late_filter(c, em, sh, late_first, r1 - late_first);
+        late_filter(em, sh, late_first, r1 - late_first);
     } else if (collects) {
         __syncthreads();
         int base = sh.cand_base;
