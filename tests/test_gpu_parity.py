@@ -1243,6 +1243,40 @@ def test_where_a_rules_rows_are_selected_in_a_cache_of_many_times_their_length(o
     assert ctx.wait_timeouts() == 0
 
 
+def test_a_captured_rule_call_follows_the_lengths_it_is_replayed_with(own_ctx):
+    """A captured pair of launches decides anew in every replay: lengths of which the second launch selects and lengths of
+    which the first does, in turn, against the eager call."""
+    lb, ctx = H.binding(), own_ctx
+    ctx.set_option(lb.OPT_N_WG, 24)
+    w = wl.scaled(wl.WORKLOADS["c1"], batch=6, max_len=9000, k=100, planted=1)
+    mask = np.tile(np.array([1, 0, 1, 0], np.uint8), w.n_q_heads // 4)
+    inp = wl.make_layer(w, mask=mask, lens=np.full(6, 9000, np.int32), l_cap=w.max_len)
+    dl = H.DeviceLayer(inp, w.k, np.tile(np.arange(w.k, dtype=np.int32), (6, w.n_kv_heads, 1)))
+    dl.shape = lb.make_shape(6, w.n_q_heads, w.n_kv_heads, w.max_len, w.k, kv=dl.k_cache, prob_rule=2, prob_param=0.8)
+
+    def call():
+        ctx.decode_attn(dl.shape, dl.q, dl.k_cache, dl.v_cache, mask, dl.idx_in, dl.out, dl.idx_out, dl.lengths, dl.workspace)
+
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            call()
+    torch.cuda.synchronize()
+    for i, lens in enumerate(([1000, 1, 900, 1000, 64, 950], [5000, 4097, 4700, 5000, 4999, 4160]) * 2):
+        _say("replay %d, up to %d rows" % (i, max(lens)))
+        dl.lengths.copy_(torch.tensor(lens, dtype=torch.int32))
+        got = []
+        for run in (graph.replay, call):
+            dl.out.fill_(float("nan"))
+            dl.idx_out.fill_(-7)
+            run()
+            torch.cuda.synchronize()
+            got.append((dl.out.clone(), dl.idx_out.clone()))
+        assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1]), "replay %d" % i
+        assert (dl.idx_out != -7).all() and ctx.wait_timeouts() == 0
+
+
 @pytest.mark.parametrize("L,k", [(3000, 2000), (9000, 5000), (50000, 2000)])
 def test_top_p_crosses_its_mass_among_equal_keys(ctx, L, k):
     """More equal keys than are looked at one by one hold the position where the mass is reached: the rest of
