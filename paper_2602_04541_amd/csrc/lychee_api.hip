@@ -80,9 +80,10 @@ struct lychee_ctx {
 namespace {
 
 // Layout of lychee_ctx::sync_dev
-constexpr size_t kSyncGen = 0, kSyncExit = 64, kSyncApart = 128;
+constexpr size_t kSyncGen = 0, kSyncApart = 128, kSyncExit = 256;  // uint32 [1 + kExitGroups], lines of their own
 constexpr size_t kSyncRows = (size_t)kMaxBatch * kMaxKvHeads;  // (sequence, KV head) pairs a shape can have
-constexpr size_t kSyncThr = 4096;                               // uint64 [kSyncRows]
+constexpr size_t kSyncThr = 8192;                               // uint64 [kSyncRows]
+static_assert(kSyncExit + 4 * kLineWords * (1 + kExitGroups) <= kSyncThr, "");
 constexpr size_t kSyncSet = kSyncThr + kSyncRows * 8;           // uint32 [kSetFlagWords]
 constexpr size_t kSyncSeg = kSyncSet + kSetFlagWords * 4;  // uint32 [kSyncRows][2]
 constexpr size_t kSyncCount = kSyncSeg + kSyncRows * 8;         // int32 [3][kSyncRows]

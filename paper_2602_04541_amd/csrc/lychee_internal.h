@@ -36,6 +36,12 @@ __host__ __device__ constexpr int set_flag_at(int b, int g, int n_kv_heads)
 {
     return b == 0 ? g * kSetFlagStride : kMaxKvHeads * kSetFlagStride + b * n_kv_heads + g;
 }
+// Atomics on one 128-byte line are served one after the other, 11 ns each, and loads of other lines queue up behind
+// them: 64 workgroups that read 32 KB each take 0.65 us beside nothing, 4.0 us beside 448 additions to one word, 0.65
+// beside the same additions to 32 words of lines of their own.  So counters that many workgroups reach at once lie this
+// many 32-bit words apart, and what all of a launch's workgroups count, they count in groups (count_in).
+constexpr int kLineWords = 32;
+constexpr int kExitGroups = 32;
 constexpr int kPieceBlocks = 5;           // blocks of streaming or gathering that the fixed costs of a piece are worth
 constexpr float kMinusBig = -1.0e30f;    // "no score yet" sentinel of the running maximum
 
@@ -135,8 +141,8 @@ struct LaunchPlan {
 //                 segment merges the segment's partials into `out`
 //   own select    in the build that selects for its own layer: by the last n_tail workgroups, a score row each,
 //                 or by whoever completed the row's segment (see `apart`); cur's kept sets are copied by front units
-// Flags carry the launch's generation, a counter in device memory that the last workgroup to
-// finish advances: a flag of an earlier launch, or of an earlier replay of a captured launch,
+// Flags carry the launch's generation, a counter in device memory that is advanced once all
+// workgroups have read it (count_in): a flag of an earlier launch, or of an earlier replay of a captured launch,
 // never matches.
 struct LayerLaunch {
     Common c;              // (first, as above)
@@ -151,8 +157,8 @@ struct LayerLaunch {
     uint64_t gate_mask;    // bit g: KV head g's inherited set is written by this launch's front units
     uint32_t *apart;       // nullptr, or the launch is one of a pair: the first leaves here whether it leaves its
                            // rows to the second (rows_in_turn)
-    uint32_t *gen;         // the generation (read at the start, advanced at the end)
-    uint32_t *exit_count;  // workgroups that have finished
+    uint32_t *gen;         // the generation
+    uint32_t *exit_count;  // lines of: groups that have counted in, then each group's workgroups (count_in)
     unsigned long long *thr_flags;  // [B * n_rgroups] {generation, threshold} of cur's score rows
     uint32_t *set_flags;   // (set_flag_at) generation once the set of (sequence, KV head) is final
     uint32_t *seg_count;   // [B * H_kv * 2] blocks done so far of each R / G segment (zero between launches)

@@ -59,6 +59,7 @@ struct SharedLayer {
     __align__(16) int32_t at[12];  // the piece in hand: sequence, KV head, heads, blocks of the run; pieces of its segment, first and end row, slot; its blocks, its segment's
     FrontPlan front;               // who runs front units
     uint32_t gen;                  // the generation of this launch's flags
+    int32_t closes;                // this workgroup was the last of its group to count in
 };
 template <bool kUnits>
 union SharedRole {
@@ -79,6 +80,34 @@ __device__ __forceinline__ uint32_t load_agent(const uint32_t *p)
 __device__ __forceinline__ void store_agent(uint32_t *p, uint32_t v)
 {
     __hip_atomic_store((LYCHEE_GLOBAL uint32_t *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Every workgroup of a launch counts itself in once it has read the generation, among every kExitGroups-th
+// workgroup; the last of a group counts the group in at its end (closes_launch), and the last of those advances the
+// generation.  Whoever still runs then compares flags with the one it has read.  Returns what count_in_last
+// makes of it.  (Counted on one word, each at its end, the 440 workgroups without a piece in a layer
+// of 4K left together and held up the others' first rows, asked for just then, by 4 us; and the last workgroup's
+// addition, 0.5 us, stood at the end of every launch.)
+__device__ __forceinline__ uint32_t count_in(const LYCHEE_CONSTANT LayerLaunch *A, int w, uint32_t &gen)
+{
+    asm volatile("" : "+v"(gen) : : "memory");  // (the generation has arrived)
+    return __hip_atomic_fetch_add((LYCHEE_GLOBAL uint32_t *)A->exit_count + kLineWords * (1 + w % kExitGroups), 1u,
+                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool count_in_last(const LYCHEE_CONSTANT LayerLaunch *A, int w, int W, uint32_t before)
+{
+    if (before != (uint32_t)((W - 1 - w % kExitGroups) / kExitGroups)) return false;
+    store_agent(A->exit_count + kLineWords * (1 + w % kExitGroups), 0u);  // as every launch finds it
+    return true;
+}
+__device__ __forceinline__ void closes_launch(const LYCHEE_CONSTANT LayerLaunch *A, int W, uint32_t gen)
+{
+    const uint32_t groups = W < kExitGroups ? W : kExitGroups;
+    const uint32_t before = __hip_atomic_fetch_add((LYCHEE_GLOBAL uint32_t *)A->exit_count, 1u, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+    if (before != groups - 1u) return;
+    store_agent(A->exit_count, 0u);
+    store_agent(A->gen, gen + 1u);
 }
 
 // Blocks of 64 rows of all sequences of a batch, the same in every lane.
@@ -178,8 +207,8 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
     if (SELECTS == 2 && A->apart != nullptr && uni(load_agent(A->apart)) == 0u) return;
 
     // The generation is only ever used by thread 0 (it sets, polls and advances the flags), which
-    // keeps it in a register: the load is not waited for before its first use, late in the launch.
-    const uint32_t gen = tid == 0 ? load_agent(A->gen) : 0u;
+    // keeps it in a register: the load is not waited for before its first use.
+    uint32_t gen = tid == 0 ? load_agent(A->gen) : 0u;
     if (tid < c.batch) pool.len[tid] = clamp_len(gload(c.lengths + tid), c.max_len);
     if (SELECTS == 3)
         for (int i = tid; i < kMaxBatch * kMaxKvHeads / 32; i += kThreads) wanted[i] = 0;
@@ -245,6 +274,8 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
         }
         __builtin_amdgcn_s_setprio(0);
     }
+    uint32_t counted = 0;
+    if (tid == 0) counted = count_in(A, w, gen);  // (the answer is there before the first piece is found)
 
     // ------------------------------------------------------------------ the two row spaces
     // Per sequence: blocks of 64 cache rows per retrieval KV head, blocks of gathered rows per
@@ -337,7 +368,8 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             pool.role[1][3] = TG;
             pool.extra[0] = extra_r;
             pool.extra[1] = extra_g;
-            pool.gen = gen;  // (its load, issued when the kernel started, has long arrived)
+            pool.gen = gen;
+            pool.closes = count_in_last(A, w, W, counted);
         }
         kd = Kind{first, W_R, n_rseg, TR, uni((int)nb_r), extra_r};
         next = Kind{Wn < 2 ? first : first + W_R, W_G, n_gseg, TG, uni((int)nb_g), extra_g};
@@ -643,15 +675,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
     }
 
     // ------------------------------------------------------------------ the generation moves on
-    if (fresh_tid() == 0) {
-        const LYCHEE_CONSTANT LayerLaunch *A = arg_of<LayerLaunch>();
-        const uint32_t old = __hip_atomic_fetch_add((LYCHEE_GLOBAL uint32_t *)A->exit_count, 1u, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT);
-        if (old == (uint32_t)W - 1u) {
-            store_agent(A->exit_count, 0u);
-            store_agent(A->gen, pool.gen + 1u);
-        }
-    }
+    if (fresh_tid() == 0 && pool.closes) closes_launch(arg_of<LayerLaunch>(), W, pool.gen);
 }
 
 }  // namespace
