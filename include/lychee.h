@@ -13,7 +13,7 @@
  *   - Pointers are DEVICE pointers unless a parameter says HOST.  The caller owns every
  *     buffer; the library neither frees nor keeps them after the call's stream-ordered
  *     work has finished.  Nothing is allocated inside a call (a context allocates, once, in
- *     lychee_create: a 4 MiB device arena with its pinned mirror, and about 0.6 MiB of flags and
+ *     lychee_create: a 4 MiB device arena with its pinned mirror, and about 14 MiB of flags and
  *     counters through which the workgroups of a layer launch hand results to one another).
  *   - Calls only enqueue work on `hip_stream` (a hipStream_t; NULL = the default stream) and
  *     never read device memory from the host.  The layer calls (lychee_decode_attn,

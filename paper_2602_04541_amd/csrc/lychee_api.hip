@@ -82,13 +82,13 @@ namespace {
 // Layout of lychee_ctx::sync_dev
 constexpr size_t kSyncGen = 0, kSyncApart = 128, kSyncExit = 256;  // uint32 [1 + kExitGroups], lines of their own
 constexpr size_t kSyncRows = (size_t)kMaxBatch * kMaxKvHeads;  // (sequence, KV head) pairs a shape can have
-constexpr size_t kSyncThr = 8192;                               // uint64 [kSyncRows]
+constexpr size_t kSyncThr = 8192;                               // uint64 [kSyncRows][kLineWords / 2]
 static_assert(kSyncExit + 4 * kLineWords * (1 + kExitGroups) <= kSyncThr, "");
-constexpr size_t kSyncSet = kSyncThr + kSyncRows * 8;           // uint32 [kSetFlagWords]
-constexpr size_t kSyncSeg = kSyncSet + kSetFlagWords * 4;  // uint32 [kSyncRows][2]
-constexpr size_t kSyncCount = kSyncSeg + kSyncRows * 8;         // int32 [3][kSyncRows]
-constexpr size_t kSyncArrived = kSyncCount + 3 * kSyncRows * 4; // uint32 [kSyncRows]
-constexpr size_t kSyncBytes = kSyncArrived + kSyncRows * 4;
+constexpr size_t kSyncSet = kSyncThr + kSyncRows * kLineWords * 4;  // uint32 [kSetFlagWords]
+constexpr size_t kSyncSeg = kSyncSet + kSetFlagWords * 4;  // uint32 [kSyncRows][2][kLineWords]
+constexpr size_t kSyncCount = kSyncSeg + kSyncRows * 2 * kLineWords * 4;  // int32 [3][kSyncRows][kLineWords]
+constexpr size_t kSyncArrived = kSyncCount + 3 * kSyncRows * kLineWords * 4;  // uint32 [kSyncRows][kLineWords]
+constexpr size_t kSyncBytes = kSyncArrived + kSyncRows * kLineWords * 4;
 
 constexpr int kWsWg = 768;        // largest grid a launch uses
 constexpr int kPartSlots = 1024;  // partial slots per head in the workspace: static runs + chunks
@@ -313,6 +313,7 @@ void fill_common(Common &c, const lychee_ctx *ctx, const lychee_shape &s, const 
     c.prob_param = s.prob_param;
     c.max_len = s.max_len;
     c.sel_stride = w.sel_stride;
+    c.count_stride = 1;
     c.list_row = w.list_row;
     c.n_wg = n_wg;
     c.part_stride = kPartSlots;
@@ -467,6 +468,7 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
     memset(&p, 0, sizeof p);
     const int W = grid_of(ctx);
     fill_common(p.c, ctx, s, w, lengths, W);
+    p.c.count_stride = kLineWords;  // (count_bank)
     const bool blocks = s.block_size == 64;
     if (prev != nullptr) {
         p.prev = *prev;
@@ -526,7 +528,7 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
 // The candidate counters of a layer that a layer launch streams: one of the context's two banks.
 int32_t *count_bank(lychee_ctx *ctx, int bank)
 {
-    return reinterpret_cast<int32_t *>(ctx->sync_dev + kSyncCount) + (size_t)bank * kSyncRows;
+    return reinterpret_cast<int32_t *>(ctx->sync_dev + kSyncCount) + (size_t)bank * kSyncRows * kLineWords;
 }
 
 int check_step_pointers(int32_t n_layers, const void *const *q, const void *const *k_cache,

@@ -60,6 +60,7 @@ struct Common {
     int32_t block_shift;  // 0: sets name positions; 6: blocks of 64 positions (App. C)
     int32_t prob_rule;    // 0: budget only; 1: Threshold, 2: Top-p (Sec. 4.4.1) with parameter
     float prob_param;     //   prob_param, on the softmax of the pooled logits
+    int32_t count_stride; // words from one score row's candidate counter to the next
     int32_t list_row;     // capacity, in entries, of one score row's candidate list
     int32_t n_wg;         // grid size of this launch
     int32_t part_stride;  // partial slots per head
@@ -97,7 +98,7 @@ struct LayerDesc {
                            // pooled selection logits, per piece (Threshold / Top-p rules only)
     unsigned long long *list;  // [B*n_rgroups][list_row] candidates in no particular order:
                                // ordered key in the low 32 bits, position in the high 32 bits
-    int32_t *list_count;   // [B*n_rgroups] candidates found (may exceed list_row: list unusable; kListUnusable)
+    int32_t *list_count;   // [B*n_rgroups][count_stride] candidates found (may exceed list_row: list unusable; kListUnusable)
     uint32_t *thr;         // [B*n_rgroups] ordered key a score must reach to be a candidate
     int32_t *idx_out;      // [B][H_kv][k] where this layer's sets are written
     const int32_t *idx_src[kMaxKvHeads];  // per KV head: base of the [B][H_kv][k] array that
@@ -159,10 +160,10 @@ struct LayerLaunch {
                            // rows to the second (rows_in_turn)
     uint32_t *gen;         // the generation
     uint32_t *exit_count;  // lines of: groups that have counted in, then each group's workgroups (count_in)
-    unsigned long long *thr_flags;  // [B * n_rgroups] {generation, threshold} of cur's score rows
+    unsigned long long *thr_flags;  // [B * n_rgroups][kLineWords / 2] {generation, threshold} of cur's score rows
     uint32_t *set_flags;   // (set_flag_at) generation once the set of (sequence, KV head) is final
-    uint32_t *seg_count;   // [B * H_kv * 2] blocks done so far of each R / G segment (zero between launches)
-    uint32_t *thr_arrived; // [B * n_rgroups] threshold units of a score row that have left their keys (likewise)
+    uint32_t *seg_count;   // [B * H_kv * 2][kLineWords] blocks done so far of each R / G segment (zero between launches)
+    uint32_t *thr_arrived; // [B * n_rgroups][kLineWords] threshold units of a score row that have left their keys (likewise)
 };
 // 0: no selection anywhere in the launch (the dense baseline); 1: the hybrid build; 2: the one
 // that also knows the probability rules; 3: the one, rules included, that selects for `cur` instead of `prev`

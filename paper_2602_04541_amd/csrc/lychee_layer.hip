@@ -257,12 +257,12 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                 const int n_rc = cur.n_rgroups;
                 const int b = u / n_rc, rgi = u % n_rc;
                 const int64_t row = (int64_t)b * n_rc + rgi;
-                unsigned long long *flag = A->thr_flags + row;
+                unsigned long long *flag = A->thr_flags + row * (kLineWords / 2);
                 ThrSplit split;
                 split.sub = (j - nS - nC) % kThrSplit;
                 split.n_sub = kThrSplit;
                 split.keys = reinterpret_cast<uint32_t *>(cur.sel + row * c.sel_stride);  // (free until a select ranks this row whole)
-                split.arrived = A->thr_arrived + row;
+                split.arrived = A->thr_arrived + row * kLineWords;
                 switch (__builtin_popcount(cur.rmask[cur.rgroup[rgi]] & ((1u << c.group) - 1u))) {
                 case 1: threshold_unit<1>(c, cur, b, rgi, sel, pool, flag, gen, split); break;
                 case 2: threshold_unit<2>(c, cur, b, rgi, sel, pool, flag, gen, split); break;
@@ -568,7 +568,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                     if (COLLECT && desc_u32(dw, offsetof(LayerDesc, emit_sel))) {
                         const int64_t row = (int64_t)pc.b * n_rseg + gi;
                         em.list = desc_ptr<unsigned long long>(dw, offsetof(LayerDesc, list)) + row * c.list_row;
-                        em.count = desc_ptr<int32_t>(dw, offsetof(LayerDesc, list_count)) + row;
+                        em.count = desc_ptr<int32_t>(dw, offsetof(LayerDesc, list_count)) + row * c.count_stride;
                         em.cap = c.list_row;
                         em.direct = c.block_shift != 0;
                         if (c.prob_rule != 0)
@@ -577,7 +577,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                         const int n = budget_of(c, pc.len_b);
                         em.thr_known = needs_no_sample(n, pc.len_b);
                         em.thr = n == pc.len_b && c.prob_rule == 0 ? 0xFFFFFFFFu : 0u;
-                        em.thr_flag = A->thr_flags + row;
+                        em.thr_flag = A->thr_flags + row * (kLineWords / 2);
                         em.gen = my_gen;
                         em.timeouts = c.stats + 2;
                     }
@@ -606,7 +606,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                 int last = 1, selects = 1;
                 const bool awaited = kNow && !gather && A->n_tail > 0;  // by the workgroup that selects the row
                 if (pieces > 1 || awaited) {
-                    uint32_t *counter = A->seg_count + (((int64_t)b * cc.n_kv_heads + g) * 2 + kind);
+                    uint32_t *counter = A->seg_count + (((int64_t)b * cc.n_kv_heads + g) * 2 + kind) * kLineWords;
                     const uint32_t mine = (uint32_t)pool.at[8];
                     const uint32_t old = __hip_atomic_fetch_add((LYCHEE_GLOBAL uint32_t *)counter, mine, __ATOMIC_RELAXED,
                                                                 __HIP_MEMORY_SCOPE_AGENT);
@@ -665,10 +665,10 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
             for (uint32_t rows = uni(wanted[i >> 5]); rows != 0; rows &= rows - 1u) {
                 const int row = i + __builtin_ctz(rows);
                 const int b = row / n_rseg, g = cur.rgroup[row % n_rseg];
-                if (own >= 0 && !await_rows(c, A->seg_count + ((int64_t)b * c.n_kv_heads + g) * 2,
+                if (own >= 0 && !await_rows(c, A->seg_count + ((int64_t)b * c.n_kv_heads + g) * 2 * kLineWords,
                                             (uint32_t)(pool.len[b] + kBlockRows - 1) / kBlockRows, pool))
                     break;
-                select_unit<true>(c, cur, b, g, sel, pool, A->thr_flags + row, pool.gen);
+                select_unit<true>(c, cur, b, g, sel, pool, A->thr_flags + row * (kLineWords / 2), pool.gen);
                 __syncthreads();
             }
         }

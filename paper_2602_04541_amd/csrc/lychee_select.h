@@ -290,7 +290,7 @@ __device__ __forceinline__ void threshold_unit(ArgCommon &c, const LayerDesc &p,
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         gstore(p.thr + row, key);  // (a later launch's select starts from it)
     };
-    if (publish == nullptr && tid == 0) gstore(p.list_count + row, (int32_t)0);
+    if (publish == nullptr && tid == 0) gstore(p.list_count + row * c.count_stride, (int32_t)0);
     if (split.sub == 0 && p.q_keep != nullptr && tid < c.group * (kHeadDim / 8)) {
         // the group's query rows (consecutive heads, 16 chunks of 16 bytes each)
         const int64_t at = ((int64_t)b * c.n_q_heads + p.rgroup[rgi] * c.group) * kHeadDim + tid * 8;
@@ -944,7 +944,7 @@ __device__ __forceinline__ void select_unit(ArgCommon &c, const LayerDesc &p, in
     if (n == L && !by_prob) {  // everything is selected
         for (int i = fresh_tid(); i < c.k; i += kThreads) gstore_through(dst + i, (int32_t)(i < L ? i : -1));
         if (fresh_tid() == 0 && c.block_shift == 0 && rgi != 0xFF)
-            gstore(p.list_count + ((int64_t)b * p.n_rgroups + rgi), (int32_t)0);  // (nothing was collected; see below)
+            gstore(p.list_count + ((int64_t)b * p.n_rgroups + rgi) * c.count_stride, (int32_t)0);  // (nothing was collected; see below)
         return;
     }
     const int64_t row = (int64_t)b * p.n_rgroups + rgi;
@@ -959,7 +959,7 @@ __device__ __forceinline__ void select_unit(ArgCommon &c, const LayerDesc &p, in
         head[u] = gload(list + (i < c.list_row ? i : c.list_row - 1));
     }
     // block-granular: the streaming left every block's score at its place in the list
-    const int total = c.block_shift ? L : gload(p.list_count + row);
+    const int total = c.block_shift ? L : gload(p.list_count + row * c.count_stride);
     // No entry lies below the row's threshold.  (A select of the launch that streamed the row takes it
     // from where the row's pieces did; rows whose pieces asked nobody may not have one there yet.)
     uint32_t floor_key = 0;
@@ -1030,7 +1030,7 @@ __device__ __forceinline__ void select_unit(ArgCommon &c, const LayerDesc &p, in
         select_from(M, 0u, len, keep, L, dst, sh);
     }
     for (int i = keep + fresh_tid(); i < c.k; i += kThreads) gstore_through(dst + i, (int32_t)-1);
-    if (clear_count && fresh_tid() == 0) gstore(p.list_count + row, (int32_t)0);
+    if (clear_count && fresh_tid() == 0) gstore(p.list_count + row * c.count_stride, (int32_t)0);
 }
 
 

@@ -362,7 +362,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_pool_kernel(const LaunchPl
                 if (COLLECT && desc_u32(dw, offsetof(LayerDesc, emit_sel))) {
                     const int64_t row = (int64_t)b * (int)desc_u32(dw, offsetof(LayerDesc, n_rgroups)) + gi;
                     em.list = desc_ptr<unsigned long long>(dw, offsetof(LayerDesc, list)) + row * c.list_row;
-                    em.count = desc_ptr<int32_t>(dw, offsetof(LayerDesc, list_count)) + row;
+                    em.count = desc_ptr<int32_t>(dw, offsetof(LayerDesc, list_count)) + row * c.count_stride;
                     em.thr = c.block_shift ? 0u : gload(desc_ptr<uint32_t>(dw, offsetof(LayerDesc, thr)) + row);
                     em.cap = c.list_row;
                     em.direct = c.block_shift != 0;
