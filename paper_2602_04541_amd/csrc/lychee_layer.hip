@@ -90,9 +90,12 @@ __device__ __forceinline__ void store_agent(uint32_t *p, uint32_t v)
 // addition, 0.5 us, stood at the end of every launch.)
 __device__ __forceinline__ uint32_t count_in(const LYCHEE_CONSTANT LayerLaunch *A, int w, uint32_t &gen)
 {
-    asm volatile("" : "+v"(gen) : : "memory");  // (the generation has arrived)
-    return __hip_atomic_fetch_add((LYCHEE_GLOBAL uint32_t *)A->exit_count + kLineWords * (1 + w % kExitGroups), 1u,
-                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t at = kLineWords * (1 + w % kExitGroups);
+    // (The generation has arrived; and the address is opaque: to an address that it knows to be the same in every lane the
+    // compiler adds for the wavefront as a whole and waits for the answer on the spot.)
+    asm volatile("" : "+v"(gen), "+v"(at) : : "memory");
+    return __hip_atomic_fetch_add((LYCHEE_GLOBAL uint32_t *)A->exit_count + at, 1u, __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ bool count_in_last(const LYCHEE_CONSTANT LayerLaunch *A, int w, int W, uint32_t before)
 {
@@ -209,12 +212,20 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
     // The generation is only ever used by thread 0 (it sets, polls and advances the flags), which
     // keeps it in a register: the load is not waited for before its first use.
     uint32_t gen = tid == 0 ? load_agent(A->gen) : 0u;
-    if (tid < c.batch) pool.len[tid] = clamp_len(gload(c.lengths + tid), c.max_len);
+    // (all loads before the first wait)
+    int len = 0;
+    uint32_t word_cur = 0, word_prev = 0;
+    if (tid < c.batch) len = gload(c.lengths + tid);
+    if (tid < kDescWords) {
+        word_cur = reinterpret_cast<const LYCHEE_CONSTANT uint32_t *>(&A->cur)[tid];
+        word_prev = reinterpret_cast<const LYCHEE_CONSTANT uint32_t *>(&A->prev)[tid];
+    }
     if (SELECTS == 3)
         for (int i = tid; i < kMaxBatch * kMaxKvHeads / 32; i += kThreads) wanted[i] = 0;
+    if (tid < c.batch) pool.len[tid] = clamp_len(len, c.max_len);
     if (tid < kDescWords) {
-        desc_cur[tid] = reinterpret_cast<const LYCHEE_CONSTANT uint32_t *>(&A->cur)[tid];
-        desc_prev[tid] = reinterpret_cast<const LYCHEE_CONSTANT uint32_t *>(&A->prev)[tid];
+        desc_cur[tid] = word_cur;
+        desc_prev[tid] = word_prev;
     }
     __syncthreads();
     const LayerDesc &cur = *reinterpret_cast<const LayerDesc *>(desc_cur);
