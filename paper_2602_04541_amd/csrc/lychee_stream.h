@@ -369,6 +369,76 @@ __device__ __forceinline__ void stream_rows(ArgCommon &c, const uint16_t *kbase,
     cand_left = cand_n;  // the caller writes these out, one reservation for the whole workgroup
 }
 
+// A LATE piece of at most one block of 64 rows (position-granular when it collects): a tile per wavefront, rows 16w ..
+// 16w+15, nothing to pipeline.  Latency bounds such a piece.  (As a span of stream_rows two of the wavefronts had two
+// tiles of rows one after the other and two had none, and a gather's set entries went through LDS between
+// two barriers: from the set's flag to the last row 5.2 us in a layer of a 4K step, now 2.9; the step 690 and 633 us, a single 4K layer
+// 17.4 and 16.2.)
+template <int NH, bool GATHER>
+__device__ __forceinline__ void short_rows(ArgCommon &c, const uint16_t *kbase, const uint16_t *vbase,
+                                           const uint4 (&qf)[NH], Acc<NH> &acc, int L, int r0, int r1,
+                                           const int32_t *idx_src, const Emit &em, float sel_mul, float &pool_m,
+                                           float &pool_l, SharedAttn &sh)
+{
+    const int tid = fresh_tid();
+    const int lane = tid & 63;
+    const int rs = lane >> 4;
+    const int ch = lane & 15;
+    const int first = r0 + 16 * uni(tid >> 6) + rs;  // of the lane's four rows, every fourth
+    Tile t;
+    t.valid = 0;
+    int row[4];
+    if (GATHER) {
+        const int bshift = c.block_shift;
+        const int n_units = units_of(c, L);
+        int e[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int r = first + 4 * j;
+            e[j] = gload(idx_src + ((r < r1 ? r : r1 - 1) >> bshift));
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {  // (the entries' checks as in stream_rows)
+            const int r = first + 4 * j;
+            const bool named = r < r1 && (uint32_t)e[j] < (uint32_t)n_units;
+            const int tpos = named ? (e[j] << bshift) + (r & ((1 << bshift) - 1)) : 0;
+            const bool ok = named && tpos < L;
+            row[j] = ok ? tpos : 0;
+            t.valid |= (ok ? 1 : 0) << j;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int r = first + 4 * j;
+            row[j] = r < r1 ? r : r1 - 1;
+            t.valid |= (r < r1 ? 1 : 0) << j;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int64_t off = (int64_t)row[j] * c.stride_t + ch * 8;
+        t.k[j] = load_stream16(kbase + off);
+        t.v[j] = load_stream16(vbase + off);
+    }
+    float sel[4];
+    consume_tile<NH>(t, qf, acc, c.scale_log2e, sel);
+    if (!GATHER && em.list != nullptr) {
+        // lane ch (< 4) of a row slot holds the score of row first + 4 * ch
+        const int j = ch & 3;
+        float mine = sel[0];
+        mine = (j == 1) ? sel[1] : mine;
+        mine = (j == 2) ? sel[2] : mine;
+        mine = (j == 3) ? sel[3] : mine;
+        const int r = first + 4 * j;
+        const float score = sel_value(mine, sel_mul);
+        if (em.pool_ml != nullptr && ch < 4 && r < r1) {
+            pool_m = score;  // (one row per lane)
+            pool_l = 1.0f;
+        }
+        if (ch < 4) sh.keys[r - r0] = ordered_key(score);
+    }
+}
+
 // One (workgroup, segment) piece: rows/entries [r0, r1) of segment (b, g) for the heads in
 // hmask.  Leaves one un-normalised partial per head in `slot`; the piece that ends the
 // segment also records how many slots the segment has.
@@ -422,7 +492,9 @@ __device__ __forceinline__ void run_piece(ArgCommon &c, const uint16_t *q, const
     float pool_m = kMinusBig, pool_l = 0.0f;  // per lane: log-sum-exp state of the pooled logits
     int cand_left = 0;                        // candidates still in this wavefront's LDS buffer
 
-    if (GATHER) {
+    if (LATE && r1 - r0 <= kBlockRows && (GATHER || em.direct == 0)) {
+        short_rows<NH, GATHER>(c, kbase, vbase, qf, acc, L, r0, r1, idx_src, em, sel_mul, pool_m, pool_l, sh);
+    } else if (GATHER) {
         // rows r0 .. r1-1 of the gathered sequence are row (r mod 2^shift) of set entry r >> shift
         const int shift = c.block_shift;
         const int chunk_rows = kIdxChunk << shift;

@@ -98,6 +98,33 @@ def test_edge_shapes(ctx, case):
     H.check_layer(ctx, inp, mask, k, idx_in, "edge%s" % (case,))
 
 
+@pytest.mark.parametrize("block", [1, 64])
+@pytest.mark.parametrize("Hkv,G", [(2, 1), (1, 2), (2, 3), (1, 4)])
+def test_pieces_of_at_most_one_block_of_rows(ctx, Hkv, G, block):
+    """Layer calls whose streamed and gathered pieces end at the edges of a wavefront's tile of 16 rows and of the
+    block of 64, with a set of which some entries name nothing."""
+    rng = np.random.default_rng(100 * Hkv + G)
+    for L, k in ((1, 1), (15, 15), (16, 3), (17, 16), (31, 17), (48, 47), (49, 33), (63, 64), (64, 64), (65, 63), (129, 65)):
+        k = -(-k // block)
+        w = wl.scaled(wl.WORKLOADS["c1"], n_q_heads=Hkv * G, n_kv_heads=Hkv, max_len=L, k=k, planted=min(8, L),
+                      retrieval_heads=())
+        mask = (rng.random(Hkv * G) < 0.5).astype(np.uint8)
+        mask[0], mask[-1] = 1, 0
+        inp = wl.make_layer(w, mask=mask, lens=np.asarray([L], np.int32), l_cap=L)
+        idx_in = H.previous_layer_sets(inp, k, block=block)
+        _say("short pieces %dx%d L=%d k=%d block %d" % (Hkv, G, L, k, block))
+        H.check_layer(ctx, inp, mask, k, idx_in, "L=%d k=%d" % (L, k), block=block)
+        if block == 1 and k > 2:  # (entries that name nothing leave the outputs of the set without them)
+            few = idx_in[:, :, :k - 2].copy()
+            junk = idx_in.copy()
+            junk[:, :, k - 2:] = (-1, 10 ** 6)
+            out_few, _ = H.run_hybrid(ctx, H.DeviceLayer(inp, k - 2, few), mask)
+            out_junk, _ = H.run_hybrid(ctx, H.DeviceLayer(inp, k, junk), mask)
+            H.assert_outputs_close(out_junk, out_few, "ignored entries, L=%d k=%d" % (L, k))
+        if block == 1:
+            H.check_prob_rule_layer(ctx, inp, mask, k, 2, 0.8, "top-p L=%d k=%d" % (L, k), idx_in)
+
+
 def test_inherited_sets_in_any_order_and_with_ignored_entries(ctx):
     """idx_in need not be sorted; negative and out-of-range entries are skipped."""
     w = wl.scaled(wl.WORKLOADS["c1"], max_len=900, k=96, planted=8)
