@@ -120,6 +120,19 @@ __device__ __forceinline__ float sum_halves32(float x)
     const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
     return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
 }
+// The same sums of several numbers at once: a's over each pair of rows in the even rows, b's in the odd ones; then,
+// of two such, a's (four rows), b's, c's and d's in rows 0 to 3.  One swap and one addition for two numbers
+// instead of a copy, a swap and an addition for each.
+__device__ __forceinline__ float sum_rows16_pair(float a, float b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+    return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+__device__ __forceinline__ float sum_halves32_pair(float ab, float cd)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, ab), __builtin_bit_cast(uint32_t, cd), false, false);
+    return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+}
 __device__ __forceinline__ float max_rows16(float x)
 {
     const uint32_t u = __builtin_bit_cast(uint32_t, x);
@@ -236,6 +249,12 @@ __device__ __forceinline__ void gstore_through(unsigned long long *p, unsigned l
 {
     __hip_atomic_store((LYCHEE_GLOBAL unsigned long long *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ void gstore_through(float *p, float2 v)  // (8-byte aligned)
+{
+    gstore_through(reinterpret_cast<unsigned long long *>(p),
+                   (unsigned long long)__builtin_bit_cast(uint32_t, v.x) | ((unsigned long long)__builtin_bit_cast(uint32_t, v.y) << 32));
+}
+__device__ __forceinline__ void gstore_f2(float *p, float2 v) { *(LYCHEE_GLOBAL f32x2_t *)p = f32x2_t{v.x, v.y}; }
 __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 __device__ __forceinline__ float4 gload_f4(const float *p)
@@ -315,6 +334,13 @@ __device__ __forceinline__ int fresh_tid()
 
 // A value that is the same in every lane, said so to the compiler (a scalar register).
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+template <typename T>
+__device__ __forceinline__ T *uni(T *p)
+{
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    return reinterpret_cast<T *>((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v) |
+                                 ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32));
+}
 __device__ __forceinline__ uint32_t uni(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 
 __device__ __forceinline__ uint32_t desc_u32(const uint32_t *dw, size_t off)

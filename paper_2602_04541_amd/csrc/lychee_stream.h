@@ -524,11 +524,13 @@ __device__ __forceinline__ void run_piece(ArgCommon &c, const uint16_t *q, const
         lw = sum_halves32(sum_rows16(lw));
         acc.l[h] = lw;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            float ow = acc.o[h][e] * a;
-            ow = sum_halves32(sum_rows16(ow));
-            acc.o[h][e] = ow;
-        }
+        for (int e = 0; e < 8; ++e) acc.o[h][e] *= a;
+        // (row slot rs is left with columns rs and 4 + rs of its eight)
+        float pair[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) pair[e] = sum_rows16_pair(acc.o[h][2 * e], acc.o[h][2 * e + 1]);
+        acc.o[h][0] = sum_halves32_pair(pair[0], pair[1]);
+        acc.o[h][1] = sum_halves32_pair(pair[2], pair[3]);
     }
     const bool pooled_lse = !GATHER && em.pool_ml != nullptr;
     if (pooled_lse) {  // wave-uniform: merge the lanes' pooled log-sum-exp states
@@ -545,16 +547,14 @@ __device__ __forceinline__ void run_piece(ArgCommon &c, const uint16_t *q, const
     __syncthreads();  // red_o / idx_s readers of the previous piece are done
     // (the accumulators go to LDS first: nothing below needs them, and kept in registers across
     // the key filter they were spilled)
-    if (rs == 0) {
 #pragma unroll
-        for (int h = 0; h < NH; ++h) {
-            float *dst = sh.red_o + (wave * kMaxGroup + h) * kHeadDim + ch * 8;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) dst[e] = acc.o[h][e];
-            if (ch == 0) {
-                sh.red_ml[(wave * kMaxGroup + h) * 2 + 0] = acc.m[h];
-                sh.red_ml[(wave * kMaxGroup + h) * 2 + 1] = acc.l[h];
-            }
+    for (int h = 0; h < NH; ++h) {
+        float *dst = sh.red_o + (wave * kMaxGroup + h) * kHeadDim + ch * 8;
+        dst[rs] = acc.o[h][0];
+        dst[4 + rs] = acc.o[h][1];
+        if (lane == 0) {
+            sh.red_ml[(wave * kMaxGroup + h) * 2 + 0] = acc.m[h];
+            sh.red_ml[(wave * kMaxGroup + h) * 2 + 1] = acc.l[h];
         }
     }
     int cand_base = 0;
@@ -577,40 +577,47 @@ __device__ __forceinline__ void run_piece(ArgCommon &c, const uint16_t *q, const
     }
     __syncthreads();
     if (!LATE && collects && tid == kThreads - 1) sh.cand_base = cand_base;
-    if (tid < kHeadDim) {
+    // Wavefront h merges head h, two columns a lane.  (A column a thread, one head after the other, took two
+    // wavefronts four times as many instructions for four heads: 0.85 us of the chain that ends a layer.)
+    static_assert(kMaxGroup <= kWaves && kHeadDim == 128, "a wavefront per head, two columns per lane");
+    if (uni(wave) < NH) {
+        const int h = uni(wave);
+        int head = heads[0];
 #pragma unroll
-        for (int h = 0; h < NH; ++h) {
-            float M = kMinusBig;
+        for (int i = 1; i < NH; ++i) head = i == h ? heads[i] : head;
+        float2 ml[kWaves], ow[kWaves];
 #pragma unroll
-            for (int w = 0; w < kWaves; ++w) M = fmaxf(M, sh.red_ml[(w * kMaxGroup + h) * 2]);
-            float o = 0.0f, l = 0.0f;
+        for (int w = 0; w < kWaves; ++w) {
+            ml[w] = *reinterpret_cast<const float2 *>(sh.red_ml + (w * kMaxGroup + h) * 2);
+            ow[w] = *reinterpret_cast<const float2 *>(sh.red_o + (w * kMaxGroup + h) * kHeadDim + 2 * lane);
+        }
+        float M = kMinusBig;
 #pragma unroll
-            for (int w = 0; w < kWaves; ++w) {
-                const float a = fast_exp2((sh.red_ml[(w * kMaxGroup + h) * 2] - M) * c_log2e);
-                o = fmaf(a, sh.red_o[(w * kMaxGroup + h) * kHeadDim + tid], o);
-                l = fmaf(a, sh.red_ml[(w * kMaxGroup + h) * 2 + 1], l);
-            }
-            const int64_t bh = (int64_t)b * c.n_q_heads + heads[h];
-            const int64_t prow = bh * c.part_stride + slot;
-            if (LATE && alone_out != nullptr) {
-                gstore(alone_out + bh * kHeadDim + tid, f32_to_bf16_rne(l > 0.0f ? o / l : 0.0f));
-            } else if (LATE) {
-                gstore_through(part_o + prow * kHeadDim + tid, o);
-                if (tid == 0) {
-                    gstore_through(part_ml + prow * 2 + 0, M);
-                    gstore_through(part_ml + prow * 2 + 1, l);
-                }
-            } else {
-                gstore(part_o + prow * kHeadDim + tid, o);
-                if (tid == 0) {
-                    gstore(part_ml + prow * 2 + 0, M);
-                    gstore(part_ml + prow * 2 + 1, l);
-                }
-            }
-            if (tid == 0 && ends_segment) {
-                if (LATE) gstore_through(part_count + bh, (int32_t)(slot + 1));
-                else gstore(part_count + bh, (int32_t)(slot + 1));
-            }
+        for (int w = 0; w < kWaves; ++w) M = fmaxf(M, ml[w].x);
+        float2 o = make_float2(0.0f, 0.0f);
+        float l = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            const float a = fast_exp2((ml[w].x - M) * c_log2e);
+            o.x = fmaf(a, ow[w].x, o.x);
+            o.y = fmaf(a, ow[w].y, o.y);
+            l = fmaf(a, ml[w].y, l);
+        }
+        const int64_t bh = (int64_t)b * c.n_q_heads + head;
+        const int64_t prow = bh * c.part_stride + slot;
+        if (LATE && alone_out != nullptr) {
+            const uint32_t lo = f32_to_bf16_rne(l > 0.0f ? o.x / l : 0.0f), hi = f32_to_bf16_rne(l > 0.0f ? o.y / l : 0.0f);
+            gstore(reinterpret_cast<uint32_t *>(alone_out + bh * kHeadDim) + lane, lo | (hi << 16));
+        } else if (LATE) {
+            gstore_through(part_o + prow * kHeadDim + 2 * lane, o);
+            if (lane == 0) gstore_through(part_ml + prow * 2, make_float2(M, l));
+        } else {
+            gstore_f2(part_o + prow * kHeadDim + 2 * lane, o);
+            if (lane == 0) gstore_f2(part_ml + prow * 2, make_float2(M, l));
+        }
+        if (lane == 0 && ends_segment) {
+            if (LATE) gstore_through(part_count + bh, (int32_t)(slot + 1));
+            else gstore(part_count + bh, (int32_t)(slot + 1));
         }
     }
     if (pooled_lse && tid == 0) {  // the piece's pooled log-sum-exp state, same slot
