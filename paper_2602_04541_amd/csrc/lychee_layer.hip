@@ -590,6 +590,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
                         em.thr = n == pc.len_b && c.prob_rule == 0 ? 0xFFFFFFFFu : 0u;
                         em.thr_flag = A->thr_flags + row * (kLineWords / 2);
                         em.gen = my_gen;
+                        em.read_now = kNow;
                         em.timeouts = c.stats + 2;
                     }
                     dispatch_piece<false, true>(__builtin_popcount(pc.hmask), c, dq, dk, dv, nullptr, em, d_part_o, d_part_ml,

@@ -117,6 +117,7 @@ struct Emit {
     const unsigned long long *thr_flag;
     uint32_t gen;
     int32_t thr_known;
+    int32_t read_now;          // this launch selects from the list (or else a later one)
     uint32_t *timeouts;        // counts waits that gave up
 };
 
@@ -129,12 +130,15 @@ constexpr int32_t kListUnusable = 1 << 30;
 // before this one, and waits for nothing itself.  If that does not happen within wait_polls polls nothing is
 // to be collected, and the list is marked: what the other pieces list may well be as many as the select
 // needs, but it lacks this one's rows, so that the select has to rank the whole row.
+__device__ __forceinline__ unsigned long long load_threshold(const Emit &em)
+{
+    return __hip_atomic_load((const LYCHEE_GLOBAL unsigned long long *)em.thr_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 __device__ __forceinline__ uint32_t wait_threshold(const Emit &em)
 {
     const int polls = arg_of<Common>()->wait_polls;  // (read here: kept through a piece it cost 20 spilled scalar registers)
     for (int spin = 0; spin < polls; ++spin) {
-        const unsigned long long v = __hip_atomic_load((const LYCHEE_GLOBAL unsigned long long *)em.thr_flag,
-                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long v = load_threshold(em);
         if ((uint32_t)(v >> 32) == em.gen) return (uint32_t)v;
         __builtin_amdgcn_s_sleep(2);
     }
@@ -151,15 +155,18 @@ __device__ __forceinline__ uint32_t wait_threshold(const Emit &em)
 // rows that leaves the first two wavefronts to the partial.  (Counted and scanned by the whole workgroup
 // ahead of the partial, four barriers and the answer of the one reservation stood between the last row and the
 // partial, and a piece that ended before its threshold was out held its partial back.)
+// early: the row's threshold word as it was a while ago (its load takes 0.7 us): usually the threshold is there.
 constexpr int kFilterRows = kKeyBuf / kWaves;
-__device__ __forceinline__ void late_filter(const Emit &em, const SharedAttn &sh, int first_row, int n_rows)
+__device__ __forceinline__ void late_filter(const Emit &em, const SharedAttn &sh, int first_row, int n_rows,
+                                            unsigned long long early = 0)
 {
     const int tid = fresh_tid();
     const int lane = tid & 63;
     const int i0 = uni(kWaves - 1 - (tid >> 6)) * kFilterRows;
     if (i0 >= n_rows) return;  // (uniform in the wavefront)
     const int i1 = n_rows < i0 + kFilterRows ? n_rows : i0 + kFilterRows;
-    const uint32_t thr = em.thr_known ? em.thr : uni(wait_threshold(em));
+    const uint32_t early_gen = uni((uint32_t)(early >> 32)), early_thr = uni((uint32_t)early);
+    const uint32_t thr = em.thr_known ? em.thr : early_gen == em.gen ? early_thr : uni(wait_threshold(em));
     constexpr int kRounds = kFilterRows / 64;
     uint32_t key[kRounds];
     uint32_t n = 0;
@@ -513,6 +520,8 @@ __device__ __forceinline__ void run_piece(ArgCommon &c, const uint16_t *q, const
 
     at_rows_done();  // what the caller wants in flight while the partial is merged and written
     if (!LATE && collects && lane == 0) sh.cand_left[wave] = cand_left;
+    unsigned long long early = 0;
+    if (LATE && collects && em.read_now && !em.thr_known) early = load_threshold(em);
     // Merge the 4 row slots of the wavefront (lanes l, l^16, l^32, l^48).
     const float c_log2e = c.scale_log2e;
 #pragma unroll
@@ -635,7 +644,7 @@ __device__ __forceinline__ void run_piece(ArgCommon &c, const uint16_t *q, const
         }
     }
     if (LATE && collects) {
-        late_filter(em, sh, late_first, r1 - late_first);
+        late_filter(em, sh, late_first, r1 - late_first, early);
     } else if (collects) {
         __syncthreads();
         int base = sh.cand_base;
