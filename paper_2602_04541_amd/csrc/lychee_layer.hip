@@ -138,7 +138,7 @@ __device__ __forceinline__ void publish_set(uint32_t *flag, uint32_t gen)
     if (fresh_tid() == 0) store_agent(flag, gen);
 }
 
-// Before a gather piece reads a set that a front unit of this launch writes.
+// Before a gather piece reads (by gload_through) a set that a front unit of this launch writes.
 __device__ __forceinline__ void await_set(ArgCommon &c, const uint32_t *flag, uint32_t gen, SharedLayer &pool)
 {
     if (fresh_tid() == 0) {
@@ -151,7 +151,6 @@ __device__ __forceinline__ void await_set(ArgCommon &c, const uint32_t *flag, ui
         if (spin == polls) atomicAdd(c.stats + 2, 1u);  // (the piece then reads whatever the array holds; entries are range-checked)
     }
     __syncthreads();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
 }
 
 // Before a workgroup at the end of the grid selects a row: until the row's pieces have counted in all of its

@@ -376,59 +376,69 @@ __device__ __forceinline__ void stream_rows(ArgCommon &c, const uint16_t *kbase,
     cand_left = cand_n;  // the caller writes these out, one reservation for the whole workgroup
 }
 
-// A LATE piece of at most one block of 64 rows (position-granular when it collects): a tile per wavefront, rows 16w ..
-// 16w+15, nothing to pipeline.  Latency bounds such a piece.  (As a span of stream_rows two of the wavefronts had two
-// tiles of rows one after the other and two had none, and a gather's set entries went through LDS between
-// two barriers: from the set's flag to the last row 5.2 us in a layer of a 4K step, now 2.9; the step 690 and 633 us, a single 4K layer
-// 17.4 and 16.2.)
-template <int NH, bool GATHER>
+// A LATE piece of at most kTiles blocks of 64 rows (position-granular when it collects): a tile of each block per
+// wavefront, rows 16w .. 16w+15 of it, all loads at once.  Latency bounds such a piece.  (As a span of
+// stream_rows two of the wavefronts had two tiles of rows of a block one after the other and two had none, and a
+// gather's set entries went through LDS between two barriers: from the set's flag to the last row 5.2 us
+// in a layer of a 4K step, now 2.9; the step 690 and 633 us, a single 4K layer 17.4 and 16.2.)
+template <int NH, bool GATHER, int kTiles>
 __device__ __forceinline__ void short_rows(ArgCommon &c, const uint16_t *kbase, const uint16_t *vbase,
                                            const uint4 (&qf)[NH], Acc<NH> &acc, int L, int r0, int r1,
                                            const int32_t *idx_src, const Emit &em, float sel_mul, float &pool_m,
                                            float &pool_l, SharedAttn &sh)
 {
+    static_assert(GATHER || kTiles == 1, "a streamed piece keeps one tile's keys");
     const int tid = fresh_tid();
     const int lane = tid & 63;
     const int rs = lane >> 4;
     const int ch = lane & 15;
-    const int first = r0 + 16 * uni(tid >> 6) + rs;  // of the lane's four rows, every fourth
-    Tile t;
-    t.valid = 0;
-    int row[4];
+    const int first = r0 + 16 * uni(tid >> 6) + rs;  // of the lane's four rows of a tile, every fourth
+    Tile t[kTiles];
+    int row[kTiles][4];
     if (GATHER) {
         const int bshift = c.block_shift;
         const int n_units = units_of(c, L);
-        int e[4];
+        int e[kTiles][4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = first + 4 * j;
-            e[j] = gload(idx_src + ((r < r1 ? r : r1 - 1) >> bshift));
-        }
+        for (int i = 0; i < kTiles; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {  // (the entries' checks as in stream_rows)
-            const int r = first + 4 * j;
-            const bool named = r < r1 && (uint32_t)e[j] < (uint32_t)n_units;
-            const int tpos = named ? (e[j] << bshift) + (r & ((1 << bshift) - 1)) : 0;
-            const bool ok = named && tpos < L;
-            row[j] = ok ? tpos : 0;
-            t.valid |= (ok ? 1 : 0) << j;
+            for (int j = 0; j < 4; ++j) {
+                const int r = first + kBlockRows * i + 4 * j;
+                e[i][j] = gload_through(idx_src + ((r < r1 ? r : r1 - 1) >> bshift));
+            }
+#pragma unroll
+        for (int i = 0; i < kTiles; ++i) {
+            t[i].valid = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {  // (the entries' checks as in stream_rows)
+                const int r = first + kBlockRows * i + 4 * j;
+                const bool named = r < r1 && (uint32_t)e[i][j] < (uint32_t)n_units;
+                const int tpos = named ? (e[i][j] << bshift) + (r & ((1 << bshift) - 1)) : 0;
+                const bool ok = named && tpos < L;
+                row[i][j] = ok ? tpos : 0;
+                t[i].valid |= (ok ? 1 : 0) << j;
+            }
         }
     } else {
+        t[0].valid = 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int r = first + 4 * j;
-            row[j] = r < r1 ? r : r1 - 1;
-            t.valid |= (r < r1 ? 1 : 0) << j;
+            row[0][j] = r < r1 ? r : r1 - 1;
+            t[0].valid |= (r < r1 ? 1 : 0) << j;
         }
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int64_t off = (int64_t)row[j] * c.stride_t + ch * 8;
-        t.k[j] = load_stream16(kbase + off);
-        t.v[j] = load_stream16(vbase + off);
-    }
+    for (int i = 0; i < kTiles; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int64_t off = (int64_t)row[i][j] * c.stride_t + ch * 8;
+            t[i].k[j] = load_stream16(kbase + off);
+            t[i].v[j] = load_stream16(vbase + off);
+        }
     float sel[4];
-    consume_tile<NH>(t, qf, acc, c.scale_log2e, sel);
+#pragma unroll
+    for (int i = 0; i < kTiles; ++i) consume_tile<NH>(t[i], qf, acc, c.scale_log2e, sel);
     if (!GATHER && em.list != nullptr) {
         // lane ch (< 4) of a row slot holds the score of row first + 4 * ch
         const int j = ch & 3;
@@ -500,7 +510,9 @@ __device__ __forceinline__ void run_piece(ArgCommon &c, const uint16_t *q, const
     int cand_left = 0;                        // candidates still in this wavefront's LDS buffer
 
     if (LATE && r1 - r0 <= kBlockRows && (GATHER || em.direct == 0)) {
-        short_rows<NH, GATHER>(c, kbase, vbase, qf, acc, L, r0, r1, idx_src, em, sel_mul, pool_m, pool_l, sh);
+        short_rows<NH, GATHER, 1>(c, kbase, vbase, qf, acc, L, r0, r1, idx_src, em, sel_mul, pool_m, pool_l, sh);
+    } else if (LATE && GATHER && r1 - r0 <= 2 * kBlockRows) {
+        short_rows<NH, true, 2>(c, kbase, vbase, qf, acc, L, r0, r1, idx_src, em, sel_mul, pool_m, pool_l, sh);
     } else if (GATHER) {
         // rows r0 .. r1-1 of the gathered sequence are row (r mod 2^shift) of set entry r >> shift
         const int shift = c.block_shift;
@@ -509,7 +521,7 @@ __device__ __forceinline__ void run_piece(ArgCommon &c, const uint16_t *q, const
             const int e1 = e0 + chunk_rows < r1 ? e0 + chunk_rows : r1;
             const int n_entries = (e1 - e0 + (1 << shift) - 1) >> shift;
             __syncthreads();  // the previous chunk's readers are done
-            for (int i = tid; i < n_entries; i += kThreads) sh.idx_s[i] = gload(idx_src + (e0 >> shift) + i);
+            for (int i = tid; i < n_entries; i += kThreads) sh.idx_s[i] = LATE ? gload_through(idx_src + (e0 >> shift) + i) : gload(idx_src + (e0 >> shift) + i);
             __syncthreads();
             stream_rows<NH, true, LATE>(c, kbase, vbase, qf, acc, L, e0, e1, sh.idx_s, em, 0.0f, nullptr, cand_left, pool_m, pool_l, sh);
         }

@@ -99,12 +99,16 @@ def test_edge_shapes(ctx, case):
 
 
 @pytest.mark.parametrize("block", [1, 64])
+@pytest.mark.parametrize("n_wg", [0, 2])
 @pytest.mark.parametrize("Hkv,G", [(2, 1), (1, 2), (2, 3), (1, 4)])
-def test_pieces_of_at_most_one_block_of_rows(ctx, Hkv, G, block):
-    """Layer calls whose streamed and gathered pieces end at the edges of a wavefront's tile of 16 rows and of the
-    block of 64, with a set of which some entries name nothing."""
+def test_pieces_of_a_few_tiles(ctx, Hkv, G, n_wg, block):
+    """Layer calls whose streamed and gathered pieces end at the edges of a wavefront's tile of 16 rows and of one
+    and two blocks of 64 (on a grid of two workgroups a segment is a piece), with a set of which some entries name
+    nothing."""
     rng = np.random.default_rng(100 * Hkv + G)
-    for L, k in ((1, 1), (15, 15), (16, 3), (17, 16), (31, 17), (48, 47), (49, 33), (63, 64), (64, 64), (65, 63), (129, 65)):
+    ctx.set_option(H.binding().OPT_N_WG, n_wg)
+    for L, k in ((1, 1), (15, 15), (16, 3), (17, 16), (31, 17), (48, 47), (49, 33), (63, 64), (64, 64), (65, 63), (129, 65),
+                 (150, 80), (200, 81), (128, 127), (128, 128), (300, 129)):
         k = -(-k // block)
         w = wl.scaled(wl.WORKLOADS["c1"], n_q_heads=Hkv * G, n_kv_heads=Hkv, max_len=L, k=k, planted=min(8, L),
                       retrieval_heads=())
