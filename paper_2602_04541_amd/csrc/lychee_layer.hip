@@ -36,7 +36,10 @@
 // write-back of the whole L2, executed by every workgroup, costs more than the layer): they are
 // written with write-through stores, the writer waits until those have completed before it
 // counts itself in, and the merging workgroup takes an acquire fence.  The sets are handed over
-// the same way: written through, waited for, then flagged.
+// the same way: written through, waited for, then flagged; but hundreds of workgroups read them, and an acquire
+// fence invalidates the caches of its whole XCD, so they are read past the caches instead (gload_through; with
+// a fence in every gathering workgroup a 32K layer of the model loop took 29.5 us, now 26.0).  The few that merge keep
+// theirs: partials read past the caches, in loads of 8 bytes, made the 36-layer step at 128K 1748 us instead of 1690.
 #include "lychee_internal.h"
 #include "lychee_device.h"
 #include "lychee_stream.h"

@@ -11,7 +11,7 @@ namespace {
 // out = (sum_s w_s o_s) / (sum_s w_s l_s),  w_s = 2^((m_s - M) log2(e)/sqrt(d)),  M = max_s m_s,
 // over a head's partial slots in ascending order (a fixed summation tree), for all NH heads of a
 // segment at once (in a layer launch by the workgroup that has just written the segment's last
-// partial, in a phased step one head per unit).
+// partial, in a phased step by a unit).
 // It stands at the end of the layer's chain and is latency, not bytes: the partial outputs of up to
 // kGrp * kU slots are asked for before anything else; meanwhile wavefront h turns head h's (m, l)
 // pairs into weights (in LDS); then thread (head, group, column quad) sums its group's slots, and
