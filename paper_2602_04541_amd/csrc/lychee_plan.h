@@ -163,4 +163,20 @@ LYCHEE_HD inline int32_t gather_block_rows(int32_t r_blocks, int32_t g_blocks, i
     return (int64_t)r_blocks + g_blocks > 12ll * n_wg || max_len >= 7 << 14 ? 48 : kGatherRows;
 }
 
+// Unit u of the merges of a launch: all query heads of one KV head of one sequence of a layer.  Every unit has as
+// many heads as every other, so that units dealt in turn are an even deal for any grid.  (A unit for each KV head's
+// retrieval heads and one for its sparse heads, in turn: half of them empty in a dense step or with one query head a
+// KV head, and on an even grid all of either kind on the same workgroups.  36 layers, 8 KV heads, the merging launch
+// with those and with these, us: one query head each, 8 sequences 24.6 and 14.6, dense 25.3 and 15.4; four, one
+// sequence 10.4 and 9.5, dense 11.8 and 9.3; four, 8 sequences 31.4 and 25.7, dense 32.3 and 19.6.)
+struct MergeAt {
+    int32_t layer, b, g;
+};
+LYCHEE_HD inline int32_t merge_units(int32_t n_layers, int32_t batch, int32_t n_kv_heads) { return n_layers * batch * n_kv_heads; }
+LYCHEE_HD inline MergeAt merge_at(int32_t u, int32_t batch, int32_t n_kv_heads)
+{
+    const int32_t bg = u % (batch * n_kv_heads);
+    return MergeAt{u / (batch * n_kv_heads), bg / n_kv_heads, bg % n_kv_heads};
+}
+
 }  // namespace lychee

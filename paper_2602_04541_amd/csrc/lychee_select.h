@@ -63,10 +63,13 @@ __device__ __forceinline__ void combine_segment(ArgCommon &c, const LayerDesc &p
         for (int s0 = lane; s0 < count; s0 += 4 * 64) {
             float2 ml[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < 4; ++u) {
+                if (u > 0 && s0 - lane + 64 * u >= count) break;  // (uniform)
                 ml[u] = gload_f2(reinterpret_cast<const float *>(pm + (pm_at + (uint32_t)min(s0 + 64 * u, count - 1) * 8)));
+            }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
+                if (u > 0 && s0 - lane + 64 * u >= count) break;
                 const int s = s0 + 64 * u;
                 const float m = ml[u].y > 0.0f ? ml[u].x : kMinusBig;  // (a piece without a valid row leaves l = 0)
                 if (s < count) {

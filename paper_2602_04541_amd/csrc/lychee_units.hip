@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_small_kernel(const LaunchP
         const uint32_t incl_t = block_scan(cnt_t, pool.scan, tot[2]);
         tot[0] = (uint32_t)tot_s;
         tot[3] = (uint32_t)(tot_s >> 32);
-        tot[1] = (uint32_t)(P.c_count * c.batch * c.n_kv_heads * 2);
+        tot[1] = (uint32_t)merge_units(P.c_count, c.batch, c.n_kv_heads);
         tot[4] = (uint32_t)P.a_count;
         if (t < kMaxLayers) {
             pool.upre[0][t + 1] = (int32_t)(uint32_t)incl_s;
@@ -127,21 +127,23 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_small_kernel(const LaunchP
                 if (SELECTS == 1) select_unit<false>(c, L, b, L.rgroup[u % L.n_rgroups], su.sel, pool);
                 if (SELECTS == 2) select_unit<true>(c, L, b, L.rgroup[u % L.n_rgroups], su.sel, pool);
             } else if ((u -= (int)tot[0]) < (int)tot[1]) {
-                // The retrieval heads of a KV head, or its sparse ones, together: they have the same slots.  (Head by head a
-                // step of 36 layers was 1152 units, three rounds of what is a chain of latencies.)
-                const int li = u / (c.batch * c.n_kv_heads * 2);
-                const LayerDesc &L = stage(P.c_first + li);
-                const int bg = (u % (c.batch * c.n_kv_heads * 2)) >> 1;
-                const int b = bg / c.n_kv_heads, g = bg % c.n_kv_heads;
-                const uint32_t hmask = ((u & 1) != 0 ? ~(uint32_t)L.rmask[g] : (uint32_t)L.rmask[g]) & ((1u << c.group) - 1u);
-                if (hmask != 0) {  // (uniform)
-                    int count = uni(gload(L.part_count + (int64_t)b * c.n_q_heads + g * c.group + __builtin_ctz(hmask)));
+                // The heads of a KV head: its retrieval heads, which have the same slots, and then its sparse ones.  (Head
+                // by head a step of 36 layers was 1152 units, three rounds of what is a chain of latencies.)
+                const MergeAt at = merge_at(u, c.batch, c.n_kv_heads);
+                const LayerDesc &L = stage(P.c_first + at.layer);
+                const int lane = fresh_tid() & 63;
+                const int counts = gload(L.part_count + (int64_t)at.b * c.n_q_heads + at.g * c.group + (lane < c.group ? lane : 0));
+                const uint32_t rmask = uni((uint32_t)L.rmask[at.g]);
+                for (int kind = 0; kind < 2; ++kind) {
+                    const uint32_t hmask = (kind != 0 ? ~rmask : rmask) & ((1u << c.group) - 1u);
+                    if (hmask == 0) continue;
+                    int count = __builtin_amdgcn_readlane(counts, __builtin_ctz(hmask));
                     count = count < 1 ? 1 : (count > c.part_stride ? c.part_stride : count);  // (every head has a piece)
                     switch (__builtin_popcount(hmask)) {
-                    case 1: combine_segment<1, true>(c, L, b, g, hmask, count, su.comb); break;
-                    case 2: combine_segment<2, true>(c, L, b, g, hmask, count, su.comb); break;
-                    case 3: combine_segment<3, true>(c, L, b, g, hmask, count, su.comb); break;
-                    default: combine_segment<4, true>(c, L, b, g, hmask, count, su.comb); break;
+                    case 1: combine_segment<1, true>(c, L, at.b, at.g, hmask, count, su.comb); break;
+                    case 2: combine_segment<2, true>(c, L, at.b, at.g, hmask, count, su.comb); break;
+                    case 3: combine_segment<3, true>(c, L, at.b, at.g, hmask, count, su.comb); break;
+                    default: combine_segment<4, true>(c, L, at.b, at.g, hmask, count, su.comb); break;
                     }
                 }
             } else if ((u -= (int)tot[1]) < (int)tot[2]) {

@@ -48,3 +48,16 @@ extern "C" int32_t threshold_alone(int32_t n, int32_t L, int32_t r_blocks, int32
 {
     return lychee::threshold_alone(n, L, r_blocks, n_wg, margin, fits);
 }
+
+extern "C" int32_t merge_units(int32_t n_layers, int32_t batch, int32_t n_kv_heads)
+{
+    return lychee::merge_units(n_layers, batch, n_kv_heads);
+}
+
+extern "C" void merge_at(int32_t u, int32_t batch, int32_t n_kv_heads, int32_t *out)
+{
+    const lychee::MergeAt at = lychee::merge_at(u, batch, n_kv_heads);
+    out[0] = at.layer;
+    out[1] = at.b;
+    out[2] = at.g;
+}

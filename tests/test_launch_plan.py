@@ -203,3 +203,18 @@ def test_one_unit_takes_a_threshold_where_the_launch_is_short_and_the_rest_fits_
         if got:   # what reaches the threshold, for f of the n best among 512 sampled rows, with a tenth to spare
             f = n * 512 / L
             assert (f + margin * f ** 0.5 + 6) * L / 512 <= 0.9 * fits * (1 + 1e-5)
+
+
+def test_every_merge_of_a_phased_step_is_a_kv_head_of_its_own(plan):
+    """Units are dealt to the workgroups in turn, which is an even deal if each has the same to do: no unit is empty or
+    holds part of a KV head's heads, however the heads are divided into retrieval and sparse ones."""
+    out = (ctypes.c_int32 * 3)()
+    for n, batch, kv in ((1, 1, 1), (36, 1, 8), (36, 8, 8), (5, 3, 7), (127, 16, 2), (2, 256, 64)):
+        total = plan.merge_units(n, batch, kv)
+        seen = set()
+        for u in range(total):
+            plan.merge_at(u, batch, kv, out)
+            layer, b, g = out
+            assert 0 <= layer < n and 0 <= b < batch and 0 <= g < kv
+            seen.add((layer, b, g))
+        assert len(seen) == total == n * batch * kv
