@@ -738,7 +738,7 @@ int lychee_create(lychee_ctx **out, int device)
     ok = ok && hipMemset(ctx->arena_dev, 0, kArenaReserved) == hipSuccess;
     ok = ok && hipMalloc(reinterpret_cast<void **>(&ctx->sync_dev), kSyncBytes) == hipSuccess;
     ok = ok && hipMemset(ctx->sync_dev, 0, kSyncBytes) == hipSuccess;
-    const uint32_t first_gen = 1;  // (zero is what the untouched flags hold)
+    const uint32_t first_gen = kFirstGeneration;
     ok = ok && hipMemcpy(ctx->sync_dev + kSyncGen, &first_gen, sizeof first_gen, hipMemcpyHostToDevice) == hipSuccess;
     ok = ok && hipGetSymbolAddress(&ctx->static_scratch, HIP_SYMBOL(scratch)) == hipSuccess &&
          ctx->static_scratch != nullptr;

@@ -113,7 +113,7 @@ __device__ __forceinline__ void closes_launch(const LYCHEE_CONSTANT LayerLaunch 
                                                    __HIP_MEMORY_SCOPE_AGENT);
     if (before != groups - 1u) return;
     store_agent(A->exit_count, 0u);
-    store_agent(A->gen, gen + 1u);
+    store_agent(A->gen, next_generation(gen));
 }
 
 // Blocks of 64 rows of all sequences of a batch, the same in every lane.

@@ -24,6 +24,12 @@ LYCHEE_HD inline int32_t quot_by(int32_t a, int32_t b, float inv, U u)
     return (int32_t)(q + (r >= b ? 1u : 0u) - (r < 0 ? 1u : 0u));
 }
 
+// The generation of the layer launch after that of generation `gen`.  None is 0, also where the 32 bits wrap (30 hours
+// of launches of 26 us): 0 is what a flag that nobody has written holds, and a threshold word that nobody has asked
+// for (late_filter), and neither may pass for one of this launch.
+constexpr uint32_t kFirstGeneration = 1;
+LYCHEE_HD inline uint32_t next_generation(uint32_t gen) { return gen + 1u != 0u ? gen + 1u : kFirstGeneration; }
+
 // Capacity, in entries, of one score row's candidate list.  A threshold unit aims at n = min(k, L)
 // candidates plus six standard deviations of its sample (a few thousand at the usual sizes),
 // and makes every row a candidate when L <= kDirectLen or L <= 2k.  A list that still

@@ -155,7 +155,8 @@ __device__ __forceinline__ uint32_t wait_threshold(const Emit &em)
 // rows that leaves the first two wavefronts to the partial.  (Counted and scanned by the whole workgroup
 // ahead of the partial, four barriers and the answer of the one reservation stood between the last row and the
 // partial, and a piece that ended before its threshold was out held its partial back.)
-// early: the row's threshold word as it was a while ago (its load takes 0.7 us): usually the threshold is there.
+// early: the row's threshold word as it was a while ago (its load takes 0.7 us): usually the threshold is there; 0,
+// which is of no generation, if it was not asked for.
 constexpr int kFilterRows = kKeyBuf / kWaves;
 __device__ __forceinline__ void late_filter(const Emit &em, const SharedAttn &sh, int first_row, int n_rows,
                                             unsigned long long early = 0)

@@ -11,6 +11,10 @@ extern "C" void front_plan(int32_t selects, int32_t copies, int32_t thresholds, 
     out[1] = p.n_aside;
 }
 
+extern "C" uint32_t first_generation() { return lychee::kFirstGeneration; }
+
+extern "C" uint32_t next_generation(uint32_t gen) { return lychee::next_generation(gen); }
+
 extern "C" int32_t list_row_entries(int32_t max_len, int32_t k, int32_t blocks)
 {
     return lychee::list_row_entries(max_len, k, blocks != 0);

@@ -218,3 +218,19 @@ def test_every_merge_of_a_phased_step_is_a_kv_head_of_its_own(plan):
             assert 0 <= layer < n and 0 <= b < batch and 0 <= g < kv
             seen.add((layer, b, g))
         assert len(seen) == total == n * batch * kv
+
+
+def test_no_launch_has_the_generation_of_flags_that_nobody_has_written(plan):
+    """Flags start at 0 and a threshold word that was not asked for is 0: across the wrap of the 32 bits too no
+    generation is, and it differs from the one before it."""
+    plan.first_generation.restype = plan.next_generation.restype = ctypes.c_uint32
+    plan.next_generation.argtypes = [ctypes.c_uint32]
+    assert plan.first_generation() != 0
+    for start in (plan.first_generation(), 2 ** 31 - 2, 2 ** 32 - 3):
+        gen = start
+        for _ in range(6):
+            after = plan.next_generation(gen)
+            assert after not in (0, gen)
+            gen = after
+    with open(os.path.join(CSRC, "lychee_layer.hip")) as f:   # (what the launches do: the only store of the word)
+        assert [line.strip() for line in f if "store_agent(A->gen," in line] == ["store_agent(A->gen, next_generation(gen));"]
