@@ -583,9 +583,8 @@ __device__ __forceinline__ void run_piece(ArgCommon &c, const uint16_t *q, const
     // the piece's last window of keys: rows late_first .. r1 - 1
     const int late_first = r0 + (r1 - r0 > 0 ? (r1 - r0 - 1) / kKeyBuf * kKeyBuf : 0);
     if (!LATE && collects && tid == kThreads - 1) {
-        // room for the workgroup's last candidates, asked for by a thread that writes no
-        // partial, as early as every wavefront's count is known: the answer is on its way
-        // while the others merge
+        // room for the workgroup's last candidates, asked for as early as every wavefront's count is
+        // known: the answer is on its way while the heads are merged (this wavefront merges one of four)
         int n = 0;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) n += sh.cand_left[w];
@@ -598,7 +597,6 @@ __device__ __forceinline__ void run_piece(ArgCommon &c, const uint16_t *q, const
         sh.pool_ml[2 * wave + 1] = pool_l;
     }
     __syncthreads();
-    if (!LATE && collects && tid == kThreads - 1) sh.cand_base = cand_base;
     // Wavefront h merges head h, two columns a lane.  (A column a thread, one head after the other, took two
     // wavefronts four times as many instructions for four heads: 0.85 us of the chain that ends a layer.)
     static_assert(kMaxGroup <= kWaves && kHeadDim == 128, "a wavefront per head, two columns per lane");
@@ -659,6 +657,7 @@ __device__ __forceinline__ void run_piece(ArgCommon &c, const uint16_t *q, const
     if (LATE && collects) {
         late_filter(em, sh, late_first, r1 - late_first, early);
     } else if (collects) {
+        if (tid == kThreads - 1) sh.cand_base = cand_base;  // (waits for the answer: not ahead of the merge)
         __syncthreads();
         int base = sh.cand_base;
         for (int w = 0; w < wave; ++w) base += sh.cand_left[w];

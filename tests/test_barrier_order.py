@@ -53,3 +53,12 @@ def test_the_count_of_the_last_entries_is_read_before_it_is_reset():
     assert len(re.findall(read, rule)) == 1
     # (right after the read, ahead of every branch: the ways out of the loop differ in what they do next)
     assert re.match(r";\s*__syncthreads\(\);", rule[re.search(read, rule).end():]), "no barrier right after the read"
+
+
+def test_the_answer_of_the_list_reservation_is_waited_for_after_the_merge():
+    """In a pooled piece the last wavefront asks for the room of the piece's last candidates and, of four heads, merges
+    one: it stores the answer, which it waits for, behind that, and ahead of the barrier that the readers pass."""
+    piece = block_after(source("lychee_stream.h"), "__device__ __forceinline__ void run_piece")
+    seen = events(piece[piece.index("int cand_base = 0;"):], ask=r"cand_base = __hip_atomic_fetch_add", answer=r"sh\.cand_base = cand_base",
+                  merge=r"if \(uni\(wave\) < NH\)", read=r"int base = sh\.cand_base")
+    assert seen == ["ask", "barrier", "merge", "answer", "barrier", "read"], seen
