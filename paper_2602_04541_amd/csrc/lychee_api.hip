@@ -402,6 +402,18 @@ struct Launcher {
             p.n_rseg[l] = (uint8_t)host_table[l].n_rgroups;
             p.keeps[l] = (uint8_t)(host_table[l].copy_keep != 0);
         }
+        if (r.c_count) {
+            bool any_sparse = false;
+            for (int l = r.c_first; l < r.c_first + r.c_count; ++l) any_sparse |= host_table[l].n_sgroups > 0;
+            int others = r.t_count * s.batch * s.n_kv_heads + r.a_count;
+            for (int l = r.s_first; l < r.s_first + r.s_count; ++l)
+                others += s.batch * (host_table[l].copy_keep ? s.n_kv_heads : host_table[l].n_rgroups);
+            // (a segment's runs, and the chunks that the end of the row space is dealt in)
+            const int64_t seg_blocks = (s.max_len + kBlockRows - 1) / kBlockRows;
+            const int slots = (int)(seg_blocks / c.chunk_blocks) + 2;
+            p.c_split = merge_split(r.c_count * s.batch * s.n_kv_heads, c.group, any_sparse, others, slots, c.n_wg);
+            p.c_parts = merge_parts(p.c_split, c.group);
+        }
         for (int l = r.g_first; l < r.g_first + r.g_count; ++l) p.n_gseg[l] = (uint8_t)host_table[l].n_sgroups;
         for (int l = r.s_first; l < r.s_first + r.s_count; ++l) p.selects |= host_table[l].n_rgroups > 0;
         const int cls = r.r_count ? LYCHEE_KERNEL_STREAM : r.g_count ? LYCHEE_KERNEL_GATHER

@@ -118,7 +118,8 @@ struct LaunchPlan {
     const LayerDesc *layers;
     int32_t r_first, r_count;    // retrieval streaming
     int32_t g_first, g_count;    // sparse gather
-    int32_t c_first, c_count;    // combine
+    int32_t c_first, c_count;    // combine,
+    int32_t c_split, c_parts;    //   in so many units for each KV head (merge_split)
     int32_t a_first, a_count;    // cache append
     int32_t t_first, t_count;    // selection thresholds
     int32_t s_first, s_count;    // select (and set copies)

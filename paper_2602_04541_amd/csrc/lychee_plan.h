@@ -169,20 +169,38 @@ LYCHEE_HD inline int32_t gather_block_rows(int32_t r_blocks, int32_t g_blocks, i
     return (int64_t)r_blocks + g_blocks > 12ll * n_wg || max_len >= 7 << 14 ? 48 : kGatherRows;
 }
 
-// Unit u of the merges of a launch: all query heads of one KV head of one sequence of a layer.  Every unit has as
-// many heads as every other, so that units dealt in turn are an even deal for any grid.  (A unit for each KV head's
-// retrieval heads and one for its sparse heads, in turn: half of them empty in a dense step or with one query head a
-// KV head, and on an even grid all of either kind on the same workgroups.  36 layers, 8 KV heads, the merging launch
-// with those and with these, us: one query head each, 8 sequences 24.6 and 14.6, dense 25.3 and 15.4; four, one
-// sequence 10.4 and 9.5, dense 11.8 and 9.3; four, 8 sequences 31.4 and 25.7, dense 32.3 and 19.6.)
-struct MergeAt {
-    int32_t layer, b, g;
-};
-LYCHEE_HD inline int32_t merge_units(int32_t n_layers, int32_t batch, int32_t n_kv_heads) { return n_layers * batch * n_kv_heads; }
-LYCHEE_HD inline MergeAt merge_at(int32_t u, int32_t batch, int32_t n_kv_heads)
+// How a phased step's merges are dealt: a unit merges all query heads of a KV head, its retrieval heads and then its
+// sparse ones; or the heads of one of the two kinds; or one head.  kv_heads: KV heads over all sequences and layers;
+// others: units of other kinds in the launch; slots: the most that a head can have.
+//
+// A unit is a chain of latencies, about 2.7 us, whether it merges one head or four of the same kind, and 2 us more
+// for a second kind; four heads take another 3 us for every 48 slots beyond the first 48, one head 4 us for 190.
+// Units are dealt to the workgroups in turn.  So: a head each where every head has a workgroup of its own; a kind
+// each likewise (half of these units are empty in a dense step); else KV heads, of which none is empty and all have as
+// much to do.  Heads again up to three rounds of them where they have more than two rounds of 48 slots.
+// us of the merging launch with KV heads, kinds and heads, 8 KV heads of four query heads, one sequence: 8 layers of
+// 4096 rows 7.1, 5.2, 4.9; 24 layers 7.4, 5.7, 7.8; 36 7.6, 8.1, 10.2; of 32768 (66 slots) 8 layers 7.8, 6.5, 6.4;
+// 36 10.3, 10.7, 13.0, dense 10.4, 13.3, 13.0; of 65536 (130 slots) 24 layers 16.0, 14.5, 10.5; 44 17.5, 18.6, 14.7; 60
+// 12.5, 11.7, 17.0, dense 14.6, 18.8, 17.2.  (Kinds in every step: 8 sequences of 8192, 36 layers, 31.4, dense 32.3, with
+// KV heads 25.0 and 18.2; of one query head, which are the same by KV head and by head, 25.8 and 25.1, now 17.5 and 14.6.)
+enum { kMergeKvHeads = 0, kMergeKinds = 1, kMergeHeads = 2 };
+LYCHEE_HD inline int32_t merge_split(int32_t kv_heads, int32_t group, bool any_sparse, int32_t others, int32_t slots, int32_t n_wg)
 {
-    const int32_t bg = u % (batch * n_kv_heads);
-    return MergeAt{u / (batch * n_kv_heads), bg / n_kv_heads, bg % n_kv_heads};
+    const int64_t heads = (int64_t)kv_heads * group;
+    if (group == 1 || heads + others <= n_wg || (slots > 2 * 48 && heads <= 3ll * n_wg)) return kMergeHeads;
+    return any_sparse && 2ll * kv_heads + others <= n_wg ? kMergeKinds : kMergeKvHeads;
+}
+LYCHEE_HD inline int32_t merge_parts(int32_t split, int32_t group)
+{
+    return split == kMergeHeads ? group : (split == kMergeKinds ? 2 : 1);
+}
+// Which of a KV head's query heads its part-th unit merges.  rmask: its retrieval heads.
+LYCHEE_HD inline uint32_t merge_heads(int32_t split, int32_t part, uint32_t rmask, int32_t group)
+{
+    const uint32_t all = (1u << group) - 1u;
+    if (split == kMergeHeads) return 1u << part;
+    if (split == kMergeKinds) return (part != 0 ? ~rmask : rmask) & all;
+    return all;
 }
 
 }  // namespace lychee

@@ -54,9 +54,10 @@ namespace {
 
 // ------------------------------------------------------------------------------ the kernels
 // Launches that carry T, S and C units: unit j runs on workgroup j mod W.  SELECTS = 0 is
-// the lighter build for launches without S units on retrieval groups (their candidates held
+// the build for launches without S units on retrieval groups (their candidates held
 // in registers set this kernel's register budget, and spill code with it), 1 the build with
-// them, 2 the one whose S units also know the probability rules.
+// them and without T and C units (with those in it the select launch of a 36-layer step of 8 sequences of 8192
+// took 24.7 us, without 24.1), 2 the one whose S units also know the probability rules.
 template <int SELECTS>
 __global__ __launch_bounds__(kThreads, 2) void lychee_small_kernel(const LaunchPlan P)
 {
@@ -91,7 +92,7 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_small_kernel(const LaunchP
         const uint32_t incl_t = block_scan(cnt_t, pool.scan, tot[2]);
         tot[0] = (uint32_t)tot_s;
         tot[3] = (uint32_t)(tot_s >> 32);
-        tot[1] = (uint32_t)merge_units(P.c_count, c.batch, c.n_kv_heads);
+        tot[1] = (uint32_t)(P.c_count * c.batch * c.n_kv_heads * P.c_parts);
         tot[4] = (uint32_t)P.a_count;
         if (t < kMaxLayers) {
             pool.upre[0][t + 1] = (int32_t)(uint32_t)incl_s;
@@ -126,27 +127,33 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_small_kernel(const LaunchP
                 const int b = u / L.n_rgroups;
                 if (SELECTS == 1) select_unit<false>(c, L, b, L.rgroup[u % L.n_rgroups], su.sel, pool);
                 if (SELECTS == 2) select_unit<true>(c, L, b, L.rgroup[u % L.n_rgroups], su.sel, pool);
-            } else if ((u -= (int)tot[0]) < (int)tot[1]) {
-                // The heads of a KV head: its retrieval heads, which have the same slots, and then its sparse ones.  (Head
-                // by head a step of 36 layers was 1152 units, three rounds of what is a chain of latencies.)
-                const MergeAt at = merge_at(u, c.batch, c.n_kv_heads);
-                const LayerDesc &L = stage(P.c_first + at.layer);
+            } else if (u -= (int)tot[0], SELECTS == 0 && u < (int)tot[1]) {
+                // Heads of a KV head (merge_split): the retrieval heads among them, which have the same slots, then the
+                // sparse ones.
+                const int kv_head = quot_uni(u, P.c_parts);
+                const int part = u - kv_head * P.c_parts;
+                const int row = quot_uni(kv_head, c.n_kv_heads);  // (layer, sequence)
+                const int g = kv_head - row * c.n_kv_heads;
+                const int li = quot_uni(row, c.batch);
+                const int b = row - li * c.batch;
+                const LayerDesc &L = stage(P.c_first + li);
                 const int lane = fresh_tid() & 63;
-                const int counts = gload(L.part_count + (int64_t)at.b * c.n_q_heads + at.g * c.group + (lane < c.group ? lane : 0));
-                const uint32_t rmask = uni((uint32_t)L.rmask[at.g]);
+                const int counts = gload(L.part_count + (int64_t)b * c.n_q_heads + g * c.group + (lane < c.group ? lane : 0));
+                const uint32_t rmask = P.c_split == kMergeHeads ? ~0u : uni((uint32_t)L.rmask[g]);  // (a head is of one kind)
+                const uint32_t of = merge_heads(P.c_split, part, rmask, c.group);
                 for (int kind = 0; kind < 2; ++kind) {
-                    const uint32_t hmask = (kind != 0 ? ~rmask : rmask) & ((1u << c.group) - 1u);
+                    const uint32_t hmask = (kind != 0 ? ~rmask : rmask) & of;
                     if (hmask == 0) continue;
                     int count = __builtin_amdgcn_readlane(counts, __builtin_ctz(hmask));
                     count = count < 1 ? 1 : (count > c.part_stride ? c.part_stride : count);  // (every head has a piece)
                     switch (__builtin_popcount(hmask)) {
-                    case 1: combine_segment<1, true>(c, L, at.b, at.g, hmask, count, su.comb); break;
-                    case 2: combine_segment<2, true>(c, L, at.b, at.g, hmask, count, su.comb); break;
-                    case 3: combine_segment<3, true>(c, L, at.b, at.g, hmask, count, su.comb); break;
-                    default: combine_segment<4, true>(c, L, at.b, at.g, hmask, count, su.comb); break;
+                    case 1: combine_segment<1, true>(c, L, b, g, hmask, count, su.comb); break;
+                    case 2: combine_segment<2, true>(c, L, b, g, hmask, count, su.comb); break;
+                    case 3: combine_segment<3, true>(c, L, b, g, hmask, count, su.comb); break;
+                    default: combine_segment<4, true>(c, L, b, g, hmask, count, su.comb); break;
                     }
                 }
-            } else if ((u -= (int)tot[1]) < (int)tot[2]) {
+            } else if (u -= (int)tot[1], SELECTS == 0 && u < (int)tot[2]) {
                 const int li = find_item(pool.upre[2], P.t_count, u);
                 const LayerDesc &L = stage(P.t_first + li);
                 u -= pool.upre[2][li];
@@ -473,6 +480,7 @@ hipError_t launch_units(const LaunchPlan &plan, hipStream_t stream)
     const bool pooled = plan.r_count + plan.g_count > 0;
     const bool small = plan.t_count + plan.s_count + plan.c_count + plan.a_count > 0;
     if (pooled == small) return hipErrorInvalidValue;  // a launch carries one family of units
+    if (plan.selects && plan.t_count + plan.c_count > 0) return hipErrorInvalidValue;  // (not in the builds that select)
     const dim3 grid(plan.c.n_wg), block(kThreads);
     if (small && plan.selects && plan.c.prob_rule != 0)
         hipLaunchKernelGGL((lychee_small_kernel<2>), grid, block, 0, stream, plan);

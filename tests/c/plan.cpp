@@ -53,15 +53,14 @@ extern "C" int32_t threshold_alone(int32_t n, int32_t L, int32_t r_blocks, int32
     return lychee::threshold_alone(n, L, r_blocks, n_wg, margin, fits);
 }
 
-extern "C" int32_t merge_units(int32_t n_layers, int32_t batch, int32_t n_kv_heads)
+extern "C" int32_t merge_split(int32_t kv_heads, int32_t group, int32_t any_sparse, int32_t others, int32_t slots, int32_t n_wg)
 {
-    return lychee::merge_units(n_layers, batch, n_kv_heads);
+    return lychee::merge_split(kv_heads, group, any_sparse != 0, others, slots, n_wg);
 }
 
-extern "C" void merge_at(int32_t u, int32_t batch, int32_t n_kv_heads, int32_t *out)
+extern "C" int32_t merge_parts(int32_t split, int32_t group) { return lychee::merge_parts(split, group); }
+
+extern "C" uint32_t merge_heads(int32_t split, int32_t part, uint32_t rmask, int32_t group)
 {
-    const lychee::MergeAt at = lychee::merge_at(u, batch, n_kv_heads);
-    out[0] = at.layer;
-    out[1] = at.b;
-    out[2] = at.g;
+    return lychee::merge_heads(split, part, rmask, group);
 }

@@ -376,6 +376,39 @@ def test_phased_step_skips_partials_without_a_row(ctx):
         H.assert_outputs_close(H.bf16_tensor_to_f64(outs[l]), out_ref, "layer %d" % l)
 
 
+@pytest.mark.parametrize("G,n_wg,l_cap,split", [(4, 52, 400, 2), (4, 51, 400, 1), (4, 28, 400, 1), (4, 27, 400, 0), (4, 16, 50000, 2),
+                                                (4, 15, 50000, 0), (3, 28, 400, 1), (2, 7, 400, 0), (1, 5, 400, 2)])
+def test_phased_steps_on_either_side_of_how_their_merges_are_dealt(ctx, plan, G, n_wg, l_cap, split):
+    """Three layers of two sequences and two KV heads: a head, a kind of heads or a KV head a unit, in one round and in
+    several, and the dense step beside it."""
+    lb = H.binding()
+    n_layers, B, Hkv, k = 3, 2, 2, 40
+    slots = -(-l_cap // 64) // max(8, -(-(-(-l_cap // 64)) // 192)) + 2
+    assert plan.merge_split(n_layers * B * Hkv, G, 1, B * Hkv, slots, n_wg) == split
+    rng = np.random.default_rng(G)
+    masks = np.concatenate([np.ones((1, Hkv * G), np.uint8), (rng.random((n_layers - 1, Hkv * G)) < 0.4).astype(np.uint8)])
+    lens = np.asarray([300, 50], np.int32)
+    w = wl.scaled(wl.WORKLOADS["c4"], batch=B, n_q_heads=Hkv * G, n_kv_heads=Hkv, max_len=l_cap, k=k, n_layers=n_layers, planted=6)
+    layers = [wl.make_layer(w, layer=l, device="cuda", mask=masks[l], lens=lens, l_cap=l_cap) for l in range(n_layers)]
+    shape = lb.make_shape(B, Hkv * G, Hkv, l_cap, k, kv=layers[0].k_cache)
+    ws = lb.alloc_workspace(shape, n_layers=n_layers)
+    ws.fill_(0xFF)
+    outs, dense = ([torch.full_like(ly.q, float("nan")) for ly in layers] for _ in range(2))
+    idx_final = torch.full((B, Hkv, k), -9, dtype=torch.int32, device="cuda")
+    args = [[getattr(ly, name) for ly in layers] for name in ("q", "k_cache", "v_cache")]
+    lens_d = torch.from_numpy(lens).cuda()
+    ctx.set_option(lb.OPT_N_WG, n_wg)
+    _say("phased step, groups of %d heads, %d workgroups" % (G, n_wg))
+    ctx.decode_step(shape, *args, masks, None, outs, idx_final, lens_d, ws)
+    ctx.dense_decode_step(shape, *args, dense, lens_d, ws)
+    torch.cuda.synchronize()
+    idx = None
+    for l, ly in enumerate(layers):
+        out_ref, idx, _ = H.oracle_layer(ly, masks[l], k, idx)
+        H.assert_outputs_close(H.bf16_tensor_to_f64(outs[l]), out_ref, "layer %d" % l)
+        H.assert_outputs_close(H.bf16_tensor_to_f64(dense[l]), H.oracle_layer(ly, np.ones_like(masks[l]), k, None)[0], "dense %d" % l)
+
+
 # ------------------------------------------------------------------ boundary behaviour
 def test_error_codes_and_index_validator(ctx):
     lb = H.binding()

@@ -1,5 +1,6 @@
 """How launches are laid out (csrc/lychee_plan.h), compiled for the host (no GPU needed)."""
 import ctypes
+import itertools
 import os
 import random
 import shutil
@@ -205,19 +206,25 @@ def test_one_unit_takes_a_threshold_where_the_launch_is_short_and_the_rest_fits_
             assert (f + margin * f ** 0.5 + 6) * L / 512 <= 0.9 * fits * (1 + 1e-5)
 
 
-def test_every_merge_of_a_phased_step_is_a_kv_head_of_its_own(plan):
-    """Units are dealt to the workgroups in turn, which is an even deal if each has the same to do: no unit is empty or
-    holds part of a KV head's heads, however the heads are divided into retrieval and sparse ones."""
-    out = (ctypes.c_int32 * 3)()
-    for n, batch, kv in ((1, 1, 1), (36, 1, 8), (36, 8, 8), (5, 3, 7), (127, 16, 2), (2, 256, 64)):
-        total = plan.merge_units(n, batch, kv)
-        seen = set()
-        for u in range(total):
-            plan.merge_at(u, batch, kv, out)
-            layer, b, g = out
-            assert 0 <= layer < n and 0 <= b < batch and 0 <= g < kv
-            seen.add((layer, b, g))
-        assert len(seen) == total == n * batch * kv
+def test_merges_of_a_phased_step_are_dealt_evenly(plan):
+    """Every head is merged once, however a KV head's heads are divided into retrieval and sparse ones; where workgroups
+    take several units no unit is empty and every one has as many heads; one kind or one head a unit only where each
+    has a workgroup of its own (or heads of many slots take up to three rounds)."""
+    splits = set()
+    for kv_heads, group, sparse, others, slots, n_wg in itertools.product(
+            (1, 64, 128, 129, 255, 256, 257, 512, 513, 4096, 127 * 16 * 64), (1, 2, 3, 4), (0, 1), (0, 8), (4, 96, 97, 194), (1, 512, 768)):
+        split = plan.merge_split(kv_heads, group, sparse, others, slots, n_wg)
+        parts = plan.merge_parts(split, group)
+        splits.add(split)
+        for rmask in range(1 << group) if sparse else [(1 << group) - 1]:
+            masks = [plan.merge_heads(split, part, rmask, group) for part in range(parts)]
+            assert sum(masks) == (1 << group) - 1 and sum(bin(m).count("1") for m in masks) == group, (split, rmask, masks)
+            if kv_heads * parts + others > n_wg:
+                assert len({bin(m).count("1") for m in masks}) == 1, (split, rmask, masks)
+        if kv_heads * parts + others > n_wg and parts > 1:
+            assert slots > 96 and kv_heads * parts <= 3 * n_wg
+        assert sparse or split != 1      # (a dense step's units of the sparse kind would all be empty)
+    assert splits == {0, 1, 2}
 
 
 def test_no_launch_has_the_generation_of_flags_that_nobody_has_written(plan):
