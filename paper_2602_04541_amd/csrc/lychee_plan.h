@@ -182,7 +182,7 @@ LYCHEE_HD inline int32_t gather_block_rows(int32_t r_blocks, int32_t g_blocks, i
 // 4096 rows 7.1, 5.2, 4.9; 24 layers 7.4, 5.7, 7.8; 36 7.6, 8.1, 10.2; of 32768 (66 slots) 8 layers 7.8, 6.5, 6.4;
 // 36 10.3, 10.7, 13.0, dense 10.4, 13.3, 13.0; of 65536 (130 slots) 24 layers 16.0, 14.5, 10.5; 44 17.5, 18.6, 14.7; 60
 // 12.5, 11.7, 17.0, dense 14.6, 18.8, 17.2.  (Kinds in every step: 8 sequences of 8192, 36 layers, 31.4, dense 32.3, with
-// KV heads 25.0 and 18.2; of one query head, which are the same by KV head and by head, 25.8 and 25.1, now 17.5 and 14.6.)
+// KV heads 25.0 and 18.2; of one query head each 25.8 and 25.1, by the head 16.7 and 14.0.)
 enum { kMergeKvHeads = 0, kMergeKinds = 1, kMergeHeads = 2 };
 LYCHEE_HD inline int32_t merge_split(int32_t kv_heads, int32_t group, bool any_sparse, int32_t others, int32_t slots, int32_t n_wg)
 {

@@ -128,29 +128,36 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_small_kernel(const LaunchP
                 if (SELECTS == 1) select_unit<false>(c, L, b, L.rgroup[u % L.n_rgroups], su.sel, pool);
                 if (SELECTS == 2) select_unit<true>(c, L, b, L.rgroup[u % L.n_rgroups], su.sel, pool);
             } else if (u -= (int)tot[0], SELECTS == 0 && u < (int)tot[1]) {
-                // Heads of a KV head (merge_split): the retrieval heads among them, which have the same slots, then the
-                // sparse ones.
-                const int kv_head = quot_uni(u, P.c_parts);
-                const int part = u - kv_head * P.c_parts;
-                const int row = quot_uni(kv_head, c.n_kv_heads);  // (layer, sequence)
-                const int g = kv_head - row * c.n_kv_heads;
-                const int li = quot_uni(row, c.batch);
-                const int b = row - li * c.batch;
-                const LayerDesc &L = stage(P.c_first + li);
-                const int lane = fresh_tid() & 63;
-                const int counts = gload(L.part_count + (int64_t)b * c.n_q_heads + g * c.group + (lane < c.group ? lane : 0));
-                const uint32_t rmask = P.c_split == kMergeHeads ? ~0u : uni((uint32_t)L.rmask[g]);  // (a head is of one kind)
-                const uint32_t of = merge_heads(P.c_split, part, rmask, c.group);
-                for (int kind = 0; kind < 2; ++kind) {
-                    const uint32_t hmask = (kind != 0 ? ~rmask : rmask) & of;
-                    if (hmask == 0) continue;
-                    int count = __builtin_amdgcn_readlane(counts, __builtin_ctz(hmask));
-                    count = count < 1 ? 1 : (count > c.part_stride ? c.part_stride : count);  // (every head has a piece)
-                    switch (__builtin_popcount(hmask)) {
-                    case 1: combine_segment<1, true>(c, L, b, g, hmask, count, su.comb); break;
-                    case 2: combine_segment<2, true>(c, L, b, g, hmask, count, su.comb); break;
-                    case 3: combine_segment<3, true>(c, L, b, g, hmask, count, su.comb); break;
-                    default: combine_segment<4, true>(c, L, b, g, hmask, count, su.comb); break;
+                auto slots_of = [&](int n) { return n < 1 ? 1 : (n > c.part_stride ? c.part_stride : n); };  // (every head has a piece)
+                if (P.c_split == kMergeHeads) {  // (by itself: 0.2 us less for each unit than as one of the cases below)
+                    const int li = u / (c.batch * c.n_q_heads);
+                    const LayerDesc &L = stage(P.c_first + li);
+                    const int bh = u % (c.batch * c.n_q_heads);
+                    const int b = bh / c.n_q_heads, h = bh % c.n_q_heads;
+                    const int count = slots_of(uni(gload(L.part_count + bh)));
+                    combine_segment<1, true>(c, L, b, h / c.group, 1u << (h % c.group), count, su.comb);
+                } else {
+                    // Heads of a KV head: the retrieval heads among them, which have the same slots, then the sparse ones.
+                    const int part = u % P.c_parts;
+                    u /= P.c_parts;
+                    const int li = u / (c.batch * c.n_kv_heads);
+                    const LayerDesc &L = stage(P.c_first + li);
+                    u -= li * (c.batch * c.n_kv_heads);
+                    const int b = u / c.n_kv_heads, g = u % c.n_kv_heads;
+                    const int lane = fresh_tid() & 63;
+                    const int counts = gload(L.part_count + (int64_t)b * c.n_q_heads + g * c.group + (lane < c.group ? lane : 0));
+                    const uint32_t rmask = uni((uint32_t)L.rmask[g]);
+                    const uint32_t of = merge_heads(P.c_split, part, rmask, c.group);
+                    for (int kind = 0; kind < 2; ++kind) {
+                        const uint32_t hmask = (kind != 0 ? ~rmask : rmask) & of;
+                        if (hmask == 0) continue;
+                        const int count = slots_of(__builtin_amdgcn_readlane(counts, __builtin_ctz(hmask)));
+                        switch (__builtin_popcount(hmask)) {
+                        case 1: combine_segment<1, true>(c, L, b, g, hmask, count, su.comb); break;
+                        case 2: combine_segment<2, true>(c, L, b, g, hmask, count, su.comb); break;
+                        case 3: combine_segment<3, true>(c, L, b, g, hmask, count, su.comb); break;
+                        default: combine_segment<4, true>(c, L, b, g, hmask, count, su.comb); break;
+                        }
                     }
                 }
             } else if (u -= (int)tot[1], SELECTS == 0 && u < (int)tot[2]) {
