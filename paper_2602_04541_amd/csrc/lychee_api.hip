@@ -537,7 +537,7 @@ int layer_launch(lychee_ctx *ctx, const lychee_shape &s, const Workspace &w, con
     return LYCHEE_OK;
 }
 
-// The candidate counters of a layer that a layer launch streams: one of the context's two banks.
+// The candidate counters of a layer that a layer launch streams: one of the context's three banks.
 int32_t *count_bank(lychee_ctx *ctx, int bank)
 {
     return reinterpret_cast<int32_t *>(ctx->sync_dev + kSyncCount) + (size_t)bank * kSyncRows * kLineWords;

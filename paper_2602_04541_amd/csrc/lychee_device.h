@@ -230,7 +230,7 @@ __device__ __forceinline__ void gstore(T *p, T v)
 // Write-through store: the value goes through the XCD's L2 to device memory, and the store counts
 // as outstanding (vmcnt) until it is there.  A workgroup on another XCD that learns, through an
 // agent-scope atomic issued after wait_stores(), that the data exists reads it after an acquire
-// fence.  This is what lets a workgroup hand a partial result to another one in the same launch
+// fence, or past the caches (gload_through).  This is what lets a workgroup hand a partial result to another one in the same launch
 // without the agent-scope release fence, whose write-back of the whole L2 costs tens of
 // microseconds when hundreds of workgroups execute it.
 __device__ __forceinline__ void gstore_through(float *p, float v)

@@ -320,11 +320,13 @@ __global__ __launch_bounds__(kThreads, 2) void lychee_layer_kernel(const LayerLa
         // block 1.2 to 1.7 us), so a segment counts kPieceBlocks blocks more than it has.
         // (64 sequences of 61 to 3001 rows: a run of equal blocks held up to nine short
         // segments, half the workgroups were done after 70 us and the last after 110.  Few segments of
-        // a batch, us without and with: model loop of 8 x 2000-5000 rows, 4 layers, 142.6 and 129.1, of
-        // 5 x 6000-24000 197.8 and 185.8; a layer call of 8 x 3000-8192 30.1 and 23.8.)
+        // a batch, us without and with: model loop of 8 x 2000-5000 rows, 4 layers, 125.5 and 121.4, of
+        // 5 x 6000-24000 180.8 and 171.0; a layer call of 8 x 3000-8192 with one and two retrieval heads the same.)
         // Not the few gathers of a launch that selects its own rows: the blocks also weigh the split of the
         // grid, and there the streaming, which the select follows, should end first (8 x 3000-8192, four retrieval heads:
-        // 32.8, with them 35.5).  A single sequence's segments end with a run.
+        // 32.8, with them 35.5, when a piece's fixed cost was higher.  It is no longer so: k = 256, 1024 and 2048 31.2,
+        // 39.7 and 42.5, with them 30.3, 35.0 and 42.3; one retrieval head 22.7, 28.4 and 35.6, with them 21.7, 26.6
+        // and 32.3.)  A single sequence's segments end with a run.
         const int extra_r = !single || 8 * n_rseg > W ? kPieceBlocks : 0;
         const int extra_g = (!single && !kNow) || 8 * n_gseg * c.batch > W ? kPieceBlocks : 0;
         nb_r += nb_r ? extra_r : 0;

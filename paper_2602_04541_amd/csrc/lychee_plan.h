@@ -70,10 +70,10 @@ struct FrontPlan {
 // How many: one workgroup per unit, but never more than a quarter of the grid; and beyond a sixteenth of it
 // (which a launch does not notice) only as many as run the units in turn, about 8 us each, in half of the
 // time that the streaming takes (5.5 ns a block at 6 TB/s), since the pieces need the thresholds when
-// they end.  On 512 workgroups, us a layer with 32, 64 and 128 in front: 8 sequences of 16411 to 98304 rows
-// 153, 153, 163; 64 of 8192: 336, 236, 203; 64 of 16384: 426, 351, 384.  (By the cache's capacity, and on a
+// they end.  On 512 workgroups, us a layer of the model loop with 32, 64 and 128 in front: 8 sequences of 16411 to 98304
+// rows 142, 144, 152; 64 of 8192: 357, 271, 238; 64 of 16384: 435, 349, 360.  (By the cache's capacity, and on a
 // sixteenth of the grid beside anything longer than 120 us, 64 sequences of 2000 to 5056 rows took 165 us in
-// a cache of 65536 rows and 125 in one of 5056, and 64 of 8192 took 340 a layer of the model loop.)
+// a cache of 65536 rows and 125 in one of 5056, and 64 of 8192 took 340 a layer.)
 LYCHEE_HD inline FrontPlan front_plan(int32_t selects, int32_t copies, int32_t thresholds, bool gated, int32_t r_blocks,
                                       int32_t n_wg)
 {
@@ -96,8 +96,8 @@ LYCHEE_HD inline FrontPlan front_plan(int32_t selects, int32_t copies, int32_t t
 // Selecting there begins when a row's last piece has counted itself in, beside the merge of its partials, which
 // takes 4 us.  What it costs is the streaming that these workgroups would have done, rows / n_wg of 5.5 ns a
 // block: up to 1/64 of it at any length, or up to 1/16 where that is no more than 1.5 us.  us a call, selected after the
-// merge and at the end of the grid: two KV heads at 4K 25.1 and 21.8, four retrieval heads of eight KV heads at
-// 32K 34.9 and 31.2, at 100K with k = 8192 70.7 and 64.8.
+// merge and at the end of the grid: two KV heads at 4K 20.4 and 16.4, four retrieval heads of eight KV heads at
+// 32K 33.1 and 27.1, at 100K with k = 8192 70.6 and 63.8.
 LYCHEE_HD inline int32_t tail_selects(int32_t rows, int32_t r_blocks, int32_t n_wg)
 {
     if (n_wg < 64) return 0;
@@ -107,9 +107,8 @@ LYCHEE_HD inline int32_t tail_selects(int32_t rows, int32_t r_blocks, int32_t n_
 // Whether a plain layer call under a probability rule selects in a second launch, a workgroup per row, instead of in
 // its own.  r_blocks: blocks of 64 rows that the launch streams at most, by the cache's capacity.  A select with a rule takes up to 15 us, and of more rows than a quarter of the workgroups some complete
 // several and select them in turn; a streaming of more than 32 blocks a workgroup hides that.  us a call
-// in one launch and in two, 64 sequences of four retrieval heads, Top-p: of 1/3 to 1024 rows 66 and 57, 61 to 3001 rows
-// (in 4096) 106 and 92, 1/3 to 6000 142 and 165; a Threshold, 61 to 1001 rows 58 and 51; 32 sequences of 1/3 to
-// 1000 rows, Top-p, 41 and 44.  (Not the faster side everywhere: 64 of 1000 to 3000 in 3000 95 and 102.)
+// in one launch and in two, Top-p, 64 sequences of four retrieval heads in three KV heads: of 1 to 1000 rows 68.6 and
+// 63.8, 61 to 3001 (in 4096) 96 and 87.  (Not the faster side everywhere: 1000 to 3000 in 3000 91.5 and 98.)
 LYCHEE_HD inline bool rules_apart(int32_t rows, int32_t r_blocks, int32_t n_wg)
 {
     return 4 * rows > n_wg && r_blocks <= 32 * n_wg;
@@ -120,11 +119,11 @@ LYCHEE_HD inline bool rules_apart(int32_t rows, int32_t r_blocks, int32_t n_wg)
 // lengths, and the second returns at once if nothing is left to it (2 us).  r_blocks: what the n_wg streaming
 // workgroups take; shortest: blocks of the shortest segment; both with the blocks that a segment counts beyond
 // those it has.  Rows are selected in turn where a workgroup's run holds several segments, so: where it holds more
-// than two of the shortest.  us a call selected by the first launch and by the second, Top-p, three score rows a
-// sequence (blocks of a run over the shortest segment's): 64 sequences of 2000 to 5000 rows (1.3) 121 and 138, 1000
-// to 3000 (1.7) 98 and 111, 800 to 2400 (1.8) 96 and 104, 500 to 2000 (2.3) 100 and 95, 61 to 3001 (5) 116 and
-// 103, 61 to 6000 (7) 130 and 131, 61 to 12000 (11) 208 and 185; 128 of 300 to 1000 (4) 123 and 110; 256 of 61 to
-// 1000 (12) 228 and 187; 128 of 1000 to 3000 (3.4) 178 and 186.
+// than two of the shortest.  us a call selected by the first launch and by the second, Top-p, 64 sequences of three
+// score rows in a cache of 65536 rows (blocks of a run over the shortest segment's): 2000 to 5000 rows (1.3) 118 and
+// 133, 1000 to 3000 (1.7) 96 and 106, 500 to 2000 (2.3) 94 and 92, 61 to 3001 (5) 106 and 99, 61 to 12000 (11) 198 and
+// 182.  When the rule was made also: 800 to 2400 (1.8) 96 and 104; 61 to 6000 (7) 130 and 131; 128 sequences of 300 to
+// 1000 (4) 123 and 110, of 1000 to 3000 (3.4) 178 and 186; 256 of 61 to 1000 (12) 228 and 187.
 LYCHEE_HD inline bool rows_in_turn(int32_t r_blocks, int32_t n_wg, int32_t shortest)
 {
     return r_blocks > 2 * shortest * n_wg;
@@ -138,12 +137,15 @@ constexpr int32_t kAloneSample = 512;
 // threshold may so be taken by one unit behind a long streaming, from fewer samples, which costs the select up to
 // what its registers hold).
 // The four hand their keys to the one that ranks them through device memory: stores, a counter, loads, each of which takes about
-// 2 us beside the streaming's first loads, so that the threshold is out after 14 us, and a piece of a short
-// launch is done with its rows after 12.  From fewer samples the threshold lets more rows through for the same
+// 2 us beside the streaming's first loads, and a piece of a short launch is done with its rows before the
+// threshold is out.  From fewer samples the threshold lets more rows through for the same
 // safety: with f of the n best among 512 rows, (f + 6 sqrt f + 6) / f times n.  So: where the streaming takes less
 // than the hand-over (five blocks per workgroup), and what is let through (n, or L if no more are) still fits the
-// select's registers with a tenth to spare.  The pieces' filter of a 32K layer of 3 retrieval heads, k = 2048: 18.0
-// us after the launch with four units, 15.9 with one.
+// select's registers with a tenth to spare.  us with four units and with one: layer calls of 16384 rows with one, three
+// and five retrieval heads 20.7 and 20.0, 20.7 and 19.8, 22.7 and 22.2; of 32768, k = 2048, with one to five 24.0 and
+// 21.9, 24.6 and 24.2, 25.2 and 25.3, 26.7 and 27.8, 26.8 and 27.6.  (So the line lies far out since pieces ask for
+// the threshold ahead of their partials; eight layers of the model loop of 32768 with one retrieval head take 166 and
+// 174, with three and five the same.)
 LYCHEE_HD inline float threshold_target(float f, float margin) { return f + margin * __builtin_sqrtf(f) + 6.0f; }
 LYCHEE_HD inline bool threshold_alone(int32_t n, int32_t L, int32_t r_blocks, int32_t n_wg, float margin, int32_t fits)
 {
@@ -161,9 +163,9 @@ constexpr int32_t kGatherRows = 64;
 // start late and should have more workgroups than as many streamed rows, but only where rows and not
 // latencies fill the launch: beyond 12 blocks per workgroup, by the cache's capacity, and for the longest
 // sequences.  Model loop, time with 64 over time with 48: two sequences (blocks per workgroup) at 48K (12) 0.98,
-// 64K (16) 1.05; four at 16K (9) 0.96, 32K (18) 0.99, 64K (33) 1.06 to 1.11; eight at 8K (9) 1.01, 16K (18) 1.00, 64K
-// (66) 1.07; 64 at 1K (9) 0.94, 3K (26) 1.09, 8K (72) 1.06.  One sequence of 1 to 5 retrieval heads: 64K 0.91 to 0.99,
-// 96K 0.96 to 1.02, 112K 0.98 to 1.02, 128K 0.95 to 1.08, and 1.04 over the 36 layers of a step.
+// 64K (16) 1.01; four at 16K (9) 0.98, 32K (18) 0.98; eight at 8K (9) 0.98, 16K (18) 1.00; 64 at 1K (9) 1.00, 3K (26)
+// 1.04, 8K (72) 1.03; one sequence of three retrieval heads at 64K 1.00, 96K 0.98, 128K 1.01.  (When the rule was made
+// 64K and more of two to eight sequences 1.05 to 1.11, 128K of 1 to 5 retrieval heads 0.95 to 1.08.)
 LYCHEE_HD inline int32_t gather_block_rows(int32_t r_blocks, int32_t g_blocks, int32_t max_len, int32_t n_wg)
 {
     return (int64_t)r_blocks + g_blocks > 12ll * n_wg || max_len >= 7 << 14 ? 48 : kGatherRows;

@@ -704,7 +704,7 @@ __device__ __forceinline__ void write_ordered(const Entries &E, int L, int32_t *
         }
         // Staged in LDS and copied out with coalesced write-through stores: the set is in device
         // memory once the unit's stores have completed, whoever reads it next (a gather piece of
-        // the same launch, on another XCD, after an acquire).
+        // the same launch, on another XCD, past its caches).
         for (uint32_t c0 = base; c0 < end; c0 += (uint32_t)kStage) {
             E.for_kept(w0, span, [&](const uint32_t (&pos)[8]) {
                 // (all lookups of a group before its first store: a lookup after a store waits for

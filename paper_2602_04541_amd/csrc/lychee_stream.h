@@ -151,8 +151,9 @@ __device__ __forceinline__ uint32_t wait_threshold(const Emit &em)
 
 // LATE pieces: lists the rows of a window of n_rows keys in sh.keys that reach the threshold; row i of the window is
 // position first_row + i.  Each wavefront filters 1024 rows for itself, the last one first: it asks for the
-// threshold, counts by ballots, reserves list space, writes.  At the end of a piece of up to 2048
-// rows that leaves the first two wavefronts to the partial.  (Counted and scanned by the whole workgroup
+// threshold, counts by ballots, reserves list space, writes.  At the end of a piece wavefront h comes here after
+// it has merged head h: of up to 1024 rows the wavefront that filters merges the fourth of four heads, of up to 2048
+// the other one the third; no head waits for a filter.  (Counted and scanned by the whole workgroup
 // ahead of the partial, four barriers and the answer of the one reservation stood between the last row and the
 // partial, and a piece that ended before its threshold was out held its partial back.)
 // early: the row's threshold word as it was a while ago (its load takes 0.7 us): usually the threshold is there; 0,
